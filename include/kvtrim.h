@@ -95,10 +95,9 @@ typedef struct {
 
 /* Context life cycle (host side, synchronous).  kvtrim_create allocates the
  * workspace on the current device; kvtrim_workspace_bytes says how large it is.
- * One tuning knob is read from the environment at creation: KVTRIM_ATT_CHUNK = rows per
- * split-K chunk of the stand-alone attention kernel (a multiple of 64 in [256, 65536];
- * default 512, and larger for caches above 8 M entries so that at most 16384 full chunks
- * exist).  It changes the order of floating-point sums in attention, nothing else. */
+ * One tuning knob is read from the environment at creation: KVTRIM_ATT_BLOCKS = most blocks
+ * among which the stand-alone attention kernel shares its rows (1 .. 65536, default 768).
+ * It changes the order of floating-point sums in attention, nothing else. */
 kvtrim_status kvtrim_create(kvtrim_ctx **out, const kvtrim_config *cfg);
 kvtrim_status kvtrim_destroy(kvtrim_ctx *ctx);
 size_t kvtrim_workspace_bytes(const kvtrim_config *cfg);
@@ -420,9 +419,8 @@ kvtrim_status kvtrim_paged_score_select(kvtrim_ctx *ctx, const kvtrim_paged_cach
  * everything but out / lse, which agree within the attention tolerance: a page that this step's eviction emptied is
  * still listed when the attention's chunk table is built, so the fp32 sums may group differently.  With a small
  * evict_hint the mask kernel of the decode-step selection applies the eviction as it writes the mask (which saves
- * the pass of kvtrim_paged_evict over all pages), its scoring kernel also builds the attention's chunk table, and
- * the attention's merge kernel takes the emptied pages out of the block tables: five kernels per step.  Any other
- * hint runs the four calls. */
+ * the pass of kvtrim_paged_evict over all pages) and the attention's merge kernel takes the emptied pages out of the
+ * block tables: five kernels per step.  Any other hint runs the four calls. */
 kvtrim_status kvtrim_paged_decode_step(kvtrim_ctx *ctx, kvtrim_paged_cache *c, const void *k_new, const void *v_new,
                                        const float *log_beta_new, const float *log_tail_new, const int32_t *pos_new,
                                        const int32_t *now, const int64_t *budget, float *score_out, uint8_t *keep_out,

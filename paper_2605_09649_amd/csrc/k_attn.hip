@@ -1,8 +1,8 @@
 // Stage 4: GQA decode attention over the ragged retained caches (Sec. 2.1, Eq. reform, r in {0,1}).
 //
-// Split-K over fixed-size chunks of each segment so that very unequal segment lengths still
-// fill the chip: a fixed grid of blocks shares the rows of the chunk table equally, each block
-// walking a contiguous stretch of it.  Inside a chunk a wavefront walks tiles of 16 rows:
+// Split-K over the rows of all segments of the call so that very unequal segment lengths still
+// fill the chip: a grid of blocks shares the rows equally, each block walking a contiguous stretch
+// of them.  Inside it a wavefront walks tiles of 16 rows:
 //   Q.K^T  one MFMA 16x16 accumulator per tile (rows = 16 keys, columns = the G query heads,
 //          padded to 16); K fragments are loaded straight from HBM in the operand layout
 //          (lane = key row, four lanes share 64 contiguous bytes of the row).
@@ -20,7 +20,11 @@
 namespace kvtrim {
 
 constexpr int ATT_THREADS = 256;
-constexpr int ATT_PLAN_BLOCKS = 16;         // blocks that share the filling of the chunk table
+constexpr int ATT_ROUND = 64;               // rows of a round: one tile for each of a block's four wavefronts
+// Segments up to which every block adds up the segments' lengths itself (in LDS) instead of reading a table that a
+// kernel before it has written.  That kernel takes 5.5 us at 256 segments; 4096 segments are 16 lengths and starts per
+// thread, 48 KB out of L2 per block, and 32 KB of LDS, with which three blocks still fit a compute unit.
+constexpr int ATT_SCAN_SEGS = 4096;
 
 typedef __attribute__((ext_vector_type(4))) float float4v;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -28,17 +32,6 @@ typedef __attribute__((ext_vector_type(4))) short short4v;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(4))) unsigned v4u;
 typedef __attribute__((ext_vector_type(2))) unsigned v2u;
-
-__global__ __launch_bounds__(1024) void k_att_plan(CacheView c, Shape sh, Workspace ws, int chunk,
-                                                   int layer_begin, int layer_end, int64_t max_chunks) {
-    const int H = sh.n_kv_heads, L = sh.n_layers;
-    auto in_range = [=](int g) {
-        const int layer = (g / H) % L;
-        return layer >= layer_begin && layer < layer_end;
-    };
-    build_chunk_table(c.seg_len, c.seg_start, sh.nseg, in_range, chunk, c.cap, ws.att_chunk_prefix,
-                      ws.att_desc, max_chunks, ws.att_row_prefix, ws.err, (int)blockIdx.x, (int)gridDim.x);
-}
 
 template <int D>
 struct Frag;
@@ -71,17 +64,85 @@ struct Frag<64> {
     static __device__ __forceinline__ unsigned word(vec x, int w) { return w == 0 ? x.x : x.y; }
 };
 
+// Rows of segment g as the attention walks them (PAGED: the slots of its pages) and where they start; an unusable
+// table entry sets *bad and counts no rows.
+template <bool PAGED>
+__device__ __forceinline__ int att_rows(const CacheView& c, const AttPages& pt, int g, int nseg, int64_t* start, bool* bad) {
+    if (PAGED) {
+        const int npg = pt.seg_pages[g], live = pt.seg_live[g];
+        *start = (int64_t)g * pt.max_pps;
+        if (npg < 0 || npg > pt.max_pps || live < 0 || (int64_t)live > (int64_t)npg * KVTRIM_PAGE_SIZE) {
+            *bad = true;
+            return 0;
+        }
+        return npg * KVTRIM_PAGE_SIZE;
+    }
+    const int len = c.seg_len[g];
+    const int64_t st = c.seg_start[g];
+    const int64_t nxt = g + 1 < nseg ? c.seg_start[g + 1] : c.cap;
+    *start = st;
+    if (len < 0 || st < 0 || st + len > c.cap || st + len > nxt) {
+        *bad = true;
+        return 0;
+    }
+    return len;
+}
+
+// The segments of a layer range, in order, are numbered 0 .. n_in - 1 ("ordinals").
+__device__ __forceinline__ int seg_of_ordinal(int o, int per, int layer_begin, const Shape& sh) {
+    const int seq = o / per;
+    return seq * sh.segs_per_seq + layer_begin * sh.n_kv_heads + (o - seq * per);
+}
+
+// More than ATT_SCAN_SEGS segments: one block writes the rows before each ordinal (ws.att_row_prefix) ahead of
+// k_att_partial.
+template <bool PAGED>
+__global__ __launch_bounds__(1024) void k_att_plan(CacheView c, AttPages pt, Shape sh, Workspace ws, int layer_begin, int per, int n_in) {
+    __shared__ int64_t s_scan[17];
+    __shared__ int s_bad;
+    if (threadIdx.x == 0) s_bad = 0;
+    __syncthreads();
+    bool bad = false;
+    int64_t carry = 0;
+    for (int base = 0; base < n_in; base += 1024) {
+        const int o = base + (int)threadIdx.x;
+        int64_t st, tot;
+        const int rows = o < n_in ? att_rows<PAGED>(c, pt, seg_of_ordinal(o, per, layer_begin, sh), sh.nseg, &st, &bad) : 0;
+        const int64_t ex = block_excl_scan<int64_t>(rows, s_scan, &tot);
+        if (o < n_in) ws.att_row_prefix[o] = carry + ex;
+        carry += tot;
+    }
+    if (bad) s_bad = 1;
+    __syncthreads();
+    if (s_bad || carry > ((int64_t)1 << 31) - ATT_ROUND) {        // an unusable table: no rows at all
+        for (int o = threadIdx.x; o < n_in; o += 1024) ws.att_row_prefix[o] = 0;
+        carry = 0;
+        if (threadIdx.x == 0) atomicOr(ws.err, ERR_LAYOUT);
+    }
+    if (threadIdx.x == 0) ws.att_row_prefix[n_in] = carry;
+}
+
 // partial layout: [slot][G][D + 2] = (m in base-2 units, l, o[D] unnormalised)
 // SOFT: retention-gated attention of Sec. 2.2 - the logit of entry i gets the bias (t - i) log(beta_i),
 // t = now[seq] (the weights beta^(t-i) e^z of the soft form); otherwise hard eviction, no bias.
-// PAGED: the chunk is a run of pages of a paged cache - cd.first indexes the first of them in the block
-// tables, cd.n counts their slots; slots with a negative position are empty and take no part (their
-// logit is -inf and their V row, which may hold anything, is replaced by zeros).
-template <int D, int G, bool SOFT, bool PAGED>
-__global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, const uint16_t* __restrict__ q,
-                                                             Shape sh, Workspace ws, int chunk,
-                                                             float scale_log2, const int32_t* __restrict__ now,
-                                                             int round_rows, int extra_base) {
+// PAGED: a segment's rows are the slots of its pages in block-table order; slots with a negative position are empty and
+// take no part (their logit is -inf and their V row, which may hold anything, is replaced by zeros).
+// PLANNED: the rows before each segment come from k_att_plan; otherwise every block adds them up itself.
+//
+// The rows of the layer range's segments, one segment after the other (N rows in all), are shared out equally: block b
+// of nb = min(grid, N / 64) starts at the row b N / nb, rounded down to a multiple of 64 inside its segment, and ends
+// where block b + 1 starts (64 rows or more later, so no share is empty).  With few rows (one layer of a model: 33 K rows, 17 MB) that is one round per
+// block, so all of the call's rows are in flight at once and the call is a chain of latencies: lengths -> scan in LDS ->
+// rows -> partial result.  (It used to be a kernel that built a table of 512-row chunks, then seven dependent loads in
+// front of the first row: 42 us a layer with the merge, 32 layers of 8 KV heads, 1.05 M entries; now 14.4 us.)
+// A block keeps ONE online-softmax state for as long as its rows belong to the same segment: a partial result is
+// written per (block, segment) run, at slot block + ordinal (a step to the next run advances one of the two).
+// On this GPU a stream of reads slows down by far more than the bytes suggest when result writes are mixed into
+// it (8.5 MB of writes in a 1.1 GB read stream cost 12 us of 170), so the fewer partial results the better.
+template <int D, int G, bool SOFT, bool PAGED, bool PLANNED>
+__global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, AttPages pt, const uint16_t* __restrict__ q,
+                                                             Shape sh, Workspace ws, float scale_log2,
+                                                             const int32_t* __restrict__ now, int layer_begin, int per, int n_in) {
     typedef Frag<D> F;
     typedef typename F::vec vec;
     constexpr int E = F::E;
@@ -89,45 +150,79 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, const 
     __shared__ float s_m[NSTREAM][G], s_l[NSTREAM][G];
     constexpr int SO = D + 8;                                     // a 32-byte skew between heads
     __shared__ __attribute__((aligned(16))) float s_o[NSTREAM][G][SO];
+    __shared__ int64_t s_scan[17];
+    __shared__ int s_bad;
+    extern __shared__ int32_t s_tab[];                            // !PLANNED: [n_in + 1] rows before each ordinal, [n_in] starts
 
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    // The grid is fixed (a few blocks per compute unit).  The rows of the layer range's segments, one segment after the
-    // other (ws.att_row_prefix; N rows in all), are shared out equally: block b starts at the row b N / nb, rounded down
-    // to a multiple of round_rows inside its segment (64: a round of the four wavefronts; a whole chunk when the
-    // partial-result buffer has no extra slots to spare), and ends where block b + 1 starts.  A
-    // block keeps ONE online-softmax state for as long as its rows belong to the same segment: a partial result is
-    // written per (block, segment) run and not per chunk - at the slot of the chunk that the run starts with, or at
-    // slot extra_base + b when the run starts inside a chunk (the block before it owns that chunk's slot).
-    // On this GPU a stream of reads slows down by far more than the bytes suggest when result writes are mixed into
-    // it (8.5 MB of writes in a 1.1 GB read stream cost 12 us of 170), so the fewer partial results the better.
-    const int total = ws.att_chunk_prefix[sh.nseg];
-    const int nb = min((int)gridDim.x, total);
-    if ((int)blockIdx.x >= nb) return;
-    const int64_t* rp = ws.att_row_prefix;
-    const int64_t N = rp[sh.nseg];
-    // where the rows e0 <= e1 of the concatenation lie: the segment s with rp[s] <= e < rp[s + 1] (nseg behind the last row)
+    const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int32_t* s_start = s_tab + n_in + 1;
+    bool bad = false;
+    // the segments outside the range are looked at as well: a call on a cache with an unusable table gives no result
+    for (int g = (int)blockIdx.x * ATT_THREADS + tid; g < sh.nseg; g += (int)gridDim.x * ATT_THREADS) {
+        int64_t st;
+        (void)att_rows<PAGED>(c, pt, g, sh.nseg, &st, &bad);
+    }
+    if (bad) atomicOr(ws.err, ERR_LAYOUT);
+    int64_t N;
+    if (!PLANNED) {
+        if (tid == 0) s_bad = 0;
+        bad = false;
+        const int each = (n_in + ATT_THREADS - 1) / ATT_THREADS;  // consecutive ordinals per thread
+        int64_t mine = 0;
+        for (int i = 0; i < each; ++i) {
+            const int o = tid * each + i;
+            if (o >= n_in) break;
+            int64_t st;
+            const int rows = att_rows<PAGED>(c, pt, seg_of_ordinal(o, per, layer_begin, sh), sh.nseg, &st, &bad);
+            s_tab[o] = rows;
+            if (!PAGED) s_start[o] = (int32_t)st;                 // (below 2^31: cap is, and an entry beyond it is bad)
+            mine += rows;
+        }
+        int64_t ex = block_excl_scan<int64_t>(mine, s_scan, &N);
+        if (bad) s_bad = 1;
+        for (int i = 0; i < each; ++i) {
+            const int o = tid * each + i;
+            if (o >= n_in) break;
+            const int rows = s_tab[o];
+            s_tab[o] = (int32_t)ex;
+            ex += rows;
+        }
+        if (tid == 0) s_tab[n_in] = (int32_t)N;
+        __syncthreads();
+        if (s_bad || N > ((int64_t)1 << 31) - ATT_ROUND) {
+            if (tid == 0) atomicOr(ws.err, ERR_LAYOUT);
+            return;
+        }
+        // the merge kernel reads the same prefix from memory (by then a paged cache's tables may be in change)
+        for (int o = (int)blockIdx.x * ATT_THREADS + tid; o <= n_in; o += (int)gridDim.x * ATT_THREADS) ws.att_row_prefix[o] = s_tab[o];
+    } else {
+        N = ws.att_row_prefix[n_in];
+    }
+    auto rp = [&](int o) -> int64_t { return PLANNED ? ws.att_row_prefix[o] : (int64_t)s_tab[o]; };
+    const int nb = (int)min((int64_t)gridDim.x, max(N / ATT_ROUND, (int64_t)1));
+    if ((int)blockIdx.x >= nb || N == 0) return;
+    // where the rows e0 <= e1 of the concatenation lie: the ordinal s with rp(s) <= e < rp(s + 1) (n_in behind the last row)
     // and the round of rows inside it.  A 64-way search, both rows at once: every lane looks at one point of each
-    // remaining range, so 4096 segments take two rounds of one load instead of twelve loads one after the other.
+    // remaining range, so 4096 segments take two rounds instead of twelve reads one after the other.
     int seg_b, row_b, seg_e, row_e;
     {
         const int64_t e0 = (int64_t)blockIdx.x * N / nb, e1 = (int64_t)(blockIdx.x + 1) * N / nb;
-        int lo0 = 0, hi0 = sh.nseg, lo1 = 0, hi1 = sh.nseg;        // invariant: rp[lo] <= e < rp[hi]   (rp[0] = 0, rp[nseg] = N)
+        int lo0 = 0, hi0 = n_in, lo1 = 0, hi1 = n_in;              // invariant: rp(lo) <= e < rp(hi)   (rp(0) = 0, rp(n_in) = N)
         while (hi0 - lo0 > 1 || hi1 - lo1 > 1) {
             const int st0 = (hi0 - lo0 + 63) / 64, st1 = (hi1 - lo1 + 63) / 64;   // lane l probes lo + (l + 1) stride
             const int i0 = lo0 + (lane + 1) * st0, i1 = lo1 + (lane + 1) * st1;
-            const bool in0 = i0 < hi0 && rp[min(i0, sh.nseg)] <= e0, in1 = i1 < hi1 && rp[min(i1, sh.nseg)] <= e1;
+            const bool in0 = i0 < hi0 && rp(min(i0, n_in)) <= e0, in1 = i1 < hi1 && rp(min(i1, n_in)) <= e1;
             const int n0 = __popcll(__ballot(in0)), n1 = __popcll(__ballot(in1));   // (monotone: the first n lanes)
             hi0 = min(hi0, lo0 + (n0 + 1) * st0);
             lo0 += n0 * st0;
             hi1 = min(hi1, lo1 + (n1 + 1) * st1);
             lo1 += n1 * st1;
         }
-        seg_b = e0 >= N ? sh.nseg : lo0;
-        row_b = e0 >= N ? 0 : (int)(e0 - rp[lo0]) / round_rows * round_rows;
-        seg_e = e1 >= N ? sh.nseg : lo1;
-        row_e = e1 >= N ? 0 : (int)(e1 - rp[lo1]) / round_rows * round_rows;
+        seg_b = e0 >= N ? n_in : lo0;
+        row_b = e0 >= N ? 0 : (int)(e0 - rp(lo0)) / ATT_ROUND * ATT_ROUND;
+        seg_e = e1 >= N ? n_in : lo1;
+        row_e = e1 >= N ? 0 : (int)(e1 - rp(lo1)) / ATT_ROUND * ATT_ROUND;
     }
-    if (seg_b == seg_e && row_b == row_e) return;                 // (shares of less than a round: a later block has the rows)
     const int c16 = lane & 15, b4 = lane >> 4;
     const vec* kp = reinterpret_cast<const vec*>(c.k);
     const vec* vp = reinterpret_cast<const vec*>(c.v);
@@ -188,12 +283,13 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, const 
         }
         __syncthreads();                                          // (the next run's partials may overwrite LDS)
     };
-    for (int seg = seg_b; seg <= seg_e && seg < sh.nseg; ++seg) {
-    const int c0 = ws.att_chunk_prefix[seg], c1 = ws.att_chunk_prefix[seg + 1];
-    const int run_lo = seg == seg_b ? row_b : 0;                  // this block's rows of the segment: [run_lo, run_hi)
-    const int run_hi = seg == seg_e ? row_e : (int)(rp[seg + 1] - rp[seg]);
-    if (c0 >= c1 || run_lo >= run_hi) continue;                   // (uniform over the block)
-    const int run_slot = run_lo % chunk == 0 ? c0 + run_lo / chunk : extra_base + (int)blockIdx.x;
+    for (int ord = seg_b; ord <= seg_e && ord < n_in; ++ord) {
+    const int seg_rows = (int)(rp(ord + 1) - rp(ord));
+    const int run_lo = ord == seg_b ? row_b : 0;                  // this block's rows of the segment: [run_lo, run_hi)
+    const int run_hi = ord == seg_e ? row_e : seg_rows;           // (a multiple of 64, or the segment's end)
+    if (run_lo >= run_hi) continue;                               // (uniform over the block)
+    const int seg = seg_of_ordinal(ord, per, layer_begin, sh);
+    const int64_t seg_start = PAGED ? (int64_t)seg * pt.max_pps : (PLANNED ? c.seg_start[seg] : (int64_t)s_start[ord]);
     reset();
     {   // query fragments: lane (query c16, k-group b4), MFMA step j covers elements (4j + b4)*E ..
         const int seq = seg / sh.segs_per_seq, lh = seg % sh.segs_per_seq;
@@ -204,33 +300,23 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, const 
             qf[j] = c16 < G ? reinterpret_cast<const vec*>(q + qrow * D)[4 * j + b4] : F::zero();
         t_now = SOFT ? now[seq] : 0;
     }
-    const int ch_first = c0 + run_lo / chunk, ch_last = min(c1 - 1, c0 + (run_hi - 1) / chunk);
-    for (int ch = ch_first; ch <= ch_last; ++ch) {
-    const ChunkDesc cd = ws.att_desc[ch];
-    int4 pgs = make_int4(0, 0, 0, 0);
-    if (PAGED) pgs = reinterpret_cast<const int4*>(ws.att_pages)[ch];   // the chunk's pages, beside its descriptor
-    const int ch_row0 = (ch - c0) * chunk;                        // the chunk's first row in the segment's numbering
-    const int row_end = cd.n;                                     // the chunk's rows are [0, n) counted from cd.first ...
-    const int off = max(run_lo - ch_row0, 0), row_stop = min(row_end, run_hi - ch_row0);   // ... and this block's are [off, row_stop)
-    const int64_t base = cd.first;
-
-    // PAGED: the (at most four) pages of the run come from the plan's table beside the descriptors, so no
-    // load of the loop waits for a look-up in the block table
-    int pg0 = 0, pg1 = 0, pg2 = 0, pg3 = 0;
+    const int last = seg_rows - 1;
+    // PAGED: lane l holds the pool page of the segment's page win / 128 + l, so that no load of a tile waits for a look-up in
+    // the block table; a run of more than 64 pages is walked in windows of 64
+    constexpr int WINDOW = 64 * KVTRIM_PAGE_SIZE;
+    int win = PAGED ? run_lo & ~(KVTRIM_PAGE_SIZE - 1) : 0;
+    do {
+    const int win_hi = PAGED ? min(run_hi, win + WINDOW) : run_hi;
+    int pg_mine = 0;
     if (PAGED) {
-        const int np = row_end >> 7, hi = (int)(c.cap >> 7) - 1;
-        pg0 = min(max(pgs.x, 0), hi);
-        pg1 = np > 1 ? min(max(pgs.y, 0), hi) : 0;
-        pg2 = np > 2 ? min(max(pgs.z, 0), hi) : 0;
-        pg3 = np > 3 ? min(max(pgs.w, 0), hi) : 0;
+        const int pg = pt.block_table[seg_start + min(win / KVTRIM_PAGE_SIZE + lane, seg_rows / KVTRIM_PAGE_SIZE - 1)];
+        pg_mine = min(max(pg, 0), pt.n_pages - 1);                // (clamped: no reader leaves the pool)
+        if (pg != pg_mine) atomicOr(ws.err, ERR_LAYOUT);
     }
-
-    for (int r0 = off + wave * 16; r0 < row_stop; r0 += 64) {
-        const int last = row_end - 1;
-        int64_t rbase = base;                                     // entry of row 0 in this 16-row group's numbering
-        if (PAGED) {                                              // 16 | page size: the group lies in one page
-            const int pi = r0 >> 7;
-            const int pg = pi == 0 ? pg0 : (pi == 1 ? pg1 : (pi == 2 ? pg2 : pg3));
+    for (int r0 = max(run_lo, win) + wave * 16; r0 < win_hi; r0 += ATT_ROUND) {
+        int64_t rbase = seg_start;                                // entry of row 0 in this 16-row group's numbering
+        if (PAGED) {                                              // 16 | page size: the group lies in one page, the same for all lanes
+            const int pg = __builtin_amdgcn_readlane(pg_mine, (r0 - win) / KVTRIM_PAGE_SIZE);
             rbase = (int64_t)pg * KVTRIM_PAGE_SIZE - (r0 & ~(KVTRIM_PAGE_SIZE - 1));
         }
         // K in MFMA operand layout: lane -> row r0 + c16, vectors 4j + b4
@@ -241,10 +327,15 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, const 
         // V coalesced: lane -> row r0 + 4*b4 + i, vector c16
 #pragma unroll
         for (int i = 0; i < 4; ++i) vf[i] = F::ld(vp + (rbase + min(r0 + 4 * b4 + i, last)) * VPR + c16);
-        int ps[4] = {0, 0, 0, 0};                                 // PAGED: the positions of the lane's slots, asked for with the rows
-        if (PAGED) {
+        int ps[4] = {0, 0, 0, 0};                                 // PAGED, SOFT: the positions of the lane's slots, asked for with the rows
+        float lbv[4] = {0.f, 0.f, 0.f, 0.f};
+        if (PAGED || SOFT) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) ps[i] = c.pos[rbase + min(r0 + 4 * b4 + i, last)];
+        }
+        if (SOFT) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) lbv[i] = c.log_beta[rbase + min(r0 + 4 * b4 + i, last)];
         }
 
         float4v acc = {0.f, 0.f, 0.f, 0.f};
@@ -255,11 +346,9 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, const 
         float tmax = -INFINITY;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int row = r0 + 4 * b4 + i;
-            const int64_t e = rbase + min(row, last);
             float zi = acc[i] * scale_log2;
-            if (SOFT) zi = fmaf((float)(t_now - c.pos[e]) * c.log_beta[e], 1.4426950408889634f, zi);
-            bool valid = row < row_end;
+            if (SOFT) zi = fmaf((float)(t_now - ps[i]) * lbv[i], 1.4426950408889634f, zi);
+            bool valid = r0 + 4 * b4 + i <= last;
             if (PAGED) {                                          // an empty slot takes no part
                 valid = valid && ps[i] >= 0;
                 if (!valid) vf[i] = F::zero();
@@ -307,20 +396,21 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, const 
                                                                    __builtin_bit_cast(bf16x8, pb), o[2 * w + 1], 0, 0, 0);
         }
     }
-
-    }                                                             // (chunks of the run)
-    flush(run_slot);
+    win += WINDOW;
+    } while (PAGED && win < run_hi);                              // (windows of the run)
+    flush((int)blockIdx.x + ord);
     }                                                             // (segments of the block)
 }
 
-// One block per segment of the layer range: merges the partial results of its chunks, a tile
-// of COMB_TILE chunks at a time.  Phase A brings the tile's (m, l) pairs into LDS and turns
-// them into weights 2^(m - M); phase B lets every thread sum "its" (query head, d) column over
-// the tile with loads that do not depend on each other, so all of them are in flight at once.
-constexpr int COMB_TILE = 128;
+// Merges the partial results of every segment of the layer range.  A block of 512 threads is 512 / D groups of D threads;
+// HB query heads of a segment share a block, RG groups share a head.  Every thread owns one column of its head and every
+// RG-th partial result; a tile's columns are asked for together with the (m, l) pairs of its results - which every
+// wavefront turns into the weights 2^(m - M) by itself, a lane per result - so a tile costs one round of loads and no
+// barrier; the groups of a head meet in LDS once, at the end.  (With all heads in a block and three barriers per tile
+// the loads went in batches of eight: 5.8 us for the 70 results of a segment in a one-layer call, now 4.5.)
 constexpr int COMB_THREADS = 512;
-static_assert(COMB_THREADS / 64 >= 8, "one wavefront of the merge kernel per query head of a group");
-// Housekeeping that nothing in this launch reads rides behind the merging blocks of the grid, so that it needs no
+constexpr int COMB_LOADS = 16;                                    // partial results of a tile per thread
+// Housekeeping that nothing in this launch reads rides beside the merging blocks of the grid, so that it needs no
 // launch of its own:
 //   EXTRA_TIDY (the paged decode step in one call): one block per segment takes the pages emptied by the step's
 //              eviction out of the segment's block table;
@@ -333,277 +423,234 @@ struct CombineExtra {
     const int32_t* kept;
 };
 
-// PERSIST: the partial results come from k_att_partial's fixed grid of persist_nb blocks - one per (block, segment)
-// run, at the slot of the run's first chunk or, for a run that starts inside a chunk, at slot extra_base + block -
-// and not one per chunk (the fused row mover's partials).
-template <int D, int EXTRA, bool PERSIST>
+// RUNS: the partial results come from k_att_partial launched with `runs_nb` blocks, one per (block, segment) run; else
+// one per chunk of the fused row mover (chunk_prefix).
+template <int D, int HB, int EXTRA, bool RUNS>
 __global__ __launch_bounds__(COMB_THREADS) void k_att_combine(Shape sh, Workspace ws,
                                                               const int32_t* __restrict__ chunk_prefix,
-                                                              int layer_begin, int layer_end,
+                                                              int layer_begin, int per,
                                                               float* __restrict__ out, float* __restrict__ lse,
-                                                              CombineExtra ex, int persist_nb, int round_rows,
-                                                              int chunk_rows, int extra_base) {
-    __shared__ float s_m[COMB_TILE][8], s_w[COMB_TILE][8], s_l[COMB_TILE][8];
-    __shared__ float s_M[8], s_a[8], s_L[8];
-    const int G = sh.group;
-    const int nl = layer_end - layer_begin;
-    const int per = nl * sh.n_kv_heads;
-    if (EXTRA != EXTRA_NONE && (int)blockIdx.x >= sh.n_seq * per) {
-        const int xb = (int)blockIdx.x - sh.n_seq * per;
-        if (EXTRA == EXTRA_TIDY) tidy_segment<COMB_THREADS>(ex.tidy, xb, ws.err);
-        if (EXTRA == EXTRA_UNSTAGE) unstage_chunk<D>(ex.c, ex.stage, ex.kept, sh, ws, xb * (COMB_THREADS / 64) + (int)(threadIdx.x >> 6));
+                                                              CombineExtra ex, int runs_nb) {
+    constexpr int EG = COMB_THREADS / D;                          // groups of threads: 4 (D = 128) or 8 (D = 64)
+    constexpr int RG = EG / HB;                                   // ... that share a head
+    constexpr int TILE = RG * COMB_LOADS;                         // partial results per tile: 16 to 128
+    constexpr int TW = (TILE + 63) / 64;                          // ... per lane of a wavefront
+    __shared__ float s_acc[EG][D];
+    const int G = sh.group, n_in = sh.n_seq * per, gb = (G + HB - 1) / HB, nmerge = n_in * gb;
+    int mb = (int)blockIdx.x;                                     // which merge
+    if (EXTRA == EXTRA_TIDY) {                                    // (in front: a tidying block takes longer than a merging one)
+        if (mb < sh.nseg) {
+            tidy_segment<COMB_THREADS>(ex.tidy, mb, ws.err);
+            return;
+        }
+        mb -= sh.nseg;
+    }
+    if (EXTRA == EXTRA_UNSTAGE && mb >= nmerge) {
+        unstage_chunk<D>(ex.c, ex.stage, ex.kept, sh, ws, (mb - nmerge) * (COMB_THREADS / 64) + (int)(threadIdx.x >> 6));
         return;
     }
-    const int seq = blockIdx.x / per, r = blockIdx.x % per;
-    const int layer = layer_begin + r / sh.n_kv_heads, head = r % sh.n_kv_heads;
-    const int seg = (seq * sh.n_layers + layer) * sh.n_kv_heads + head;
-    if (__hip_atomic_load(ws.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;   // tables may be stale
-    const int c0 = chunk_prefix[seg];
-    const int c1 = min(chunk_prefix[seg + 1], (int)ws.max_att_chunks);
-    const int64_t hq0 = ((int64_t)seq * sh.n_layers + layer) * sh.n_q_heads + (int64_t)head * G;
-    const float LN2 = 0.6931471805599453f;
-    constexpr int PAIRS = (8 * D + COMB_THREADS - 1) / COMB_THREADS;   // (query head, d) pairs per thread, G <= 8
-    const int tid = threadIdx.x;
-    float acc[PAIRS];
-#pragma unroll
-    for (int p = 0; p < PAIRS; ++p) acc[p] = 0.f;
-    if (tid < 8) {
-        s_M[tid] = -INFINITY;
-        s_L[tid] = 0.f;
-    }
-    const size_t stride = (size_t)G * (D + 2);
-    // entries to merge: entry e sits at slot_of(e).  PERSIST: block b of the attention kernel started at row b N / nb of
-    // the concatenated segments (ws.att_row_prefix), rounded down to a multiple of round_rows inside its segment, and
-    // ended where block b + 1 started.  The blocks that had rows of this segment are b0 - the last one that starts at
-    // or before the segment's first row - up to b1, the last one that starts inside it; each left one partial result:
-    // b0 at slot c0, a later one at the slot of the chunk it started with or, if it started inside a chunk, at its own
-    // extra slot.  (A block whose start and end round to the same row had nothing to do: weight zero.)
-    int n = c1 - c0, b0 = 0, nb = 1;
-    int64_t N = 0, r0s = 0, r1s = 0;                              // rows of all segments / before this one / up to its end
-    if (PERSIST) {
-        const int64_t total = chunk_prefix[sh.nseg];
-        N = ws.att_row_prefix[sh.nseg];
-        r0s = ws.att_row_prefix[seg];
-        r1s = ws.att_row_prefix[seg + 1];
-        nb = (int)min((int64_t)persist_nb, total);
-        if (c1 > c0 && r1s > r0s) {
-            const int64_t lim0 = min(r0s + round_rows, r1s);      // starts below this row round down to the segment's first
+    const int tid = threadIdx.x, lane = lane_id(), d = tid % D;
+    const int eg = __builtin_amdgcn_readfirstlane(tid / D), rg = eg / HB;   // (64 divides D: the same in all lanes of a wavefront)
+    const int ord = mb / gb, g = mb % gb * HB + eg % HB;          // (a head past the last one: nothing to merge)
+    const int seg = seg_of_ordinal(ord, per, layer_begin, sh);
+    const int err = __hip_atomic_load(ws.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // The results of the segment sit at the slots base, base + 1, ... (n of them).  RUNS: block b of the attention kernel
+    // started at row b N / nb of the concatenated segments (ws.att_row_prefix), rounded down to a multiple of ATT_ROUND
+    // inside its segment, and ended where block b + 1 started.  The blocks that had rows of this segment are b0 - the last
+    // one that starts at or before the segment's first row - up to the last one that starts inside it; each left one
+    // partial result, at slot block + ordinal.
+    int base, n;
+    if (RUNS) {
+        const int64_t N = ws.att_row_prefix[n_in], r0s = ws.att_row_prefix[ord], r1s = ws.att_row_prefix[ord + 1];
+        const int64_t nb = min((int64_t)runs_nb, max(N / ATT_ROUND, (int64_t)1));
+        int b0 = 0;
+        n = 0;
+        if (r1s > r0s) {
+            const int64_t lim0 = min(r0s + ATT_ROUND, r1s);       // starts below this row round down to the segment's first
             b0 = (int)((lim0 * nb + N - 1) / N) - 1;
-            n = (int)((r1s * nb + N - 1) / N) - 1 - b0 + 1;
-        } else {
-            n = 0;
+            n = (int)((r1s * nb + N - 1) / N) - b0;
         }
+        base = b0 + ord;
+    } else {
+        base = chunk_prefix[seg];
+        n = min(chunk_prefix[seg + 1], (int)ws.max_att_chunks) - base;
     }
-    __shared__ int s_slot[PERSIST ? COMB_TILE : 1];               // PERSIST: the slots of the tile's entries (-1: nothing there)
-    auto slot_of = [&](int e) -> int {
-        if (!PERSIST) return c0 + e;
-        if (e == 0) return c0;
-        const int b = b0 + e;
-        const int64_t eb = (int64_t)b * N / nb, en = (int64_t)(b + 1) * N / nb;
-        const int row = (int)(eb - r0s) / round_rows * round_rows;
-        if (en < r1s && (int)(en - r0s) / round_rows * round_rows == row) return -1;   // an empty share
-        return row % chunk_rows == 0 ? c0 + row / chunk_rows : extra_base + b;
-    };
-    for (int t0 = 0; t0 < n; t0 += COMB_TILE) {
-        const int nt = min(COMB_TILE, n - t0);
-        __syncthreads();
-        for (int i = tid; i < nt * G; i += COMB_THREADS) {
-            const int slot = slot_of(t0 + i / G);
-            if (PERSIST && i % G == 0) s_slot[i / G] = max(slot, c0);           // (an empty share: any slot, with weight zero)
-            const float* p = ws.att_partial + (size_t)max(slot, c0) * stride + (size_t)(i % G) * (D + 2);
-            s_m[i / G][i % G] = slot < 0 ? -INFINITY : p[0];
-            s_l[i / G][i % G] = slot < 0 ? 0.f : p[1];
-        }
-        __syncthreads();
-        const int wv = tid >> 6, ln = tid & 63;                    // wavefront g of the block serves query head g (G <= 8 wavefronts)
-        if (wv < G) {                                             // running maximum and rescale factor per query head
-            float tm = -INFINITY;
-            for (int i = ln; i < nt; i += 64) tm = fmaxf(tm, s_m[i][wv]);
+    if (err != 0) return;                                         // the tables may be stale
+    if (g >= G) n = 0;
+    const size_t stride = (size_t)G * (D + 2);
+    const float* part = ws.att_partial + (size_t)g * (D + 2);
+    float acc = 0.f, M = -INFINITY, L = 0.f;
+    for (int t0 = 0; t0 < n; t0 += TILE) {
+        float m[TW], l[TW], x[COMB_LOADS];
 #pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) tm = fmaxf(tm, __shfl_xor(tm, d, 64));
-            if (ln == 0) {
-                const float old = s_M[wv];
-                tm = fmaxf(tm, old);
-                const float ms = tm == -INFINITY ? 0.f : tm;
-                s_a[wv] = __builtin_amdgcn_exp2f(old - ms);
-                s_M[wv] = tm;
-            }
-        }
-        __syncthreads();
-        for (int i = tid; i < nt * G; i += COMB_THREADS) {
-            const float M = s_M[i % G];
-            s_w[i / G][i % G] = __builtin_amdgcn_exp2f(s_m[i / G][i % G] - (M == -INFINITY ? 0.f : M));
-        }
-        __syncthreads();
-        if (wv < G) {
-            float lv = 0.f;
-            for (int i = ln; i < nt; i += 64) lv += s_l[i][wv] * s_w[i][wv];
-#pragma unroll
-            for (int d = 32; d >= 1; d >>= 1) lv += __shfl_xor(lv, d, 64);
-            if (ln == 0) s_L[wv] = s_L[wv] * s_a[wv] + lv;
+        for (int w = 0; w < TW; ++w) {
+            const int e = t0 + w * 64 + lane;
+            const bool in = e < n && (TILE >= 64 || lane < TILE);
+            const float* p = part + (size_t)(base + min(e, n - 1)) * stride;
+            const float mm = p[0], ll = p[1];
+            m[w] = in ? mm : -INFINITY;
+            l[w] = in ? ll : 0.f;
         }
 #pragma unroll
-        for (int p = 0; p < PAIRS; ++p) {
-            const int idx = tid + p * COMB_THREADS;
-            if (idx >= G * D) break;
-            const int g = idx / D, d = idx % D;
-            const float* base = ws.att_partial + (size_t)g * (D + 2) + 2 + d;
-            float av = acc[p] * s_a[g];
-            int i = 0;
-            for (; i + 8 <= nt; i += 8) {
-                float x[8];
+        for (int u4 = 0; u4 < COMB_LOADS; u4 += 4) {              // result t0 + u RG + rg; past the last one: that one, with weight zero
+            if (t0 + u4 * RG < n) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = base[(size_t)(PERSIST ? s_slot[i + u] : c0 + t0 + i + u) * stride];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) av = fmaf(x[u], s_w[i + u][g], av);
-            }
-            if (PERSIST) {                                        // (a handful of entries: all of them in flight at once)
-                float x[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) x[u] = base[(size_t)s_slot[min(i + u, nt - 1)] * stride];
-#pragma unroll
-                for (int u = 0; u < 8; ++u)
-                    if (i + u < nt) av = fmaf(x[u], s_w[i + u][g], av);
+                for (int u = u4; u < u4 + 4; ++u) x[u] = part[(size_t)(base + min(t0 + u * RG + rg, n - 1)) * stride + 2 + d];
             } else {
-                for (; i < nt; ++i) av = fmaf(base[(size_t)(c0 + t0 + i) * stride], s_w[i][g], av);
+#pragma unroll
+                for (int u = u4; u < u4 + 4; ++u) x[u] = 0.f;
             }
-            acc[p] = av;
+        }
+        float tm = m[0];
+#pragma unroll
+        for (int w = 1; w < TW; ++w) tm = fmaxf(tm, m[w]);
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) tm = fmaxf(tm, __shfl_xor(tm, s, 64));
+        const float Mn = fmaxf(M, tm), ms = Mn == -INFINITY ? 0.f : Mn;
+        const float alpha = __builtin_amdgcn_exp2f(M - ms);       // (M = -inf gives 0; acc and L are 0 then)
+        float lv = 0.f;
+#pragma unroll
+        for (int w = 0; w < TW; ++w) {
+            m[w] = __builtin_amdgcn_exp2f(m[w] - ms);             // the weight of result t0 + w 64 + lane
+            lv += l[w] * m[w];
+        }
+#pragma unroll
+        for (int s = 32; s >= 1; s >>= 1) lv += __shfl_xor(lv, s, 64);
+        L = L * alpha + lv;
+        M = Mn;
+        acc *= alpha;
+#pragma unroll
+        for (int u = 0; u < COMB_LOADS; ++u) {
+            const int e = u * RG + rg;                            // (rg < RG, which divides 64: e / 64 = u RG / 64)
+            acc = fmaf(x[u], __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(m[u * RG / 64]), e & 63)), acc);
         }
     }
-    __syncthreads();
+    if (RG > 1) {
+        s_acc[eg][d] = acc;
+        __syncthreads();
+        if (rg == 0) {
 #pragma unroll
-    for (int p = 0; p < PAIRS; ++p) {
-        const int idx = tid + p * COMB_THREADS;
-        if (idx >= G * D) break;
-        const int g = idx / D, d = idx % D;
-        const float L = s_L[g];
-        out[(hq0 + g) * D + d] = L > 0.f ? acc[p] / L : 0.f;
-        if (d == 0 && lse) lse[hq0 + g] = L > 0.f ? (s_M[g] + __builtin_amdgcn_logf(L)) * LN2 : -INFINITY;
+            for (int k = 1; k < RG; ++k) acc += s_acc[k * HB + eg][d];
+        }
     }
+    if (rg != 0 || g >= G) return;
+    const int seq = seg / sh.segs_per_seq, layer = (seg % sh.segs_per_seq) / sh.n_kv_heads, head = seg % sh.n_kv_heads;
+    const int64_t hq = ((int64_t)seq * sh.n_layers + layer) * sh.n_q_heads + (int64_t)head * G + g;
+    out[hq * D + d] = L > 0.f ? acc / L : 0.f;
+    if (d == 0 && lse) lse[hq] = L > 0.f ? (M + __builtin_amdgcn_logf(L)) * 0.6931471805599453f : -INFINITY;
 }
 
-template <int D, int G>
-static void launch_partial(const CacheView& c, const uint16_t* q, const Shape& sh, const Workspace& ws,
-                           int chunk, float scale_log2, const int32_t* now, bool paged, unsigned blocks,
-                           int round_rows, int extra_base, hipStream_t st) {
-    if (paged)
-        hipLaunchKernelGGL((k_att_partial<D, G, false, true>), dim3(blocks), dim3(ATT_THREADS), 0, st, c, q, sh, ws, chunk, scale_log2, now, round_rows, extra_base);
-    else if (now)
-        hipLaunchKernelGGL((k_att_partial<D, G, true, false>), dim3(blocks), dim3(ATT_THREADS), 0, st, c, q, sh, ws, chunk, scale_log2, now, round_rows, extra_base);
+// What a call of the attention kernel needs: the segments of its layer range, the grid, the LDS for the row prefix.
+struct AttCall {
+    int layer_begin, per, n_in, nb;
+    bool planned;
+    size_t lds;
+};
+static AttCall att_call(const kvtrim_ctx* ctx, int64_t cap, int32_t layer_begin, int32_t layer_end, bool paged) {
+    AttCall a;
+    a.layer_begin = layer_begin;
+    a.per = (layer_end - layer_begin) * ctx->shape.n_kv_heads;
+    a.n_in = ctx->shape.n_seq * a.per;
+    // a block per round of 64 rows at most, and a slot per block and segment in the partial-result buffer
+    int64_t nb = cap / ATT_ROUND + 1;
+    if (nb > ctx->att_blocks) nb = ctx->att_blocks;
+    if (nb > ctx->ws.att_slots - a.n_in) nb = ctx->ws.att_slots - a.n_in;
+    a.nb = (int)nb;
+    a.planned = a.n_in > ATT_SCAN_SEGS;
+    a.lds = a.planned ? 0 : ((size_t)(paged ? 1 : 2) * a.n_in + 1) * sizeof(int32_t);
+    return a;
+}
+
+template <int D, int G, bool SOFT, bool PAGED>
+static void launch_partial(const AttCall& a, const CacheView& c, const AttPages& pt, const uint16_t* q, const Shape& sh,
+                           const Workspace& ws, float scale_log2, const int32_t* now, hipStream_t st) {
+    if (a.planned)
+        hipLaunchKernelGGL((k_att_partial<D, G, SOFT, PAGED, true>), dim3(a.nb), dim3(ATT_THREADS), a.lds, st, c, pt, q, sh, ws, scale_log2, now, a.layer_begin, a.per, a.n_in);
     else
-        hipLaunchKernelGGL((k_att_partial<D, G, false, false>), dim3(blocks), dim3(ATT_THREADS), 0, st, c, q, sh, ws, chunk, scale_log2, now, round_rows, extra_base);
+        hipLaunchKernelGGL((k_att_partial<D, G, SOFT, PAGED, false>), dim3(a.nb), dim3(ATT_THREADS), a.lds, st, c, pt, q, sh, ws, scale_log2, now, a.layer_begin, a.per, a.n_in);
 }
 
 template <int D>
-static bool dispatch_partial(int G, const CacheView& c, const uint16_t* q, const Shape& sh, const Workspace& ws,
-                             int chunk, float scale_log2, const int32_t* now, bool paged, unsigned blocks,
-                             int round_rows, int extra_base, hipStream_t st) {
-    switch (G) {
-#define KVTRIM_CASE(g) case g: launch_partial<D, g>(c, q, sh, ws, chunk, scale_log2, now, paged, blocks, round_rows, extra_base, st); return true;
+static bool dispatch_partial(const AttCall& a, const CacheView& c, const AttPages* pages, const uint16_t* q, const Shape& sh,
+                             const Workspace& ws, float scale_log2, const int32_t* now, hipStream_t st) {
+    const AttPages pt = pages ? *pages : AttPages{};
+    switch (sh.group) {
+#define KVTRIM_CASE(g)                                                                                          \
+    case g:                                                                                                     \
+        if (pages) launch_partial<D, g, false, true>(a, c, pt, q, sh, ws, scale_log2, now, st);                 \
+        else if (now) launch_partial<D, g, true, false>(a, c, pt, q, sh, ws, scale_log2, now, st);              \
+        else launch_partial<D, g, false, false>(a, c, pt, q, sh, ws, scale_log2, now, st);                      \
+        return true;
         KVTRIM_CASE(1) KVTRIM_CASE(2) KVTRIM_CASE(3) KVTRIM_CASE(4) KVTRIM_CASE(5) KVTRIM_CASE(6) KVTRIM_CASE(7) KVTRIM_CASE(8)
 #undef KVTRIM_CASE
         default: return false;
     }
 }
 
-// The fixed grid of k_att_partial for a table of at most max_chunks chunks of `chunk` rows: nb blocks, whose shares
-// start at multiples of 64 rows when the partial-result buffer has nb slots to spare behind the chunks' own (for the
-// runs that start inside a chunk), else at whole chunks.
-struct AttGrid {
-    int nb, round_rows, chunk_rows, extra_base;
-};
-static AttGrid att_grid(const kvtrim_ctx* ctx, int64_t max_chunks, int chunk) {
-    AttGrid g;
-    g.nb = (int)(max_chunks < ctx->att_blocks ? max_chunks : ctx->att_blocks);
-    g.extra_base = (int)max_chunks;
-    g.chunk_rows = chunk;
-    g.round_rows = max_chunks + g.nb <= ctx->ws.max_att_chunks && chunk % 64 == 0 ? 64 : chunk;
-    return g;
-}
-
-int att_chunk_for(const kvtrim_ctx* ctx, int64_t cap) {
-    int64_t chunk = (cap / 16384 + 63) / 64 * 64;
-    return (int)(chunk < ctx->att_chunk_min ? ctx->att_chunk_min : chunk);
-}
-
-kvtrim_status launch_attn(kvtrim_ctx* ctx, const CacheView& c, const uint16_t* q, const int32_t* soft_now,
-                          int32_t layer_begin, int32_t layer_end, float scale, float* out, float* lse,
-                          hipStream_t st) {
+// The merge kernel, of about `results` partial results in all: extra_blocks more blocks do the housekeeping named by EXTRA.
+template <int EXTRA, bool RUNS>
+static kvtrim_status launch_merge(kvtrim_ctx* ctx, const int32_t* chunk_prefix, int32_t layer_begin, int32_t layer_end, float* out,
+                                  float* lse, int64_t results, const CombineExtra& ex, int64_t extra_blocks, int runs_nb, hipStream_t st) {
     const Shape& sh = ctx->shape;
-    const Workspace& ws = ctx->ws;
-    const int chunk = att_chunk_for(ctx, c.cap);
-    const int64_t max_chunks = c.cap / chunk + sh.nseg;
-    const AttGrid ag = att_grid(ctx, max_chunks, chunk);
-    const int nb = ag.nb;
+    const int per = (layer_end - layer_begin) * sh.n_kv_heads;
+    // A head to a block, its threads sharing the results, where that fits the chip at once (1024 blocks) and a segment has
+    // a round of loads: 256 segments of 64 results, 4 heads: 11.1 us against 14.0 with the heads side by side in a block.
+    // Else heads side by side: 256 segments of 4 results (the paged step) 5.0 us against 7.5; 960 segments of 10 (2 heads,
+    // D = 64) 5.8 us against 9.  With the unstaging wavefronts behind them the merging blocks must leave them room
+    // (256 segments of 32 results: 10.2 us against 11.6).
+    const int64_t n_in = (int64_t)sh.n_seq * per;
+    const bool one = n_in * sh.group <= (EXTRA == EXTRA_UNSTAGE ? 256 : 1024) && results / n_in >= COMB_LOADS;
+    const int hb = one || sh.group == 1 ? 1 : (sh.group == 2 ? 2 : 4);
+    const unsigned nblk = (unsigned)(n_in * ((sh.group + hb - 1) / hb) + extra_blocks);
+    ProfScope prof(ctx, K_ATT_COMBINE, st);
+#define KVTRIM_CASE(D, HB) hipLaunchKernelGGL((k_att_combine<D, HB, EXTRA, RUNS>), dim3(nblk), dim3(COMB_THREADS), 0, st, sh, ctx->ws, chunk_prefix, layer_begin, per, out, lse, ex, runs_nb)
+    if (sh.head_dim == 128) {
+        if (hb == 1) KVTRIM_CASE(128, 1);
+        else if (hb == 2) KVTRIM_CASE(128, 2);
+        else KVTRIM_CASE(128, 4);
+    } else {
+        if (hb == 1) KVTRIM_CASE(64, 1);
+        else if (hb == 2) KVTRIM_CASE(64, 2);
+        else KVTRIM_CASE(64, 4);
+    }
+#undef KVTRIM_CASE
+    KVTRIM_HIP(ctx, hipGetLastError());
+    return KVTRIM_OK;
+}
+
+// Attention over a ragged cache (pages == NULL; soft_now: the soft form) or over the pages of a paged one (c: the
+// pool).  tidy: the merge kernel's launch also takes the pages that an eviction emptied out of the block tables.
+kvtrim_status launch_attn(kvtrim_ctx* ctx, const CacheView& c, const AttPages* pages, const uint16_t* q, const int32_t* soft_now,
+                          int32_t layer_begin, int32_t layer_end, float scale, float* out, float* lse, hipStream_t st,
+                          const PagedView* tidy) {
+    const Shape& sh = ctx->shape;
+    const AttCall a = att_call(ctx, c.cap, layer_begin, layer_end, pages != nullptr);
     const float scale_log2 = scale * 1.4426950408889634f;
-    { ProfScope prof(ctx, K_ATT_PLAN, st);
-      hipLaunchKernelGGL(k_att_plan, dim3(ATT_PLAN_BLOCKS), dim3(1024), 0, st, c, sh, ws, chunk, layer_begin, layer_end, max_chunks); }
+    if (a.planned) {
+        ProfScope prof(ctx, pages ? K_PG_ATT_PLAN : K_ATT_PLAN, st);
+        if (pages)
+            hipLaunchKernelGGL(k_att_plan<true>, dim3(1), dim3(1024), 0, st, c, *pages, sh, ctx->ws, a.layer_begin, a.per, a.n_in);
+        else
+            hipLaunchKernelGGL(k_att_plan<false>, dim3(1), dim3(1024), 0, st, c, AttPages{}, sh, ctx->ws, a.layer_begin, a.per, a.n_in);
+    }
     bool ok;
     {
         ProfScope prof(ctx, K_ATT_PARTIAL, st);
-        ok = sh.head_dim == 128
-                  ? dispatch_partial<128>(sh.group, c, q, sh, ws, chunk, scale_log2, soft_now, false, (unsigned)nb, ag.round_rows, ag.extra_base, st)
-                  : dispatch_partial<64>(sh.group, c, q, sh, ws, chunk, scale_log2, soft_now, false, (unsigned)nb, ag.round_rows, ag.extra_base, st);
+        ok = sh.head_dim == 128 ? dispatch_partial<128>(a, c, pages, q, sh, ctx->ws, scale_log2, soft_now, st)
+                                : dispatch_partial<64>(a, c, pages, q, sh, ctx->ws, scale_log2, soft_now, st);
     }
     if (!ok) return KVTRIM_EINVAL;
-    return launch_combine(ctx, ws.att_chunk_prefix, layer_begin, layer_end, out, lse, st, nb, ag.round_rows, ag.chunk_rows, ag.extra_base);
-}
-
-// Attention over the page runs listed in ws.att_desc / ws.att_chunk_prefix (built by the paged plan
-// kernel; the pages themselves are looked up in block_table): one block per run, then the
-// per-segment merge.
-kvtrim_status launch_attn_paged(kvtrim_ctx* ctx, const CacheView& pool, const int32_t* block_table, const uint16_t* q,
-                                int max_chunks, int32_t layer_begin, int32_t layer_end, float scale, float* out,
-                                float* lse, hipStream_t st, const PagedView* tidy) {
-    const Shape& sh = ctx->shape;
-    Workspace ws = ctx->ws;
-    ws.pg_block_table = block_table;
-    constexpr int chunk = ATT_PAGE_GROUP * KVTRIM_PAGE_SIZE;
-    const AttGrid ag = att_grid(ctx, max_chunks, chunk);
-    const int nb = ag.nb;
-    const float scale_log2 = scale * 1.4426950408889634f;
-    bool ok;
-    {
-        ProfScope prof(ctx, K_ATT_PARTIAL, st);
-        ok = sh.head_dim == 128
-                 ? dispatch_partial<128>(sh.group, pool, q, sh, ws, chunk, scale_log2, nullptr, true, (unsigned)nb, ag.round_rows, ag.extra_base, st)
-                 : dispatch_partial<64>(sh.group, pool, q, sh, ws, chunk, scale_log2, nullptr, true, (unsigned)nb, ag.round_rows, ag.extra_base, st);
-    }
-    if (!ok) return KVTRIM_EINVAL;
-    if (!tidy) return launch_combine(ctx, ws.att_chunk_prefix, layer_begin, layer_end, out, lse, st, nb, ag.round_rows, ag.chunk_rows, ag.extra_base);
-    // the merge, and in the same launch one block per segment that tidies its block table
+    if (!tidy) return launch_merge<EXTRA_NONE, true>(ctx, nullptr, layer_begin, layer_end, out, lse, a.nb, CombineExtra{}, 0, a.nb, st);
     CombineExtra ex{};
     ex.tidy = *tidy;
-    const unsigned nblk = (unsigned)(sh.n_seq * (layer_end - layer_begin) * sh.n_kv_heads + sh.nseg);
-    ProfScope prof(ctx, K_ATT_COMBINE, st);
-    if (sh.head_dim == 128)
-        hipLaunchKernelGGL((k_att_combine<128, EXTRA_TIDY, true>), dim3(nblk), dim3(COMB_THREADS), 0, st, sh, ws, ws.att_chunk_prefix, layer_begin, layer_end, out, lse, ex, nb, ag.round_rows, ag.chunk_rows, ag.extra_base);
-    else
-        hipLaunchKernelGGL((k_att_combine<64, EXTRA_TIDY, true>), dim3(nblk), dim3(COMB_THREADS), 0, st, sh, ws, ws.att_chunk_prefix, layer_begin, layer_end, out, lse, ex, nb, ag.round_rows, ag.chunk_rows, ag.extra_base);
-    KVTRIM_HIP(ctx, hipGetLastError());
-    return KVTRIM_OK;
+    return launch_merge<EXTRA_TIDY, true>(ctx, nullptr, layer_begin, layer_end, out, lse, a.nb, ex, sh.nseg, a.nb, st);
 }
 
-// Merges the per-chunk partial results in ws.att_partial; chunk_prefix[g] .. chunk_prefix[g+1]
-// are the chunks of segment g.
+// Merges the partial results that the fused row mover left in ws.att_partial, one per chunk; chunk_prefix[g] ..
+// chunk_prefix[g+1] are the chunks of segment g, about max_chunks in all.
 kvtrim_status launch_combine(kvtrim_ctx* ctx, const int32_t* chunk_prefix, int32_t layer_begin,
-                             int32_t layer_end, float* out, float* lse, hipStream_t st, int persist_nb, int round_rows,
-                             int chunk_rows, int extra_base) {
-    const Shape& sh = ctx->shape;
-    const Workspace& ws = ctx->ws;
-    const unsigned nblk = (unsigned)(sh.n_seq * (layer_end - layer_begin) * sh.n_kv_heads);
-    ProfScope prof(ctx, K_ATT_COMBINE, st);
-    if (persist_nb > 0) {
-        if (sh.head_dim == 128)
-            hipLaunchKernelGGL((k_att_combine<128, EXTRA_NONE, true>), dim3(nblk), dim3(COMB_THREADS), 0, st, sh, ws, chunk_prefix, layer_begin, layer_end, out, lse, CombineExtra{}, persist_nb, round_rows, chunk_rows, extra_base);
-        else
-            hipLaunchKernelGGL((k_att_combine<64, EXTRA_NONE, true>), dim3(nblk), dim3(COMB_THREADS), 0, st, sh, ws, chunk_prefix, layer_begin, layer_end, out, lse, CombineExtra{}, persist_nb, round_rows, chunk_rows, extra_base);
-    } else if (sh.head_dim == 128)
-        hipLaunchKernelGGL((k_att_combine<128, EXTRA_NONE, false>), dim3(nblk), dim3(COMB_THREADS), 0, st, sh, ws, chunk_prefix, layer_begin, layer_end, out, lse, CombineExtra{}, 0, 1, 1, 0);
-    else
-        hipLaunchKernelGGL((k_att_combine<64, EXTRA_NONE, false>), dim3(nblk), dim3(COMB_THREADS), 0, st, sh, ws, chunk_prefix, layer_begin, layer_end, out, lse, CombineExtra{}, 0, 1, 1, 0);
-    KVTRIM_HIP(ctx, hipGetLastError());
-    return KVTRIM_OK;
+                             int32_t layer_end, float* out, float* lse, int64_t max_chunks, hipStream_t st) {
+    return launch_merge<EXTRA_NONE, false>(ctx, chunk_prefix, layer_begin, layer_end, out, lse, max_chunks * (layer_end - layer_begin) / ctx->shape.n_layers, CombineExtra{}, 0, 0, st);
 }
 
 // The merge after the in-place row mover: the launch also puts the rows that the mover parked in `stage` into their
@@ -611,21 +658,12 @@ kvtrim_status launch_combine(kvtrim_ctx* ctx, const int32_t* chunk_prefix, int32
 kvtrim_status launch_combine_unstage(kvtrim_ctx* ctx, const int32_t* chunk_prefix, int32_t layer_begin, int32_t layer_end,
                                      float* out, float* lse, const CacheViewMut& c, const CacheViewMut& stage,
                                      const int32_t* kept, int64_t max_chunks, hipStream_t st) {
-    const Shape& sh = ctx->shape;
-    const Workspace& ws = ctx->ws;
     CombineExtra ex{};
     ex.c = c;
     ex.stage = stage;
     ex.kept = kept;
-    const int64_t per_block = COMB_THREADS / 64;
-    const unsigned nblk = (unsigned)(sh.n_seq * (layer_end - layer_begin) * sh.n_kv_heads + (max_chunks + per_block - 1) / per_block);
-    ProfScope prof(ctx, K_ATT_COMBINE, st);
-    if (sh.head_dim == 128)
-        hipLaunchKernelGGL((k_att_combine<128, EXTRA_UNSTAGE, false>), dim3(nblk), dim3(COMB_THREADS), 0, st, sh, ws, chunk_prefix, layer_begin, layer_end, out, lse, ex, 0, 1, 1, 0);
-    else
-        hipLaunchKernelGGL((k_att_combine<64, EXTRA_UNSTAGE, false>), dim3(nblk), dim3(COMB_THREADS), 0, st, sh, ws, chunk_prefix, layer_begin, layer_end, out, lse, ex, 0, 1, 1, 0);
-    KVTRIM_HIP(ctx, hipGetLastError());
-    return KVTRIM_OK;
+    constexpr int64_t per_block = COMB_THREADS / 64;
+    return launch_merge<EXTRA_UNSTAGE, false>(ctx, chunk_prefix, layer_begin, layer_end, out, lse, max_chunks * (layer_end - layer_begin) / ctx->shape.n_layers, ex, (max_chunks + per_block - 1) / per_block, 0, st);
 }
 
 }  // namespace kvtrim

@@ -625,7 +625,7 @@ kvtrim_status launch_compact_attn(kvtrim_ctx* ctx, const CacheView& src, const u
                      : dispatch_gather<64>(sh.group, dim3((unsigned)dst_chunks), st, src, dst, q, sh, ws, scale_log2, layer_begin, layer_end);
         }
         if (!ok) return KVTRIM_EINVAL;
-        return launch_combine(ctx, ws.att_chunk_prefix, layer_begin, layer_end, out, lse, st);
+        return launch_combine(ctx, ws.att_chunk_prefix, layer_begin, layer_end, out, lse, dst_chunks, st);
     }
     if (max_chunks > ws.max_att_chunks || sparse) {
         // Run the two stages one after the other, which computes the same thing: when there are too many source
@@ -635,7 +635,7 @@ kvtrim_status launch_compact_attn(kvtrim_ctx* ctx, const CacheView& src, const u
         CacheView d;
         d.k = dst.k; d.v = dst.v; d.log_beta = dst.log_beta; d.pos = dst.pos;
         d.seg_start = dst.seg_start; d.seg_len = dst.seg_len; d.cap = dst.cap; d.log_tail = dst.log_tail;
-        return launch_attn(ctx, d, q, nullptr, layer_begin, layer_end, scale, out, lse, st);
+        return launch_attn(ctx, d, nullptr, q, nullptr, layer_begin, layer_end, scale, out, lse, st);
     }
     launch_cmp_scan(ctx, src, keep, kept, dst, reserve, st);
     bool ok;
@@ -647,7 +647,7 @@ kvtrim_status launch_compact_attn(kvtrim_ctx* ctx, const CacheView& src, const u
                  : dispatch_fused<64, false>(sh.group, dim3((unsigned)max_chunks), st, src, keep, dst, dst, q, sh, ws, scale_log2, layer_begin, layer_end);
     }
     if (!ok) return KVTRIM_EINVAL;
-    return launch_combine(ctx, ws.cmp_chunk_prefix, layer_begin, layer_end, out, lse, st);
+    return launch_combine(ctx, ws.cmp_chunk_prefix, layer_begin, layer_end, out, lse, max_chunks, st);
 }
 
 kvtrim_status launch_compact_attn_inplace(kvtrim_ctx* ctx, const CacheViewMut& c, const uint8_t* keep, const int32_t* kept,
@@ -711,7 +711,7 @@ kvtrim_status launch_decode_step(kvtrim_ctx* ctx, const CacheViewMut& srcm, cons
             default: return KVTRIM_EINVAL;
         }
     }
-    return launch_combine(ctx, ws.cmp_chunk_prefix, layer_begin, layer_end, out, lse, st);
+    return launch_combine(ctx, ws.cmp_chunk_prefix, layer_begin, layer_end, out, lse, max_chunks, st);
 }
 
 // The decode step in one call with stages 3 + 4 inside the cache: four kernels (score + resolve, move + attend, the

@@ -349,8 +349,8 @@ __global__ __launch_bounds__(1024) void k_pg_plan(PagedView pc, Shape sh, const 
             ws.tie_thr[g] = 0;
         }
     }
-    const int total = build_page_table<1>(pc, sh.nseg, [](int) { return true; }, ws.cmp_chunk_prefix, ws.cmp_desc,
-                                          ws.max_cmp_chunks, ws.sel_entry_prefix, ws.err, blockIdx.x, PG_TABLE_BLOCKS);
+    const int total = build_page_table(pc, sh.nseg, ws.cmp_chunk_prefix, ws.cmp_desc, ws.max_cmp_chunks,
+                                       ws.sel_entry_prefix, ws.err, blockIdx.x, PG_TABLE_BLOCKS);
     if (blockIdx.x != 0) return;
     if (tid < hist_blocks) {
         const int cpb = (total + hist_blocks - 1) / hist_blocks;
@@ -380,18 +380,6 @@ __global__ __launch_bounds__(1024) void k_pg_plan(PagedView pc, Shape sh, const 
         ws.seq_done[seq] = 0;
         if (thr_out) thr_out[seq] = 0xFFFFFFFFu;
     }
-}
-
-__global__ __launch_bounds__(1024) void k_pg_att_plan(PagedView pc, Shape sh, Workspace ws, int layer_begin,
-                                                      int layer_end) {
-    const int H = sh.n_kv_heads, L = sh.n_layers;
-    auto in_range = [=](int g) {
-        const int layer = (g / H) % L;
-        return layer >= layer_begin && layer < layer_end;
-    };
-    static_assert(ATT_PAGE_GROUP == 4, "ws.att_pages holds four pages per chunk");
-    build_page_table<ATT_PAGE_GROUP>(pc, sh.nseg, in_range, ws.att_chunk_prefix, ws.att_desc, ws.max_att_chunks, nullptr,
-                                     ws.err, blockIdx.x, gridDim.x, ws.att_pages, ws.att_row_prefix);
 }
 
 // Mask of the paged selection: a block takes PG_PER_BLOCK pages, a thread four consecutive slots
@@ -754,6 +742,10 @@ static CacheView pool_view(const kvtrim_paged_cache* c) {
     return v;
 }
 
+static AttPages att_pages(const kvtrim_paged_cache* c) {
+    return AttPages{c->block_table, c->seg_pages, c->seg_live, c->n_pages, c->max_pages_per_seg};
+}
+
 // what is wrong with the arguments of an attention call over pages (NULL if nothing)
 static const char* paged_attn_problem(const kvtrim_ctx* ctx, const kvtrim_paged_cache* c, const void* q, int32_t layer_begin,
                                       int32_t layer_end, float softmax_scale, const float* out) {
@@ -953,17 +945,13 @@ kvtrim_status kvtrim_paged_decode_step(kvtrim_ctx* ctx, kvtrim_paged_cache* c, c
         pg.evict_seg_live = c->seg_live;
         pg.evict_page_live = c->page_live;
         pg.evict_page_owner = c->page_owner;
-        // ... whose scoring kernel also builds the attention's chunk table; the merge kernel of the attention tidies
-        // the block tables afterwards: five kernels in all
+        // ... the merge kernel of the attention tidies the block tables afterwards: five kernels in all
         if (const char* p = paged_attn_problem(ctx, c, q, layer_begin, layer_end, softmax_scale, out)) return bad(ctx, p);
-        pg.plan_layer_begin = layer_begin;
-        pg.plan_layer_end = layer_end;
         rc = launch_score_select_paged(ctx, pool_view(c), pg, now, budget, score_out, keep_out, kept_out, thr_key_out, st, true);
         if (rc != KVTRIM_OK) return rc;
         const PagedView pv = view_of(c);
-        const int max_chunks = c->n_pages / ATT_PAGE_GROUP + ctx->shape.nseg;
-        return launch_attn_paged(ctx, pool_view(c), c->block_table, (const uint16_t*)q, max_chunks, layer_begin, layer_end,
-                                 softmax_scale, out, lse, st, &pv);
+        const AttPages pt = att_pages(c);
+        return launch_attn(ctx, pool_view(c), &pt, (const uint16_t*)q, nullptr, layer_begin, layer_end, softmax_scale, out, lse, st, &pv);
     }
     return kvtrim_paged_attn(ctx, c, q, layer_begin, layer_end, softmax_scale, out, lse, hip_stream);
 }
@@ -1007,14 +995,8 @@ kvtrim_status kvtrim_paged_attn(kvtrim_ctx* ctx, const kvtrim_paged_cache* c, co
     if (const char* p = paged_problem(ctx, c)) return bad(ctx, p);
     if (const char* p = paged_attn_problem(ctx, c, q, layer_begin, layer_end, softmax_scale, out)) return bad(ctx, p);
     hipStream_t st = (hipStream_t)hip_stream;
-    {
-        ProfScope prof(ctx, K_PG_ATT_PLAN, st);
-        hipLaunchKernelGGL(k_pg_att_plan, dim3(PG_TABLE_BLOCKS), dim3(1024), 0, st, view_of(c), ctx->shape, ctx->ws,
-                           layer_begin, layer_end);
-    }
-    const int max_chunks = c->n_pages / ATT_PAGE_GROUP + ctx->shape.nseg;   // sum over segments of ceil(pages / group)
-    return launch_attn_paged(ctx, pool_view(c), c->block_table, (const uint16_t*)q, max_chunks, layer_begin, layer_end,
-                             softmax_scale, out, lse, st);
+    const AttPages pt = att_pages(c);
+    return launch_attn(ctx, pool_view(c), &pt, (const uint16_t*)q, nullptr, layer_begin, layer_end, softmax_scale, out, lse, st);
 }
 
 }  // extern "C"

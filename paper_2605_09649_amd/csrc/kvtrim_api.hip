@@ -36,7 +36,7 @@ struct Layout {
     size_t off[41];
     int32_t fl_cap;
     size_t total;
-    int64_t max_sel_chunks, max_cmp_chunks, max_att_chunks, gat_slots;
+    int64_t max_sel_chunks, max_cmp_chunks, max_att_chunks, att_slots, gat_slots;
 };
 
 static size_t bump(size_t& cur, size_t bytes) {
@@ -52,14 +52,15 @@ static Layout layout_of(const kvtrim_config* c, bool select_only) {
     const int G = c->n_q_heads / c->n_kv_heads;
     l.max_sel_chunks = c->max_entries / SEL_CHUNK + nseg;
     l.max_cmp_chunks = select_only ? 0 : c->max_entries / CMP_CHUNK + nseg;
-    // the attention chunk grows with the capacity (att_chunk_for) so that at most 16384 full
-    // chunks plus one ragged tail per segment ever exist
-    // (the fused stage 3+4 kernel also writes one partial result per 128-entry compaction chunk;
-    // it is used for caches of up to 524288 such chunks = 67 M entries, larger ones take the two-call path;
-    // the buffer is [chunk][G][D + 2] fp32, 2 KB per chunk at G = 4, D = 128)
+    // the fused stage 3+4 kernel writes one partial result per 128-entry compaction chunk; it is used for caches of up to
+    // 524288 such chunks = 67 M entries, larger ones take the two-call path.  The stand-alone attention writes one per
+    // block (at most one per 64 rows, ATT_BLOCKS of them) and segment.  The buffer is [slot][G][D + 2] fp32, 2 KB per
+    // slot at G = 4, D = 128
     const int64_t full = c->max_entries / CMP_CHUNK < 524288 ? c->max_entries / CMP_CHUNK : 524288;
     const int64_t att = select_only ? 0 : full + nseg + 1;
     l.max_att_chunks = att;
+    const int64_t rounds = c->max_entries / 64 + 1;
+    l.att_slots = select_only ? 0 : att + (rounds < ATT_BLOCKS ? rounds : ATT_BLOCKS);
     const size_t seg_tables = select_only ? 0 : 1;                             // per-segment arrays the selection does not use
     size_t cur = 0;
     l.off[0] = bump(cur, (nseg + 1) * sizeof(int32_t));                        // sel_chunk_prefix
@@ -74,7 +75,7 @@ static Layout layout_of(const kvtrim_config* c, bool select_only) {
     l.off[9] = bump(cur, l.max_cmp_chunks * sizeof(int64_t));                  // cmp_chunk_dst
     l.off[10] = bump(cur, seg_tables * (nseg + 1) * sizeof(int32_t));          // att_chunk_prefix
     l.off[11] = bump(cur, l.max_att_chunks * sizeof(ChunkDesc));               // att_desc
-    l.off[12] = bump(cur, (size_t)l.max_att_chunks * G * (c->head_dim + 2) * sizeof(float)); // att_partial
+    l.off[12] = bump(cur, (size_t)l.att_slots * G * (c->head_dim + 2) * sizeof(float)); // att_partial
     l.off[13] = bump(cur, 256);                                                // err (word 0), fast_stat (bytes 64..79)
     l.off[14] = bump(cur, (nseg + 1) * sizeof(int64_t));                       // sel_entry_prefix
     l.off[15] = bump(cur, HIST_BLOCKS_MAX * sizeof(int4));                     // sel_blk
@@ -99,7 +100,6 @@ static Layout layout_of(const kvtrim_config* c, bool select_only) {
     l.off[31] = bump(cur, (size_t)c->n_seq * l.fl_cap * sizeof(int32_t));      // fl_pos
     l.off[32] = bump(cur, (size_t)c->n_seq * l.fl_cap * sizeof(int32_t));      // fl_idx
     l.off[33] = bump(cur, seg_tables * (size_t)nseg * sizeof(int32_t));        // step_len
-    l.off[34] = bump(cur, l.max_att_chunks * 4 * sizeof(int32_t));             // att_pages
     l.off[35] = bump(cur, seg_tables * (size_t)nseg * sizeof(StepSegRec));     // step_rec
     l.off[36] = bump(cur, seg_tables * (size_t)c->n_seq * STEP_MAX_EVICT * sizeof(int32_t));   // step_evl
     l.off[37] = bump(cur, (size_t)l.max_cmp_chunks * sizeof(uint32_t));        // step_chunk_ev
@@ -126,7 +126,6 @@ static void bind(const Layout& l, char* b, Workspace& w) {
     w.att_chunk_prefix = (int32_t*)(b + l.off[10]);
     w.att_desc = (ChunkDesc*)(b + l.off[11]);
     w.att_partial = (float*)(b + l.off[12]);
-    w.pg_block_table = nullptr;
     w.err = (int32_t*)(b + l.off[13]);
     w.fast_stat = (unsigned long long*)(b + l.off[13] + 64);
     w.sel_entry_prefix = (int64_t*)(b + l.off[14]);
@@ -148,7 +147,6 @@ static void bind(const Layout& l, char* b, Workspace& w) {
     w.fl_pos = (int32_t*)(b + l.off[31]);
     w.fl_idx = (int32_t*)(b + l.off[32]);
     w.step_len = (int32_t*)(b + l.off[33]);
-    w.att_pages = (int32_t*)(b + l.off[34]);
     w.step_rec = (StepSegRec*)(b + l.off[35]);
     w.step_evl = (int32_t*)(b + l.off[36]);
     w.step_chunk_ev = (uint32_t*)(b + l.off[37]);
@@ -160,6 +158,7 @@ static void bind(const Layout& l, char* b, Workspace& w) {
     w.max_sel_chunks = l.max_sel_chunks;
     w.max_cmp_chunks = l.max_cmp_chunks;
     w.max_att_chunks = l.max_att_chunks;
+    w.att_slots = l.att_slots;
 }
 
 bool config_valid(const kvtrim_config* c) { return config_ok(c); }
@@ -245,12 +244,7 @@ kvtrim_status kvtrim_create(kvtrim_ctx** out, const kvtrim_config* cfg) {
     memset(ctx, 0, sizeof(*ctx));
     ctx->cfg = *cfg;
     shape_of(cfg, ctx->shape);
-    ctx->att_chunk_min = 512;
-    if (const char* e = getenv("KVTRIM_ATT_CHUNK")) {            // tuning knob: rows per attention chunk
-        const int v = atoi(e);
-        if (v >= 256 && v <= 65536 && v % 64 == 0) ctx->att_chunk_min = v;
-    }
-    ctx->att_blocks = 768;                                        // three blocks of k_att_partial per compute unit
+    ctx->att_blocks = ATT_BLOCKS;
     if (const char* e = getenv("KVTRIM_ATT_BLOCKS")) {           // tuning knob
         const int v = atoi(e);
         if (v >= 1 && v <= 65536) ctx->att_blocks = v;
@@ -443,7 +437,7 @@ kvtrim_status kvtrim_decode_attn(kvtrim_ctx* ctx, const kvtrim_cache* c, const v
     if (layer_begin < 0 || layer_end > ctx->cfg.n_layers || layer_begin >= layer_end)
         return invalid(ctx, "empty or out-of-range layer range");
     if (!(softmax_scale == softmax_scale)) return invalid(ctx, "softmax_scale is NaN");
-    return launch_attn(ctx, view_of(c), (const uint16_t*)q, nullptr, layer_begin, layer_end, softmax_scale, out, lse,
+    return launch_attn(ctx, view_of(c), nullptr, (const uint16_t*)q, nullptr, layer_begin, layer_end, softmax_scale, out, lse,
                        (hipStream_t)hip_stream);
 }
 
@@ -457,7 +451,7 @@ kvtrim_status kvtrim_decode_attn_soft(kvtrim_ctx* ctx, const kvtrim_cache* c, co
     if (layer_begin < 0 || layer_end > ctx->cfg.n_layers || layer_begin >= layer_end)
         return invalid(ctx, "empty or out-of-range layer range");
     if (!(softmax_scale == softmax_scale)) return invalid(ctx, "softmax_scale is NaN");
-    return launch_attn(ctx, view_of(c), (const uint16_t*)q, now, layer_begin, layer_end, softmax_scale, out, lse,
+    return launch_attn(ctx, view_of(c), nullptr, (const uint16_t*)q, now, layer_begin, layer_end, softmax_scale, out, lse,
                        (hipStream_t)hip_stream);
 }
 

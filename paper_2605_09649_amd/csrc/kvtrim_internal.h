@@ -18,6 +18,7 @@ constexpr int CMP_THREADS = CMP_CHUNK / CMP_WAVE_ROWS * 64;   // 512: one wavefr
 constexpr int RADIX_BITS0 = 11, RADIX_BITS1 = 11, RADIX_BITS2 = 10;
 constexpr int RADIX_BINS = 2048;     // bins of the widest pass
 constexpr int HIST_BLOCKS_MAX = 512; // blocks of a histogram pass (few and fat: see k_select.hip)
+constexpr int ATT_BLOCKS = 768;       // most blocks of the attention kernel: three per compute unit
 constexpr int DONE_WORDS = 128;      // 4 sets of 32 counters (three histogram passes, the tie count)
 constexpr int HIST_REPLICAS = 8;     // copies of the merged histogram (spreads the device-scope atomics)
 
@@ -94,8 +95,16 @@ struct PagedArgs {
     int32_t* evict_seg_live;
     int32_t* evict_page_live;
     int32_t* evict_page_owner;
-    // layers [plan_layer_begin, plan_layer_end) whose attention chunk table the scoring kernel also builds (none: no table)
-    int32_t plan_layer_begin, plan_layer_end;
+};
+
+// A paged cache as the attention walks it: the block tables ([nseg][max_pps] pages of the pool), pages and live entries
+// per segment.
+struct AttPages {
+    const int32_t* block_table;
+    const int32_t* seg_pages;
+    const int32_t* seg_live;
+    int32_t n_pages;
+    int32_t max_pps;
 };
 
 // The decode step in one call (kvtrim_decode_step): the tokens that enter the cache in this step (laid out as kvtrim_append takes them;
@@ -169,12 +178,10 @@ struct Workspace {
     int32_t* cmp_chunk_prefix;   // [nseg+1]
     ChunkDesc* cmp_desc;         // [max_cmp_chunks]
     int64_t* cmp_chunk_dst;      // [max_cmp_chunks] first dst entry of the chunk's survivors (| CMP_DST_FULL)
-    int32_t* att_pages;          // [max_att_chunks][4] paged attention: the pages of a chunk, beside its descriptor
     // attention
-    int32_t* att_chunk_prefix;   // [nseg+1]
+    int32_t* att_chunk_prefix;   // [nseg+1] the gathering fused kernel: the destination's chunks
     ChunkDesc* att_desc;         // [max_att_chunks]
-    float* att_partial;          // [max_att_chunks][G][D+2]  (m, l, o[D]) per query head
-    const int32_t* pg_block_table; // paged attention only: the caller's block tables (set per launch)
+    float* att_partial;          // [att_slots][G][D+2]  (m, l, o[D]) per query head
     int32_t* err;                // sticky device flag
     // decode-step selection: state carried from call to call, and the per-call candidate lists
     uint32_t* fast_hi;           // [n_seq] entries with key < fast_hi are listed (0: nothing known yet)
@@ -197,10 +204,11 @@ struct Workspace {
     // gathering fused kernel (sparse selections): the source row of every destination row, CMP_CHUNK slots per
     // destination chunk, written by the compaction scan
     int32_t* gat_src;            // [gat_slots]
-    int64_t* att_row_prefix;     // [nseg+1] attention: rows (paged: slots) of the layer range's segments before each segment
+    int64_t* att_row_prefix;     // [nseg+1] attention: rows (paged: slots) before each segment of the layer range, counted inside the range
     uint32_t* gate_done;         // [n_layers] gate forward: blocks of a layer that have left their part of the readout (zero between calls)
     int64_t gat_slots;
     int64_t max_sel_chunks, max_cmp_chunks, max_att_chunks;
+    int64_t att_slots;           // partial results the buffer holds: max_att_chunks and a block of the attention kernel per 64 rows more
 };
 
 }  // namespace kvtrim
@@ -223,8 +231,7 @@ struct kvtrim_ctx {
     size_t ws_bytes;
     int32_t* err_host;           // pinned mirror of the device flag
     int device;
-    int att_chunk_min;           // rows per attention chunk (multiple of 64, >= 256); KVTRIM_ATT_CHUNK overrides
-    int att_blocks;              // blocks of the attention kernel's fixed grid; KVTRIM_ATT_BLOCKS overrides
+    int att_blocks;              // most blocks of the attention kernel; KVTRIM_ATT_BLOCKS overrides
     char last_error[256];
     // instrumentation
     uint64_t prof_mask;
@@ -234,9 +241,6 @@ struct kvtrim_ctx {
 };
 
 namespace kvtrim {
-
-// Upper bound on attention chunks for a cache of `cap` entries, and the chunk size used.
-int att_chunk_for(const kvtrim_ctx* ctx, int64_t cap);
 
 kvtrim_status launch_score(kvtrim_ctx*, const CacheView&, const int32_t* now, float* score, hipStream_t);
 kvtrim_status launch_select(kvtrim_ctx*, const CacheView&, const float* score, const int64_t* budget,
@@ -265,16 +269,14 @@ kvtrim_status launch_score_select_general(kvtrim_ctx*, const CacheView&, const i
                                           float* score, uint8_t* keep, int32_t* kept, uint32_t* thr, hipStream_t);
 kvtrim_status launch_compact(kvtrim_ctx*, const CacheView& src, const uint8_t* keep, const int32_t* kept,
                              const CacheViewMut& dst, int32_t reserve, hipStream_t);
-kvtrim_status launch_attn(kvtrim_ctx*, const CacheView&, const uint16_t* q, const int32_t* soft_now,
-                          int32_t layer_begin, int32_t layer_end, float scale, float* out, float* lse, hipStream_t);
+struct PagedView;
+// pages: c is the pool of a paged cache.  tidy: the merge kernel's launch also takes the pages that an eviction emptied
+// out of the block tables
+kvtrim_status launch_attn(kvtrim_ctx*, const CacheView& c, const AttPages* pages, const uint16_t* q, const int32_t* soft_now,
+                          int32_t layer_begin, int32_t layer_end, float scale, float* out, float* lse, hipStream_t,
+                          const PagedView* tidy = nullptr);
 void launch_select_passes_paged(kvtrim_ctx*, const float* score, const SelTables&, int hist_blocks, int pass,
                                 uint32_t* thr, hipStream_t);
-struct PagedView;
-// tidy: the merge kernel's launch also takes the pages that an eviction emptied out of the block tables
-kvtrim_status launch_attn_paged(kvtrim_ctx*, const CacheView& pool, const int32_t* block_table, const uint16_t* q,
-                                int max_chunks,
-                                int32_t layer_begin, int32_t layer_end, float scale, float* out, float* lse,
-                                hipStream_t, const PagedView* tidy = nullptr);
 // gat: also writes the table of the DESTINATION's CMP_CHUNK-row chunks (ws.att_chunk_prefix / ws.att_desc) and the source
 // row of every destination row (ws.gat_src) - what the gathering instance of the fused kernel reads.
 void launch_cmp_scan_aligned(kvtrim_ctx*, const CacheView& src, const uint8_t* keep, const int32_t* kept,
@@ -295,11 +297,9 @@ kvtrim_status launch_cmp_copy(kvtrim_ctx*, const CacheView& src, const uint8_t* 
 kvtrim_status launch_occupancy(kvtrim_ctx*, const CacheView&, const int32_t* now, double* occ, hipStream_t);
 void launch_cmp_scan(kvtrim_ctx*, const CacheView& src, const uint8_t* keep, const int32_t* kept,
                      const CacheViewMut& dst, int32_t reserve, hipStream_t);
-// persist_nb > 0: the partial results are those of k_att_partial launched with that many blocks (one per block and
-// segment; shares start at multiples of round_rows, chunks have chunk_rows rows, extra slots from extra_base on)
+// Merges the fused row mover's partial results, one per chunk
 kvtrim_status launch_combine(kvtrim_ctx*, const int32_t* chunk_prefix, int32_t layer_begin, int32_t layer_end,
-                             float* out, float* lse, hipStream_t, int persist_nb = 0, int round_rows = 1, int chunk_rows = 1,
-                             int extra_base = 0);
+                             float* out, float* lse, int64_t max_chunks, hipStream_t);
 // ... whose launch also finishes an in-place compaction: the rows parked in `stage` go to their places
 kvtrim_status launch_combine_unstage(kvtrim_ctx*, const int32_t* chunk_prefix, int32_t layer_begin, int32_t layer_end,
                                      float* out, float* lse, const CacheViewMut& c, const CacheViewMut& stage,

@@ -25,34 +25,26 @@ struct PagedView {
 };
 
 constexpr int PG_TABLE_BLOCKS = 16;        // blocks that share the building of a chunk table
-constexpr int ATT_PAGE_GROUP = 4;          // pages per attention chunk (512 rows, the ragged path's chunk)
+constexpr int ATT_PAGE_GROUP = 4;          // an attention call takes at most this many pages per slot of the partial-result buffer
 
 // ---------------------------------------------------------------------------------------------
-// Chunk table of a paged cache: the pages of every segment with in_range(g), in segment order,
-// GROUP pages to a chunk.  prefix[g] = first chunk of segment g, prefix[nseg] = number of chunks;
-// entry_prefix (optional) counts the live entries of the segments before g.
-//   GROUP == 1: desc = {first slot of the page, page size, segment}           (selection)
-//   GROUP  > 1: desc = {index of the group's first block-table entry, slots of the group, segment},
-//               pages_out[chunk][GROUP] = the group's pages (clamped into the pool), so that the reader
-//               has them with the descriptor and not one dependent load later  (attention)
+// Chunk table of a paged cache for the selection: the pages of every segment, in segment order, one chunk per page.
+// prefix[g] = first chunk of segment g, prefix[nseg] = number of chunks, desc = {first slot of the page, page size,
+// segment}; entry_prefix counts the live entries of the segments before g.
 // Built by `nparts` blocks: every block scans the per-segment counts (a few thousand integers),
 // block `part` fills the descriptors of the segments g = part (mod nparts), one wavefront per
-// segment, and block 0 writes the prefixes (slot_prefix, optional: the slots - pages times the page size - of the
-// in-range segments before g).  Returns the number of chunks.  Counts that do not
+// segment, and block 0 writes the prefixes.  Returns the number of chunks.  Counts that do not
 // fit raise ERR_LAYOUT and leave the table empty; a page id out of range raises it too and is
 // clamped, so that no reader leaves the pool.
-template <int GROUP, typename InRange>
-__device__ __forceinline__ int build_page_table(const PagedView& pc, int nseg, InRange in_range, int32_t* prefix,
-                                                ChunkDesc* desc, int64_t max_chunks, int64_t* entry_prefix,
-                                                int32_t* err, int part, int nparts, int32_t* pages_out = nullptr,
-                                                int64_t* slot_prefix = nullptr) {
+__device__ __forceinline__ int build_page_table(const PagedView& pc, int nseg, int32_t* prefix, ChunkDesc* desc,
+                                                int64_t max_chunks, int64_t* entry_prefix, int32_t* err, int part, int nparts) {
     __shared__ uint64_t s_scan[17];
     __shared__ int s_bad;
     __shared__ int s_c0[1024], s_n[1024];
     const int tid = threadIdx.x;
     if (tid == 0) s_bad = 0;
     __syncthreads();
-    uint64_t carry = 0, slot_carry = 0;
+    uint64_t carry = 0;
     for (int base = 0; base < nseg; base += blockDim.x) {
         const int g = base + tid;
         uint64_t v = 0;
@@ -63,10 +55,8 @@ __device__ __forceinline__ int build_page_table(const PagedView& pc, int nseg, I
             if (npg < 0 || npg > pc.max_pps || live < 0 || (int64_t)live > (int64_t)npg * P) {
                 s_bad = 1;
                 npg = 0;
-            } else if (in_range(g)) {
-                v = ((uint64_t)live << 32) | (uint64_t)((npg + GROUP - 1) / GROUP);
             } else {
-                npg = 0;
+                v = ((uint64_t)live << 32) | (uint64_t)npg;
             }
         }
         uint64_t tot;
@@ -75,13 +65,7 @@ __device__ __forceinline__ int build_page_table(const PagedView& pc, int nseg, I
         const int c0 = (int)(ex & 0xffffffffu);
         if (g < nseg && part == 0) {
             prefix[g] = c0;
-            if (entry_prefix) entry_prefix[g] = (int64_t)(ex >> 32);
-        }
-        if (slot_prefix) {                                           // slots of the in-range segments before g
-            uint64_t stot;
-            const uint64_t sex = slot_carry + block_excl_scan<uint64_t>((uint64_t)npg * P, s_scan, &stot);
-            slot_carry += stot;
-            if (g < nseg && part == 0) slot_prefix[g] = (int64_t)sex;
+            entry_prefix[g] = (int64_t)(ex >> 32);
         }
         s_c0[tid] = c0;
         s_n[tid] = npg;
@@ -99,18 +83,9 @@ __device__ __forceinline__ int build_page_table(const PagedView& pc, int nseg, I
                     bad_page |= pg < 0 || pg >= pc.n_pages;
                     ChunkDesc d;
                     d.seg = gg;
-                    if (GROUP == 1) {
-                        d.first = (int64_t)min(max(pg, 0), pc.n_pages - 1) * P;
-                        d.n = P;
-                        desc[cc + i] = d;
-                    } else {
-                        if (pages_out) pages_out[(int64_t)(cc + i / GROUP) * GROUP + i % GROUP] = min(max(pg, 0), pc.n_pages - 1);
-                        if (i % GROUP == 0) {
-                            d.first = row + i;
-                            d.n = P * min(GROUP, nn - i);
-                            desc[cc + i / GROUP] = d;
-                        }
-                    }
+                    d.first = (int64_t)min(max(pg, 0), pc.n_pages - 1) * P;
+                    d.n = P;
+                    desc[cc + i] = d;
                 }
                 if (__any(bad_page) && lane == 0) atomicOr(err, ERR_LAYOUT);
             }
@@ -123,8 +98,7 @@ __device__ __forceinline__ int build_page_table(const PagedView& pc, int nseg, I
             if (tid == 0) atomicOr(err, ERR_LAYOUT);
             for (int g = tid; g <= nseg; g += blockDim.x) {
                 prefix[g] = 0;
-                if (entry_prefix) entry_prefix[g] = 0;
-                if (slot_prefix) slot_prefix[g] = 0;
+                entry_prefix[g] = 0;
             }
         }
         __syncthreads();
@@ -132,8 +106,7 @@ __device__ __forceinline__ int build_page_table(const PagedView& pc, int nseg, I
     }
     if (tid == 0 && part == 0) {
         prefix[nseg] = (int32_t)total;
-        if (entry_prefix) entry_prefix[nseg] = (int64_t)(carry >> 32);
-        if (slot_prefix) slot_prefix[nseg] = (int64_t)slot_carry;
+        entry_prefix[nseg] = (int64_t)(carry >> 32);
     }
     __syncthreads();
     return (int)total;

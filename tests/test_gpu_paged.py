@@ -306,3 +306,13 @@ def test_defragmentation_of_a_tight_pool_changes_nothing():
     check(results)
     d = results[0]["defrag"]                                      # right after the build every segment is packed
     assert d["tight"] and d["pages_before"] == d["pages_after"] and d["free_gain"] == 0
+
+
+@pytest.mark.parametrize("S,seg_len", [(1, [9000, 70, 0, 8300]),           # 71 and 65 pages: more than a wavefront's window of 64
+                                       (1040, [3, 0, 130, 1])])            # 4160 segments: the table kernel runs first
+def test_paged_attention_over_long_and_over_many_segments(S, seg_len, monkeypatch):
+    # with one block for everything a run covers whole segments
+    monkeypatch.setenv("KVTRIM_ATT_BLOCKS", "1" if S == 1 else "768")
+    w = wl(S, 2, 2, 2, 64)
+    c, now = ki.ragged_cache(w, seg_len * S, reserve=1, salt=13)
+    check(run_paged_both(w, [[sum(seg_len) - 20] * S, [sum(seg_len) - 25] * S], device=DEV, cache_dict=c, now0=now.numpy()))

@@ -729,3 +729,44 @@ def test_many_segments_take_the_prefix_kernel_and_report_errors():
     kv.kvtrim_compact(ctx, src, keep, kept, roomy, 0)
     assert kv.kvtrim_poll_error(ctx) == 0
     assert compare_caches(device_cache_to_host(w, roomy), oracle.compact(hc, np.ones(hc.cap, np.uint8), hc.cap, 0))
+
+
+@pytest.mark.parametrize("S,L,H,G,D,layers", [(257, 4, 4, 2, 64, (0, 4)),       # 4112 segments: the table kernel runs first
+                                              (256, 4, 4, 2, 64, (0, 4)),       # 4096: every block adds up the lengths itself
+                                              (512, 3, 4, 1, 64, (1, 2)),       # ... of a layer range of a longer table
+                                              (1, 2, 2, 3, 128, (0, 2))])
+def test_attention_over_many_segments(S, L, H, G, D, layers):
+    # segments of 0 to 150 entries (under, at and over a round of 64 rows), so that shares end everywhere in them
+    w = wl(S, L, H, G, D)
+    rng = np.random.default_rng(S + L)
+    seg_len = rng.choice([0, 1, 15, 16, 17, 63, 64, 65, 128, 150], w.nseg)
+    c, _ = ki.ragged_cache(w, seg_len, salt=41)
+    hc = host_cache(w, c)
+    ctx = kv.Context(S, L, H, H * G, D, hc.cap)
+    q = ki.decode_inputs(w, 0)["q"]
+    scale = 1.0 / math.sqrt(D)
+    ref, ref_lse = oracle.attend(hc, bf16_bits(q), scale)
+    out = torch.full(ref.shape, 99.0, dtype=torch.float32, device=DEV)
+    lse = torch.full(ref_lse.shape, 99.0, dtype=torch.float32, device=DEV)
+    kv.kvtrim_decode_attn(ctx, kv.Cache.from_dict(c, DEV), q.to(DEV), *layers, scale, out, lse)
+    assert kv.kvtrim_poll_error(ctx) == 0
+    inside, outside = slice(*layers), [x for x in range(L) if not layers[0] <= x < layers[1]]
+    o, l = out.cpu().numpy(), lse.cpu().numpy()
+    assert np.all(o[:, outside] == 99.0) and np.all(l[:, outside] == 99.0)
+    assert attn_error(o[:, inside], ref[:, inside]) <= ATTN_TOL
+    fin = np.isfinite(ref_lse[:, inside])
+    assert np.array_equal(np.isneginf(l[:, inside]), ~fin)
+    assert np.abs(l[:, inside][fin] - ref_lse[:, inside][fin]).max() <= 2e-3
+
+
+def test_attention_on_a_bad_table_outside_the_layer_range_gives_no_result():
+    # a segment table that overlaps in a layer that is not asked for: the call reports it and writes nothing
+    w = wl(1, 2, 2, 2, 64)
+    c, _ = ki.ragged_cache(w, [100, 200, 300, 50], salt=42)
+    ctx = kv.Context(1, 2, 2, 4, 64, c["cap"])
+    q = ki.decode_inputs(w, 0)["q"].to(DEV)
+    out = torch.full((1, 2, 4, 64), 99.0, dtype=torch.float32, device=DEV)
+    c["seg_len"][0] = 150
+    kv.kvtrim_decode_attn(ctx, kv.Cache.from_dict(c, DEV), q, 1, 2, 0.125, out, None)
+    assert kv.kvtrim_poll_error(ctx) == -6                               # KVTRIM_ELAYOUT
+    assert torch.all(out == 99.0)
