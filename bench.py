@@ -122,7 +122,7 @@ def bench_gate(args):
     for i in range(W):
         forward(xs[i % 4])
     torch.cuda.synchronize()
-    kv.kvtrim_profile_begin(ctx, (0x1F << 23) | (1 << 29))       # k_gate_hidden, _readout, _fold, _prefill, _retile, _dot
+    kv.kvtrim_profile_begin(ctx, (0x1F << 23) | (3 << 29))       # k_gate_hidden, _readout, _fold, _prefill, _retile, _dot, _slice
     t0 = time.perf_counter()
     for i in range(K):
         forward(xs[i % 4])
@@ -148,13 +148,16 @@ def bench_gate(args):
             roof["third_kernel"] = {"kernel": "k_gate_retile", "avg_launch_ms": t_ms,
                                     "achieved": 2 * w1_bytes / (t_ms * 1e-3) / 1e9, "unit": "GB/s"}
     else:
-        first, second = "k_gate_hidden", "k_gate_dot" if "k_gate_dot" in prof else "k_gate_readout"
+        # k_gate_slice holds both layers (the second folded into one vector per (layer, head): a fold in front of it unless
+        # the weights are prepared); k_gate_hidden the first layer, with a readout kernel behind it
+        sliced = "k_gate_slice" in prof
+        first = "k_gate_slice" if sliced else "k_gate_hidden"
+        second = "k_gate_fold" if sliced else ("k_gate_dot" if "k_gate_dot" in prof else "k_gate_readout")
         h_ms = prof[first][0] / prof[first][1]
-        # (prepared weights, up to 16 tokens: the readout rides in the first-layer kernel and there is no second one)
         r_ms = prof[second][0] / prof[second][1] if second in prof else None
-        # first layer: W1 once per 64 tokens of a call, x once per 16-row tile group (cached), u written once (one
-        # kernel: the folded vectors read, per block its parts of the readout sums written and read once instead)
-        alg_hidden = w1_bytes + L * n_tok * dm * 2 + (L * n_tok * dg * 4 if r_ms is not None else L * H * (dg + 1) * 4 + 2 * L * (dg // 16) * H * n_tok * 4)
+        # first layer: W1 once per 64 tokens of a call, x once (cached), u written once (k_gate_slice: the folded vectors
+        # read, per block its parts of the readout sums written and read once instead)
+        alg_hidden = w1_bytes + L * n_tok * dm * 2 + (L * H * (dg + 1) * 4 + 2 * L * (dg // 64) * H * n_tok * 4 if sliced else L * n_tok * dg * 4)
         if n_tok <= 64:
             roof = {"bound": "hbm", "kernel": first, "achieved": alg_hidden / (h_ms * 1e-3) / 1e9,
                     "peak": HBM_PEAK_GBS, "unit": "GB/s", "traffic": measured_traffic(f"gate_decode_{n_tok}tok", first),
@@ -162,7 +165,7 @@ def bench_gate(args):
         else:
             roof = {"bound": "mfma", "kernel": first, "achieved": flops_hidden / (h_ms * 1e-3) / 1e12,
                     "peak": 2500.0, "unit": "TFLOP/s", "traffic": None, "flops_per_launch": flops_hidden}
-        second_bytes = (L * H * (dg + 1) * 4 if second == "k_gate_dot" else w2_bytes) + L * n_tok * dg * 4
+        second_bytes = w2_bytes + L * H * (dg + 1) * 4 if sliced else (L * H * (dg + 1) * 4 if second == "k_gate_dot" else w2_bytes) + L * n_tok * dg * 4
     roof["frac"] = roof["achieved"] / roof["peak"]
     roof["avg_launch_ms"] = h_ms
     third = roof.pop("third_kernel", None)

@@ -473,9 +473,9 @@ typedef struct {
 } kvtrim_gate;
 
 /* Bytes of scratch kvtrim_gate_forward needs for n_tok tokens and n_layers layers of a range:
- * n_tok * n_layers * d_g floats (short calls keep the hidden activations u there in fp32; calls of 128 tokens
- * and more keep the folded readout vectors there and, where it fits - from about d_model / 2 tokens on - a
- * copy of W1 in matrix-core operand order); 0 for invalid arguments.  Host-only, no GPU call. */
+ * n_tok * n_layers * d_g floats (short calls keep the hidden activations u there in fp32, longer ones the folded
+ * readout vectors and the blocks' parts of the readout sums or, where it fits - from about d_model / 2 tokens on -
+ * a copy of W1 in matrix-core operand order); 0 for invalid arguments.  Host-only, no GPU call. */
 size_t kvtrim_gate_scratch_bytes(const kvtrim_gate *g, int32_t n_tok, int32_t n_layers);
 
 /* x: bf16 [layer_end - layer_begin][n_tok][d_model], 16-byte aligned, the representation of each
@@ -486,10 +486,12 @@ size_t kvtrim_gate_scratch_bytes(const kvtrim_gate *g, int32_t n_tok, int32_t n_
  * - with one token per sequence this is segment order, the layout kvtrim_append takes.
  * scratch: device memory, 16-byte aligned, at least kvtrim_gate_scratch_bytes(...) bytes, contents
  * undefined afterwards.  Enqueues two or three kernels on the stream; allocates nothing.  Arithmetic:
- * bf16 products accumulated in fp32 on the matrix cores.  Calls below 128 tokens carry u to 16 mantissa
+ * bf16 products accumulated in fp32 on the matrix cores.  Calls of up to 16 tokens carry u to 16 mantissa
  * bits into the second layer; longer calls use that the second layer and the readout are both linear
  * (z = (W2^T w_g) . u + w_g . c2 + b_g), fold them into one fp32 vector per (layer, head) first and keep u
- * in fp32.  Results agree with an fp64 evaluation to about 1e-5 relative in log beta either way. */
+ * in fp32 (unless there are many KV heads and few tokens: then as the short ones).  Results agree with an fp64
+ * evaluation to about 1e-5 relative in log beta either way.  Some calls keep arrival counters in the context's
+ * workspace: as for every call on a context, two gate calls on one context must not run at the same time. */
 kvtrim_status kvtrim_gate_forward(kvtrim_ctx *ctx, const kvtrim_gate *g, const void *x, int32_t n_tok,
                                   int32_t layer_begin, int32_t layer_end, int32_t horizon, void *scratch,
                                   float *log_beta_out, float *log_tail_out, void *hip_stream);
@@ -503,10 +505,8 @@ kvtrim_status kvtrim_gate_forward(kvtrim_ctx *ctx, const kvtrim_gate *g, const v
  * the stream.  The buffer is valid for as long as the weights it was made from are unchanged.
  * kvtrim_gate_forward_prepared: same arguments, outputs and arithmetic contract as kvtrim_gate_forward (g must
  * be the gate the buffer was prepared from; scratch as for kvtrim_gate_forward); calls of every length then read
- * the readout as one dot product per (token, layer, head), and the one-kernel path that kvtrim_gate_forward
- * takes from 128 tokens on is taken from 24 tokens on, reading W1 from the operand-order copy.  Calls of up to 16
- * tokens (with at most 16 KV heads) are one kernel as well; it keeps one arrival counter per layer in the context's
- * workspace, so - as for every call on a context - two gate calls on one context must not run at the same time. */
+ * the readout as one dot product per (token, layer, head) and W1 from the operand-order copy.  Calls are one kernel
+ * (more than 32 KV heads: two), whose blocks split the hidden units or the tokens, by the number of tokens. */
 size_t kvtrim_gate_prepared_bytes(const kvtrim_gate *g, int32_t n_layers, int32_t n_kv_heads);
 kvtrim_status kvtrim_gate_prepare(kvtrim_ctx *ctx, const kvtrim_gate *g, void *prepared, void *hip_stream);
 kvtrim_status kvtrim_gate_forward_prepared(kvtrim_ctx *ctx, const kvtrim_gate *g, const void *prepared, const void *x,

@@ -9,6 +9,11 @@
 // Both layers are dense contractions and run on the matrix cores (MFMA 16x16x32 bf16, fp32
 // accumulation); with one token per sequence they are bound by streaming the weights once from
 // HBM, and the unused token columns of the MFMA tile cost nothing.
+//   k_gate_slice    up to some hundred tokens, from folded readout vectors: a block owns a slice of 16 to 64 hidden
+//                   units and up to 128 tokens; see further down.
+//   k_gate_prefill  more tokens: a block owns all hidden units and up to 128 tokens; see further down.
+//   k_gate_fold, k_gate_retile   what both derive from the weights, once (prepared) or in the call.
+// and for what those do not take (up to 16 tokens without prepared weights, more than 32 heads, ...):
 //   k_gate_hidden   a block owns 16 rows of W1 of one layer (64 rows when a call brings more than 16
 //                   tokens) and up to 64 tokens; its four wavefronts split the contraction over
 //                   d_model, are summed through LDS, and write u in fp32.
@@ -16,7 +21,6 @@
 //                   (u = hi + lo to 2^-17 relative) so that the second layer keeps fp32-like
 //                   accuracy on the bf16 matrix cores; every wavefront takes 16-row tiles of W2,
 //                   folds its rows with w_g, and the block adds b_g and applies log-sigmoid.
-//   k_gate_fold, k_gate_retile, k_gate_prefill   calls of 128 tokens and more: see further down.
 // The contraction index may be permuted freely as long as both operands use the same permutation:
 // a lane loads 32 contiguous bytes of its row per 64-wide step (so four lanes read one full
 // 128-byte line) and feeds the two halves to two MFMAs.
@@ -25,6 +29,7 @@
 namespace kvtrim {
 
 typedef __attribute__((ext_vector_type(4))) float gate_f4;
+typedef __attribute__((ext_vector_type(4))) unsigned gate_u4;
 typedef __attribute__((ext_vector_type(8))) __bf16 gate_bf8;
 
 __device__ __forceinline__ gate_f4 mma_bf16(uint4 a, uint4 b, gate_f4 c) {
@@ -66,26 +71,21 @@ constexpr int GH_ROWS = 16;
 // rows: with more than 16 tokens a block takes MT = 4 tiles of W1 so that x is read by a quarter of the blocks.
 // TILED: W1 comes from the operand-order copy of a prepared buffer (`tiled` points at the first layer of the
 // range: [layer][16-row tile][64-wide step][half][lane] 16-byte pieces), so a wavefront load reads 1 KB in one piece.
-// DOT (one tile of tokens, one tile of rows, prepared weights): the readout from the folded vectors happens here as
-// well, so u never goes to memory and the call is one kernel.  z = v . u + s is a sum over the hidden units, of which
-// a block holds 16: it leaves its part of every (token, head) sum in `part` ([layer][block][head][token], the
-// caller's scratch buffer), and the block of a layer that arrives last (one counter per layer, left at zero) adds
-// the parts in block order - the same order whichever block that is.
+// What the readout from folded vectors needs: z = v . u + s.
 struct GateDot {
     const float* v;          // [layers of the range][heads][d_g]
     const float* s;          // [layers of the range][heads]
     float* part;
-    uint32_t* done;          // [layers of the range]
+    uint32_t* done;          // [layers of the range][GATE_TOKEN_TILES]
     float* log_beta_out;
     float* log_tail_out;
     int n_heads, n_layers, horizon;
 };
 
-template <int NT, int MT, bool TILED, bool DOT>
+template <int NT, int MT, bool TILED>
 __global__ __launch_bounds__(GH_THREADS) void k_gate_hidden(GateView g, const uint16_t* __restrict__ x, int n_tok,
                                                             int layer_begin, const uint4* __restrict__ tiled,
-                                                            float* __restrict__ u, GateDot dot) {
-    static_assert(!DOT || (NT == 1 && MT == 1 && TILED), "the readout rides in the 16 x 16 instance only");
+                                                            float* __restrict__ u) {
     __shared__ float s_part[4][NT][16 * MT][17];
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const int r16 = lane & 15, g4 = lane >> 4;
@@ -114,15 +114,6 @@ __global__ __launch_bounds__(GH_THREADS) void k_gate_hidden(GateView g, const ui
     for (int m = 0; m < MT; ++m)
 #pragma unroll
         for (int t = 0; t < NT; ++t) acc[m][t] = gate_f4{0.f, 0.f, 0.f, 0.f};
-    // DOT: the folded vectors' entries for this thread's hidden unit, asked for before the stream of W1 starts
-    constexpr int DOT_HEADS = DOT ? 16 : 1;
-    float vh[DOT_HEADS];
-    if (DOT) {
-#pragma unroll
-        for (int h = 0; h < DOT_HEADS; ++h)
-            vh[h] = h < dot.n_heads ? dot.v[((size_t)lr * dot.n_heads + h) * g.d_g + row0 + (tid & 15)] : 0.f;
-    }
-
     // 64 contraction indices per step (8 uint4 of a row); AHEAD steps of weights are loaded ahead
     constexpr int AHEAD = MT == 1 ? 4 : 2;
     const int steps = kw >> 6;                                       // kw is a multiple of 64
@@ -168,55 +159,6 @@ __global__ __launch_bounds__(GH_THREADS) void k_gate_hidden(GateView g, const ui
             for (int r = 0; r < 4; ++r) s_part[wave][t][16 * m + 4 * g4 + r][r16] = acc[m][t][r];
     __syncthreads();
     constexpr int ROWS = 16 * MT;
-    if (DOT) {
-        static_assert(GH_THREADS == 256, "one (hidden unit, token) pair per thread");
-        __shared__ int s_last;
-        const int row = tid & 15, tok = tid >> 4;                   // (a token's 16 hidden units sit in 16 neighbouring lanes)
-        const int nblk = gridDim.x;
-        float su = 0.f;
-        if (tok < n_tok) {
-            const float a = s_part[0][0][row][tok] + s_part[1][0][row][tok] + s_part[2][0][row][tok] + s_part[3][0][row][tok] +
-                            g.c1[(size_t)layer * g.d_g + row0 + row];
-            su = a / (1.0f + __expf(-a));
-        }
-#pragma unroll
-        for (int h = 0; h < DOT_HEADS; ++h) {
-            if (h >= dot.n_heads) break;                          // (uniform)
-            float p = su * vh[h];
-            p += __shfl_xor(p, 1, 64);
-            p += __shfl_xor(p, 2, 64);
-            p += __shfl_xor(p, 4, 64);
-            p += __shfl_xor(p, 8, 64);
-            if (row == 0 && tok < n_tok)
-                __hip_atomic_store(&dot.part[(((size_t)lr * nblk + blockIdx.x) * dot.n_heads + h) * n_tok + tok], p, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-        }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this thread's parts are acknowledged ...
-        __syncthreads();                                          // ... and so are the whole block's, before it arrives
-        if (tid == 0) s_last = atomicAdd(&dot.done[lr], 1u) == (unsigned)nblk - 1u;
-        __syncthreads();
-        if (!s_last) return;
-        if (tid == 0) __hip_atomic_store(&dot.done[lr], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (for the next call)
-        for (int item = tid; item < n_tok * dot.n_heads; item += GH_THREADS) {
-            const int tk = item / dot.n_heads, h = item % dot.n_heads;
-            float z = 0.f;
-            for (int b0 = 0; b0 < nblk; b0 += 16) {               // 16 parts asked for at once, added in block order
-                float pt[16];
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    pt[i] = b0 + i < nblk ? __hip_atomic_load(&dot.part[(((size_t)lr * nblk + b0 + i) * dot.n_heads + h) * n_tok + tk],
-                                                              __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                          : 0.f;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) z += pt[i];
-            }
-            const float lb = log_sigmoid(z + dot.s[(size_t)lr * dot.n_heads + h]);
-            const size_t o = ((size_t)tk * dot.n_layers + layer_begin + lr) * dot.n_heads + h;
-            dot.log_beta_out[o] = lb;
-            if (dot.log_tail_out) dot.log_tail_out[o] = log_tail_of(lb, dot.horizon);
-        }
-        return;
-    }
     for (int idx = tid; idx < NT * 16 * ROWS; idx += GH_THREADS) {
         const int row = idx % ROWS, tk = (idx / ROWS) & 15, t = idx / (16 * ROWS);
         const int tok = tok0 + 16 * t + tk;
@@ -525,6 +467,7 @@ __global__ __launch_bounds__(GT_THREADS) void k_gate_retile(GateView g, int laye
 // that the blocks an XCD runs at one time belong to one layer (ids are dealt to the eight XCDs in turn), so
 // W1_l is shared through that XCD's L2.
 constexpr int GP_THREADS = 512, GP_HEADS_MAX = 8;
+constexpr int GP_MIN_TOK = 128;          // k_gate_prefill with the weight-only work in the call: below this it does not pay
 constexpr int GP_GROUP_BYTES = 272, GP_HALF_BYTES = 4 * GP_GROUP_BYTES, GP_TILE_BYTES = 2 * GP_HALF_BYTES;   // 272, 1088, 2176
 
 template <int HT, int TT, bool TILED>
@@ -725,15 +668,244 @@ __global__ __launch_bounds__(GP_THREADS) void k_gate_prefill(GateView g, const u
     }
 }
 
-// Below this many tokens the fold's extra pass over W2 and the few blocks of the prefill kernel do not pay.
-#ifndef KVTRIM_GATE_PREFILL_MIN_TOK
-#define KVTRIM_GATE_PREFILL_MIN_TOK 128
-#endif
-constexpr int GP_MIN_TOK = KVTRIM_GATE_PREFILL_MIN_TOK;
-constexpr int GP_MIN_TOK_PREPARED = 24;
+// Few to some hundred tokens with folded readout vectors: what counts is that W1 streams at the rate of the memory, so
+// the call must spread over the whole chip whatever the number of tokens.  A block of 8 wavefronts owns 16 MT hidden
+// units (a slice) of one layer and 16 TT tokens: wavefront (kh, m) takes the 16-row tile m and share kh of the 8 / MT
+// shares of the contraction.  W1 goes from memory to registers with streaming loads, two groups of GS steps ahead, the
+// token rows through LDS (loaded coalesced, parked in operand order as in k_gate_prefill), one barrier per group.  32
+// layers of 512 units are 256 blocks of 64 units - one per compute unit.  Short groups win over long ones (1 token: 25.6
+// us with GS 2, 28.3 with 8), streaming loads over plain ones by 2 to 4 us (W1 is not read again before the step between
+// two calls has gone through the caches).
+// u stays in registers: the shares of the contraction meet in LDS, every wavefront of a row tile then holds the same sums
+// and takes some of the heads.  z = v . u + s is a sum over the slices of a layer: a block leaves its part of every
+// (head, token) sum in `part` ([layer][slice][head][token], the caller's scratch buffer), and the block of a layer and
+// token tile that arrives last (counters in the workspace, left at zero) adds the parts in slice order - the same order
+// whichever block that is.  Blocks are dealt to the eight XCDs in contiguous runs of (layer, slice, token tile), so that
+// the blocks that share token rows, and those that share a slice of W1, share an L2.
+// Measured (32 layers, d_model 4096, 512 units, 8 heads, prepared; 134 MB of W1, 21 us at 6.5 TB/s): 1 token 35.0 -> 25.6
+// us, 32 tokens 86.9 -> 28.5, 64 tokens 83.6 -> 31.3, 128 tokens 81.4 -> 42.3, 256 tokens 80.8 -> 69.1 (before: up to 16
+// tokens 1024 blocks of 16 units, from 24 tokens on k_gate_prefill's 32-token blocks, 32 to 256 of them).
+constexpr int GSL_THREADS = 512, GSL_HEADS_MAX = 32, GSL_TILES_MAX = GATE_TOKEN_TILES;
 
-static bool prefill_shape(const kvtrim_ctx* ctx, const GateView& g) {
-    return g.d_g % 128 == 0 && g.d_g <= 512 && ctx->shape.n_kv_heads <= GP_HEADS_MAX;
+template <int TT, int GS, int MT, bool TILED>
+__global__ __launch_bounds__(GSL_THREADS) void k_gate_slice(GateView g, const uint16_t* __restrict__ x, int n_tok, int layer_begin,
+                                                            int nl, const uint4* __restrict__ tiled, GateDot dot) {
+    constexpr int TOK = 16 * TT, HID = 16 * MT, KS = 8 / MT;          // KS shares of the contraction
+    constexpr int XL = 2 * GS * TT / MT;                             // loads of token rows per lane and group
+    static_assert(XL * MT == 2 * GS * TT, "the wavefronts of a share load its token rows in equal parts");
+    constexpr int BUF = KS * GS * TT * GP_TILE_BYTES;                // one group's token rows: [share of the contraction][step][token tile]
+    constexpr int SUMS = TT * (8 > MT * GSL_HEADS_MAX / 16 ? 8 : MT * GSL_HEADS_MAX / 16) * 1024;   // what the readout keeps in LDS
+    __shared__ __align__(16) char s_x[2 * BUF < SUMS ? SUMS : 2 * BUF];
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int kh = wave / MT, m = wave % MT;
+    const int r16 = lane & 15, g4 = lane >> 4;
+    const int slices = g.d_g / HID, tiles = (n_tok + TOK - 1) / TOK;
+    const int n_blk = nl * slices * tiles, per_xcd = (int)gridDim.x >> 3;
+    const int id = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+    if (id >= n_blk) return;                                         // whole block, before any barrier
+    const int tile = id % tiles, slice = id / tiles % slices, lr = id / (tiles * slices);
+    const int tok0 = tile * TOK, layer = layer_begin + lr, hid = slice * HID + 16 * m;
+    const int steps = g.d_model >> 6, share = (steps + KS - 1) / KS;  // 64-wide steps, in all and per share
+    const int step0 = min(kh * share, steps - 1), hs = min(share, steps - kh * share);   // this share's (hs <= 0: none)
+    const int last = max(hs - 1, 0), groups = (share + GS - 1) / GS;
+
+    const uint32_t row_bytes = 2u * (uint32_t)g.d_model;
+    const char* wbase = TILED ? reinterpret_cast<const char*>(tiled + (((size_t)lr * (g.d_g >> 4) + (hid >> 4)) * steps + step0) * 128 + lane)
+                              : reinterpret_cast<const char*>(g.w1 + ((size_t)layer * g.d_g + hid + r16) * g.d_model) + (size_t)step0 * 128 + 32 * g4;
+    constexpr int w_step = TILED ? 2048 : 128, w_half = TILED ? 1024 : 16;
+    // token rows: load q of a lane is piece lane % 8 of row lane / 8 + 8 (o % 2) of token tile o / 2 % TT, step o / 2 / TT,
+    // o = MT q + m; rows past the end repeat the last token and are never written
+    const char* xp[XL];
+    int park[XL];
+#pragma unroll
+    for (int q = 0; q < XL; ++q) {
+        const int o = MT * q + m, row = 8 * (o & 1) + (lane >> 3), tt = (o >> 1) % TT, st = (o >> 1) / TT;
+        const int tok = min(tok0 + 16 * tt + row, n_tok - 1);
+        xp[q] = reinterpret_cast<const char*>(x) + ((size_t)lr * n_tok + tok) * row_bytes + (size_t)step0 * 128 + 16 * (lane & 7);
+        park[q] = ((kh * GS + st) * TT + tt) * GP_TILE_BYTES + (lane & 1) * GP_HALF_BYTES + ((lane & 7) >> 1) * GP_GROUP_BYTES + row * 16;
+    }
+    const int read_off = kh * GS * TT * GP_TILE_BYTES + g4 * GP_GROUP_BYTES + r16 * 16;
+
+    gate_f4 acc[TT];
+#pragma unroll
+    for (int j = 0; j < TT; ++j) acc[j] = gate_f4{0.f, 0.f, 0.f, 0.f};
+    gate_u4 a0[GS][2], a1[GS][2];
+    gate_u4 x0[XL], x1[XL];
+    // past the end the loads repeat the last step, whose products are left out
+    auto load_a = [&](int grp, gate_u4 (&a)[GS][2]) {
+#pragma unroll
+        for (int i = 0; i < GS; ++i) {
+            const char* p = wbase + (size_t)min(grp * GS + i, last) * w_step;
+            const gate_u4* p0 = reinterpret_cast<const gate_u4*>(p);
+            const gate_u4* p1 = reinterpret_cast<const gate_u4*>(p + w_half);
+            a[i][0] = __builtin_nontemporal_load(p0);
+            a[i][1] = __builtin_nontemporal_load(p1);
+        }
+    };
+    auto load_x = [&](int grp, gate_u4 (&xr)[XL]) {
+#pragma unroll
+        for (int q = 0; q < XL; ++q)
+            xr[q] = *reinterpret_cast<const gate_u4*>(xp[q] + (size_t)min(grp * GS + (MT * q + m) / 2 / TT, last) * 128);
+    };
+    auto park_x = [&](int buf, const gate_u4 (&xr)[XL]) {
+#pragma unroll
+        for (int q = 0; q < XL; ++q) *reinterpret_cast<gate_u4*>(s_x + buf * BUF + park[q]) = xr[q];
+    };
+    auto multiply = [&](int grp, const gate_u4 (&a)[GS][2]) {
+        const char* base = s_x + (grp & 1) * BUF + read_off;
+#pragma unroll
+        for (int i = 0; i < GS; ++i) {
+            if (grp * GS + i < hs) {                                 // (uniform)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int j = 0; j < TT; ++j)
+                        acc[j] = mma_bf16(__builtin_bit_cast(uint4, a[i][h]), *reinterpret_cast<const uint4*>(base + (i * TT + j) * GP_TILE_BYTES + h * GP_HALF_BYTES), acc[j]);
+            }
+        }
+    };
+    // During group G: its rows are in buffer G % 2, those of groups G + 1 and G + 2 are on their way to registers; the
+    // former are parked at its end into the other buffer - which group G - 1 was read from, before the previous barrier.
+    load_x(0, x0);
+    load_x(1, x1);
+    load_a(0, a0);
+    load_a(1, a1);
+    // what the readout needs first, asked for before the stream of W1: biases, this wavefront's first readout vector, s
+    const int n_heads = dot.n_heads;
+    auto v_of = [&](int h) { return *reinterpret_cast<const float4*>(dot.v + ((size_t)lr * n_heads + h) * g.d_g + hid + 4 * g4); };
+    const float4 c = *reinterpret_cast<const float4*>(g.c1 + (size_t)layer * g.d_g + hid + 4 * g4);
+    float4 w = v_of(min(kh, n_heads - 1));
+    const float s_first = dot.s[(size_t)lr * n_heads + tid % n_heads];
+    park_x(0, x0);
+    load_x(2, x0);
+    __syncthreads();
+    for (int grp = 0; grp < groups; grp += 2) {
+        multiply(grp, a0);
+        load_a(grp + 2, a0);
+        park_x(1, x1);
+        __syncthreads();
+        load_x(grp + 3, x1);
+        multiply(grp + 1, a1);
+        load_a(grp + 3, a1);
+        park_x(0, x0);
+        __syncthreads();
+        load_x(grp + 4, x0);
+    }
+
+    // acc[j][r] = this half's pre-activation of (hidden hid + 4 g4 + r, token tok0 + 16 j + r16)
+    gate_f4* s_acc = reinterpret_cast<gate_f4*>(s_x);                // [wave][token tile][lane]: 8 TT KB
+    float* s_z = reinterpret_cast<float*>(s_x);                      // then [row tile][head][token]: TT MT KB for 16 heads
+#pragma unroll
+    for (int j = 0; j < TT; ++j) s_acc[(wave * TT + j) * 64 + lane] = acc[j];
+    const float cc[4] = {c.x, c.y, c.z, c.w};
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < TT; ++j) {
+        gate_f4 sum = s_acc[(m * TT + j) * 64 + lane];
+#pragma unroll
+        for (int k = 1; k < KS; ++k) sum += s_acc[((k * MT + m) * TT + j) * 64 + lane];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float t = sum[r] + cc[r];
+            acc[j][r] = t / (1.0f + __expf(-t));
+        }
+    }
+    __syncthreads();
+    for (int h = kh; h < n_heads; h += KS) {
+        const float4 next = v_of(min(h + KS, n_heads - 1));
+#pragma unroll
+        for (int j = 0; j < TT; ++j) {
+            float t = acc[j][0] * w.x;
+            t = fmaf(acc[j][1], w.y, t);
+            t = fmaf(acc[j][2], w.z, t);
+            t = fmaf(acc[j][3], w.w, t);
+            t += __shfl_xor(t, 16, 64);
+            t += __shfl_xor(t, 32, 64);
+            if (g4 == 0) s_z[(m * n_heads + h) * TOK + 16 * j + r16] = t;
+        }
+        w = next;
+    }
+    __syncthreads();
+    const int here = min(TOK, n_tok - tok0), items = n_heads * here;
+    auto part_of = [&](int sl, int h) { return dot.part + (((size_t)lr * slices + sl) * n_heads + h) * n_tok + tok0; };
+    for (int i = tid; i < items; i += GSL_THREADS) {
+        const int h = i / here, tk = i - h * here;
+        float z = 0.f;
+#pragma unroll
+        for (int k = 0; k < MT; ++k) z += s_z[(k * n_heads + h) * TOK + tk];
+        __hip_atomic_store(part_of(slice, h) + tk, z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __shared__ int s_last;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                 // this thread's parts are acknowledged ...
+    __syncthreads();                                                 // ... and so are the whole block's, before it arrives
+    uint32_t* done = dot.done + lr * GSL_TILES_MAX + tile;
+    if (tid == 0) s_last = atomicAdd(done, 1u) == (unsigned)slices - 1u;
+    __syncthreads();
+    if (!s_last) return;
+    if (tid == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (for the next call)
+    for (int i = tid; i < items; i += GSL_THREADS) {
+        const int tk = i / n_heads, h = i - tk * n_heads;            // (neighbouring threads write neighbouring outputs)
+        float z = i == tid ? s_first : dot.s[(size_t)lr * n_heads + h];
+        for (int s0 = 0; s0 < slices; s0 += 8) {                     // 8 parts asked for at once, added in slice order
+            float p[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                p[k] = s0 + k < slices ? __hip_atomic_load(part_of(s0 + k, h) + tk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) z += p[k];
+        }
+        const float lb = log_sigmoid(z);
+        const size_t o = ((size_t)(tok0 + tk) * dot.n_layers + layer) * n_heads + h;
+        dot.log_beta_out[o] = lb;
+        if (dot.log_tail_out) dot.log_tail_out[o] = log_tail_of(lb, dot.horizon);
+    }
+}
+
+// Floats of the folded vectors and constants, rounded up to 16 bytes.
+static size_t folded_floats(const GateView& g, int n_layers, int n_heads) {
+    return ((size_t)n_layers * n_heads * (g.d_g + 1) + 3) & ~(size_t)3;
+}
+
+// How a call is run: the per-token kernels (first layer, then readout), one k_gate_slice or one k_gate_prefill, with
+// tt token tiles of 16 and (k_gate_slice) mt row tiles per block.
+constexpr int GATE_PER_TOKEN = 0, GATE_SLICE = 1, GATE_PREFILL = 2;
+struct GatePlan {
+    int kind, tt, mt;
+};
+static GatePlan gate_plan(const kvtrim_ctx* ctx, const GateView& g, int n_tok, int nl, bool prepared) {
+    const int n_heads = ctx->shape.n_kv_heads;
+    auto tiles = [&](int tt) { return (int64_t)((n_tok + 16 * tt - 1) / (16 * tt)); };
+    auto rounds = [](int64_t blocks) { return (double)((blocks + 255) / 256); };   // of one block per compute unit
+    const double r = g.d_model / 4096.0;
+    // Both kernels' times are a fixed part (launch, first loads, readout) and one that grows with d_model per round of
+    // blocks; measured (us, fixed + per round at d_model 4096): k_gate_slice with 64 tokens 8 + 24 - or 8 + 12 with slices
+    // of 32 units - with 128 tokens 15 + 27, whatever the number of hidden units; k_gate_prefill with 32 / 64 / 128
+    // tokens and 512 units 7 + 71 / 80 / 120, or 7 + 40 / 50 / 110 while the weights of the call stay in the chip's
+    // last-level cache (256 MB).
+    const int64_t slices = g.d_g / 64;
+    const double s8 = 15 + 27 * r * rounds(nl * slices * tiles(8));
+    double s4 = 8 + 24 * r * rounds(nl * slices * tiles(4));
+    if (nl * 2 * slices * tiles(4) <= 256) s4 = 8 + 12 * r;
+    const int tt = n_tok <= 16 ? 1 : (n_tok <= 32 ? 2 : (n_tok <= 64 || s4 <= s8 ? 4 : 8));
+    // slices of 64 units, halved while that still is one round of blocks (1 layer, 1 token: 15.6 / 11.5 / 9.4 us with 64 /
+    // 32 / 16 units; 20 layers: 64 units 19.4 us, 32 units - two rounds - 22.6) and the parts of the sums still fit the scratch buffer
+    int mt = 4;
+    while (tt < 8 && mt > (tt < 4 ? 1 : 2) && nl * (g.d_g / (8 * mt)) * tiles(tt) <= 256 && n_heads <= 8 * mt) mt >>= 1;
+    // the parts of the sums must fit the scratch buffer, behind the folded vectors when those are made in the call
+    const size_t part = (size_t)nl * (g.d_g / (16 * mt)) * n_heads * n_tok;
+    const bool slice_ok = n_heads <= GSL_HEADS_MAX && tiles(tt) <= GSL_TILES_MAX && (prepared || tt > 1) &&
+                          part + (prepared ? 0 : folded_floats(g, nl, n_heads)) <= (size_t)n_tok * nl * g.d_g;
+    const bool prefill_ok = g.d_g % 128 == 0 && g.d_g <= 512 && n_heads <= GP_HEADS_MAX && (prepared || n_tok >= GP_MIN_TOK);
+    const bool cached = (size_t)nl * g.d_g * g.d_model * 2 <= (size_t)100 << 20;
+    const double share = r * g.d_g / 512;
+    const double p2 = rounds(nl * tiles(2)) * (cached ? 40 : 71), p4 = rounds(nl * tiles(4)) * (cached ? 50 : 80),
+                 p8 = rounds(nl * tiles(8)) * (cached ? 110 : 120);
+    // (more than a round of 128-token blocks: their rate per token counts, and that is the best)
+    const int ptt = nl * tiles(8) > 256 ? 8 : (p2 < p4 && p2 < p8 ? 2 : (p4 < p8 ? 4 : 8));
+    if (slice_ok && (!prefill_ok || tt < 4 || (tt == 8 ? s8 : s4) <= 7 + share * (ptt == 2 ? p2 : (ptt == 4 ? p4 : p8)))) return {GATE_SLICE, tt, mt};
+    if (prefill_ok) return {GATE_PREFILL, ptt, 0};
+    return {GATE_PER_TOKEN, 0, 0};
 }
 
 // Readout from folded vectors for calls that went through the per-token first-layer kernels: one wavefront
@@ -765,15 +937,11 @@ __global__ __launch_bounds__(GD_THREADS) void k_gate_dot(const float* __restrict
 
 // Layout of a prepared buffer (kvtrim_gate_prepare): v [L][heads][d_g], s [L][heads], padding to 16 bytes, then
 // W1 of all L layers in operand-order tiles.
-static size_t prepared_fold_floats(const GateView& g, int n_layers, int n_heads) {
-    return ((size_t)n_layers * n_heads * (g.d_g + 1) + 3) & ~(size_t)3;
-}
-
 kvtrim_status launch_gate_prepare(kvtrim_ctx* ctx, const GateView& g, float* prepared, hipStream_t st) {
     const int L = ctx->shape.n_layers, n_heads = ctx->shape.n_kv_heads;
     float* v = prepared;
     float* sconst = prepared + (size_t)L * n_heads * g.d_g;
-    uint4* tiled = reinterpret_cast<uint4*>(prepared + prepared_fold_floats(g, L, n_heads));
+    uint4* tiled = reinterpret_cast<uint4*>(prepared + folded_floats(g, L, n_heads));
     {
         ProfScope prof(ctx, K_GATE_FOLD, st);
         hipLaunchKernelGGL(k_gate_fold, dim3(n_heads, L), dim3(GF_THREADS), 0, st, g, 0, n_heads, v, sconst);
@@ -798,24 +966,25 @@ kvtrim_status launch_gate(kvtrim_ctx* ctx, const GateView& g, const float* prepa
     // the folded vectors and the tiled W1 of the layer range, when prepared
     const float* pv = prepared ? prepared + (size_t)layer_begin * n_heads * g.d_g : nullptr;
     const float* ps = prepared ? prepared + (size_t)L * n_heads * g.d_g + (size_t)layer_begin * n_heads : nullptr;
-    const uint4* ptiled = prepared ? reinterpret_cast<const uint4*>(prepared + prepared_fold_floats(g, L, n_heads)) +
+    const uint4* ptiled = prepared ? reinterpret_cast<const uint4*>(prepared + folded_floats(g, L, n_heads)) +
                                          (size_t)layer_begin * (g.d_g >> 4) * (g.d_model >> 6) * 128
                                    : nullptr;
-    // with prepared weights the folded kernel has no per-call passes to pay for and wins from 24 tokens on
-    // (measured: 17 tokens 55 us per-token kernels, 24 tokens 58 / 58 us folded, 32 tokens 60 / 58, 64 tokens 80 / 58)
-    if (n_tok >= (prepared ? GP_MIN_TOK_PREPARED : GP_MIN_TOK) && prefill_shape(ctx, g)) {
+    const GatePlan plan = gate_plan(ctx, g, n_tok, nl, prepared != nullptr);
+    if (plan.kind != GATE_PER_TOKEN) {
         const float* v = pv;
         const float* sconst = ps;
         const uint4* tiled = ptiled;
         bool use_tiled = prepared != nullptr;
+        float* part = scratch;
         if (!prepared) {
-            // scratch: v [nl][heads][d_g], s [nl][heads], then (16-byte aligned) the tiled copy of W1 if the buffer
-            // - n_tok * nl * d_g floats - has room for it, which also means the call is long enough for the pass to pay
+            // scratch: v [nl][heads][d_g], s [nl][heads], then (16-byte aligned) k_gate_slice's parts of the sums, or - for
+            // k_gate_prefill - the tiled copy of W1 if the buffer (n_tok * nl * d_g floats) has room for it, which also
+            // means the call is long enough for the pass to pay
             float* sv = scratch;
             float* ss = scratch + (size_t)nl * n_heads * g.d_g;
-            const size_t fold_floats = ((size_t)nl * n_heads * (g.d_g + 1) + 3) & ~(size_t)3;
+            const size_t fold_floats = folded_floats(g, nl, n_heads);
             const size_t tiled_floats = (size_t)nl * g.d_g * g.d_model / 2;
-            use_tiled = fold_floats + tiled_floats <= (size_t)n_tok * nl * g.d_g;
+            use_tiled = plan.kind == GATE_PREFILL && fold_floats + tiled_floats <= (size_t)n_tok * nl * g.d_g;
             uint4* st_tiled = reinterpret_cast<uint4*>(scratch + fold_floats);
             {
                 ProfScope prof(ctx, K_GATE_FOLD, st);
@@ -830,12 +999,30 @@ kvtrim_status launch_gate(kvtrim_ctx* ctx, const GateView& g, const float* prepa
             v = sv;
             sconst = ss;
             tiled = st_tiled;
+            part = scratch + fold_floats;
+        }
+        if (plan.kind == GATE_SLICE) {
+            ProfScope prof(ctx, K_GATE_SLICE, st);
+            const GateDot dot{v, sconst, part, ctx->ws.gate_done, log_beta_out, log_tail_out, n_heads, L, horizon};
+            const int64_t blocks = (int64_t)nl * (g.d_g / (16 * plan.mt)) * ((n_tok + 16 * plan.tt - 1) / (16 * plan.tt));
+            const dim3 grid((unsigned)((blocks + 7) / 8 * 8));
+#define KVTRIM_CASE(TT, GS, MT)                                                                                              \
+    case TT * 8 + MT:                                                                                                        \
+        if (use_tiled) hipLaunchKernelGGL((k_gate_slice<TT, GS, MT, true>), grid, dim3(GSL_THREADS), 0, st, g, x, n_tok, layer_begin, nl, tiled, dot); \
+        else hipLaunchKernelGGL((k_gate_slice<TT, GS, MT, false>), grid, dim3(GSL_THREADS), 0, st, g, x, n_tok, layer_begin, nl, tiled, dot);          \
+        break;
+            switch (plan.tt * 8 + plan.mt) {
+                KVTRIM_CASE(1, 2, 4) KVTRIM_CASE(1, 2, 2) KVTRIM_CASE(1, 1, 1) KVTRIM_CASE(2, 1, 4) KVTRIM_CASE(2, 1, 2)
+                KVTRIM_CASE(2, 1, 1) KVTRIM_CASE(4, 1, 4) KVTRIM_CASE(4, 1, 2) KVTRIM_CASE(8, 1, 4)
+                default: return KVTRIM_EINVAL;
+            }
+#undef KVTRIM_CASE
+            KVTRIM_HIP(ctx, hipGetLastError());
+            return KVTRIM_OK;
         }
         {
             ProfScope prof(ctx, K_GATE_PREFILL, st);
-            // tokens per block: 128, or 64 / 32 while that is what it takes to have a block for every compute unit
-            int tt = 8;
-            while (tt > 2 && (int64_t)nl * ((n_tok + 16 * tt - 1) / (16 * tt)) < 256) tt >>= 1;
+            const int tt = plan.tt;
             const int tiles = (n_tok + 16 * tt - 1) / (16 * tt);
             const dim3 grid(8u * (unsigned)((nl + 7) / 8) * (unsigned)tiles);
 #define KVTRIM_GATE_PREFILL(HT, TT, TILED)                                                                                    \
@@ -862,42 +1049,23 @@ kvtrim_status launch_gate(kvtrim_ctx* ctx, const GateView& g, const float* prepa
         KVTRIM_HIP(ctx, hipGetLastError());
         return KVTRIM_OK;
     }
-    // up to 16 tokens with prepared weights: the readout rides in the first-layer kernel (its parts of the sums,
-    // heads * d_g / 16 numbers per token and layer, fit the scratch buffer's d_g when there are at most 16 heads)
-    if (prepared && n_tok <= 16 && n_heads <= 16) {
-        ProfScope prof(ctx, K_GATE_HIDDEN, st);
-        GateDot dot;
-        dot.v = pv;
-        dot.s = ps;
-        dot.part = scratch;
-        dot.done = ctx->ws.gate_done;
-        dot.log_beta_out = log_beta_out;
-        dot.log_tail_out = log_tail_out;
-        dot.n_heads = n_heads;
-        dot.n_layers = L;
-        dot.horizon = horizon;
-        hipLaunchKernelGGL((k_gate_hidden<1, 1, true, true>), dim3(g.d_g / GH_ROWS, nl, 1), dim3(GH_THREADS), 0, st, g, x, n_tok,
-                           layer_begin, ptiled, nullptr, dot);
-        KVTRIM_HIP(ctx, hipGetLastError());
-        return KVTRIM_OK;
-    }
     {
         ProfScope prof(ctx, K_GATE_HIDDEN, st);
         const dim3 grid1(g.d_g / GH_ROWS, nl, 1);
         const dim3 grid4(g.d_g / (4 * GH_ROWS), nl, 1);              // d_g is a multiple of 64
         if (n_tok <= 16 && prepared)
-            hipLaunchKernelGGL((k_gate_hidden<1, 1, true, false>), grid1, dim3(GH_THREADS), 0, st, g, x, n_tok, layer_begin, ptiled, scratch, GateDot{});
+            hipLaunchKernelGGL((k_gate_hidden<1, 1, true>), grid1, dim3(GH_THREADS), 0, st, g, x, n_tok, layer_begin, ptiled, scratch);
         else if (n_tok <= 32 && prepared)
-            hipLaunchKernelGGL((k_gate_hidden<2, 4, true, false>), grid4, dim3(GH_THREADS), 0, st, g, x, n_tok, layer_begin, ptiled, scratch, GateDot{});
+            hipLaunchKernelGGL((k_gate_hidden<2, 4, true>), grid4, dim3(GH_THREADS), 0, st, g, x, n_tok, layer_begin, ptiled, scratch);
         else if (n_tok <= 64 && prepared)
-            hipLaunchKernelGGL((k_gate_hidden<4, 4, true, false>), grid4, dim3(GH_THREADS), 0, st, g, x, n_tok, layer_begin, ptiled, scratch, GateDot{});
+            hipLaunchKernelGGL((k_gate_hidden<4, 4, true>), grid4, dim3(GH_THREADS), 0, st, g, x, n_tok, layer_begin, ptiled, scratch);
         else if (n_tok <= 16)
-            hipLaunchKernelGGL((k_gate_hidden<1, 1, false, false>), grid1, dim3(GH_THREADS), 0, st, g, x, n_tok, layer_begin, ptiled, scratch, GateDot{});
+            hipLaunchKernelGGL((k_gate_hidden<1, 1, false>), grid1, dim3(GH_THREADS), 0, st, g, x, n_tok, layer_begin, ptiled, scratch);
         else if (n_tok <= 32)
-            hipLaunchKernelGGL((k_gate_hidden<2, 4, false, false>), grid4, dim3(GH_THREADS), 0, st, g, x, n_tok, layer_begin, ptiled, scratch, GateDot{});
+            hipLaunchKernelGGL((k_gate_hidden<2, 4, false>), grid4, dim3(GH_THREADS), 0, st, g, x, n_tok, layer_begin, ptiled, scratch);
         else if (n_tok < 256)                                        // below that the tiled kernel cannot fill the chip
-            hipLaunchKernelGGL((k_gate_hidden<4, 4, false, false>), dim3(grid4.x, nl, (n_tok + 63) / 64), dim3(GH_THREADS), 0, st, g, x, n_tok,
-                               layer_begin, ptiled, scratch, GateDot{});
+            hipLaunchKernelGGL((k_gate_hidden<4, 4, false>), dim3(grid4.x, nl, (n_tok + 63) / 64), dim3(GH_THREADS), 0, st, g, x, n_tok,
+                               layer_begin, ptiled, scratch);
         else
             hipLaunchKernelGGL(k_gate_hidden_gemm, dim3((g.d_g + GG_BM - 1) / GG_BM, (n_tok + GG_BN - 1) / GG_BN, nl), dim3(256), 0,
                                st, g, x, n_tok, layer_begin, scratch);

@@ -107,7 +107,7 @@ static Layout layout_of(const kvtrim_config* c, bool select_only) {
     l.gat_slots = select_only ? 0 : c->max_entries / 4 + ((int64_t)nseg + 1) * CMP_CHUNK;
     l.off[38] = bump(cur, (size_t)l.gat_slots * sizeof(int32_t));              // gat_src
     l.off[39] = bump(cur, seg_tables * (size_t)(nseg + 1) * sizeof(int64_t));  // att_row_prefix
-    l.off[40] = bump(cur, (size_t)c->n_layers * sizeof(uint32_t));             // gate_done
+    l.off[40] = bump(cur, (size_t)c->n_layers * GATE_TOKEN_TILES * sizeof(uint32_t));   // gate_done
     l.total = (cur + 255) & ~(size_t)255;
     return l;
 }
@@ -299,7 +299,7 @@ static const char* const kernel_names[KVTRIM_N_KERNELS] = {
     "k_score", "k_sel_plan", "k_sel_hist<0>", "k_sel_hist<1>", "k_sel_hist<2>", "k_sel_count", "k_sel_mask",
     "k_cmp_scan", "k_cmp_copy", "k_att_plan", "k_att_partial", "k_att_combine", "k_append", "k_cmp_attn", "k_occupancy",
     "k_pg_init", "k_pg_append", "k_pg_score", "k_pg_plan", "k_pg_count", "k_pg_evict", "k_pg_tidy", "k_pg_att_plan", "k_gate_hidden", "k_gate_readout",
-    "k_gate_fold", "k_gate_prefill", "k_gate_retile", "k_pg_defrag", "k_gate_dot", "reserved30", "k_cmp_unstage",
+    "k_gate_fold", "k_gate_prefill", "k_gate_retile", "k_pg_defrag", "k_gate_dot", "k_gate_slice", "k_cmp_unstage",
     "k_fast_scan", "k_fast_mask", "reserved34", "reserved35", "reserved36", "reserved37", "reserved38", "reserved39"};
 
 const char* kvtrim_kernel_name(int32_t id) { return id >= 0 && id < KVTRIM_N_KERNELS ? kernel_names[id] : nullptr; }

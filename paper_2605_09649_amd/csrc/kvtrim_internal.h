@@ -19,6 +19,7 @@ constexpr int RADIX_BITS0 = 11, RADIX_BITS1 = 11, RADIX_BITS2 = 10;
 constexpr int RADIX_BINS = 2048;     // bins of the widest pass
 constexpr int HIST_BLOCKS_MAX = 512; // blocks of a histogram pass (few and fat: see k_select.hip)
 constexpr int ATT_BLOCKS = 768;       // most blocks of the attention kernel: three per compute unit
+constexpr int GATE_TOKEN_TILES = 16;  // token tiles of a gate call that finishes inside its first-layer kernel
 constexpr int DONE_WORDS = 128;      // 4 sets of 32 counters (three histogram passes, the tie count)
 constexpr int HIST_REPLICAS = 8;     // copies of the merged histogram (spreads the device-scope atomics)
 
@@ -205,7 +206,7 @@ struct Workspace {
     // destination chunk, written by the compaction scan
     int32_t* gat_src;            // [gat_slots]
     int64_t* att_row_prefix;     // [nseg+1] attention: rows (paged: slots) before each segment of the layer range, counted inside the range
-    uint32_t* gate_done;         // [n_layers] gate forward: blocks of a layer that have left their part of the readout (zero between calls)
+    uint32_t* gate_done;         // [n_layers][GATE_TOKEN_TILES] gate forward: blocks of a layer and token tile that have left their part of the readout (zero between calls)
     int64_t gat_slots;
     int64_t max_sel_chunks, max_cmp_chunks, max_att_chunks;
     int64_t att_slots;           // partial results the buffer holds: max_att_chunks and a block of the attention kernel per 64 rows more
@@ -217,7 +218,7 @@ namespace kvtrim {
 enum KernelId {
     K_SCORE = 0, K_SEL_PLAN, K_SEL_HIST0, K_SEL_HIST1, K_SEL_HIST2, K_SEL_COUNT, K_SEL_MASK,
     K_CMP_SCAN, K_CMP_COPY, K_ATT_PLAN, K_ATT_PARTIAL, K_ATT_COMBINE, K_APPEND, K_CMP_ATTN, K_OCCUPANCY,
-    K_PG_INIT, K_PG_APPEND, K_PG_SCORE, K_PG_PLAN, K_PG_COUNT, K_PG_EVICT, K_PG_TIDY, K_PG_ATT_PLAN, K_GATE_HIDDEN, K_GATE_READOUT, K_GATE_FOLD, K_GATE_PREFILL, K_GATE_RETILE, K_PG_DEFRAG, K_GATE_DOT, K_RESERVED_30, K_CMP_UNSTAGE,
+    K_PG_INIT, K_PG_APPEND, K_PG_SCORE, K_PG_PLAN, K_PG_COUNT, K_PG_EVICT, K_PG_TIDY, K_PG_ATT_PLAN, K_GATE_HIDDEN, K_GATE_READOUT, K_GATE_FOLD, K_GATE_PREFILL, K_GATE_RETILE, K_PG_DEFRAG, K_GATE_DOT, K_GATE_SLICE, K_CMP_UNSTAGE,
     K_FAST_SCAN, K_FAST_MASK, K_RESERVED_34, K_RESERVED_35, K_RESERVED_36, K_RESERVED_37, K_RESERVED_38, K_RESERVED_39, K_COUNT
 };
 static_assert(K_COUNT == KVTRIM_N_KERNELS, "kernel table out of step with the header");

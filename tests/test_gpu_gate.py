@@ -220,3 +220,55 @@ def test_host_side_argument_checks_of_the_gate():
         kv.kvtrim_gate_forward_prepared(ctx, gate, prepared, x, 2, 1, 1, 1, scratch, lb)   # empty layer range
     kv.kvtrim_gate_forward_prepared(ctx, gate, prepared, x, 2, 0, L, 1, scratch, lb)
     assert kv.kvtrim_poll_error(ctx) == 0
+
+
+@pytest.mark.parametrize("L,H,d_model,d_g,n_tok,prepared,kernel", [
+    (2, 3, 256, 64, 1, True, "k_gate_slice"),        # slices of 16 units, eight shares of four steps: half of them have none
+    (2, 9, 768, 192, 15, True, "k_gate_slice"),      # twelve steps in eight shares, more heads than wavefronts
+    (2, 32, 256, 128, 16, True, "k_gate_slice"),     # the most heads, a full token tile
+    (2, 33, 256, 128, 16, True, "k_gate_hidden"),    # ... one more: the two-kernel path
+    (6, 2, 256, 512, 33, True, "k_gate_slice"),      # four token tiles, slices of 32 units
+    (9, 2, 512, 512, 31, True, "k_gate_slice"),      # two token tiles, slices of 32 units
+    (33, 2, 256, 512, 17, True, "k_gate_slice"),     # two token tiles, slices of 64 units, more blocks than compute units
+    (33, 1, 256, 512, 2, True, "k_gate_slice"),      # one token tile, slices of 64 units
+    (20, 9, 256, 512, 65, True, "k_gate_slice"),     # two blocks of 64 tokens or one of 128, a tail of one
+    (33, 2, 1024, 576, 130, True, "k_gate_slice"),   # 128-token blocks, hidden width above 512
+    (1, 2, 256, 64, 700, True, "k_gate_slice"),      # eleven 64-token blocks along the tokens
+    (1, 2, 256, 64, 8193, True, "k_gate_hidden"),    # more token tiles than there are counters
+    (3, 2, 256, 192, 40, False, "k_gate_slice"),     # vectors folded in the call, W1 straight from its rows
+    (2, 8, 256, 64, 17, False, "k_gate_slice"),      # ... the scratch buffer just holds vectors and parts
+    (2, 16, 256, 64, 17, False, "k_gate_hidden"),    # ... and with twice the heads it does not
+    (8, 2, 1024, 384, 519, True, "k_gate_prefill"),  # 32-token blocks
+    (40, 1, 256, 512, 641, True, "k_gate_prefill"),  # 64- or 128-token blocks
+    (40, 1, 256, 512, 900, False, "k_gate_prefill"),  # 128-token blocks, everything derived in the call
+])
+def test_gate_path_by_tokens_heads_and_widths(L, H, d_model, d_g, n_tok, prepared, kernel):
+    # every path a call can take, at the sizes where its tiles, shares and slices end
+    w = ki.gate_weights(L, H, d_model, d_g, 5, b_g=3.5, seed=31 + n_tok)
+    og = oracle.Gate(bf16_bits(w["w1"]), w["c1"].numpy(), bf16_bits(w["w2"]), w["c2"].numpy(), w["w_g"].numpy(), 3.5)
+    x = ki.gate_inputs(L, n_tok, d_model, salt=n_tok)
+    pick = sorted({i for i in (0, 1, 15, 16, 63, 64, 127, 128, n_tok // 2, n_tok - 2, n_tok - 1) if 0 <= i < n_tok})
+    ctx = kv.Context(1, L, H, H, 64, 1024)
+    gate = kv.Gate.from_dict(w, DEV)
+    scratch = torch.empty(kv.kvtrim_gate_scratch_bytes(gate, n_tok, L) // 4, dtype=torch.float32, device=DEV)
+    prep = torch.empty(kv.kvtrim_gate_prepared_bytes(gate, L, H) // 4, dtype=torch.float32, device=DEV)
+    if prepared:
+        kv.kvtrim_gate_prepare(ctx, gate, prep)
+    names = [kv.kvtrim_kernel_name(i) for i in range(40)]
+    mask = sum(1 << i for i, n in enumerate(names) if n.startswith("k_gate"))
+    _, lb_ref, lt_ref = oracle.gate_forward(og, bf16_bits(x[:, pick].contiguous()), 0, L, 2)
+    outs = []
+    for again in range(2):                                        # (the arrival counters are back at zero; same bits)
+        lb = torch.full((n_tok, L, H), float("nan"), dtype=torch.float32, device=DEV)
+        lt = torch.full((n_tok, L, H), float("nan"), dtype=torch.float32, device=DEV)
+        kv.kvtrim_profile_begin(ctx, mask)
+        if prepared:
+            kv.kvtrim_gate_forward_prepared(ctx, gate, prep, x.to(DEV), n_tok, 0, L, 2, scratch, lb, lt)
+        else:
+            kv.kvtrim_gate_forward(ctx, gate, x.to(DEV), n_tok, 0, L, 2, scratch, lb, lt)
+        assert kernel in kv.kvtrim_profile_end(ctx)
+        outs.append(lb.cpu())
+        assert torch.isfinite(lb).all() and torch.isfinite(lt).all()
+        assert rel_err(lb[pick].cpu().numpy(), lb_ref) <= RTOL
+        assert np.max(np.abs(lt[pick].cpu().numpy() - lt_ref)) <= 1e-3 * np.max(np.abs(lt_ref)) + 1e-6
+    assert torch.equal(outs[0], outs[1])
