@@ -5,8 +5,8 @@
 // on the order-preserving uint32 image of the fp32 score.  Each pass builds per-block
 // histograms in LDS and merges them with device-scope atomics into replicated global histograms.
 // Every block of pass p + 1 finds the digit of pass p itself, by walking the merged histogram of
-// pass p in its prologue; only the last pass uses "last block done" (per sequence: the last block
-// that holds entries of the sequence fixes the final digit, the threshold key and the tie quota).
+// pass p in its prologue; behind the last pass a block per sequence fixes the final digit, the
+// threshold key and the tie quota.
 // The first pass can compute the score on the fly (stage 1 fused: it reads log beta and the
 // position instead of a score array and writes the score out as it goes).
 // Entries above the threshold are kept; entries equal to it are kept in storage order
@@ -23,28 +23,47 @@ constexpr int CNT_THREADS = 1024;
 constexpr int HIST_THREADS = 1024;    // histogram passes: few fat blocks, so that few device-scope
 constexpr int HIST_BLOCKS = HIST_BLOCKS_MAX;   // atomics meet on one address when the LDS histograms are merged
                                       // (the merged histogram is also kept in HIST_REPLICAS copies)
+constexpr int PLAN_TABLE_BLOCKS = 8;  // blocks of the plan kernel that share the filling of the chunk table
 constexpr int PLAN_ZERO_BLOCKS = 8;   // extra blocks of the plan kernel that clear the histograms
+constexpr int MASK_BLOCKS = 1536;     // most blocks of the mask kernel's long form (six per compute unit, what fits at once)
+constexpr int MASK_LONG = 8192;       // chunks from which it pays (16 K chunks: 30 us against 57; 6 K: 17.9 against 15.4)
+
+// The sequence that chunk `ch` belongs to.
+__device__ __forceinline__ int seq_of_chunk(const int32_t* prefix, const Shape& sh, int ch) {
+    int lo = 0, hi = sh.n_seq;                                    // prefix[lo * segs] <= ch < prefix[hi * segs]
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (prefix[mid * sh.segs_per_seq] <= ch) lo = mid;
+        else hi = mid;
+    }
+    return lo;
+}
 
 __global__ __launch_bounds__(1024) void k_sel_plan(CacheView c, Shape sh, const int64_t* __restrict__ budget,
                                                    Workspace ws, int32_t* __restrict__ kept_out,
                                                    uint32_t* __restrict__ thr_out, int hist_blocks) {
-    if (blockIdx.x > 0) {                      // clear the (replicated) histograms of the three passes
+    if (blockIdx.x >= PLAN_TABLE_BLOCKS) {     // clear the (replicated) histograms of the three passes
         const int64_t n = (int64_t)3 * HIST_REPLICAS * sh.n_seq * RADIX_BINS;   // 65536 sequences: 3.2 G words
-        for (int64_t i = (blockIdx.x - 1) * blockDim.x + threadIdx.x; i < n; i += (gridDim.x - 1) * blockDim.x)
+        for (int64_t i = (blockIdx.x - PLAN_TABLE_BLOCKS) * blockDim.x + threadIdx.x; i < n; i += (gridDim.x - PLAN_TABLE_BLOCKS) * blockDim.x)
             ws.hist[i] = 0;
         return;
     }
-    for (int i = threadIdx.x; i < DONE_WORDS; i += blockDim.x) ws.done[i] = 0;
-    for (int g = threadIdx.x; g < sh.nseg; g += blockDim.x) kept_out[g] = 0;
+    if (blockIdx.x == 0) {
+        for (int i = threadIdx.x; i < DONE_WORDS; i += blockDim.x) ws.done[i] = 0;
+        for (int g = threadIdx.x; g < sh.nseg; g += blockDim.x) kept_out[g] = 0;
+    }
+    // (one block filled the table of 33.5 M entries - 16 K chunks - in 16.5 us; eight take 8)
     const int total = build_chunk_table(c.seg_len, c.seg_start, sh.nseg, [](int) { return true; }, SEL_CHUNK, c.cap,
-                                        ws.sel_chunk_prefix, ws.sel_desc, ws.max_sel_chunks, ws.sel_entry_prefix, ws.err);
+                                        ws.sel_chunk_prefix, ws.sel_desc, ws.max_sel_chunks, ws.sel_entry_prefix, ws.err,
+                                        (int)blockIdx.x, PLAN_TABLE_BLOCKS);
+    if (blockIdx.x != 0) return;
     if ((int)threadIdx.x < hist_blocks) {                         // chunk range of every histogram block
         const int cpb = (total + hist_blocks - 1) / hist_blocks;
         const int c0 = min(total, (int)threadIdx.x * cpb), c1 = min(total, c0 + cpb);
         int4 r = make_int4(c0, c1, 0, -1);
         if (c0 < c1) {
-            r.z = ws.sel_desc[c0].seg / sh.segs_per_seq;
-            r.w = ws.sel_desc[c1 - 1].seg / sh.segs_per_seq;
+            r.z = seq_of_chunk(ws.sel_chunk_prefix, sh, c0);
+            r.w = seq_of_chunk(ws.sel_chunk_prefix, sh, c1 - 1);
         }
         ws.sel_blk[threadIdx.x] = r;
     }
@@ -63,18 +82,16 @@ __global__ __launch_bounds__(1024) void k_sel_plan(CacheView c, Shape sh, const 
         st.need_rank = 0;
         ws.sel[seq] = st;                                         // final slot (what the count and mask kernels read)
         ws.sel[sh.n_seq + seq] = st;                              // state before the first digit
-        ws.seq_done[seq] = 0;
         if (thr_out) thr_out[seq] = 0xFFFFFFFFu;                  // stands for a sequence that keeps nothing
     }
 }
 
 // One digit of the threshold key: walks the merged histogram of pass P (the sum of its replicas) of sequence
 // `seq` from the top bin down to the bin that holds the entry of rank st.rank (1-based, descending key order)
-// and returns the state with that digit appended.  Called by all threads of a 1024-thread block; `cnt_out`
-// gets the population of the chosen bin.
+// and returns the state with that digit appended.  Called by all threads of a 1024-thread block.
 template <int P>
 __device__ __forceinline__ SelState next_digit(const uint32_t* __restrict__ hist_pass, int n_seq, int seq, SelState st,
-                                               int64_t* lds64, SelState* s_state, uint32_t* cnt_out) {
+                                               int64_t* lds64, SelState* s_state) {
     constexpr int NB = P == 2 ? 1024 : 2048;
     constexpr int PER = NB / 1024;                                // bins per thread (1 or 2), thread 0 owns the highest bins
     const int tid = threadIdx.x;
@@ -101,7 +118,6 @@ __device__ __forceinline__ SelState next_digit(const uint32_t* __restrict__ hist
                 o.prefix = (st.prefix << bits) | bin;
                 o.rank = st.rank - above;
                 *s_state = o;
-                *cnt_out = cnt[i];
                 break;
             }
             above += cnt[i];
@@ -116,8 +132,6 @@ __device__ __forceinline__ SelState next_digit(const uint32_t* __restrict__ hist
 // Histogram of the next digit over the entries whose higher digits equal the prefix found so
 // far.  A block takes a contiguous range of chunks and walks it as a flat range of entry slots
 // (every load independent of the previous one); its LDS histogram is flushed per sequence.
-// Only one thread per block issues the device-scope fence (a fence per wavefront costs an L2
-// write-back each and dominated the pass).
 // SHIFT = log2 of the chunk size of the table (2048-entry chunks of a ragged cache, 128-slot pages of a
 // paged one); PAGED: a slot counts only if its position is not negative.
 // SCORE (first pass of a ragged cache only): the score is computed here from log beta and the position (Eq.
@@ -158,8 +172,7 @@ __device__ __forceinline__ void reload_quad_tail(const T* __restrict__ base, con
 template <int PASS, int SHIFT, bool PAGED, bool SCORE = false>
 __global__ __launch_bounds__(HIST_THREADS, 8) void k_sel_hist(const float* __restrict__ score, Shape sh,
                                                            Workspace ws, SelTables tb,
-                                                           uint32_t* __restrict__ thr_out, CacheView c,
-                                                           const int32_t* __restrict__ now,
+                                                           CacheView c, const int32_t* __restrict__ now,
                                                            float* __restrict__ score_w, bool vec) {
     static_assert(!SCORE || (PASS == 0 && !PAGED), "the score is fused into the first pass over a ragged cache only");
     constexpr int NB = PASS == 2 ? 1024 : 2048;
@@ -168,8 +181,6 @@ __global__ __launch_bounds__(HIST_THREADS, 8) void k_sel_hist(const float* __res
     __shared__ ChunkDesc s_desc[HIST_TILE];
     __shared__ int64_t lds64[17];
     __shared__ SelState s_state;
-    __shared__ uint32_t s_cnt;
-    __shared__ int is_last;
     const int tid = threadIdx.x;
     const int4 rng = ws.sel_blk[blockIdx.x];
     const int c0 = rng.x, c1 = rng.y;
@@ -191,9 +202,8 @@ __global__ __launch_bounds__(HIST_THREADS, 8) void k_sel_hist(const float* __res
             // (slots of ws.sel: [0] final, [1] after the plan, [2] after the first digit, [3] after the second)
             SelState st = ws.sel[(size_t)(PASS > 1 ? PASS : 1) * sh.n_seq + seq];
             if (PASS > 0) {
-                uint32_t unused;
                 st = next_digit<(PASS > 0 ? PASS - 1 : 0)>(ws.hist + (size_t)(PASS - 1) * HIST_REPLICAS * sh.n_seq * RADIX_BINS,
-                                                          sh.n_seq, seq, st, lds64, &s_state, &unused);
+                                                          sh.n_seq, seq, st, lds64, &s_state);
             }
             if (PASS > 0 && tid == 0) ws.sel[(size_t)(PASS + 1) * sh.n_seq + seq] = st;   // the same value from every block
             const uint32_t prefix = st.prefix;
@@ -314,56 +324,80 @@ __global__ __launch_bounds__(HIST_THREADS, 8) void k_sel_hist(const float* __res
                     h[i] = 0;
                 }
             }
-            if (PASS < 2) continue;                               // the next pass finds this pass's digit itself
-
-            // Last pass: the block that is last to add its counts for THIS sequence takes the final digit, hence
-            // the threshold key, how many of the entries equal to it survive, and whether those have to be ranked
-            // in order.  (One "last block" per sequence, so the sequences of a batch finish side by side.)
-            __syncthreads();
-            if (tid == 0) {
-                __threadfence();
-                const int p0 = tb.prefix[seq * sh.segs_per_seq], p1 = tb.prefix[(seq + 1) * sh.segs_per_seq];
-                const int cpb = (tb.prefix[sh.nseg] + (int)gridDim.x - 1) / (int)gridDim.x;   // chunks per block, as in the plan
-                const unsigned nblk = (unsigned)((p1 - 1) / cpb - p0 / cpb + 1);              // blocks that meet [p0, p1)
-                is_last = atomicAdd(&ws.seq_done[seq], 1u) == nblk - 1;
-            }
-            __syncthreads();
-            if (!is_last) continue;
-            __threadfence();
-            SelState fin = next_digit<2>(hist_pass, sh.n_seq, seq, st, lds64, &s_state, &s_cnt);
-            if (tid == 0) {
-                fin.thr_key = fin.prefix;
-                fin.tie_quota = fin.rank;
-                fin.need_rank = fin.rank < (int64_t)s_cnt;        // fewer survive than tie at the threshold
-                if (fin.need_rank) atomicOr((int*)&ws.done[127], 1);
-                if (thr_out) thr_out[seq] = fin.thr_key;
-                ws.sel[seq] = fin;
-            }
-            // The bound the decode-step selection starts from at its next call (k_fastsel.hip): a key with about
-            // 2 (k + 1) retained entries between it and the threshold (seed_distance).  The entry of
-            // that rank is walked down the three histograms as far as it shares the threshold's digits (below that
-            // the histograms count other buckets); where it leaves them, the upper edge of its bucket is taken.
-            if (ws.fl_cap > 0 && st.count > st.want) {
-                SelState sb = ws.sel[(size_t)sh.n_seq + seq];     // state before the first digit
-                const int64_t above = seed_distance(st.count - st.want, sh.segs_per_seq, ws.fl_cap);
-                sb.rank = st.want - above >= 1 ? st.want - above : 1;
-                uint32_t unused;
-                uint64_t seed;
-                sb = next_digit<0>(ws.hist, sh.n_seq, seq, sb, lds64, &s_state, &unused);
-                if (sb.prefix != (fin.prefix >> 21)) {
-                    seed = ((uint64_t)sb.prefix + 1) << 21;
-                } else {
-                    sb = next_digit<1>(ws.hist + (size_t)1 * HIST_REPLICAS * sh.n_seq * RADIX_BINS, sh.n_seq, seq, sb, lds64, &s_state, &unused);
-                    if (sb.prefix != (fin.prefix >> 10)) {
-                        seed = ((uint64_t)sb.prefix + 1) << 10;
-                    } else {
-                        sb = next_digit<2>(hist_pass, sh.n_seq, seq, sb, lds64, &s_state, &unused);
-                        seed = (uint64_t)sb.prefix + 1;
-                    }
-                }
-                if (tid == 0) ws.fast_hi[seq] = seed > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)seed;
-            }
+            // (the next kernel finds this pass's digit itself)
         }
+    }
+}
+
+// Behind the last pass, one block per sequence: the final digit, hence the threshold key, how many of the entries equal
+// to it survive and whether those have to be ranked in order; and the bound that the decode-step selection starts from
+// at its next call (k_fastsel.hip): a key with about 2 (k + 1) retained entries between it and the threshold
+// (seed_distance).  The entry of that rank is walked down the three histograms as far as it shares the threshold's
+// digits (below that the histograms count other buckets); where it leaves them, the upper edge of its bucket is taken.
+// All three histograms are asked for at once, and both ranks are looked up in the same three scans.  (This used to be
+// done by the last block of the last pass to arrive: two fences, then four walks one after the other, 35 to 40 us
+// behind the pass whatever its size; the kernel takes 8.)
+__global__ __launch_bounds__(HIST_THREADS) void k_sel_final(Shape sh, Workspace ws, uint32_t* __restrict__ thr_out) {
+    __shared__ int64_t lds64[17];
+    __shared__ int64_t s_rank[3][2];                              // per digit: rank inside the bin, of the threshold / of the bound
+    __shared__ uint32_t s_bin[3][2], s_cnt;
+    const int tid = threadIdx.x, seq = blockIdx.x;
+    const SelState st = ws.sel[(size_t)sh.n_seq + seq];           // before the first digit
+    if (st.keep_none) return;
+    // thread 0 owns the highest bins; bins of the first two passes go two to a thread
+    uint32_t c0[2] = {0, 0}, c1[2] = {0, 0}, c2 = 0;
+    const size_t pass = (size_t)HIST_REPLICAS * sh.n_seq * RADIX_BINS;
+#pragma unroll
+    for (int r = 0; r < HIST_REPLICAS; ++r) {
+        const uint32_t* h = ws.hist + ((size_t)r * sh.n_seq + seq) * RADIX_BINS;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            c0[i] += h[2047 - (2 * tid + i)];
+            c1[i] += h[pass + 2047 - (2 * tid + i)];
+        }
+        c2 += h[2 * pass + 1023 - tid];
+    }
+    const bool seed = ws.fl_cap > 0 && st.count > st.want;
+    int64_t rank_b = st.want - seed_distance(st.count - st.want, sh.segs_per_seq, ws.fl_cap);
+    rank_b = rank_b >= 1 ? rank_b : 1;
+    // the bin with the entries of rank ra / rb (1-based, from the top) of one digit: into s_bin[d], s_rank[d]
+    auto find = [&](int d, const uint32_t* cnt, int per, int nb, int64_t ra, int64_t rb) {
+        int64_t mine = 0, tot;
+        for (int i = 0; i < per; ++i) mine += cnt[i];
+        int64_t above = block_excl_scan<int64_t>(mine, lds64, &tot);
+        for (int i = 0; i < per; ++i) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int64_t r = k ? rb : ra;
+                if (above < r && r <= above + cnt[i]) {
+                    s_bin[d][k] = nb - 1 - (tid * per + i);
+                    s_rank[d][k] = r - above;
+                    if (k == 0 && d == 2) s_cnt = cnt[i];
+                }
+            }
+            above += cnt[i];
+        }
+        __syncthreads();
+    };
+    find(0, c0, 2, 2048, st.rank, rank_b);
+    find(1, c1, 2, 2048, s_rank[0][0], s_rank[0][1]);             // (the bound's only if it shares the first digit; else not used)
+    find(2, &c2, 1, 1024, s_rank[1][0], s_rank[1][1]);
+    if (tid != 0) return;
+    SelState fin = st;
+    fin.prefix = (((s_bin[0][0] << RADIX_BITS1) | s_bin[1][0]) << RADIX_BITS2) | s_bin[2][0];
+    fin.rank = s_rank[2][0];
+    fin.thr_key = fin.prefix;
+    fin.tie_quota = fin.rank;
+    fin.need_rank = fin.rank < (int64_t)s_cnt;                    // fewer survive than tie at the threshold
+    if (fin.need_rank) atomicOr((int*)&ws.done[127], 1);
+    if (thr_out) thr_out[seq] = fin.thr_key;
+    ws.sel[seq] = fin;
+    if (seed) {
+        uint64_t key;
+        if (s_bin[0][1] != s_bin[0][0]) key = ((uint64_t)s_bin[0][1] + 1) << 21;
+        else if (s_bin[1][1] != s_bin[1][0]) key = ((((uint64_t)s_bin[0][1] << RADIX_BITS1) | s_bin[1][1]) + 1) << 10;
+        else key = (uint64_t)((((s_bin[0][1] << RADIX_BITS1) | s_bin[1][1]) << RADIX_BITS2) | s_bin[2][1]) + 1;
+        ws.fast_hi[seq] = key > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)key;
     }
 }
 
@@ -428,26 +462,16 @@ __global__ __launch_bounds__(CNT_THREADS) void k_sel_count(const float* __restri
     });
 }
 
-// keep[e] = key > thr, or key == thr and the entry is among the first `quota` ties of its
-// sequence in (segment, position) order.  When every tie fits (the usual case) the kernel also
-// counts the survivors of its chunk into kept_out; otherwise the count kernel has done that.
-// A segment is stored in position order, so the ties are ranked by storage order (exclusive tie
-// counts per chunk).
-__global__ __launch_bounds__(SEL_THREADS) void k_sel_mask(const float* __restrict__ score, Shape sh,
-                                                          Workspace ws, SelTables tb, uint8_t* __restrict__ keep,
-                                                          int32_t* __restrict__ kept_out) {
-    __shared__ int32_t lds32[17];
+// The mask of one chunk entry by entry, for the cases the fast walk below does not take; returns how many survivors of
+// this thread still have to be credited to the segment (none where the count kernel has done it).
+__device__ __forceinline__ int mask_chunk(const float* __restrict__ score, const Workspace& ws, uint8_t* __restrict__ keep,
+                                          const ChunkDesc& d, int ch, const SelState& st, int32_t* lds32) {
     const int tid = threadIdx.x;
-    const int total = tb.prefix[sh.nseg];
-    const int ch = blockIdx.x;
-    if (ch >= total) return;
-    const ChunkDesc d = tb.desc[ch];
-    const SelState st = ws.sel[d.seg / sh.segs_per_seq];
     const float* s = score + d.first;
     uint8_t* kp = keep + d.first;
     if (st.keep_none) {
         for (int j = tid; j < d.n; j += SEL_THREADS) kp[j] = 0;
-        return;
+        return 0;
     }
     if (!st.need_rank) {                                          // every tie survives
         int n = 0;
@@ -457,19 +481,17 @@ __global__ __launch_bounds__(SEL_THREADS) void k_sel_mask(const float* __restric
             kp[j] = k;
             n += k;
         }
-        n = block_sum<int32_t>(n, lds32);
-        if (tid == 0 && n) atomicAdd(&kept_out[d.seg], n);
-        return;
+        return n;
     }
     const int64_t tbase = ws.chunk_tie_base[ch];
     const int eq_total = ws.chunk_eq[ch];
     if (eq_total == 0 || tbase + eq_total <= st.tie_quota) {     // every tie of this chunk survives
         for (int j = tid; j < d.n; j += SEL_THREADS) kp[j] = key_of_score(s[j]) >= st.thr_key;
-        return;
+        return 0;
     }
     if (tbase >= st.tie_quota) {                                  // no tie of this chunk survives
         for (int j = tid; j < d.n; j += SEL_THREADS) kp[j] = key_of_score(s[j]) > st.thr_key;
-        return;
+        return 0;
     }
     // the quota runs out inside this chunk: rank the ties in order
     int64_t running = tbase;
@@ -486,6 +508,100 @@ __global__ __launch_bounds__(SEL_THREADS) void k_sel_mask(const float* __restric
         if (j < d.n) kp[j] = key > st.thr_key || (is_eq && running + ex < st.tie_quota);
         running += tot;
     }
+    return 0;
+}
+
+// keep[e] = key > thr, or key == thr and the entry is among the first `quota` ties of its
+// sequence in (segment, position) order.  When every tie fits (the usual case) the kernel also
+// counts the survivors of its chunk into kept_out; otherwise the count kernel has done that.
+// A segment is stored in position order, so the ties are ranked by storage order (exclusive tie
+// counts per chunk).
+// A block takes a run of consecutive chunks.  VEC (many chunks; score 16-byte, keep 4-byte aligned): a chunk is walked in
+// aligned groups of four entries - a 16-byte load and one 4-byte store each, entry by entry where the group leaves the
+// chunk - and the next chunk's descriptor and scores are asked for before the current ones are used; survivors are
+// counted in registers and added to their segment once per run.  Otherwise a block per chunk, entry by entry: a chain of
+// five latencies per 2048 entries, which many chunks pay eight times over (33.5 M entries, 168 MB: 57 us, now 30).
+template <bool VEC>
+__global__ __launch_bounds__(SEL_THREADS) void k_sel_mask(const float* __restrict__ score, Shape sh,
+                                                          Workspace ws, SelTables tb, uint8_t* __restrict__ keep,
+                                                          int32_t* __restrict__ kept_out, int64_t cap) {
+    __shared__ int32_t lds32[17];
+    const int tid = threadIdx.x;
+    const int total = tb.prefix[sh.nseg];
+    const int per = (total + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int ch0 = (int)blockIdx.x * per, ch1 = min(total, ch0 + per);
+    if (ch0 >= ch1) return;
+    constexpr int QT = SEL_CHUNK / 4 / SEL_THREADS;               // groups per thread; an unaligned chunk has one more
+    ChunkDesc d = tb.desc[ch0], dn = d;
+    float v[QT][4], vn[QT][4];
+    auto load = [&](const ChunkDesc& cd, float (&x)[QT][4]) {
+#pragma unroll
+        for (int u = 0; u < QT; ++u) load_quad(score, quad_of(cd, tid + u * SEL_THREADS, cap), x[u]);
+    };
+    if (VEC) load(d, v);
+    int seq = -1, n = 0;
+    SelState st;
+    auto credit = [&](int seg) {                                  // the run of chunks of segment `seg` has ended
+        const int sum = block_sum<int32_t>(n, lds32);
+        if (tid == 0 && sum) atomicAdd(&kept_out[seg], sum);
+        n = 0;
+    };
+    for (int ch = ch0; ch < ch1; ++ch) {
+        if (ch + 1 < ch1) {
+            dn = tb.desc[ch + 1];
+            if (VEC) load(dn, vn);
+        }
+        if (d.seg / sh.segs_per_seq != seq) {                     // (uniform)
+            seq = d.seg / sh.segs_per_seq;
+            st = ws.sel[seq];
+        }
+        if (VEC && !st.keep_none && !st.need_rank) {              // every tie survives
+            auto put = [&](const Quad& q, const float (&x)[4]) {
+                uint32_t word = 0;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool k = key_of_score(x[i]) >= st.thr_key;
+                    word |= (uint32_t)k << (8 * i);
+                    if (i >= q.lo && i < q.hi) n += k;
+                }
+                if (q.lo == 0 && q.hi == 4) {
+                    *reinterpret_cast<uint32_t*>(keep + q.a) = word;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (i >= q.lo && i < q.hi) keep[q.a + i] = (uint8_t)(word >> (8 * i));
+                }
+            };
+#pragma unroll
+            for (int u = 0; u < QT; ++u) {
+                const Quad q = quad_of(d, tid + u * SEL_THREADS, cap);
+                if (!q.whole) reload_quad_tail(score, q, v[u]);   // (once per array at most)
+                put(q, v[u]);
+            }
+            if (tid == 0) {                                       // an unaligned full chunk: its last group
+                const Quad q = quad_of(d, QT * SEL_THREADS, cap);
+                if (q.lo < q.hi) {
+                    float x[4];
+                    load_quad(score, q, x);
+                    if (!q.whole) reload_quad_tail(score, q, x);
+                    put(q, x);
+                }
+            }
+        } else {
+            n += mask_chunk(score, ws, keep, d, ch, st, lds32);
+        }
+        if (ch + 1 == ch1 || dn.seg != d.seg) credit(d.seg);
+        d = dn;
+#pragma unroll
+        for (int u = 0; u < QT; ++u)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[u][i] = vn[u][i];
+    }
+}
+
+static void launch_select_final(kvtrim_ctx* ctx, uint32_t* thr, hipStream_t st) {
+    ProfScope prof(ctx, K_SEL_FINAL, st);
+    hipLaunchKernelGGL(k_sel_final, dim3(ctx->shape.n_seq), dim3(HIST_THREADS), 0, st, ctx->shape, ctx->ws, thr);
 }
 
 // The three histogram passes over a paged cache whose chunk table (one chunk per page) is in tb;
@@ -496,13 +612,14 @@ void launch_select_passes_paged(kvtrim_ctx* ctx, const float* score, const SelTa
     const Workspace& ws = ctx->ws;
     if (pass == 0) {
         ProfScope prof(ctx, K_SEL_HIST0, st);
-        hipLaunchKernelGGL((k_sel_hist<0, 7, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, score, sh, ws, tb, thr, CacheView(), nullptr, nullptr, false);
+        hipLaunchKernelGGL((k_sel_hist<0, 7, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, score, sh, ws, tb, CacheView(), nullptr, nullptr, false);
     } else if (pass == 1) {
         ProfScope prof(ctx, K_SEL_HIST1, st);
-        hipLaunchKernelGGL((k_sel_hist<1, 7, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, score, sh, ws, tb, thr, CacheView(), nullptr, nullptr, false);
+        hipLaunchKernelGGL((k_sel_hist<1, 7, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, score, sh, ws, tb, CacheView(), nullptr, nullptr, false);
     } else {
         ProfScope prof(ctx, K_SEL_HIST2, st);
-        hipLaunchKernelGGL((k_sel_hist<2, 7, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, score, sh, ws, tb, thr, CacheView(), nullptr, nullptr, false);
+        hipLaunchKernelGGL((k_sel_hist<2, 7, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, score, sh, ws, tb, CacheView(), nullptr, nullptr, false);
+        launch_select_final(ctx, thr, st);
     }
 }
 
@@ -523,20 +640,24 @@ static kvtrim_status launch_select_impl(kvtrim_ctx* ctx, const CacheView& c, con
     const bool vec = c.cap >= 4 && ((((uintptr_t)score) | ((uintptr_t)score_w) | ((uintptr_t)c.pos) | ((uintptr_t)c.log_beta) |
                                      ((uintptr_t)c.log_tail)) & 15) == 0;
     { ProfScope prof(ctx, K_SEL_PLAN, st);
-      hipLaunchKernelGGL(k_sel_plan, dim3(1 + PLAN_ZERO_BLOCKS), dim3(1024), 0, st, c, sh, budget, ws, kept, thr, hist_blocks); }
+      hipLaunchKernelGGL(k_sel_plan, dim3(PLAN_TABLE_BLOCKS + PLAN_ZERO_BLOCKS), dim3(1024), 0, st, c, sh, budget, ws, kept, thr, hist_blocks); }
     { ProfScope prof(ctx, K_SEL_HIST0, st);
       if (now)
-          hipLaunchKernelGGL((k_sel_hist<0, SEL_SHIFT, false, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, (const float*)nullptr, sh, ws, tb, thr, c, now, score_w, vec);
+          hipLaunchKernelGGL((k_sel_hist<0, SEL_SHIFT, false, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, (const float*)nullptr, sh, ws, tb, c, now, score_w, vec);
       else
-          hipLaunchKernelGGL((k_sel_hist<0, SEL_SHIFT, false>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, score, sh, ws, tb, thr, c, nullptr, nullptr, vec); }
+          hipLaunchKernelGGL((k_sel_hist<0, SEL_SHIFT, false>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, score, sh, ws, tb, c, nullptr, nullptr, vec); }
     { ProfScope prof(ctx, K_SEL_HIST1, st);
-      hipLaunchKernelGGL((k_sel_hist<1, SEL_SHIFT, false>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, score, sh, ws, tb, thr, c, nullptr, nullptr, vec); }
+      hipLaunchKernelGGL((k_sel_hist<1, SEL_SHIFT, false>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, score, sh, ws, tb, c, nullptr, nullptr, vec); }
     { ProfScope prof(ctx, K_SEL_HIST2, st);
-      hipLaunchKernelGGL((k_sel_hist<2, SEL_SHIFT, false>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, score, sh, ws, tb, thr, c, nullptr, nullptr, vec); }
+      hipLaunchKernelGGL((k_sel_hist<2, SEL_SHIFT, false>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, score, sh, ws, tb, c, nullptr, nullptr, vec); }
+    launch_select_final(ctx, thr, st);
     { ProfScope prof(ctx, K_SEL_COUNT, st);
       hipLaunchKernelGGL(k_sel_count, dim3(n_chunk_blocks < 256 ? n_chunk_blocks : 256), dim3(CNT_THREADS), 0, st, score, sh, ws, tb, kept); }
     { ProfScope prof(ctx, K_SEL_MASK, st);
-      hipLaunchKernelGGL(k_sel_mask, dim3(n_chunk_blocks), dim3(SEL_THREADS), 0, st, score, sh, ws, tb, keep, kept); }
+      if (n_chunk_blocks >= MASK_LONG && (((uintptr_t)score) & 15) == 0 && (((uintptr_t)keep) & 3) == 0)
+          hipLaunchKernelGGL(k_sel_mask<true>, dim3(MASK_BLOCKS), dim3(SEL_THREADS), 0, st, score, sh, ws, tb, keep, kept, c.cap);
+      else
+          hipLaunchKernelGGL(k_sel_mask<false>, dim3(n_chunk_blocks), dim3(SEL_THREADS), 0, st, score, sh, ws, tb, keep, kept, c.cap); }
     KVTRIM_HIP(ctx, hipGetLastError());
     return KVTRIM_OK;
 }

@@ -171,7 +171,6 @@ struct Workspace {
     uint32_t* hist;              // [3][HIST_REPLICAS][n_seq][RADIX_BINS]
     SelState* sel;               // [4][n_seq]: final state; state after the plan, after pass 0, after pass 1
     int32_t* chunk_old_len;      // [nseg] kvtrim_append_compact: segment lengths before the chunk was appended
-    uint32_t* seq_done;          // [n_seq] blocks of the last histogram pass that have added their counts for the sequence
     uint32_t* done;              // [DONE_WORDS] "last block" counters: per pass one top-level and 16 group counters
     int32_t* chunk_eq;           // [max_sel_chunks] entries equal to the threshold
     int64_t* chunk_tie_base;     // [max_sel_chunks] ties of the sequence before the chunk
@@ -219,7 +218,7 @@ enum KernelId {
     K_SCORE = 0, K_SEL_PLAN, K_SEL_HIST0, K_SEL_HIST1, K_SEL_HIST2, K_SEL_COUNT, K_SEL_MASK,
     K_CMP_SCAN, K_CMP_COPY, K_ATT_PLAN, K_ATT_PARTIAL, K_ATT_COMBINE, K_APPEND, K_CMP_ATTN, K_OCCUPANCY,
     K_PG_INIT, K_PG_APPEND, K_PG_SCORE, K_PG_PLAN, K_PG_COUNT, K_PG_EVICT, K_PG_TIDY, K_PG_ATT_PLAN, K_GATE_HIDDEN, K_GATE_READOUT, K_GATE_FOLD, K_GATE_PREFILL, K_GATE_RETILE, K_PG_DEFRAG, K_GATE_DOT, K_GATE_SLICE, K_CMP_UNSTAGE,
-    K_FAST_SCAN, K_FAST_MASK, K_RESERVED_34, K_RESERVED_35, K_RESERVED_36, K_RESERVED_37, K_RESERVED_38, K_RESERVED_39, K_COUNT
+    K_FAST_SCAN, K_FAST_MASK, K_SEL_FINAL, K_RESERVED_35, K_RESERVED_36, K_RESERVED_37, K_RESERVED_38, K_RESERVED_39, K_COUNT
 };
 static_assert(K_COUNT == KVTRIM_N_KERNELS, "kernel table out of step with the header");
 }  // namespace kvtrim
