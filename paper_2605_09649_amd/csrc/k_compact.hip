@@ -1,8 +1,7 @@
 // Stage 3: stable stream compaction of the retained entries into a tight ragged cache.
 //
-// k_cmp_scan  one block per segment: counts the mask per 128-entry chunk (wavefront ballot),
-//             scans the counts inside the segment and derives the destination segment table
-//             from `kept`.
+// k_cmp_scan  one block per segment: counts the mask per 128-entry chunk, scans the counts inside
+//             the segment and derives the destination segment table from `kept`.
 // k_cmp_copy  one block of 8 wavefronts per chunk: a ballot/prefix over the chunk's mask
 //             ranks the survivors; every wavefront then moves at most 16 rows in ONE batch of
 //             loads followed by one batch of stores (16 bytes per lane, whole rows per 16
@@ -10,29 +9,45 @@
 //             this chip than wavefronts that loop over several batches.
 #include "kvtrim_device.h"
 
+#include <type_traits>
+
 namespace kvtrim {
 
 constexpr int SCAN_THREADS = 1024;
-constexpr int SCAN_BATCH = 8;          // chunks whose mask bytes a wavefront requests before it counts any
+constexpr int SCAN_LANE = 16;          // mask bytes per lane and load: a wavefront's load covers 8 chunks
+constexpr int SCAN_GROUP = 64 * SCAN_LANE / CMP_CHUNK;
+constexpr int SCAN_BATCH = SCAN_THREADS / (SCAN_THREADS / 64) / SCAN_GROUP;   // loads with which the wavefronts cover a tile of SCAN_THREADS chunks: 8
+static_assert(SCAN_LANE * 8 == CMP_CHUNK, "eight lanes to a chunk");
 
-// Sums N values over the block with one pair of barriers; every thread gets every sum.
-template <int N>
-__device__ __forceinline__ void block_sum_n(int64_t (&v)[N], int64_t* lds /* [16 * N] */) {
-    const int lane = lane_id(), wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+// bit i set where byte i of the 16 is not zero
+typedef uint32_t scan_v4 __attribute__((ext_vector_type(4), aligned(1)));   // (16 bytes at any address)
+__device__ __forceinline__ uint32_t nonzero_bytes(const scan_v4& w) {
+    auto four = [](uint32_t x) {
+        const uint32_t t = ((((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) >> 7) & 0x01010101u;
+        return (t * 0x01020408u) >> 24 & 15u;
+    };
+    return four(w.x) | four(w.y) << 4 | four(w.z) << 8 | four(w.w) << 12;
+}
+
+// Sums four values over the block (1024 threads) with one barrier; every thread gets every sum.  Each step of the first
+// two halves what a lane still has to add up, so that a wavefront takes 7 shuffles instead of 24, and the 16 wavefronts'
+// sums are added by shuffles as well: with eight values one after the other and every thread reading 128 sums from LDS
+// this was most of k_cmp_scan at a thousand segments (1024 segments of 12 K entries: 51 us, now 32).
+__device__ __forceinline__ void block_sum_4(int64_t (&v)[4], int64_t* lds /* [64] */) {
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const bool up = lane & 32, odd = lane & 16;
+    int64_t a = (up ? v[2] : v[0]) + __shfl_xor(up ? v[0] : v[2], 32, 64);
+    const int64_t b = (up ? v[3] : v[1]) + __shfl_xor(up ? v[1] : v[3], 32, 64);
+    a = (odd ? b : a) + __shfl_xor(odd ? a : b, 16, 64);          // lanes 16 k .. 16 k + 15 hold value k
 #pragma unroll
-    for (int k = 0; k < N; ++k) v[k] = wave_sum(v[k]);
+    for (int s = 8; s >= 1; s >>= 1) a += __shfl_xor(a, s, 64);
+    if ((lane & 15) == 0) lds[wave * 4 + (lane >> 4)] = a;
     __syncthreads();
-    if (lane == 0) {
+    a = lds[lane];                                                // value lane % 4 of wavefront lane / 4
 #pragma unroll
-        for (int k = 0; k < N; ++k) lds[wave * N + k] = v[k];
-    }
-    __syncthreads();
+    for (int s = 32; s >= 4; s >>= 1) a += __shfl_xor(a, s, 64);
 #pragma unroll
-    for (int k = 0; k < N; ++k) {
-        int64_t s = 0;
-        for (int w = 0; w < nw; ++w) s += lds[w * N + k];
-        v[k] = s;
-    }
+    for (int k = 0; k < 4; ++k) v[k] = __shfl(a, k, 64);
 }
 
 // With many segments the per-block reduction over all segments below costs more than a launch: one block
@@ -107,12 +122,17 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
                                                            int reserve, int align, Shape sh, Workspace ws, int inplace,
                                                            int gat) {
     __shared__ int64_t lds64[17];
-    __shared__ int64_t lds_n[16 * 8];
+    __shared__ int64_t lds_n[64];
+    __shared__ int s_bad;                                         // 1: a segment table entry, 2: a count that no mask can have
     __shared__ int s_cnt[SCAN_THREADS];
     __shared__ int s_ex[SCAN_THREADS];
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const int g = blockIdx.x;
     const int nseg = sh.nseg;
+    if (!PRE) {
+        if (tid == 0) s_bad = 0;
+        __syncthreads();
+    }
 
     // Order of the memory traffic: (1) this segment's own table entry; (2) in one round, the table entries of all
     // segments (for the prefixes; !PRE) and the mask bytes of this segment's first SCAN_THREADS chunks; then
@@ -144,58 +164,73 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
         o_kp = kept[tid];
     }
 
-    // survivors per chunk of one tile of SCAN_THREADS chunks into s_cnt: one wavefront per chunk, two coalesced byte
-    // loads per lane; a wavefront requests the bytes of up to SCAN_BATCH of its chunks before it counts any
-    uint8_t b[SCAN_BATCH][CMP_CHUNK / 64];
-    auto request = [&](int tile0, int tile_n, int c0) {
+    // Mask bytes of one tile of SCAN_THREADS chunks: load u of a wavefront covers the 8 chunks from (16 u + wave) * 8 on, 16
+    // bytes per lane (at any address: a segment starts anywhere), all of them asked for at once.  They stay in registers
+    // as one bit per entry, for the counts and (gat) for the row numbers.  (A wavefront per chunk with two byte loads per
+    // lane, twice over for the row numbers, took 46 us for the 33.5 M entries of a first eviction; now 18.5.)
+    // A lane whose 16 bytes reach past the segment's end reads the segment's last 16 and shifts them into place.
+    // In two halves, the first of which - 512 chunks - is under way while the prefixes are summed.
+    scan_v4 w[SCAN_BATCH / 2];
+    uint32_t bits[SCAN_BATCH];
+    auto first_of = [&](int tile0, int u) { return (tile0 + (u * (SCAN_THREADS / 64) + wave) * SCAN_GROUP) * CMP_CHUNK; };   // (< 2^31 + a tile)
+    auto request = [&](int tile0, int half) {
 #pragma unroll
-        for (int u = 0; u < SCAN_BATCH; ++u) {
-            const int ch = tile0 + c0 + u * (SCAN_THREADS / 64);
-#pragma unroll
-            for (int r = 0; r < CMP_CHUNK / 64; ++r) {
-                const int64_t j = (int64_t)ch * CMP_CHUNK + r * 64 + lane;
-                b[u][r] = (c0 + u * (SCAN_THREADS / 64) < tile_n && j < len) ? kp[j] : (uint8_t)0;
+        for (int u = 0; u < SCAN_BATCH / 2; ++u) {
+            const int64_t j0 = first_of(tile0, half * (SCAN_BATCH / 2) + u);
+            w[u] = scan_v4{0, 0, 0, 0};
+            if (j0 < len) {                                       // (uniform)
+                if (len >= SCAN_LANE) {
+                    w[u] = *reinterpret_cast<const scan_v4*>(kp + min(j0 + lane * SCAN_LANE, (int64_t)len - SCAN_LANE));
+                } else if (lane == 0) {
+                    uint64_t lo = 0, hi = 0;
+                    for (int i = 0; i < len; ++i) (i < 8 ? lo : hi) |= (uint64_t)kp[i] << (8 * (i & 7));
+                    w[u] = scan_v4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
+                }
             }
         }
     };
-    auto count = [&](int tile_n, int c0) {
+    auto count = [&](int tile0, auto half) {                      // survivors per chunk of half a tile into s_cnt
 #pragma unroll
-        for (int u = 0; u < SCAN_BATCH; ++u) {
-            int cnt = 0;
-#pragma unroll
-            for (int r = 0; r < CMP_CHUNK / 64; ++r) cnt += __popcll(__ballot(b[u][r] != 0));
-            const int cl = c0 + u * (SCAN_THREADS / 64);
-            if (lane == 0 && cl < tile_n) s_cnt[cl] = cnt;
+        for (int i = 0; i < SCAN_BATCH / 2; ++i) {
+            constexpr int first = decltype(half)::value * (SCAN_BATCH / 2);
+            const int u = first + i;
+            const int64_t over = (int64_t)first_of(tile0, u) + lane * SCAN_LANE - ((int64_t)len - SCAN_LANE);   // bytes past the end
+            bits[u] = nonzero_bytes(w[i]);
+            if (over > 0 && len >= SCAN_LANE) bits[u] = over < SCAN_LANE ? bits[u] >> over : 0u;
+            int n = __popc(bits[u]);
+            n += __shfl_xor(n, 1, 64);
+            n += __shfl_xor(n, 2, 64);
+            n += __shfl_xor(n, 4, 64);
+            if ((lane & 7) == 0) s_cnt[(u * (SCAN_THREADS / 64) + wave) * SCAN_GROUP + (lane >> 3)] = n;
         }
     };
-    request(0, min(SCAN_THREADS, nch), wave);                     // in flight while the prefixes are summed
+    request(0, 0);                                                // in flight while the prefixes are summed
 
     if (!PRE) {
         // chunks and destination entries of the segments before g, and the totals
-        int64_t acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};   // chunks_before, dst_before, dst_total, chunks_total, bad_layout, bad_kept, runs_before, runs_total
+        int64_t acc[4] = {0, 0, 0, 0};   // chunks (before g in the low, all in the high half), destination chunks (alike), dst entries before g, all
+        bool bl = false, bk = false;
         if (tid < nseg) {
             const int i = tid;
             const int64_t o_nxt = i + 1 < nseg ? src.seg_start[i + 1] : src.cap;
-            acc[4] |= (o_len < 0 || o_st < 0 || o_st + o_len > src.cap || o_st + o_len > o_nxt);
-            acc[5] |= (o_kp < 0 || o_kp > o_len);
-            const int64_t nc = o_len > 0 ? ((int64_t)o_len + CMP_CHUNK - 1) / CMP_CHUNK : 0;
+            bl = o_len < 0 || o_st < 0 || o_st + o_len > src.cap || o_st + o_len > o_nxt;
+            bk = o_kp < 0 || o_kp > o_len;
+            // (both below 2^24 for a segment that is inside the buffers; the sums count only if none is bad)
+            const int64_t nc = o_len > 0 && !bl ? ((int64_t)o_len + CMP_CHUNK - 1) / CMP_CHUNK : 0;
+            const int64_t nrun = gat && o_len > 0 && !bl && !bk ? ((int64_t)o_kp + CMP_CHUNK - 1) / CMP_CHUNK : 0;
             const int64_t need = ((int64_t)o_kp + reserve + align - 1) / align * align;   // align = 1 unless pages are built
-            const int64_t nrun = gat && o_len > 0 ? ((int64_t)o_kp + CMP_CHUNK - 1) / CMP_CHUNK : 0;
-            acc[3] += nc;
-            acc[2] += need;
-            acc[7] += nrun;
-            if (i < g) {
-                acc[0] += nc;
-                acc[1] += need;
-                acc[6] += nrun;
-            }
+            acc[0] = nc << 32 | (i < g ? nc : 0);
+            acc[1] = nrun << 32 | (i < g ? nrun : 0);
+            acc[2] = i < g ? need : 0;
+            acc[3] = need;
         }
-        block_sum_n<8>(acc, lds_n);
-        chunks_before = acc[0];
-        dst_before = acc[1];
-        runs_before = acc[6];
-        const int64_t dst_total = acc[2], chunks_total = acc[3];
-        const bool bad_layout = acc[4] != 0 || chunks_total > ws.max_cmp_chunks || acc[7] > ws.max_att_chunks, bad_kept = acc[5] != 0;
+        if (bl || bk) atomicOr(&s_bad, bl ? 1 : 2);
+        block_sum_4(acc, lds_n);
+        chunks_before = acc[0] & 0xffffffff;
+        dst_before = acc[2];
+        runs_before = acc[1] & 0xffffffff;
+        const int64_t dst_total = acc[3], chunks_total = acc[0] >> 32;
+        const bool bad_layout = (s_bad & 1) || chunks_total > ws.max_cmp_chunks || (acc[1] >> 32) > ws.max_att_chunks, bad_kept = s_bad & 2;
         if (inplace) dst_before = start;                          // the segment keeps its place
         if (bad_layout || bad_kept || (!inplace && dst_total > dst.cap)) {   // every block takes the same decision
             if (tid == 0) {
@@ -234,10 +269,10 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
     for (int tile0 = 0; tile0 < nch; tile0 += SCAN_THREADS) {
         const int tile_n = min(SCAN_THREADS, nch - tile0);
         __syncthreads();                                          // s_cnt of the previous tile has been read
-        for (int c0 = wave; c0 < tile_n; c0 += (SCAN_THREADS / 64) * SCAN_BATCH) {
-            if (tile0 > 0 || c0 > wave) request(tile0, tile_n, c0);   // (the first batch of the first tile is already here)
-            count(tile_n, c0);
-        }
+        if (tile0 > 0) request(tile0, 0);                         // (the first one is already here)
+        count(tile0, std::integral_constant<int, 0>());
+        request(tile0, 1);
+        count(tile0, std::integral_constant<int, 1>());
         __syncthreads();
         const int ch = tile0 + tid;
         const int64_t v = tid < tile_n ? s_cnt[tid] : 0;
@@ -255,24 +290,26 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
         }
         if (gat) {
             // the source row of every destination row, in slots of CMP_CHUNK per destination chunk (the segment's
-            // chunks are consecutive, so row r of the segment has slot runs_before * CMP_CHUNK + r): a wavefront per
-            // source chunk ranks its survivors again (the mask bytes come from the cache this time)
+            // chunks are consecutive, so row r of the segment has slot runs_before * CMP_CHUNK + r)
             s_ex[tid] = (int)(running + ex);
             __syncthreads();
             int32_t* slots = ws.gat_src + runs_before * CMP_CHUNK;
-            for (int c0 = wave; c0 < tile_n; c0 += (SCAN_THREADS / 64) * SCAN_BATCH) {
-                request(tile0, tile_n, c0);
 #pragma unroll
-                for (int u = 0; u < SCAN_BATCH; ++u) {
-                    const int cl = c0 + u * (SCAN_THREADS / 64);
-                    if (cl >= tile_n) break;                      // uniform over the wavefront
-                    const uint64_t m0 = __ballot(b[u][0] != 0), m1 = __ballot(b[u][1] != 0);
-                    const int r0 = s_ex[cl] + mbcnt(m0), r1 = s_ex[cl] + __popcll(m0) + mbcnt(m1);
-                    const int32_t row = (int32_t)(start + (int64_t)(tile0 + cl) * CMP_CHUNK + lane);
-                    // (a mask with more survivors than `kept` says - reported below - must not leave the segment's slots)
-                    if (b[u][0] != 0 && r0 >= 0 && r0 < gat_slots) slots[r0] = row;
-                    if (b[u][1] != 0 && r1 >= 0 && r1 < gat_slots) slots[r1] = row + 64;
-                }
+            for (int u = 0; u < SCAN_BATCH; ++u) {
+                const int cl = (u * (SCAN_THREADS / 64) + wave) * SCAN_GROUP + (lane >> 3);
+                const int n = __popc(bits[u]);
+                int before = n;                                   // survivors of the chunk up to this lane's, then before them
+                int o = __shfl_up(before, 1, 8);
+                if ((lane & 7) >= 1) before += o;
+                o = __shfl_up(before, 2, 8);
+                if ((lane & 7) >= 2) before += o;
+                o = __shfl_up(before, 4, 8);
+                if ((lane & 7) >= 4) before += o;
+                int64_t r = (int64_t)s_ex[cl] + before - n;
+                const int32_t row = (int32_t)(start + ((int64_t)tile0 + cl) * CMP_CHUNK + (lane & 7) * SCAN_LANE);
+                // (a mask with more survivors than `kept` says - reported below - must not leave the segment's slots)
+                for (uint32_t m = bits[u]; m; m &= m - 1, ++r)
+                    if (r >= 0 && r < gat_slots) slots[r] = row + __builtin_ctz(m);
             }
         }
         running += tot;

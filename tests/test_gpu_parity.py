@@ -770,3 +770,43 @@ def test_attention_on_a_bad_table_outside_the_layer_range_gives_no_result():
     kv.kvtrim_decode_attn(ctx, kv.Cache.from_dict(c, DEV), q, 1, 2, 0.125, out, None)
     assert kv.kvtrim_poll_error(ctx) == -6                               # KVTRIM_ELAYOUT
     assert torch.all(out == 99.0)
+
+
+@pytest.mark.parametrize("reserve,lens", [
+    (3, [0, 1, 15, 16, 17, 127, 128, 129]),                  # under, at and over a lane's 16 mask bytes and a chunk; every start misaligned differently
+    (1, [1023, 1024, 1025, 2047, 2048, 2049, 4095, 8]),      # ... a wavefront's load (8 chunks) and a selection chunk
+    (2, [65536, 65537, 131072, 131073, 5, 70000, 1, 3]),     # ... half a tile and a tile of 1024 chunks of the scan
+])
+@pytest.mark.parametrize("keep_part", [2, 40])               # a block per source chunk / the gathering form
+def test_selection_and_compaction_at_the_edges_of_their_tiles(reserve, lens, keep_part):
+    w = wl(1, 2, 4, 2, 64)
+    c, now = ki.ragged_cache(w, lens, reserve=reserve, salt=50)
+    hc = host_cache(w, c)
+    total = sum(lens)
+    budget = np.array([max(total // keep_part, 1)], dtype=np.int64)
+    score = oracle.score(hc, now.numpy())
+    keep, kept, thr = oracle.select(hc, score, budget)
+    ctx = kv.Context(1, 2, 4, 8, 64, hc.cap)
+    src = kv.Cache.from_dict(c, DEV)
+    d_score = torch.zeros(hc.cap, dtype=torch.float32, device=DEV)
+    d_keep = torch.full((hc.cap,), 7, dtype=torch.uint8, device=DEV)
+    d_kept = torch.zeros(w.nseg, dtype=torch.int32, device=DEV)
+    d_thr = torch.zeros(1, dtype=torch.int32, device=DEV)
+    kv.kvtrim_score_select(ctx, src, now.to(DEV), torch.from_numpy(budget).to(DEV), d_score, d_keep, d_kept, d_thr)
+    dst = kv.Cache.empty(w.nseg, 64, int(kept.sum()) + w.nseg * reserve, DEV)
+    kv.kvtrim_compact(ctx, src, d_keep, d_kept, dst, reserve)
+    assert kv.kvtrim_poll_error(ctx) == 0
+    assert np.array_equal(d_kept.cpu().numpy(), kept)
+    assert int(d_thr.cpu().numpy().view(np.uint32)[0]) == int(thr[0])
+    k = d_keep.cpu().numpy()
+    inside = np.zeros(hc.cap, dtype=bool)
+    starts, cursor = c["seg_start"].tolist(), 0
+    for g, (s, n) in enumerate(zip(starts, lens)):
+        inside[s:s + n] = True
+        assert np.array_equal(k[s:s + n], keep[s:s + n])
+        m = torch.from_numpy(keep[s:s + n].astype(bool))
+        here = slice(cursor, cursor + int(kept[g]))
+        for name in ("k", "v", "log_beta", "pos"):
+            assert torch.equal(getattr(dst, name)[here].cpu(), c[name][s:s + n][m])
+        cursor += int(kept[g]) + reserve
+    assert np.all(k[~inside] == 7)                           # slots outside the segments are not written
