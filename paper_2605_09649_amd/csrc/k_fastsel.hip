@@ -373,10 +373,68 @@ __device__ __forceinline__ T ld_dev(const T* p) { return __hip_atomic_load(p, __
 template <typename T>
 __device__ __forceinline__ void st_dev(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
+// What the one-call decode step needs besides the scan, for the 16 segments from seg0 on, a wavefront each: the segment's
+// new tokens enter the source cache, and its part of the row mover's chunk table is written.  Both are read by the next
+// kernel only.  (A block per segment of 1024 threads was half the grid of the scoring kernel: at 4096 segments its
+// blocks alone took eight rounds of the chip.)
+__device__ __forceinline__ void write_step_tables(const CacheView& c, const Shape& sh, const Workspace& ws, const StepArgs& sa,
+                                                  int seg0, int32_t* lds32 /* [17] */) {
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    const int seg = seg0 + wave;
+    const bool mine = seg < sh.nseg;
+    bool bad = false, nocap = false;                              // (reported by the scanning blocks)
+    SegView v{};
+    if (mine) v = seg_view<SCAN_STEP>(c, seg, sh.nseg, sa, &bad, &nocap);
+    // the chunks of the segments before the block's are counted here
+    int before = 0;
+    for (int g = tid; g < seg0; g += FAST_THREADS) {
+        bool b2 = false, n2 = false;
+        before += (seg_view<SCAN_STEP>(c, g, sh.nseg, sa, &b2, &n2).len + CMP_CHUNK - 1) / CMP_CHUNK;
+    }
+    if (mine) {
+        // ---- this segment's new tokens enter the source cache (rows: 16 bytes per lane; metadata)
+        const int cnt_new = v.len - v.len_old, vpr = sh.head_dim / 8;
+        const uint4* kn = reinterpret_cast<const uint4*>(sa.k_new) + (int64_t)seg * sa.n_new * vpr;
+        const uint4* vn = reinterpret_cast<const uint4*>(sa.v_new) + (int64_t)seg * sa.n_new * vpr;
+        uint4* kd = reinterpret_cast<uint4*>(sa.src.k) + (v.start + v.len_old) * vpr;
+        uint4* vd = reinterpret_cast<uint4*>(sa.src.v) + (v.start + v.len_old) * vpr;
+        for (int i = lane; i < cnt_new * vpr; i += 64) {
+            kd[i] = kn[i];
+            vd[i] = vn[i];
+        }
+        if (lane < cnt_new) {                                     // (n_new <= STEP_MAX_NEW)
+            const int64_t e = v.start + v.len_old + lane, ni = (int64_t)seg * sa.n_new + lane;
+            sa.src.log_beta[e] = sa.lb_new[ni];
+            if (c.log_tail) sa.src.log_tail[e] = sa.lt_new[ni];
+            sa.src.pos[e] = sa.pos_new[ni];
+        }
+    }
+    before = block_sum<int32_t>(before, lds32);
+    const int nch = (v.len + CMP_CHUNK - 1) / CMP_CHUNK;          // (0 behind the last segment)
+    __syncthreads();
+    if (lane == 0) lds32[wave] = nch;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) before += lds32[w];
+    if (!mine) return;
+    for (int ch = lane; ch < nch; ch += 64) {
+        ChunkDesc d;
+        d.first = v.start + (int64_t)ch * CMP_CHUNK;
+        d.n = min(CMP_CHUNK, v.len - ch * CMP_CHUNK);
+        d.seg = seg;
+        ws.cmp_desc[before + ch] = d;
+    }
+    if (lane == 0) {
+        ws.cmp_chunk_prefix[seg] = before;
+        if (seg == sh.nseg - 1) ws.cmp_chunk_prefix[sh.nseg] = before + nch;
+        if (!sa.inplace) ws.step_len[seg] = v.len;                // (in place: the sequence's last block leaves the survivors' count there)
+    }
+}
+static_assert(STEP_MAX_NEW <= 64, "a lane per new token");
+
 // SCORE: stage 1 is computed here (and written to score_out); otherwise the scores are read from score_in.
-// STEP (implies SCORE): the decode step in one call.  Every block scores a segment's new tokens from the new-token
-// buffers; one more block per segment, behind the scanning blocks of the grid, writes their rows and metadata into
-// the source cache and the segment's part of the row mover's chunk table.  The last block of a sequence also leaves
+// STEP (implies SCORE): the decode step in one call.  Every block scores its segments' new tokens from the new-token
+// buffers; more blocks, behind the scanning ones of the grid, write their rows and metadata into the source cache and
+// the row mover's chunk table (write_step_tables).  The last block of a sequence also leaves
 // what the compaction needs: survivors per segment, the destination's segment table and - when the evicted entries
 // are on the candidate list - per chunk of 128 entries the number of entries it loses and per segment a record with
 // the start of its survivors in the destination and the indices of its evicted entries, from which a block of the
@@ -392,7 +450,7 @@ template <bool SCORE, int KIND>
 __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const int32_t* __restrict__ now,
                                                             const float* score_in, float* score_out,
                                                             const int64_t* __restrict__ budget, Shape sh, Workspace ws,
-                                                            int bps, int32_t* __restrict__ kept_out,
+                                                            int bps, int spb, int32_t* __restrict__ kept_out,
                                                             uint32_t* __restrict__ thr_out, StepArgs sa) {
     constexpr bool STEP = KIND == SCAN_STEP, PAGED = KIND == SCAN_PAGED;
     static_assert(!STEP || SCORE, "the one-call step computes the scores itself");
@@ -400,33 +458,45 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     __shared__ int s_last, s_ncand;
     __shared__ uint32_t s_base;
     // this block's candidates, before they go to the list; the last block of a sequence reuses the space (STEP)
-    __shared__ int32_t s_pool[(STEP ? 3 : 2) * FAST_STAGE];
+    __shared__ int32_t s_pool[(STEP ? 4 : 3) * FAST_STAGE];
     uint32_t* c_key = reinterpret_cast<uint32_t*>(s_pool);
     int32_t* c_pos = s_pool + FAST_STAGE;
-    int32_t* c_idx = s_pool + (STEP ? 2 : 1) * FAST_STAGE;
+    int32_t* c_seg = s_pool + 2 * FAST_STAGE;
+    int32_t* c_idx = s_pool + (STEP ? 3 : 2) * FAST_STAGE;
     __shared__ int s_ev[STEP ? STEP_MAX_SEGS : 1], s_off[STEP ? STEP_MAX_SEGS : 1];
     __shared__ int s_seqcnt[STEP ? STEP_MAX_SEQS : 1];
     static_assert(STEP_MAX_SEGS <= FAST_STAGE && STEP_MAX_SEGS <= FAST_THREADS && STEP_MAX_EVICT <= FAST_STAGE, "the step's tables reuse the staging space, one segment per thread");
     const int tid = threadIdx.x;
-    // STEP: behind the scanning blocks the grid has one block per segment that only writes the segment's tables
-    const bool tables_only = STEP && (int)blockIdx.x >= sh.nseg * bps;
-    const int seg = tables_only ? (int)blockIdx.x - sh.nseg * bps : (int)blockIdx.x / bps;
-    const int part = tables_only ? 0 : (int)blockIdx.x % bps;
-    const int seq = seg / sh.segs_per_seq;
+    // bps blocks share a segment, or (bps = 1) spb segments of a sequence share a block, FAST_THREADS / spb threads to each
+    // (whole wavefronts).  STEP: behind the scanning blocks the grid has blocks that only write the segments' tables, a
+    // wavefront per segment.
+    const int bpq = (sh.segs_per_seq + spb - 1) / spb * bps;      // scanning blocks per sequence
+    const bool tables_only = STEP && (int)blockIdx.x >= sh.n_seq * bpq;
+    const int threads = FAST_THREADS / spb, group = tid / threads, gt = tid % threads;
+    const int seq = tables_only ? 0 : (int)blockIdx.x / bpq;
+    const int blk_in_seq = tables_only ? 0 : (int)blockIdx.x % bpq;
+    const int part = blk_in_seq % bps;
+    const int seg_in_seq = blk_in_seq / bps * spb + group;
+    const bool no_seg = !tables_only && seg_in_seq >= sh.segs_per_seq;   // (the last block of a sequence may have groups to spare)
+    const int seg = seq * sh.segs_per_seq + min(seg_in_seq, sh.segs_per_seq - 1);
     // Device-scope atomics on one address are served one after the other (tens of nanoseconds each), so the
     // blocks of a sequence do not meet on one word: the list is kept in up to FAST_SUB sub-lists with a counter
     // each, the lowest key and the arrivals in FAST_SUB group words (then one top-level arrival per group).
-    const int blk_in_seq = (seg - seq * sh.segs_per_seq) * bps + part;
-    const int nblk = sh.segs_per_seq * bps;
+    const int nblk = bpq;
     const int nsub = nblk < FAST_SUB ? nblk : FAST_SUB;
     const int sub = blk_in_seq % nsub;
     if (tid == 0) s_ncand = 0;
     __syncthreads();
+    // the tables-only blocks take no part in the scan, so a sequence's last block never waits for them
+    if (tables_only) {
+        write_step_tables(c, sh, ws, sa, ((int)blockIdx.x - sh.n_seq * bpq) * (FAST_THREADS / 64), sm.lds32);
+        return;
+    }
     bool bad = false, nocap = false;
     const SegView sv0 = seg_view<KIND>(c, seg, sh.nseg, sa, &bad, &nocap);
     const int64_t start = sv0.start;
-    const int len = sv0.len;
-    if (tid == 0 && part == 0 && !tables_only && (bad || nocap)) atomicOr(ws.err, bad ? ERR_LAYOUT : ERR_CAP);
+    const int len = no_seg ? 0 : sv0.len;
+    if (gt == 0 && part == 0 && !no_seg && (bad || nocap)) atomicOr(ws.err, bad ? ERR_LAYOUT : ERR_CAP);
     const uint32_t hi = ws.fast_hi[seq];
     const uint32_t cap = (uint32_t)ws.fl_cap;
     const uint32_t subcap = cap / (uint32_t)nsub;                 // entries per sub-list
@@ -450,63 +520,19 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     ks.n_new = sa.n_new;
     ks.t1 = SCORE ? now[seq] + 1 : 0;
 
-    // STEP, the segment's tables-only block (it takes no part in the scan, so the sequence's last block never waits
-    // for this): the segment's new tokens enter the source cache, and the segment's part of the row mover's chunk
-    // table is written.  Both are read by the next kernel only.
-    if (tables_only) {
-        // ---- this segment's new tokens enter the source cache (rows: 16 bytes per thread; metadata)
-        const int cnt_new = sv0.len - sv0.len_old;
-        const int vpr = sh.head_dim / 8;
-        const uint4* kn = reinterpret_cast<const uint4*>(sa.k_new) + (int64_t)seg * sa.n_new * vpr;
-        const uint4* vn = reinterpret_cast<const uint4*>(sa.v_new) + (int64_t)seg * sa.n_new * vpr;
-        uint4* kd = reinterpret_cast<uint4*>(sa.src.k) + (start + sv0.len_old) * vpr;
-        uint4* vd = reinterpret_cast<uint4*>(sa.src.v) + (start + sv0.len_old) * vpr;
-        for (int i = tid; i < cnt_new * vpr; i += FAST_THREADS) {
-            kd[i] = kn[i];
-            vd[i] = vn[i];
-        }
-        for (int i = tid; i < cnt_new; i += FAST_THREADS) {
-            const int64_t e = start + sv0.len_old + i, ni = (int64_t)seg * sa.n_new + i;
-            sa.src.log_beta[e] = sa.lb_new[ni];
-            if (c.log_tail) sa.src.log_tail[e] = sa.lt_new[ni];
-            sa.src.pos[e] = sa.pos_new[ni];
-        }
-        // ---- and its part of the row mover's chunk table: the chunks of the segments before it are counted here
-        int before = 0;
-        for (int g = tid; g < seg; g += FAST_THREADS) {
-            bool b2 = false, n2 = false;
-            const SegView v = seg_view<KIND>(c, g, sh.nseg, sa, &b2, &n2);
-            before += (v.len + CMP_CHUNK - 1) / CMP_CHUNK;
-        }
-        before = block_sum<int32_t>(before, sm.lds32);
-        const int nch = (len + CMP_CHUNK - 1) / CMP_CHUNK;
-        for (int ch = tid; ch < nch; ch += FAST_THREADS) {
-            ChunkDesc d;
-            d.first = start + (int64_t)ch * CMP_CHUNK;
-            d.n = min(CMP_CHUNK, len - ch * CMP_CHUNK);
-            d.seg = seg;
-            ws.cmp_desc[before + ch] = d;
-        }
-        if (tid == 0) {
-            ws.cmp_chunk_prefix[seg] = before;
-            if (seg == sh.nseg - 1) ws.cmp_chunk_prefix[sh.nseg] = before + nch;
-            if (!sa.inplace) ws.step_len[seg] = len;              // (in place: the sequence's last block leaves the survivors' count there)
-        }
-        return;
-    }
-
     // ---- every entry of this block's share: score, and onto the list if its key is below the bound
     {
         uint32_t mn = 0xFFFFFFFFu;
+        const int stride = bps * threads;
         // batches of FAST_BATCH entries per thread: all loads of a batch are issued before any of them is used
-        for (int j0 = part * FAST_THREADS + tid; j0 < len; j0 += bps * FAST_THREADS * FAST_BATCH) {
+        for (int j0 = part * threads + gt; j0 < len; j0 += stride * FAST_BATCH) {
             float sv[FAST_BATCH];
             int pv[FAST_BATCH];
             int64_t at[FAST_BATCH];                               // where the entry lies in the arrays
             bool bad_page = false;
 #pragma unroll
             for (int u = 0; u < FAST_BATCH; ++u) {
-                const int j = j0 + u * bps * FAST_THREADS;
+                const int j = j0 + u * stride;
                 const bool isnew = STEP && j >= sv0.len_old;
                 at[u] = isnew ? (int64_t)seg * sa.n_new + (j - sv0.len_old) : (j < len ? ks.place(sv0, j, &bad_page) : 0);
             }
@@ -515,7 +541,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
                 float lbv[FAST_BATCH], ltv[FAST_BATCH];
 #pragma unroll
                 for (int u = 0; u < FAST_BATCH; ++u) {
-                    const int j = j0 + u * bps * FAST_THREADS;
+                    const int j = j0 + u * stride;
                     const bool in = j < len;
                     const bool isnew = STEP && j >= sv0.len_old;
                     pv[u] = in ? (isnew ? sa.pos_new : c.pos)[at[u]] : 0;
@@ -524,7 +550,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
                 }
 #pragma unroll
                 for (int u = 0; u < FAST_BATCH; ++u) {
-                    const int j = j0 + u * bps * FAST_THREADS;
+                    const int j = j0 + u * stride;
                     const float dt = (float)(ks.t1 - pv[u]);
                     sv[u] = c.log_tail ? __fmaf_rn(dt, lbv[u], ltv[u]) : __fmul_rn(dt, lbv[u]);
                     if (PAGED && pv[u] < 0) sv[u] = 0.f;          // an empty slot's score reads 0
@@ -533,14 +559,14 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
             } else {
 #pragma unroll
                 for (int u = 0; u < FAST_BATCH; ++u) {
-                    const int j = j0 + u * bps * FAST_THREADS;
+                    const int j = j0 + u * stride;
                     sv[u] = j < len ? score_in[at[u]] : 0.f;
                     pv[u] = (PAGED && j < len) ? c.pos[at[u]] : 0;
                 }
             }
 #pragma unroll
             for (int u = 0; u < FAST_BATCH; ++u) {
-                const int j = j0 + u * bps * FAST_THREADS;
+                const int j = j0 + u * stride;
                 const uint32_t key = key_of_score(sv[u]);
                 const bool live = j < len && (!PAGED || pv[u] >= 0);
                 if (live) mn = min(mn, key);
@@ -549,6 +575,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
                     if (slot < FAST_STAGE) {
                         c_key[slot] = key;
                         c_pos[slot] = (SCORE || PAGED) ? pv[u] : c.pos[at[u]];
+                        c_seg[slot] = seg;
                         if (STEP) c_idx[slot] = j;
                     }
                 }
@@ -569,7 +596,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
                 if (slot < subcap) {
                     const size_t at = (size_t)sub * subcap + slot;
                     st_dev(&lk[at], c_key[i]);
-                    st_dev(&ls[at], (int32_t)seg);
+                    st_dev(&ls[at], c_seg[i]);
                     st_dev(&lp[at], c_pos[i]);
                     if (STEP) st_dev(&li[at], c_idx[i]);
                 }
@@ -998,42 +1025,45 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
 // a live entry is marked for release (owner -2), exactly as k_pg_evict does from the mask.
 template <bool PAGED, bool EVICT = false>
 __global__ __launch_bounds__(FAST_THREADS) void k_fast_mask(CacheView c, const float* __restrict__ score, Shape sh,
-                                                            Workspace ws, int bps, uint8_t* __restrict__ keep,
+                                                            Workspace ws, int bps, int spb, uint8_t* __restrict__ keep,
                                                             int32_t* __restrict__ kept_out, PagedArgs pg) {
     __shared__ int32_t lds32[17];
-    const int tid = threadIdx.x;
-    const int seg = blockIdx.x / bps, part = blockIdx.x % bps;
-    const int seq = seg / sh.segs_per_seq;
+    // (dealt as in k_fast_scan)
+    const int bpq = (sh.segs_per_seq + spb - 1) / spb * bps, threads = FAST_THREADS / spb;
+    const int tid = (int)threadIdx.x % threads, seq = (int)blockIdx.x / bpq, blk = (int)blockIdx.x % bpq, part = blk % bps;
+    const int seg_in_seq = blk / bps * spb + (int)threadIdx.x / threads;
+    const int seg = seq * sh.segs_per_seq + min(seg_in_seq, sh.segs_per_seq - 1);
+    const int stride = bps * threads;
     StepArgs sa{};
     sa.pg = pg;
     bool bad = false, nocap = false;
     const SegView v = seg_view<PAGED ? SCAN_PAGED : SCAN_RAGGED>(c, seg, sh.nseg, sa, &bad, &nocap);
-    const int len = v.len;
+    const int len = seg_in_seq < sh.segs_per_seq ? v.len : 0;
     KeySource<false, PAGED ? SCAN_PAGED : SCAN_RAGGED> ks;
     ks.bt = pg.block_table;
     ks.n_pages = pg.n_pages;
     const FastSel fs = ws.fast_sel[seq];
     int n = 0;
     const bool seg_before = seg < fs.seg_thr, seg_same = seg == fs.seg_thr;
-    for (int j0 = part * FAST_THREADS + tid; j0 < len; j0 += bps * FAST_THREADS * FAST_BATCH) {
+    for (int j0 = part * threads + tid; j0 < len; j0 += stride * FAST_BATCH) {
         int64_t at[FAST_BATCH];
         bool bp = false;
 #pragma unroll
         for (int u = 0; u < FAST_BATCH; ++u) {
-            const int j = j0 + u * bps * FAST_THREADS;
+            const int j = j0 + u * stride;
             at[u] = j < len ? ks.place(v, j, &bp) : 0;
         }
         float sv[FAST_BATCH];
         int pv[FAST_BATCH];
 #pragma unroll
         for (int u = 0; u < FAST_BATCH; ++u) {
-            const int j = j0 + u * bps * FAST_THREADS;
+            const int j = j0 + u * stride;
             sv[u] = (j < len && fs.mode == FSEL_THRESHOLD) ? score[at[u]] : 0.f;
             pv[u] = (PAGED && j < len) ? c.pos[at[u]] : 0;
         }
 #pragma unroll
         for (int u = 0; u < FAST_BATCH; ++u) {
-            const int j = j0 + u * bps * FAST_THREADS;
+            const int j = j0 + u * stride;
             bool kf = false;
             if (j < len) {
                 kf = fs.mode == FSEL_ALL;
@@ -1060,9 +1090,34 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_mask(CacheView c, const f
             }
         }
     }
-    n = block_sum<int32_t>(n, lds32);
-    if (tid == 0 && n) atomicAdd(&kept_out[seg], n);
+    if (spb == 1) {
+        n = block_sum<int32_t>(n, lds32);
+        if (tid == 0 && n) atomicAdd(&kept_out[seg], n);
+    } else {                                                      // (a wavefront's threads share a segment)
+        n = wave_sum(n);
+        if (lane_id() == 0 && n) atomicAdd(&kept_out[seg], n);
+    }
 }
+
+// How the blocks of k_fast_scan and k_fast_mask are dealt: several to a segment of more than FAST_ENTRIES_PER_BLOCK
+// entries; several segments of a sequence to a block when a block each would be more than are resident at once (one of
+// k_fast_scan's per compute unit, two of k_fast_mask's) - a block of k_fast_scan lives 8 to 10 us whatever it has to do, so
+// 4096 segments of 2048 entries took sixteen rounds of the chip: 202 us, with sixteen segments to a block 50.
+struct ScanGrid {
+    int bps, spb;
+    unsigned blocks;
+};
+static ScanGrid scan_grid(const Shape& sh, int64_t cap, int resident) {
+    ScanGrid g;
+    const int64_t bps = cap / ((int64_t)sh.nseg * FAST_ENTRIES_PER_BLOCK);
+    g.bps = (int)(bps < 1 ? 1 : (bps > 64 ? 64 : bps));
+    g.spb = 1;
+    auto per_seq = [&](int spb) { return (int64_t)((sh.segs_per_seq + spb - 1) / spb); };
+    while (bps < 1 && g.spb < FAST_THREADS / 64 && sh.n_seq * per_seq(g.spb) > resident && 2 * g.spb <= sh.segs_per_seq) g.spb *= 2;
+    g.blocks = (unsigned)(sh.n_seq * per_seq(g.spb) * g.bps);
+    return g;
+}
+constexpr int SCAN_RESIDENT = 256, MASK_RESIDENT = 512;
 
 kvtrim_status launch_score_select(kvtrim_ctx* ctx, const CacheView& c, const int32_t* now, const int64_t* budget,
                                   float* score, uint8_t* keep, int32_t* kept, uint32_t* thr, int64_t evict_hint,
@@ -1072,13 +1127,13 @@ kvtrim_status launch_score_select(kvtrim_ctx* ctx, const CacheView& c, const int
     // the list has to hold about 3 (k + 1) entries for k evictions, spread unevenly over its sub-lists
     if (evict_hint <= 0 || 8 * (evict_hint + 1) > (int64_t)ws.fl_cap)
         return launch_score_select_general(ctx, c, now, budget, score, keep, kept, thr, st);
-    int64_t bps = c.cap / ((int64_t)sh.nseg * FAST_ENTRIES_PER_BLOCK);
-    bps = bps < 1 ? 1 : (bps > 64 ? 64 : bps);
-    const dim3 grid((unsigned)(sh.nseg * bps)), block(FAST_THREADS);
+    const dim3 block(FAST_THREADS);
+    const ScanGrid sg = scan_grid(sh, c.cap, SCAN_RESIDENT);
     { ProfScope prof(ctx, K_FAST_SCAN, st);
-      hipLaunchKernelGGL((k_fast_scan<true, SCAN_RAGGED>), grid, block, 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, (int)bps, kept, thr, StepArgs()); }
+      hipLaunchKernelGGL((k_fast_scan<true, SCAN_RAGGED>), dim3(sg.blocks), block, 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, kept, thr, StepArgs()); }
     { ProfScope prof(ctx, K_FAST_MASK, st);
-      hipLaunchKernelGGL(k_fast_mask<false>, grid, block, 0, st, c, (const float*)score, sh, ws, (int)bps, keep, kept, PagedArgs()); }
+      const ScanGrid mg = scan_grid(sh, c.cap, MASK_RESIDENT);
+      hipLaunchKernelGGL(k_fast_mask<false>, dim3(mg.blocks), block, 0, st, c, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, PagedArgs()); }
     KVTRIM_HIP(ctx, hipGetLastError());
     return KVTRIM_OK;
 }
@@ -1090,18 +1145,17 @@ kvtrim_status launch_score_select_paged(kvtrim_ctx* ctx, const CacheView& pool, 
                                         hipStream_t st, bool evict) {
     const Shape& sh = ctx->shape;
     const Workspace& ws = ctx->ws;
-    int64_t bps = pool.cap / ((int64_t)sh.nseg * FAST_ENTRIES_PER_BLOCK);
-    bps = bps < 1 ? 1 : (bps > 64 ? 64 : bps);
-    const dim3 grid((unsigned)(sh.nseg * bps)), block(FAST_THREADS);
+    const dim3 block(FAST_THREADS);
+    const ScanGrid sg = scan_grid(sh, pool.cap, SCAN_RESIDENT), mg = scan_grid(sh, pool.cap, MASK_RESIDENT);
     StepArgs sa{};
     sa.pg = pg;
     { ProfScope prof(ctx, K_FAST_SCAN, st);
-      hipLaunchKernelGGL((k_fast_scan<true, SCAN_PAGED>), grid, block, 0, st, pool, now, (const float*)nullptr, score, budget, sh, ws, (int)bps, kept, thr, sa); }
+      hipLaunchKernelGGL((k_fast_scan<true, SCAN_PAGED>), dim3(sg.blocks), block, 0, st, pool, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, kept, thr, sa); }
     { ProfScope prof(ctx, K_FAST_MASK, st);
       if (evict)
-          hipLaunchKernelGGL((k_fast_mask<true, true>), grid, block, 0, st, pool, (const float*)score, sh, ws, (int)bps, keep, kept, pg);
+          hipLaunchKernelGGL((k_fast_mask<true, true>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, pg);
       else
-          hipLaunchKernelGGL((k_fast_mask<true, false>), grid, block, 0, st, pool, (const float*)score, sh, ws, (int)bps, keep, kept, pg); }
+          hipLaunchKernelGGL((k_fast_mask<true, false>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, pg); }
     KVTRIM_HIP(ctx, hipGetLastError());
     return KVTRIM_OK;
 }
@@ -1110,11 +1164,11 @@ kvtrim_status launch_score_select_paged(kvtrim_ctx* ctx, const CacheView& pool, 
 kvtrim_status launch_step_scan(kvtrim_ctx* ctx, const CacheView& c, const int32_t* now, const int64_t* budget, float* score,
                                int32_t* kept, uint32_t* thr, const StepArgs& sa, hipStream_t st) {
     const Shape& sh = ctx->shape;
-    int64_t bps = c.cap / ((int64_t)sh.nseg * FAST_ENTRIES_PER_BLOCK);
-    bps = bps < 1 ? 1 : (bps > 64 ? 64 : bps);
+    const ScanGrid sg = scan_grid(sh, c.cap, SCAN_RESIDENT);
+    const unsigned tables = (unsigned)((sh.nseg + FAST_THREADS / 64 - 1) / (FAST_THREADS / 64));
     ProfScope prof(ctx, K_FAST_SCAN, st);
-    hipLaunchKernelGGL((k_fast_scan<true, SCAN_STEP>), dim3((unsigned)(sh.nseg * bps + sh.nseg)), dim3(FAST_THREADS), 0, st, c, now,
-                       (const float*)nullptr, score, budget, sh, ctx->ws, (int)bps, kept, thr, sa);
+    hipLaunchKernelGGL((k_fast_scan<true, SCAN_STEP>), dim3(sg.blocks + tables), dim3(FAST_THREADS), 0, st, c, now,
+                       (const float*)nullptr, score, budget, sh, ctx->ws, sg.bps, sg.spb, kept, thr, sa);
     KVTRIM_HIP(ctx, hipGetLastError());
     return KVTRIM_OK;
 }

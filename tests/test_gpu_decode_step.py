@@ -298,3 +298,22 @@ def test_four_hundred_steps_through_the_one_call_equal_the_radix_select_path_and
     assert kv.kvtrim_poll_error(one.ctx) == 0 and kv.kvtrim_poll_error(sep.ctx) == 0
     listed, fallback = kv.kvtrim_select_path_counts(one.ctx)
     assert (listed, fallback) == (steps - 1, 0)
+
+
+@pytest.mark.parametrize("S,L,H", [(3, 11, 9), (5, 13, 9), (20, 5, 13), (260, 1, 16)])   # 2, 4, 8 and 16 segments to a scanning block,
+def test_several_segments_to_a_scanning_block(S, L, H):                                   # the last block of a sequence with groups to spare
+    from paged_harness import run_paged_both
+    from test_gpu_paged import check as check_paged
+    w = wl(S, L, H, 2, 64)
+    rng = np.random.default_rng(S)
+    seg_len = rng.choice([0, 1, 63, 64, 65, 127, 130, 257], w.nseg)
+    c, now = ki.ragged_cache(w, seg_len, reserve=1, salt=S)
+    budget = [max(1, int(seg_len[s * L * H:(s + 1) * L * H].sum()) - L * H // 2) for s in range(S)]
+
+    def clone():
+        return {k: (v.clone() if torch.is_tensor(v) else v) for k, v in c.items()}
+    check(run_steps_both(w, steps=3, budget=budget, device=DEV, cache_dict=clone(), now0=now.numpy(), one_call=True, hint=L * H), (S, "step"))
+    for r in run_steps_both(w, steps=3, budget=budget, device=DEV, cache_dict=clone(), now0=now.numpy(), fused=True, hint=L * H):
+        assert r["status"] == 0 and r["score_equal"] and r["keep_equal"] and r["cache_equal"], (S, "score_select", r)
+    check_paged(run_paged_both(w, [budget] * 3, device=DEV, cache_dict=clone(), now0=now.numpy(), hint=L * H))
+    check_paged(run_paged_both(w, [budget] * 3, device=DEV, cache_dict=clone(), now0=now.numpy(), hint=L * H, one_call=True))
