@@ -114,25 +114,22 @@ struct ResolveShared {
     int32_t g_seg[FAST_BIN_DIRECT], g_pos[FAST_BIN_DIRECT];
 };
 
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_min(uint32_t v) {         // with a lane's own value where there is no other
+    return min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xF, false));
+}
 __device__ __forceinline__ uint32_t block_min_u32(uint32_t v, uint32_t* red) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v = min(v, (uint32_t)__shfl_xor((int)v, d, 64));
+    v = dpp_min<0x111, 0xF>(v);                                   // inside the rows of 16 lanes, then across them (as wave_incl_scan)
+    v = dpp_min<0x112, 0xF>(v);
+    v = dpp_min<0x114, 0xF>(v);
+    v = dpp_min<0x118, 0xF>(v);
+    v = dpp_min<0x142, 0xA>(v);
+    v = dpp_min<0x143, 0xC>(v);
     __syncthreads();
-    if (lane_id() == 0) red[threadIdx.x >> 6] = v;
+    if (lane_id() == 63) red[threadIdx.x >> 6] = v;
     __syncthreads();
     uint32_t r = 0xFFFFFFFFu;
     for (int i = 0; i < (int)(blockDim.x >> 6); ++i) r = min(r, red[i]);
-    return r;
-}
-
-__device__ __forceinline__ uint32_t block_max_u32(uint32_t v, uint32_t* red) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, d, 64));
-    __syncthreads();
-    if (lane_id() == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    uint32_t r = 0;
-    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) r = max(r, red[i]);
     return r;
 }
 
@@ -446,11 +443,11 @@ static_assert(STEP_MAX_NEW <= 64, "a lane per new token");
 // writer waits for before it arrives, and read with device-scope loads - so no block needs a fence, which on this
 // chip means a write-back of a whole L2.  The scores written here are read by the NEXT kernel only; the
 // single-block select, which has to look at every entry, recomputes them from the call's inputs.
-template <bool SCORE, int KIND>
+template <bool SCORE, int KIND, bool MULTI>
 __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const int32_t* __restrict__ now,
                                                             const float* score_in, float* score_out,
                                                             const int64_t* __restrict__ budget, Shape sh, Workspace ws,
-                                                            int bps, int spb, int32_t* __restrict__ kept_out,
+                                                            int bps, int spb_arg, int32_t* __restrict__ kept_out,
                                                             uint32_t* __restrict__ thr_out, StepArgs sa) {
     constexpr bool STEP = KIND == SCAN_STEP, PAGED = KIND == SCAN_PAGED;
     static_assert(!STEP || SCORE, "the one-call step computes the scores itself");
@@ -464,12 +461,13 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     int32_t* c_seg = s_pool + 2 * FAST_STAGE;
     int32_t* c_idx = s_pool + (STEP ? 3 : 2) * FAST_STAGE;
     __shared__ int s_ev[STEP ? STEP_MAX_SEGS : 1], s_off[STEP ? STEP_MAX_SEGS : 1];
-    __shared__ int s_seqcnt[STEP ? STEP_MAX_SEQS : 1];
-    static_assert(STEP_MAX_SEGS <= FAST_STAGE && STEP_MAX_SEGS <= FAST_THREADS && STEP_MAX_EVICT <= FAST_STAGE, "the step's tables reuse the staging space, one segment per thread");
+    __shared__ int s_seqcnt[STEP ? STEP_MAX_SEQS + 1 : 1];        // entries before each sequence
+    static_assert(STEP_MAX_EVICT < 1 << 16 && STEP_MAX_SEGS <= FAST_STAGE && STEP_MAX_SEGS <= FAST_THREADS && STEP_MAX_EVICT <= FAST_STAGE, "the step's tables reuse the staging space, one segment per thread");
     const int tid = threadIdx.x;
-    // bps blocks share a segment, or (bps = 1) spb segments of a sequence share a block, FAST_THREADS / spb threads to each
-    // (whole wavefronts).  STEP: behind the scanning blocks the grid has blocks that only write the segments' tables, a
+    // bps blocks share a segment, or (MULTI: bps = 1) spb segments of a sequence share a block, FAST_THREADS / spb threads to
+    // each (whole wavefronts).  STEP: behind the scanning blocks the grid has blocks that only write the segments' tables, a
     // wavefront per segment.
+    const int spb = MULTI ? spb_arg : 1;
     const int bpq = (sh.segs_per_seq + spb - 1) / spb * bps;      // scanning blocks per sequence
     const bool tables_only = STEP && (int)blockIdx.x >= sh.n_seq * bpq;
     const int threads = FAST_THREADS / spb, group = tid / threads, gt = tid % threads;
@@ -607,12 +605,13 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     __syncthreads();                                              // ... and so are the whole block's, before it arrives
     if (tid == 0) {
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // (thread 0's own atomics above have returned)
-        const int grp = blk_in_seq % FAST_SUB;
-        const unsigned gsize = (unsigned)(nblk - grp + FAST_SUB - 1) / FAST_SUB;   // blocks of the sequence with this group number
         int last = 0;
-        if (atomicAdd(&done[1 + grp], 1u) == gsize - 1u) {
-            const unsigned ngroups = nblk < FAST_SUB ? (unsigned)nblk : (unsigned)FAST_SUB;
-            last = atomicAdd(&done[0], 1u) == ngroups - 1u;
+        if (nblk <= 2 * FAST_SUB) {                               // few enough to meet on one word
+            last = atomicAdd(&done[0], 1u) == (unsigned)nblk - 1u;
+        } else {
+            const int grp = blk_in_seq % FAST_SUB;
+            const unsigned gsize = (unsigned)(nblk - grp + FAST_SUB - 1) / FAST_SUB;   // blocks of the sequence with this group number
+            if (atomicAdd(&done[1 + grp], 1u) == gsize - 1u) last = atomicAdd(&done[0], 1u) == FAST_SUB - 1u;
         }
         s_last = last;
     }
@@ -620,75 +619,106 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     if (!s_last) return;
 
     // ---- the last block of the sequence: everything of the sequence has been scored and listed.
-    // All it needs is requested at once: the sub-list counters, the lowest keys, every slot of the list (whether
-    // a slot holds an entry is known once the counters are here), the segment lengths, the budget.
-    uint32_t sub_n[FAST_SUB];
-    uint32_t min_key = 0xFFFFFFFFu;
-#pragma unroll
-    for (int i = 0; i < FAST_SUB; ++i) {
-        sub_n[i] = i < nsub ? ld_dev(&sub_count[i]) : 0u;
-        min_key = min(min_key, ld_dev(&grp_min[i]));
-    }
+    // All it needs is requested at once: the sub-list counters, the lowest keys, the first half of every sub-list (whether
+    // a slot holds an entry is known once the counters are here), the segment lengths, the budget.  From here on one
+    // compute unit works alone, so what counts is the chain: scans by DPP, one of them over all segments of the batch
+    // and one for the destination, the counters a lane per word, no reduction for the key range (256 segments of 4096
+    // entries, the whole kernel: 28.6 -> 22.8 us; 16 segments of 65: 21.5 -> 15.6).
+    // (a lane per word: 0..15 the sub-lists' counters, 16..31 the groups' lowest keys)
+    const int lane = lane_id();
+    uint32_t word = 0xFFFFFFFFu;
+    if (lane < FAST_SUB) word = lane < nsub ? ld_dev(&sub_count[lane]) : 0u;
+    else if (lane < 2 * FAST_SUB) word = ld_dev(&grp_min[lane - FAST_SUB]);
     uint32_t key[FAST_ITEMS];
     int sg[FAST_ITEMS], ps[FAST_ITEMS], ix[FAST_ITEMS];
     uint32_t slot_sub[FAST_ITEMS], slot_idx[FAST_ITEMS];
-#pragma unroll
-    for (int u = 0; u < FAST_ITEMS; ++u) {
-        const uint32_t i = (uint32_t)tid + (uint32_t)u * FAST_THREADS;   // slot i of the flat list buffer
-        slot_sub[u] = i / subcap;
-        slot_idx[u] = i - slot_sub[u] * subcap;
-        key[u] = 0;
-        sg[u] = ps[u] = ix[u] = 0;
+    // slot i of the flat list buffer; a wavefront takes 256 in a row - one sub-list of a full-size list, of which the first
+    // 128 are asked for before its counter is known and the rest only if it reaches them
+    auto load_slot = [&](int u) {
+        const uint32_t i = (uint32_t)((tid >> 6) * (64 * FAST_ITEMS) + u * 64 + lane);
         if (i < cap && slot_sub[u] < (uint32_t)nsub) {
             key[u] = ld_dev(&lk[i]);
             sg[u] = ld_dev(&ls[i]);
             ps[u] = ld_dev(&lp[i]);
             if (STEP) ix[u] = ld_dev(&li[i]);
         }
+    };
+#pragma unroll
+    for (int u = 0; u < FAST_ITEMS; ++u) {
+        const uint32_t i = (uint32_t)((tid >> 6) * (64 * FAST_ITEMS) + u * 64 + lane);
+        slot_sub[u] = i / subcap;
+        slot_idx[u] = i - slot_sub[u] * subcap;
+        key[u] = 0;
+        sg[u] = ps[u] = ix[u] = 0;
+        if (u < FAST_ITEMS / 2) load_slot(u);
     }
+    int64_t bud = budget[seq];
+    const int64_t bud_other = STEP && tid < sh.n_seq ? budget[tid] : 0;   // (n_seq <= FAST_THREADS in a STEP)
     const int g0 = seq * sh.segs_per_seq;
     int64_t cnt = 0;
     int64_t step_before = 0, step_total = 0;                      // STEP: destination entries before this sequence / of all sequences
     int step_chunks_before = 0;                                   // STEP: chunks of the sequences before this one
-    int my_len = 0;                                               // STEP: length of segment g0 + tid (one segment of the sequence per thread)
+    int my_len = 0;                                               // STEP: length and start of segment g0 + tid (one segment of the sequence per thread)
+    uint32_t my_start = 0;
     int32_t step_cex = 0, step_ctot = 0;                          // STEP: chunks of the sequence's segments before that one / of all of them
     if (STEP) {
-        // entries per sequence of the whole batch (the destination of a sequence starts behind all earlier ones)
-        for (int i = tid; i < sh.n_seq; i += FAST_THREADS) s_seqcnt[i] = 0;
-        __syncthreads();
-        int chunks_before = 0;
-        for (int g = tid; g < sh.nseg; g += FAST_THREADS) {
-            bool b2 = false, n2 = false;
-            const SegView v = seg_view<KIND>(c, g, sh.nseg, sa, &b2, &n2);
-            if (v.len) atomicAdd(&s_seqcnt[g / sh.segs_per_seq], v.len);
-            if (g < g0) chunks_before += (v.len + CMP_CHUNK - 1) / CMP_CHUNK;
+        // One scan over the segments of the batch (1024 at a time): entries and chunks before each, so the entries of every
+        // sequence (the destination of a sequence starts behind all earlier ones) and this sequence's part of the tables
+        // fall out of it.  (The staging space is free once the block has arrived; entries of a cache are below 2^31.)
+        uint32_t* s_len = reinterpret_cast<uint32_t*>(s_pool) + FAST_STAGE;   // per segment of this sequence
+        uint32_t* s_chb = reinterpret_cast<uint32_t*>(s_pool) + 2 * FAST_STAGE;
+        uint32_t* s_start = reinterpret_cast<uint32_t*>(s_pool) + 3 * FAST_STAGE;
+        uint64_t carry = 0;                                       // entries in the upper, chunks in the lower 28 bits
+        for (int base = 0; base < sh.nseg; base += FAST_THREADS) {
+            const int g = base + tid;
+            uint64_t v = 0;
+            int vlen = 0;
+            if (g < sh.nseg) {
+                bool b2 = false, n2 = false;
+                const SegView sv = seg_view<KIND>(c, g, sh.nseg, sa, &b2, &n2);
+                vlen = sv.len;
+                if (g >= g0 && g < g0 + sh.segs_per_seq) s_start[g - g0] = (uint32_t)sv.start;
+                v = (uint64_t)vlen << 28 | (uint64_t)((vlen + CMP_CHUNK - 1) / CMP_CHUNK);
+            }
+            uint64_t tot;
+            const uint64_t ex = carry + block_excl_scan<uint64_t>(v, reinterpret_cast<uint64_t*>(sm.lds64), &tot);
+            carry += tot;
+            if (g < sh.nseg && g % sh.segs_per_seq == 0) s_seqcnt[g / sh.segs_per_seq] = (int)(uint32_t)(ex >> 28);
             if (g >= g0 && g < g0 + sh.segs_per_seq) {
                 kept_out[g] = 0;
-                s_pool[FAST_STAGE + (g - g0)] = v.len;            // (the staging space is free once the block has arrived)
+                s_len[g - g0] = (uint32_t)vlen;
+                s_chb[g - g0] = (uint32_t)(ex & 0xFFFFFFFu);
             }
         }
-        step_chunks_before = block_sum<int32_t>(chunks_before, sm.lds32);
-        int64_t need = 0;
-        if (tid < sh.n_seq) {                                     // (n_seq <= FAST_THREADS here)
-            int64_t b = budget[tid];
-            if (b < 0) b = 0;
-            const int64_t n = s_seqcnt[tid];
-            need = (b < n ? b : n) + (int64_t)sa.reserve * sh.segs_per_seq;
-        }
-        int64_t tot;
-        const int64_t ex = block_excl_scan<int64_t>(need, sm.lds64, &tot);
-        if (tid == seq) sm.before = ex;
+        if (tid == 0) s_seqcnt[sh.n_seq] = (int)(uint32_t)(carry >> 28);
         __syncthreads();
-        step_before = sm.before;
-        step_total = tot;
+        step_chunks_before = (int)s_chb[0];
+        if (tid < sh.segs_per_seq) {
+            my_len = (int)s_len[tid];
+            my_start = s_start[tid];
+            step_cex = (int32_t)s_chb[tid] - step_chunks_before;
+        }
+        const int last_seg = sh.segs_per_seq - 1;
+        step_ctot = (int32_t)s_chb[last_seg] - step_chunks_before + ((int)s_len[last_seg] + CMP_CHUNK - 1) / CMP_CHUNK;
+        cnt = (int64_t)((uint32_t)s_seqcnt[seq + 1] - (uint32_t)s_seqcnt[seq]);
+        auto need_of = [&](int sq, int64_t b) {                   // destination entries of a sequence
+            const int64_t n = (int64_t)((uint32_t)s_seqcnt[sq + 1] - (uint32_t)s_seqcnt[sq]);
+            if (b < 0) b = 0;
+            return (b < n ? b : n) + (int64_t)sa.reserve * sh.segs_per_seq;
+        };
+        if (sh.n_seq == 1) {
+            step_total = need_of(0, bud);
+        } else {
+            const int64_t need = tid < sh.n_seq ? need_of(tid, bud_other) : 0;
+            const int64_t ex = block_excl_scan<int64_t>(need, sm.lds64, &step_total);
+            if (tid == seq) sm.before = ex;
+            __syncthreads();
+            step_before = sm.before;
+        }
         // The per-chunk eviction counts of this sequence are cleared NOW, long before they are needed: the stores
         // (write-through: the counts are added with device-scope atomics) complete while the candidates are ranked.
-        if (tid < sh.segs_per_seq) my_len = s_pool[FAST_STAGE + tid];
-        step_cex = block_excl_scan<int32_t>((my_len + CMP_CHUNK - 1) / CMP_CHUNK, sm.lds32, &step_ctot);
         if (sa.inplace || step_total <= sa.dst.cap)
             for (int i = tid; i < step_ctot; i += FAST_THREADS) st_dev(&ws.step_chunk_ev[step_chunks_before + i], 0u);
-        cnt = s_seqcnt[seq];
-        __syncthreads();
     } else {
         for (int g = g0 + tid; g < g0 + sh.segs_per_seq; g += FAST_THREADS) {
             bool b2 = false, n2 = false;
@@ -696,29 +726,26 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
             kept_out[g] = 0;                                      // the mask kernel adds its counts
         }
     }
-    int64_t bud = budget[seq];
     if (bud < 0) bud = 0;
     bool sub_overflow = false;
-    uint32_t n_list = 0;
+    uint32_t n_list = 0, min_key = 0xFFFFFFFFu;
 #pragma unroll
     for (int i = 0; i < FAST_SUB; ++i) {
-        sub_overflow = sub_overflow || sub_n[i] > subcap;
-        n_list += sub_n[i] > subcap ? subcap : sub_n[i];
+        const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)word, i);
+        sub_overflow = sub_overflow || n > subcap;
+        n_list += n > subcap ? subcap : n;
+        min_key = min(min_key, (uint32_t)__builtin_amdgcn_readlane((int)word, FAST_SUB + i));
     }
     bool valid[FAST_ITEMS], listed[FAST_ITEMS];
-    uint32_t lo = 0xFFFFFFFFu, hi_k = 0;
 #pragma unroll
     for (int u = 0; u < FAST_ITEMS; ++u) {
-        uint32_t n_here = 0;
-#pragma unroll
-        for (int q = 0; q < FAST_SUB; ++q) n_here = slot_sub[u] == (uint32_t)q ? sub_n[q] : n_here;
-        valid[u] = (uint32_t)tid + (uint32_t)u * FAST_THREADS < cap && slot_sub[u] < (uint32_t)nsub && slot_idx[u] < n_here;
+        const uint32_t n_here = (uint32_t)__shfl((int)word, (int)min(slot_sub[u], (uint32_t)FAST_SUB - 1), 64);
+        valid[u] = (uint32_t)((tid >> 6) * (64 * FAST_ITEMS) + u * 64 + lane) < cap && slot_sub[u] < (uint32_t)nsub && slot_idx[u] < n_here;
         listed[u] = valid[u];
-        if (valid[u]) {
-            lo = min(lo, key[u]);
-            hi_k = max(hi_k, key[u]);
-        }
+        if (u >= FAST_ITEMS / 2 && __any(valid[u])) load_slot(u);
     }
+    // every listed key lies in [lowest key of the sequence, bound): no reduction over the list is needed
+    uint32_t lo = min_key, hi_k = hi - 1u;
     __syncthreads();                                              // every thread has read the per-call words
     if (tid <= FAST_SUB) {                                        // ... which go back to "between calls"
         atomicExch(&done[tid], 0u);
@@ -727,25 +754,8 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
             atomicExch(&grp_min[tid], 0xFFFFFFFFu);
         }
     }
-    {   // entries of the sequence, lowest and highest listed key: one reduction
-        if (!STEP) cnt = wave_sum(cnt);
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) {
-            lo = min(lo, (uint32_t)__shfl_xor((int)lo, d, 64));
-            hi_k = max(hi_k, (uint32_t)__shfl_xor((int)hi_k, d, 64));
-        }
-        if (lane_id() == 0) {
-            sm.lds64[tid >> 6] = cnt;
-            sm.red_u[tid >> 6] = lo;
-            sm.h[tid >> 6] = hi_k;
-        }
-        __syncthreads();
-        if (!STEP) cnt = 0;
-        for (int i = 0; i < FAST_THREADS / 64; ++i) {
-            if (!STEP) cnt += sm.lds64[i];
-            lo = min(lo, sm.red_u[i]);
-            hi_k = max(hi_k, sm.h[i]);
-        }
+    if (!STEP) {
+        cnt = block_sum<int64_t>(cnt, sm.lds64);                  // entries of the sequence
     }
     const int64_t want = bud < cnt ? bud : cnt;
     const int64_t k = cnt - want;                                 // entries to evict
@@ -924,17 +934,19 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
             }
             __syncthreads();
             const int my_ev = tid < nsg ? s_ev[tid] : 0;
-            int32_t etot;
-            const int32_t eex = block_excl_scan<int32_t>(my_ev, sm.lds32, &etot);
-            int64_t ntot;
-            const int64_t nex = block_excl_scan<int64_t>(tid < nsg ? (int64_t)(my_len - my_ev) + sa.reserve : 0, sm.lds64, &ntot);
+            // evicted entries (at most STEP_MAX_EVICT) and destination entries of the segments before, in one scan
+            uint64_t tot;
+            const uint64_t ex = block_excl_scan<uint64_t>(tid < nsg ? (uint64_t)((int64_t)(my_len - my_ev) + sa.reserve) << 16 | (uint64_t)my_ev : 0,
+                                                          reinterpret_cast<uint64_t*>(sm.lds64), &tot);
+            const int32_t eex = (int32_t)(ex & 0xFFFFu);
+            const int64_t nex = (int64_t)(ex >> 16);
             if (tid < nsg) {
                 const int g = g0 + tid;
                 s_off[tid] = eex;
                 kept_out[g] = my_len - my_ev;
                 StepSegRec* rec = ws.step_rec + g;
                 if (sa.inplace) {                                 // the segment keeps its start; the row mover commits the new length
-                    rec->dst_start = c.seg_start[g];
+                    rec->dst_start = (int64_t)my_start;
                     ws.step_len[g] = my_len - my_ev;
                 } else {
                     sa.dst.seg_start[g] = step_before + nex;
@@ -1023,22 +1035,33 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
 // EVICT (PAGED only; the paged decode step in one call): stage 3 of the paged layout rides along - a live slot that
 // is not kept becomes empty (position -1), the live counts of its page and segment go down, and a page left without
 // a live entry is marked for release (owner -2), exactly as k_pg_evict does from the mask.
-template <bool PAGED, bool EVICT = false>
+template <bool PAGED, bool EVICT, bool MULTI>
 __global__ __launch_bounds__(FAST_THREADS) void k_fast_mask(CacheView c, const float* __restrict__ score, Shape sh,
-                                                            Workspace ws, int bps, int spb, uint8_t* __restrict__ keep,
+                                                            Workspace ws, int bps, int spb_arg, uint8_t* __restrict__ keep,
                                                             int32_t* __restrict__ kept_out, PagedArgs pg) {
     __shared__ int32_t lds32[17];
-    // (dealt as in k_fast_scan)
-    const int bpq = (sh.segs_per_seq + spb - 1) / spb * bps, threads = FAST_THREADS / spb;
-    const int tid = (int)threadIdx.x % threads, seq = (int)blockIdx.x / bpq, blk = (int)blockIdx.x % bpq, part = blk % bps;
-    const int seg_in_seq = blk / bps * spb + (int)threadIdx.x / threads;
-    const int seg = seq * sh.segs_per_seq + min(seg_in_seq, sh.segs_per_seq - 1);
+    // dealt as in k_fast_scan
+    const int spb = MULTI ? spb_arg : 1, threads = FAST_THREADS / spb;
+    const int tid = (int)threadIdx.x % threads;
+    int seg, part;
+    bool no_seg = false;
+    if (MULTI) {
+        const int bpq = (sh.segs_per_seq + spb - 1) / spb;        // (bps = 1)
+        const int seg_in_seq = (int)blockIdx.x % bpq * spb + (int)threadIdx.x / threads;
+        no_seg = seg_in_seq >= sh.segs_per_seq;
+        seg = (int)blockIdx.x / bpq * sh.segs_per_seq + min(seg_in_seq, sh.segs_per_seq - 1);
+        part = 0;
+    } else {
+        seg = (int)blockIdx.x / bps;
+        part = (int)blockIdx.x % bps;
+    }
+    const int seq = seg / sh.segs_per_seq;
     const int stride = bps * threads;
     StepArgs sa{};
     sa.pg = pg;
     bool bad = false, nocap = false;
     const SegView v = seg_view<PAGED ? SCAN_PAGED : SCAN_RAGGED>(c, seg, sh.nseg, sa, &bad, &nocap);
-    const int len = seg_in_seq < sh.segs_per_seq ? v.len : 0;
+    const int len = no_seg ? 0 : v.len;
     KeySource<false, PAGED ? SCAN_PAGED : SCAN_RAGGED> ks;
     ks.bt = pg.block_table;
     ks.n_pages = pg.n_pages;
@@ -1090,7 +1113,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_mask(CacheView c, const f
             }
         }
     }
-    if (spb == 1) {
+    if (!MULTI) {
         n = block_sum<int32_t>(n, lds32);
         if (tid == 0 && n) atomicAdd(&kept_out[seg], n);
     } else {                                                      // (a wavefront's threads share a segment)
@@ -1130,10 +1153,12 @@ kvtrim_status launch_score_select(kvtrim_ctx* ctx, const CacheView& c, const int
     const dim3 block(FAST_THREADS);
     const ScanGrid sg = scan_grid(sh, c.cap, SCAN_RESIDENT);
     { ProfScope prof(ctx, K_FAST_SCAN, st);
-      hipLaunchKernelGGL((k_fast_scan<true, SCAN_RAGGED>), dim3(sg.blocks), block, 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, kept, thr, StepArgs()); }
+      if (sg.spb > 1) hipLaunchKernelGGL((k_fast_scan<true, SCAN_RAGGED, true>), dim3(sg.blocks), block, 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, kept, thr, StepArgs());
+      else hipLaunchKernelGGL((k_fast_scan<true, SCAN_RAGGED, false>), dim3(sg.blocks), block, 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, kept, thr, StepArgs()); }
     { ProfScope prof(ctx, K_FAST_MASK, st);
       const ScanGrid mg = scan_grid(sh, c.cap, MASK_RESIDENT);
-      hipLaunchKernelGGL(k_fast_mask<false>, dim3(mg.blocks), block, 0, st, c, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, PagedArgs()); }
+      if (mg.spb > 1) hipLaunchKernelGGL((k_fast_mask<false, false, true>), dim3(mg.blocks), block, 0, st, c, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, PagedArgs());
+      else hipLaunchKernelGGL((k_fast_mask<false, false, false>), dim3(mg.blocks), block, 0, st, c, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, PagedArgs()); }
     KVTRIM_HIP(ctx, hipGetLastError());
     return KVTRIM_OK;
 }
@@ -1150,12 +1175,15 @@ kvtrim_status launch_score_select_paged(kvtrim_ctx* ctx, const CacheView& pool, 
     StepArgs sa{};
     sa.pg = pg;
     { ProfScope prof(ctx, K_FAST_SCAN, st);
-      hipLaunchKernelGGL((k_fast_scan<true, SCAN_PAGED>), dim3(sg.blocks), block, 0, st, pool, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, kept, thr, sa); }
+      if (sg.spb > 1) hipLaunchKernelGGL((k_fast_scan<true, SCAN_PAGED, true>), dim3(sg.blocks), block, 0, st, pool, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, kept, thr, sa);
+      else hipLaunchKernelGGL((k_fast_scan<true, SCAN_PAGED, false>), dim3(sg.blocks), block, 0, st, pool, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, kept, thr, sa); }
     { ProfScope prof(ctx, K_FAST_MASK, st);
       if (evict)
-          hipLaunchKernelGGL((k_fast_mask<true, true>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, pg);
+          { if (mg.spb > 1) hipLaunchKernelGGL((k_fast_mask<true, true, true>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, pg);
+            else hipLaunchKernelGGL((k_fast_mask<true, true, false>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, pg); }
       else
-          hipLaunchKernelGGL((k_fast_mask<true, false>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, pg); }
+          { if (mg.spb > 1) hipLaunchKernelGGL((k_fast_mask<true, false, true>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, pg);
+            else hipLaunchKernelGGL((k_fast_mask<true, false, false>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, pg); } }
     KVTRIM_HIP(ctx, hipGetLastError());
     return KVTRIM_OK;
 }
@@ -1167,7 +1195,9 @@ kvtrim_status launch_step_scan(kvtrim_ctx* ctx, const CacheView& c, const int32_
     const ScanGrid sg = scan_grid(sh, c.cap, SCAN_RESIDENT);
     const unsigned tables = (unsigned)((sh.nseg + FAST_THREADS / 64 - 1) / (FAST_THREADS / 64));
     ProfScope prof(ctx, K_FAST_SCAN, st);
-    hipLaunchKernelGGL((k_fast_scan<true, SCAN_STEP>), dim3(sg.blocks + tables), dim3(FAST_THREADS), 0, st, c, now,
+    if (sg.spb > 1) hipLaunchKernelGGL((k_fast_scan<true, SCAN_STEP, true>), dim3(sg.blocks + tables), dim3(FAST_THREADS), 0, st, c, now,
+                       (const float*)nullptr, score, budget, sh, ctx->ws, sg.bps, sg.spb, kept, thr, sa);
+    else hipLaunchKernelGGL((k_fast_scan<true, SCAN_STEP, false>), dim3(sg.blocks + tables), dim3(FAST_THREADS), 0, st, c, now,
                        (const float*)nullptr, score, budget, sh, ctx->ws, sg.bps, sg.spb, kept, thr, sa);
     KVTRIM_HIP(ctx, hipGetLastError());
     return KVTRIM_OK;

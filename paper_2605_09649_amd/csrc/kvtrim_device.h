@@ -4,15 +4,29 @@
 
 namespace kvtrim {
 
-// Inclusive scan over the 64 lanes of a wavefront.
+// The value of another lane by DPP, 0 where there is none: 4 cycles where a shuffle through LDS takes about 100.
+template <int CTRL, int ROWS, typename T>
+__device__ __forceinline__ T dpp_get(T v) {
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two registers");
+    if constexpr (sizeof(T) == 4) {
+        return (T)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+    } else {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)v, CTRL, ROWS, 0xF, false);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)((uint64_t)v >> 32), CTRL, ROWS, 0xF, false);
+        return (T)(((uint64_t)hi << 32) | lo);
+    }
+}
+
+// Inclusive scan over the 64 lanes of a wavefront, all of them active; T: a 32- or 64-bit integer.  Inside the rows of 16
+// lanes first, then a row's total goes to the row behind it, then the first half's to the second.
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan(T v) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        T o = __shfl_up(v, d, 64);
-        if (lane >= d) v += o;
-    }
+    v += dpp_get<0x111, 0xF>(v);           // row_shr:1, 2, 4, 8
+    v += dpp_get<0x112, 0xF>(v);
+    v += dpp_get<0x114, 0xF>(v);
+    v += dpp_get<0x118, 0xF>(v);
+    v += dpp_get<0x142, 0xA>(v);           // row_bcast:15 into rows 1 and 3
+    v += dpp_get<0x143, 0xC>(v);           // row_bcast:31 into rows 2 and 3
     return v;
 }
 
