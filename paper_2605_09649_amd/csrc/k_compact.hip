@@ -32,7 +32,7 @@ __device__ __forceinline__ uint32_t nonzero_bytes(const scan_v4& w) {
 // Sums four values over the block (1024 threads) with one barrier; every thread gets every sum.  Each step of the first
 // two halves what a lane still has to add up, so that a wavefront takes 7 shuffles instead of 24, and the 16 wavefronts'
 // sums are added by shuffles as well: with eight values one after the other and every thread reading 128 sums from LDS
-// this was most of k_cmp_scan at a thousand segments (1024 segments of 12 K entries: 51 us, now 32).
+// this was most of k_cmp_scan at a thousand segments (1024 segments of 12 K entries: 51 us, now 29.5).
 __device__ __forceinline__ void block_sum_4(int64_t (&v)[4], int64_t* lds /* [64] */) {
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const bool up = lane & 32, odd = lane & 16;
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
     // Mask bytes of one tile of SCAN_THREADS chunks: load u of a wavefront covers the 8 chunks from (16 u + wave) * 8 on, 16
     // bytes per lane (at any address: a segment starts anywhere), all of them asked for at once.  They stay in registers
     // as one bit per entry, for the counts and (gat) for the row numbers.  (A wavefront per chunk with two byte loads per
-    // lane, twice over for the row numbers, took 46 us for the 33.5 M entries of a first eviction; now 18.5.)
+    // lane, twice over for the row numbers, took 46 us for the 33.5 M entries of a first eviction; now 18.)
     // A lane whose 16 bytes reach past the segment's end reads the segment's last 16 and shifts them into place.
     // In two halves, the first of which - 512 chunks - is under way while the prefixes are summed.
     scan_v4 w[SCAN_BATCH / 2];

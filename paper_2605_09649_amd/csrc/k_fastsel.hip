@@ -1125,7 +1125,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_mask(CacheView c, const f
 // How the blocks of k_fast_scan and k_fast_mask are dealt: several to a segment of more than FAST_ENTRIES_PER_BLOCK
 // entries; several segments of a sequence to a block when a block each would be more than are resident at once (one of
 // k_fast_scan's per compute unit, two of k_fast_mask's) - a block of k_fast_scan lives 8 to 10 us whatever it has to do, so
-// 4096 segments of 2048 entries took sixteen rounds of the chip: 202 us, with sixteen segments to a block 50.
+// 4096 segments of 2048 entries took sixteen rounds of the chip: 202 us, with sixteen segments to a block 43.
 struct ScanGrid {
     int bps, spb;
     unsigned blocks;

@@ -52,7 +52,7 @@ __global__ __launch_bounds__(1024) void k_sel_plan(CacheView c, Shape sh, const 
         for (int i = threadIdx.x; i < DONE_WORDS; i += blockDim.x) ws.done[i] = 0;
         for (int g = threadIdx.x; g < sh.nseg; g += blockDim.x) kept_out[g] = 0;
     }
-    // (one block filled the table of 33.5 M entries - 16 K chunks - in 16.5 us; eight take 8)
+    // (one block filled the table of 33.5 M entries - 16 K chunks - in 16.5 us; eight take 6)
     const int total = build_chunk_table(c.seg_len, c.seg_start, sh.nseg, [](int) { return true; }, SEL_CHUNK, c.cap,
                                         ws.sel_chunk_prefix, ws.sel_desc, ws.max_sel_chunks, ws.sel_entry_prefix, ws.err,
                                         (int)blockIdx.x, PLAN_TABLE_BLOCKS);
@@ -336,7 +336,7 @@ __global__ __launch_bounds__(HIST_THREADS, 8) void k_sel_hist(const float* __res
 // digits (below that the histograms count other buckets); where it leaves them, the upper edge of its bucket is taken.
 // All three histograms are asked for at once, and both ranks are looked up in the same three scans.  (This used to be
 // done by the last block of the last pass to arrive: two fences, then four walks one after the other, 35 to 40 us
-// behind the pass whatever its size; the kernel takes 8.)
+// behind the pass whatever its size; the kernel takes 6 to 7.)
 __global__ __launch_bounds__(HIST_THREADS) void k_sel_final(Shape sh, Workspace ws, uint32_t* __restrict__ thr_out) {
     __shared__ int64_t lds64[17];
     __shared__ int64_t s_rank[3][2];                              // per digit: rank inside the bin, of the threshold / of the bound
