@@ -417,7 +417,7 @@ kvtrim_status kvtrim_paged_score_select(kvtrim_ctx *ctx, const kvtrim_paged_cach
  *     -> kvtrim_paged_evict(keep_out) -> kvtrim_paged_attn(q)
  * leave there (arguments as in those four calls; one row per segment in the new-token arrays) - bit for bit in
  * everything but out / lse, which agree within the attention tolerance: a page that this step's eviction emptied is
- * still listed when the attention's chunk table is built, so the fp32 sums may group differently.  With a small
+ * still listed while the attention runs, so the fp32 sums may group differently.  With a small
  * evict_hint the mask kernel of the decode-step selection applies the eviction as it writes the mask (which saves
  * the pass of kvtrim_paged_evict over all pages) and the attention's merge kernel takes the emptied pages out of the
  * block tables: five kernels per step.  Any other hint runs the four calls. */
