@@ -654,7 +654,8 @@ static kvtrim_status launch_select_impl(kvtrim_ctx* ctx, const CacheView& c, con
     { ProfScope prof(ctx, K_SEL_COUNT, st);
       hipLaunchKernelGGL(k_sel_count, dim3(n_chunk_blocks < 256 ? n_chunk_blocks : 256), dim3(CNT_THREADS), 0, st, score, sh, ws, tb, kept); }
     { ProfScope prof(ctx, K_SEL_MASK, st);
-      if (n_chunk_blocks >= MASK_LONG && (((uintptr_t)score) & 15) == 0 && (((uintptr_t)keep) & 3) == 0)
+      // (cap >= 4: a group of four that is not whole loads the array's first four entries in its place)
+      if (n_chunk_blocks >= MASK_LONG && c.cap >= 4 && (((uintptr_t)score) & 15) == 0 && (((uintptr_t)keep) & 3) == 0)
           hipLaunchKernelGGL(k_sel_mask<true>, dim3(MASK_BLOCKS), dim3(SEL_THREADS), 0, st, score, sh, ws, tb, keep, kept, c.cap);
       else
           hipLaunchKernelGGL(k_sel_mask<false>, dim3(n_chunk_blocks), dim3(SEL_THREADS), 0, st, score, sh, ws, tb, keep, kept, c.cap); }

@@ -810,3 +810,28 @@ def test_selection_and_compaction_at_the_edges_of_their_tiles(reserve, lens, kee
             assert torch.equal(getattr(dst, name)[here].cpu(), c[name][s:s + n][m])
         cursor += int(kept[g]) + reserve
     assert np.all(k[~inside] == 7)                           # slots outside the segments are not written
+
+
+@pytest.mark.parametrize("cap", [1, 3, 4, 5])
+def test_more_segments_than_a_long_mask_needs_over_a_handful_of_entries(cap):
+    # the chunk bound (a chunk per segment) asks for the mask kernel's long form, whose 16-byte loads a cache of fewer
+    # than four entries must not see
+    w = wl(2, 32, 130, 1, 64)                                # 8320 segments
+    seg_len = np.zeros(w.nseg, dtype=np.int64)
+    seg_len[[5, 4159, 4160, 8319, 17][:cap]] = 1
+    c, now = ki.ragged_cache(w, seg_len, reserve=0, salt=51)
+    hc = host_cache(w, c)
+    assert hc.cap == cap
+    budget = np.array([1, 1], dtype=np.int64)
+    score = oracle.score(hc, now.numpy())
+    keep, kept, thr = oracle.select(hc, score, budget)
+    ctx = kv.Context(w.n_seq, w.n_layers, w.n_kv_heads, w.n_q_heads, 64, cap)
+    d_score = torch.zeros(cap, dtype=torch.float32, device=DEV)
+    d_keep = torch.full((cap,), 7, dtype=torch.uint8, device=DEV)
+    d_kept = torch.zeros(w.nseg, dtype=torch.int32, device=DEV)
+    d_thr = torch.zeros(2, dtype=torch.int32, device=DEV)
+    kv.kvtrim_score_select(ctx, kv.Cache.from_dict(c, DEV), now.to(DEV), torch.from_numpy(budget).to(DEV), d_score, d_keep, d_kept, d_thr)
+    assert kv.kvtrim_poll_error(ctx) == 0
+    assert np.array_equal(d_score.cpu().numpy().view(np.uint32), score.view(np.uint32))
+    assert np.array_equal(d_keep.cpu().numpy(), keep) and np.array_equal(d_kept.cpu().numpy(), kept)
+    assert np.array_equal(d_thr.cpu().numpy().view(np.uint32), thr)
