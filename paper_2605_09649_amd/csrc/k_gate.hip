@@ -679,15 +679,16 @@ __global__ __launch_bounds__(GP_THREADS) void k_gate_prefill(GateView g, const u
 // u stays in registers: the shares of the contraction meet in LDS, every wavefront of a row tile then holds the same sums
 // and takes some of the heads.  z = v . u + s is a sum over the slices of a layer: a block leaves its part of every
 // (head, token) sum in `part` ([layer][slice][head][token], the caller's scratch buffer), and the block of a layer and
-// token tile that arrives last (counters in the workspace, left at zero) adds the parts in slice order - the same order
-// whichever block that is.  Blocks are dealt to the eight XCDs in contiguous runs of (layer, slice, token tile), so that
+// token tile that arrives last (counters in the workspace, left at zero) adds the parts, eight at a time, in slice order -
+// the same order whichever block that is - and the constant s at the end (32 parts added to it one by one cost a third of
+// the accuracy).  Blocks are dealt to the eight XCDs in contiguous runs of (layer, slice, token tile), so that
 // the blocks that share token rows, and those that share a slice of W1, share an L2.
 // Measured (32 layers, d_model 4096, 512 units, 8 heads, prepared; 134 MB of W1, 21 us at 6.5 TB/s): 1 token 35.0 -> 25.6
 // us, 32 tokens 86.9 -> 28.5, 64 tokens 83.6 -> 31.3, 128 tokens 81.4 -> 42.3, 256 tokens 80.8 -> 69.1 (before: up to 16
 // tokens 1024 blocks of 16 units, from 24 tokens on k_gate_prefill's 32-token blocks, 32 to 256 of them).
 constexpr int GSL_THREADS = 512, GSL_HEADS_MAX = 32, GSL_TILES_MAX = GATE_TOKEN_TILES;
 
-template <int TT, int GS, int MT, bool TILED>
+template <int TT, int GS, int MT, int CH, bool TILED>
 __global__ __launch_bounds__(GSL_THREADS) void k_gate_slice(GateView g, const uint16_t* __restrict__ x, int n_tok, int layer_begin,
                                                             int nl, const uint4* __restrict__ tiled, GateDot dot) {
     constexpr int TOK = 16 * TT, HID = 16 * MT, KS = 8 / MT;          // KS shares of the contraction
@@ -727,9 +728,9 @@ __global__ __launch_bounds__(GSL_THREADS) void k_gate_slice(GateView g, const ui
     }
     const int read_off = kh * GS * TT * GP_TILE_BYTES + g4 * GP_GROUP_BYTES + r16 * 16;
 
-    gate_f4 acc[TT];
+    gate_f4 acc[TT], acc2[CH == 2 ? TT : 1];                         // CH chains: the two halves of a step apart
 #pragma unroll
-    for (int j = 0; j < TT; ++j) acc[j] = gate_f4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < TT; ++j) acc[j] = acc2[CH == 2 ? j : 0] = gate_f4{0.f, 0.f, 0.f, 0.f};
     gate_u4 a0[GS][2], a1[GS][2];
     gate_u4 x0[XL], x1[XL];
     // past the end the loads repeat the last step, whose products are left out
@@ -760,8 +761,10 @@ __global__ __launch_bounds__(GSL_THREADS) void k_gate_slice(GateView g, const ui
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
 #pragma unroll
-                    for (int j = 0; j < TT; ++j)
-                        acc[j] = mma_bf16(__builtin_bit_cast(uint4, a[i][h]), *reinterpret_cast<const uint4*>(base + (i * TT + j) * GP_TILE_BYTES + h * GP_HALF_BYTES), acc[j]);
+                    for (int j = 0; j < TT; ++j) {
+                        gate_f4& sum = CH == 2 && h ? acc2[CH == 2 ? j : 0] : acc[j];
+                        sum = mma_bf16(__builtin_bit_cast(uint4, a[i][h]), *reinterpret_cast<const uint4*>(base + (i * TT + j) * GP_TILE_BYTES + h * GP_HALF_BYTES), sum);
+                    }
             }
         }
     };
@@ -797,7 +800,7 @@ __global__ __launch_bounds__(GSL_THREADS) void k_gate_slice(GateView g, const ui
     gate_f4* s_acc = reinterpret_cast<gate_f4*>(s_x);                // [wave][token tile][lane]: 8 TT KB
     float* s_z = reinterpret_cast<float*>(s_x);                      // then [row tile][head][token]: TT MT KB for 16 heads
 #pragma unroll
-    for (int j = 0; j < TT; ++j) s_acc[(wave * TT + j) * 64 + lane] = acc[j];
+    for (int j = 0; j < TT; ++j) s_acc[(wave * TT + j) * 64 + lane] = CH == 2 ? acc[j] + acc2[j] : acc[j];
     const float cc[4] = {c.x, c.y, c.z, c.w};
     __syncthreads();
 #pragma unroll
@@ -846,16 +849,15 @@ __global__ __launch_bounds__(GSL_THREADS) void k_gate_slice(GateView g, const ui
     if (tid == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (for the next call)
     for (int i = tid; i < items; i += GSL_THREADS) {
         const int tk = i / n_heads, h = i - tk * n_heads;            // (neighbouring threads write neighbouring outputs)
-        float z = i == tid ? s_first : dot.s[(size_t)lr * n_heads + h];
-        for (int s0 = 0; s0 < slices; s0 += 8) {                     // 8 parts asked for at once, added in slice order
+        float z = 0.f;
+        for (int s0 = 0; s0 < slices; s0 += 8) {                     // 8 parts asked for at once
             float p[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k)
                 p[k] = s0 + k < slices ? __hip_atomic_load(part_of(s0 + k, h) + tk, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.f;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) z += p[k];
+            z += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
         }
-        const float lb = log_sigmoid(z);
+        const float lb = log_sigmoid(z + (i == tid ? s_first : dot.s[(size_t)lr * n_heads + h]));   // (the constant last: it is the largest term)
         const size_t o = ((size_t)(tok0 + tk) * dot.n_layers + layer) * n_heads + h;
         dot.log_beta_out[o] = lb;
         if (dot.log_tail_out) dot.log_tail_out[o] = log_tail_of(lb, dot.horizon);
@@ -868,10 +870,10 @@ static size_t folded_floats(const GateView& g, int n_layers, int n_heads) {
 }
 
 // How a call is run: the per-token kernels (first layer, then readout), one k_gate_slice or one k_gate_prefill, with
-// tt token tiles of 16 and (k_gate_slice) mt row tiles per block.
+// tt token tiles of 16 and (k_gate_slice) mt row tiles per block and ch chains of sums per share of the contraction.
 constexpr int GATE_PER_TOKEN = 0, GATE_SLICE = 1, GATE_PREFILL = 2;
 struct GatePlan {
-    int kind, tt, mt;
+    int kind, tt, mt, ch;
 };
 static GatePlan gate_plan(const kvtrim_ctx* ctx, const GateView& g, int n_tok, int nl, bool prepared) {
     const int n_heads = ctx->shape.n_kv_heads;
@@ -896,16 +898,23 @@ static GatePlan gate_plan(const kvtrim_ctx* ctx, const GateView& g, int n_tok, i
     const size_t part = (size_t)nl * (g.d_g / (16 * mt)) * n_heads * n_tok;
     const bool slice_ok = n_heads <= GSL_HEADS_MAX && tiles(tt) <= GSL_TILES_MAX && (prepared || tt > 1) &&
                           part + (prepared ? 0 : folded_floats(g, nl, n_heads)) <= (size_t)n_tok * nl * g.d_g;
-    const bool prefill_ok = g.d_g % 128 == 0 && g.d_g <= 512 && n_heads <= GP_HEADS_MAX && (prepared || n_tok >= GP_MIN_TOK);
+    const bool prefill_shape = g.d_g % 128 == 0 && g.d_g <= 512 && n_heads <= GP_HEADS_MAX;
+    const bool prefill_ok = prefill_shape && (prepared || n_tok >= GP_MIN_TOK);
+    // A pre-activation is summed in four chains or more wherever the kernels that would take the call otherwise
+    // (k_gate_hidden: four) do so; k_gate_prefill and the first layer of 256 tokens and more sum in one.  Slices of 64
+    // units have two shares of the contraction, so two chains in each: free with up to two token tiles, 2 to 25 % with more
+    // (32 layers, d_model 4096, 512 units, 32 heads: 64 tokens 42.7 -> 43.9 us, 130 tokens 104 -> 131).  Relative error of
+    // log beta there 3.9e-7 with two chains in all, 3.0e-7 with four, 5.5e-7 with one.
+    const int ch = mt == 4 && (tt <= 2 || (prepared && n_tok < 256 && !prefill_shape)) ? 2 : 1;
     const bool cached = (size_t)nl * g.d_g * g.d_model * 2 <= (size_t)100 << 20;
     const double share = r * g.d_g / 512;
     const double p2 = rounds(nl * tiles(2)) * (cached ? 40 : 71), p4 = rounds(nl * tiles(4)) * (cached ? 50 : 80),
                  p8 = rounds(nl * tiles(8)) * (cached ? 110 : 120);
     // (more than a round of 128-token blocks: their rate per token counts, and that is the best)
     const int ptt = nl * tiles(8) > 256 ? 8 : (p2 < p4 && p2 < p8 ? 2 : (p4 < p8 ? 4 : 8));
-    if (slice_ok && (!prefill_ok || tt < 4 || (tt == 8 ? s8 : s4) <= 7 + share * (ptt == 2 ? p2 : (ptt == 4 ? p4 : p8)))) return {GATE_SLICE, tt, mt};
-    if (prefill_ok) return {GATE_PREFILL, ptt, 0};
-    return {GATE_PER_TOKEN, 0, 0};
+    if (slice_ok && (!prefill_ok || tt < 4 || (tt == 8 ? s8 : s4) <= 7 + share * (ptt == 2 ? p2 : (ptt == 4 ? p4 : p8)))) return {GATE_SLICE, tt, mt, ch};
+    if (prefill_ok) return {GATE_PREFILL, ptt, 0, 0};
+    return {GATE_PER_TOKEN, 0, 0, 0};
 }
 
 // Readout from folded vectors for calls that went through the per-token first-layer kernels: one wavefront
@@ -1006,14 +1015,15 @@ kvtrim_status launch_gate(kvtrim_ctx* ctx, const GateView& g, const float* prepa
             const GateDot dot{v, sconst, part, ctx->ws.gate_done, log_beta_out, log_tail_out, n_heads, L, horizon};
             const int64_t blocks = (int64_t)nl * (g.d_g / (16 * plan.mt)) * ((n_tok + 16 * plan.tt - 1) / (16 * plan.tt));
             const dim3 grid((unsigned)((blocks + 7) / 8 * 8));
-#define KVTRIM_CASE(TT, GS, MT)                                                                                              \
-    case TT * 8 + MT:                                                                                                        \
-        if (use_tiled) hipLaunchKernelGGL((k_gate_slice<TT, GS, MT, true>), grid, dim3(GSL_THREADS), 0, st, g, x, n_tok, layer_begin, nl, tiled, dot); \
-        else hipLaunchKernelGGL((k_gate_slice<TT, GS, MT, false>), grid, dim3(GSL_THREADS), 0, st, g, x, n_tok, layer_begin, nl, tiled, dot);          \
+#define KVTRIM_CASE(TT, GS, MT, CH)                                                                                          \
+    case (TT * 8 + MT) * 4 + CH:                                                                                             \
+        if (use_tiled) hipLaunchKernelGGL((k_gate_slice<TT, GS, MT, CH, true>), grid, dim3(GSL_THREADS), 0, st, g, x, n_tok, layer_begin, nl, tiled, dot); \
+        else hipLaunchKernelGGL((k_gate_slice<TT, GS, MT, CH, false>), grid, dim3(GSL_THREADS), 0, st, g, x, n_tok, layer_begin, nl, tiled, dot);          \
         break;
-            switch (plan.tt * 8 + plan.mt) {
-                KVTRIM_CASE(1, 2, 4) KVTRIM_CASE(1, 2, 2) KVTRIM_CASE(1, 1, 1) KVTRIM_CASE(2, 1, 4) KVTRIM_CASE(2, 1, 2)
-                KVTRIM_CASE(2, 1, 1) KVTRIM_CASE(4, 1, 4) KVTRIM_CASE(4, 1, 2) KVTRIM_CASE(8, 1, 4)
+            switch ((plan.tt * 8 + plan.mt) * 4 + plan.ch) {
+                KVTRIM_CASE(1, 2, 4, 2) KVTRIM_CASE(1, 2, 2, 1) KVTRIM_CASE(1, 1, 1, 1) KVTRIM_CASE(2, 1, 4, 2) KVTRIM_CASE(2, 1, 2, 1)
+                KVTRIM_CASE(2, 1, 1, 1) KVTRIM_CASE(4, 1, 4, 1) KVTRIM_CASE(4, 1, 4, 2) KVTRIM_CASE(4, 1, 2, 1) KVTRIM_CASE(8, 1, 4, 1)
+                KVTRIM_CASE(8, 1, 4, 2)
                 default: return KVTRIM_EINVAL;
             }
 #undef KVTRIM_CASE

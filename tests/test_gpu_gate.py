@@ -272,3 +272,35 @@ def test_gate_path_by_tokens_heads_and_widths(L, H, d_model, d_g, n_tok, prepare
         assert rel_err(lb[pick].cpu().numpy(), lb_ref) <= RTOL
         assert np.max(np.abs(lt[pick].cpu().numpy() - lt_ref)) <= 1e-3 * np.max(np.abs(lt_ref)) + 1e-6
     assert torch.equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("n_tok", [12, 64])
+def test_sliced_kernel_is_as_exact_as_the_two_kernels(n_tok):
+    # 32 heads take k_gate_slice, 33 k_gate_hidden + k_gate_dot, which sum a pre-activation in four chains and add a
+    # readout's constant last: the gates that both compute must be as close to 64 bits either way.  (17 layers: slices of
+    # 64 units, with the fewest shares of the contraction.  Errors are those of some thousand sums, so their 2-norms vary
+    # by a few per cent; two chains instead of four gave 1.3 times the error.)
+    L, d_model, d_g = 17, 2048, 512
+    w = ki.gate_weights(L, 33, d_model, d_g, 4, b_g=3.5, seed=5)
+    og = oracle.Gate(bf16_bits(w["w1"]), w["c1"].numpy(), bf16_bits(w["w2"]), w["c2"].numpy(), w["w_g"].numpy(), 3.5)
+    x = ki.gate_inputs(L, n_tok, d_model, salt=6)
+    pick = list(range(0, n_tok, max(1, n_tok // 16)))
+    _, ref, _ = oracle.gate_forward(og, bf16_bits(x[:, pick].contiguous()), 0, L, None)
+    names = [kv.kvtrim_kernel_name(i) for i in range(40)]
+    mask = sum(1 << i for i, n in enumerate(names) if n.startswith("k_gate"))
+    err = {}
+    for H, kernel in ((33, "k_gate_hidden"), (32, "k_gate_slice")):
+        wh = dict(w, w2=w["w2"][:, :H].contiguous(), c2=w["c2"][:, :H].contiguous())
+        ctx = kv.Context(1, L, H, H, 64, 1024)
+        gate = kv.Gate.from_dict(wh, DEV)
+        prep = torch.empty(kv.kvtrim_gate_prepared_bytes(gate, L, H) // 4, dtype=torch.float32, device=DEV)
+        scratch = torch.empty(kv.kvtrim_gate_scratch_bytes(gate, n_tok, L) // 4, dtype=torch.float32, device=DEV)
+        lb = torch.zeros(n_tok, L, H, dtype=torch.float32, device=DEV)
+        kv.kvtrim_gate_prepare(ctx, gate, prep)
+        kv.kvtrim_profile_begin(ctx, mask)
+        kv.kvtrim_gate_forward_prepared(ctx, gate, prep, x.to(DEV), n_tok, 0, L, 1, scratch, lb)
+        assert kernel in kv.kvtrim_profile_end(ctx)
+        d = lb[pick][:, :, :32].cpu().numpy().astype(np.float64) - ref[:, :, :32]
+        err[H] = np.linalg.norm(d) / np.linalg.norm(ref[:, :, :32])
+    print(f"two kernels {err[33]:.2e}, sliced {err[32]:.2e}")
+    assert err[32] <= 1.1 * err[33]
