@@ -886,18 +886,23 @@ static GatePlan gate_plan(const kvtrim_ctx* ctx, const GateView& g, int n_tok, i
     // tokens and 512 units 7 + 71 / 80 / 120, or 7 + 40 / 50 / 110 while the weights of the call stay in the chip's
     // last-level cache (256 MB).
     const int64_t slices = g.d_g / 64;
-    const double s8 = 15 + 27 * r * rounds(nl * slices * tiles(8));
-    double s4 = 8 + 24 * r * rounds(nl * slices * tiles(4));
-    if (nl * 2 * slices * tiles(4) <= 256) s4 = 8 + 12 * r;
-    const int tt = n_tok <= 16 ? 1 : (n_tok <= 32 ? 2 : (n_tok <= 64 || s4 <= s8 ? 4 : 8));
-    // slices of 64 units, halved while that still is one round of blocks (1 layer, 1 token: 15.6 / 11.5 / 9.4 us with 64 /
-    // 32 / 16 units; 20 layers: 64 units 19.4 us, 32 units - two rounds - 22.6) and the parts of the sums still fit the scratch buffer
-    int mt = 4;
-    while (tt < 8 && mt > (tt < 4 ? 1 : 2) && nl * (g.d_g / (8 * mt)) * tiles(tt) <= 256 && n_heads <= 8 * mt) mt >>= 1;
-    // the parts of the sums must fit the scratch buffer, behind the folded vectors when those are made in the call
-    const size_t part = (size_t)nl * (g.d_g / (16 * mt)) * n_heads * n_tok;
-    const bool slice_ok = n_heads <= GSL_HEADS_MAX && tiles(tt) <= GSL_TILES_MAX && (prepared || tt > 1) &&
-                          part + (prepared ? 0 : folded_floats(g, nl, n_heads)) <= (size_t)n_tok * nl * g.d_g;
+    // Row tiles of a k_gate_slice block with tt token tiles, 0 if such blocks cannot run: there is a counter for GSL_TILES_MAX
+    // token tiles, and the parts of the sums must fit the scratch buffer, behind the folded vectors when those are made in
+    // the call.  Slices of 64 units, halved while that still is one round of blocks (1 layer, 1 token: 15.6 / 11.5 / 9.4 us
+    // with 64 / 32 / 16 units; 20 layers: 64 units 19.4 us, 32 units - two rounds - 22.6) and the parts fit.
+    auto row_tiles = [&](int tt) {
+        const size_t room = (size_t)n_tok * nl * g.d_g, taken = prepared ? 0 : folded_floats(g, nl, n_heads);
+        auto fits = [&](int mt) { return (size_t)nl * (g.d_g / (16 * mt)) * n_heads * n_tok + taken <= room; };
+        if (n_heads > GSL_HEADS_MAX || tiles(tt) > GSL_TILES_MAX || !fits(4)) return 0;
+        int mt = 4;
+        while (tt < 8 && mt > (tt < 4 ? 1 : 2) && nl * (g.d_g / (8 * mt)) * tiles(tt) <= 256 && fits(mt / 2)) mt >>= 1;
+        return mt;
+    };
+    const double s8 = 15 + 27 * r * rounds(nl * slices * tiles(8)), s4 = row_tiles(4) == 2 ? 8 + 12 * r : 8 + 24 * r * rounds(nl * slices * tiles(4));
+    int tt = n_tok <= 16 ? 1 : (n_tok <= 32 ? 2 : 4);
+    if (n_tok > 64 && (!row_tiles(4) || (row_tiles(8) && s8 < s4))) tt = 8;
+    const int mt = row_tiles(tt);
+    const bool slice_ok = mt > 0 && (prepared || tt > 1);
     const bool prefill_shape = g.d_g % 128 == 0 && g.d_g <= 512 && n_heads <= GP_HEADS_MAX;
     const bool prefill_ok = prefill_shape && (prepared || n_tok >= GP_MIN_TOK);
     // A pre-activation is summed in four chains or more wherever the kernels that would take the call otherwise

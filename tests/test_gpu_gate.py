@@ -234,10 +234,14 @@ def test_host_side_argument_checks_of_the_gate():
     (20, 9, 256, 512, 65, True, "k_gate_slice"),     # two blocks of 64 tokens or one of 128, a tail of one
     (33, 2, 1024, 576, 130, True, "k_gate_slice"),   # 128-token blocks, hidden width above 512
     (1, 2, 256, 64, 700, True, "k_gate_slice"),      # eleven 64-token blocks along the tokens
+    (2, 8, 1024, 192, 1025, True, "k_gate_slice"),   # seventeen 64-token blocks, for sixteen counters: 128-token blocks
+    (1, 2, 256, 64, 2048, True, "k_gate_slice"),     # sixteen 128-token blocks
     (1, 2, 256, 64, 8193, True, "k_gate_hidden"),    # more token tiles than there are counters
     (3, 2, 256, 192, 40, False, "k_gate_slice"),     # vectors folded in the call, W1 straight from its rows
     (2, 8, 256, 64, 17, False, "k_gate_slice"),      # ... the scratch buffer just holds vectors and parts
     (2, 16, 256, 64, 17, False, "k_gate_hidden"),    # ... and with twice the heads it does not
+    (2, 16, 512, 512, 22, False, "k_gate_slice"),    # ... holds them with slices of 64 units only
+    (2, 16, 512, 512, 21, False, "k_gate_hidden"),   # ... and not even then
     (8, 2, 1024, 384, 519, True, "k_gate_prefill"),  # 32-token blocks
     (40, 1, 256, 512, 641, True, "k_gate_prefill"),  # 64- or 128-token blocks
     (40, 1, 256, 512, 900, False, "k_gate_prefill"),  # 128-token blocks, everything derived in the call
