@@ -869,6 +869,11 @@ static size_t folded_floats(const GateView& g, int n_layers, int n_heads) {
     return ((size_t)n_layers * n_heads * (g.d_g + 1) + 3) & ~(size_t)3;
 }
 
+// Whether the scratch buffer of a call (n_tok * n_layers * d_g floats) has room for W1 in operand order behind the folded vectors.
+static bool tiled_fits(const GateView& g, int n_tok, int n_layers, int n_heads) {
+    return folded_floats(g, n_layers, n_heads) + (size_t)n_layers * g.d_g * g.d_model / 2 <= (size_t)n_tok * n_layers * g.d_g;
+}
+
 // How a call is run: the per-token kernels (first layer, then readout), one k_gate_slice or one k_gate_prefill, with
 // tt token tiles of 16 and (k_gate_slice) mt row tiles per block and ch chains of sums per share of the contraction.
 constexpr int GATE_PER_TOKEN = 0, GATE_SLICE = 1, GATE_PREFILL = 2;
@@ -913,7 +918,11 @@ static GatePlan gate_plan(const kvtrim_ctx* ctx, const GateView& g, int n_tok, i
     const int ch = mt == 4 && (tt <= 2 || (prepared && n_tok < 256 && !prefill_shape)) ? 2 : 1;
     const bool cached = (size_t)nl * g.d_g * g.d_model * 2 <= (size_t)100 << 20;
     const double share = r * g.d_g / 512;
-    const double p2 = rounds(nl * tiles(2)) * (cached ? 40 : 71), p4 = rounds(nl * tiles(4)) * (cached ? 50 : 80),
+    // (128 units with W1 in operand order: a compute unit holds three blocks of 32 tokens - 75 registers, 26 KB of LDS - and
+    // up to half a round more of them costs next to nothing: 4 layers, d_model 1024, 264 / 376 blocks 17.8 / 18.9 us, with
+    // 64 tokens a block 19.6 / 20.8; 512 blocks 24.8 against 21.6)
+    const bool narrow = g.d_g == 128 && (prepared || tiled_fits(g, n_tok, nl, n_heads));
+    const double p2 = (narrow && nl * tiles(2) <= 384 ? 1 : rounds(nl * tiles(2))) * (cached ? 40 : 71), p4 = rounds(nl * tiles(4)) * (cached ? 50 : 80),
                  p8 = rounds(nl * tiles(8)) * (cached ? 110 : 120);
     // (more than a round of 128-token blocks: their rate per token counts, and that is the best)
     const int ptt = nl * tiles(8) > 256 ? 8 : (p2 < p4 && p2 < p8 ? 2 : (p4 < p8 ? 4 : 8));
@@ -997,8 +1006,7 @@ kvtrim_status launch_gate(kvtrim_ctx* ctx, const GateView& g, const float* prepa
             float* sv = scratch;
             float* ss = scratch + (size_t)nl * n_heads * g.d_g;
             const size_t fold_floats = folded_floats(g, nl, n_heads);
-            const size_t tiled_floats = (size_t)nl * g.d_g * g.d_model / 2;
-            use_tiled = plan.kind == GATE_PREFILL && fold_floats + tiled_floats <= (size_t)n_tok * nl * g.d_g;
+            use_tiled = plan.kind == GATE_PREFILL && tiled_fits(g, n_tok, nl, n_heads);
             uint4* st_tiled = reinterpret_cast<uint4*>(scratch + fold_floats);
             {
                 ProfScope prof(ctx, K_GATE_FOLD, st);

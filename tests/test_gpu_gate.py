@@ -243,6 +243,7 @@ def test_host_side_argument_checks_of_the_gate():
     (2, 16, 512, 512, 22, False, "k_gate_slice"),    # ... holds them with slices of 64 units only
     (2, 16, 512, 512, 21, False, "k_gate_hidden"),   # ... and not even then
     (8, 2, 1024, 384, 519, True, "k_gate_prefill"),  # 32-token blocks
+    (4, 2, 256, 128, 2049, True, "k_gate_prefill"),  # 32-token blocks of 128 units, a little over one per compute unit
     (40, 1, 256, 512, 641, True, "k_gate_prefill"),  # 64- or 128-token blocks
     (40, 1, 256, 512, 900, False, "k_gate_prefill"),  # 128-token blocks, everything derived in the call
 ])
