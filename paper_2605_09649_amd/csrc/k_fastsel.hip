@@ -23,7 +23,8 @@ namespace kvtrim {
 
 constexpr int FAST_ITEMS = FL_CAP_MAX / FAST_THREADS;             // list entries a thread of the resolving block holds
 constexpr int FAST_SUB = 16;                                      // sub-lists / group words per sequence
-constexpr int FAST_STAGE = 1024;                                  // candidates a block stages in LDS
+constexpr int FAST_STAGE = 1024;                                  // candidates a block of one segment stages in LDS
+constexpr int FAST_PIECE = 64;                                    // ... and puts on one sub-list before it goes on to the next
 constexpr int FAST_BATCH = 8;                                     // entries a thread loads before it uses any of them
 constexpr int FAST_BIN_DIRECT = 256;                              // a bin of at most this many entries is ranked directly
 static_assert(FAST_ITEMS * FAST_THREADS == FL_CAP_MAX, "list capacity must be a multiple of the block size");
@@ -453,20 +454,23 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     static_assert(!STEP || SCORE, "the one-call step computes the scores itself");
     __shared__ ResolveShared sm;
     __shared__ int s_last, s_ncand;
-    __shared__ uint32_t s_base;
-    // this block's candidates, before they go to the list; the last block of a sequence reuses the space (STEP)
-    __shared__ int32_t s_pool[(STEP ? 4 : 3) * FAST_STAGE];
+    __shared__ uint32_t s_base[FAST_SUB];
+    // This block's candidates, before they go to the list; the last block of a sequence reuses the space (STEP).  A block of
+    // several segments, which may be all of its sequence, stages as many as the list holds.
+    constexpr int STAGE = MULTI ? FL_CAP_MAX : FAST_STAGE;
+    __shared__ int32_t s_pool[(STEP ? 4 : 3) * STAGE];
     uint32_t* c_key = reinterpret_cast<uint32_t*>(s_pool);
-    int32_t* c_pos = s_pool + FAST_STAGE;
-    int32_t* c_seg = s_pool + 2 * FAST_STAGE;
-    int32_t* c_idx = s_pool + (STEP ? 3 : 2) * FAST_STAGE;
+    int32_t* c_pos = s_pool + STAGE;
+    int32_t* c_seg = s_pool + 2 * STAGE;
+    int32_t* c_idx = s_pool + (STEP ? 3 : 2) * STAGE;
     __shared__ int s_ev[STEP ? STEP_MAX_SEGS : 1], s_off[STEP ? STEP_MAX_SEGS : 1];
     __shared__ int s_seqcnt[STEP ? STEP_MAX_SEQS + 1 : 1];        // entries before each sequence
     static_assert(STEP_MAX_EVICT < 1 << 16 && STEP_MAX_SEGS <= FAST_STAGE && STEP_MAX_SEGS <= FAST_THREADS && STEP_MAX_EVICT <= FAST_STAGE, "the step's tables reuse the staging space, one segment per thread");
     const int tid = threadIdx.x;
     // bps blocks share a segment, or (MULTI: bps = 1) spb segments of a sequence share a block, FAST_THREADS / spb threads to
-    // each (whole wavefronts).  STEP: behind the scanning blocks the grid has blocks that only write the segments' tables, a
-    // wavefront per segment.
+    // each (whole wavefronts).  A block takes every bpq-th segment, so that neighbouring segments - a layer's, whose
+    // candidates come in the same steps - are staged by different blocks.  STEP: behind the scanning blocks the grid has blocks
+    // that only write the segments' tables, a wavefront per segment.
     const int spb = MULTI ? spb_arg : 1;
     const int bpq = (sh.segs_per_seq + spb - 1) / spb * bps;      // scanning blocks per sequence
     const bool tables_only = STEP && (int)blockIdx.x >= sh.n_seq * bpq;
@@ -474,8 +478,8 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     const int seq = tables_only ? 0 : (int)blockIdx.x / bpq;
     const int blk_in_seq = tables_only ? 0 : (int)blockIdx.x % bpq;
     const int part = blk_in_seq % bps;
-    const int seg_in_seq = blk_in_seq / bps * spb + group;
-    const bool no_seg = !tables_only && seg_in_seq >= sh.segs_per_seq;   // (the last block of a sequence may have groups to spare)
+    const int seg_in_seq = MULTI ? group * bpq + blk_in_seq : blk_in_seq / bps;
+    const bool no_seg = !tables_only && seg_in_seq >= sh.segs_per_seq;   // (a block may have a group to spare)
     const int seg = seq * sh.segs_per_seq + min(seg_in_seq, sh.segs_per_seq - 1);
     // Device-scope atomics on one address are served one after the other (tens of nanoseconds each), so the
     // blocks of a sequence do not meet on one word: the list is kept in up to FAST_SUB sub-lists with a counter
@@ -570,7 +574,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
                 if (live) mn = min(mn, key);
                 if (live && key < hi) {                           // rare: a few hundred entries per sequence and call
                     const int slot = atomicAdd(&s_ncand, 1);
-                    if (slot < FAST_STAGE) {
+                    if (slot < STAGE) {
                         c_key[slot] = key;
                         c_pos[slot] = (SCORE || PAGED) ? pv[u] : c.pos[at[u]];
                         c_seg[slot] = seg;
@@ -581,18 +585,18 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         }
         mn = block_min_u32(mn, sm.red_u);                         // (its barriers also complete s_ncand and the staged entries)
         const int ncand = s_ncand;
-        if (tid == 0) {
-            if (mn != 0xFFFFFFFFu) atomicMin(&grp_min[sub], mn);
-            // one reservation per block; a block with more candidates than it can stage makes its sub-list overflow
-            if (ncand > 0) s_base = atomicAdd(&sub_count[sub], ncand > FAST_STAGE ? cap + 1u : (uint32_t)ncand);
-        }
+        // One reservation per FAST_PIECE candidates, in neighbouring sub-lists, so that a segment with many of them does not
+        // fill its own; a block with more candidates than it can stage makes its sub-list overflow.
+        const int piece = max(FAST_PIECE, (ncand + nsub - 1) / nsub), npiece = ncand > STAGE ? 1 : (ncand + piece - 1) / piece;
+        if (tid == 0 && mn != 0xFFFFFFFFu) atomicMin(&grp_min[sub], mn);
+        if (tid < npiece) s_base[tid] = atomicAdd(&sub_count[(sub + tid) % nsub], ncand > STAGE ? cap + 1u : (uint32_t)min(piece, ncand - tid * piece));
         __syncthreads();
-        if (ncand > 0 && ncand <= FAST_STAGE) {
-            const uint32_t base = s_base;
+        if (ncand > 0 && ncand <= STAGE) {
             for (int i = tid; i < ncand; i += FAST_THREADS) {
-                const uint32_t slot = base + (uint32_t)i;
+                const int p = i / piece;
+                const uint32_t slot = s_base[p] + (uint32_t)(i - p * piece);
                 if (slot < subcap) {
-                    const size_t at = (size_t)sub * subcap + slot;
+                    const size_t at = (size_t)((sub + p) % nsub) * subcap + slot;
                     st_dev(&lk[at], c_key[i]);
                     st_dev(&ls[at], c_seg[i]);
                     st_dev(&lp[at], c_pos[i]);
@@ -1047,7 +1051,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_mask(CacheView c, const f
     bool no_seg = false;
     if (MULTI) {
         const int bpq = (sh.segs_per_seq + spb - 1) / spb;        // (bps = 1)
-        const int seg_in_seq = (int)blockIdx.x % bpq * spb + (int)threadIdx.x / threads;
+        const int seg_in_seq = (int)threadIdx.x / threads * bpq + (int)blockIdx.x % bpq;
         no_seg = seg_in_seq >= sh.segs_per_seq;
         seg = (int)blockIdx.x / bpq * sh.segs_per_seq + min(seg_in_seq, sh.segs_per_seq - 1);
         part = 0;

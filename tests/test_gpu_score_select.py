@@ -193,3 +193,76 @@ def test_bad_segment_table_is_reported():
     for hint in (0, 2):
         kv.kvtrim_score_select(ctx, dc, now.to(DEV), bud, score, keep, kept, None, evict_hint=hint)
         assert kv.kvtrim_poll_error(ctx) == -6
+
+
+def select_repeatedly(w, lens, log_beta, evictions, calls):
+    """A cache of which every call evicts `evictions` entries per sequence: one selection by the radix passes, then
+    `calls` decode-step ones, all against the oracle.  Returns the path counts."""
+    start = np.concatenate([[0], np.cumsum(lens + 1)[:-1]])
+    cap = int((lens + 1).sum())
+    c = {"k": torch.zeros(cap, 64, dtype=torch.bfloat16), "v": torch.zeros(cap, 64, dtype=torch.bfloat16),
+         "log_beta": torch.from_numpy(log_beta(cap, start)).float(),
+         "pos": torch.from_numpy((np.arange(cap) - np.repeat(start, lens + 1)).astype(np.int32)),
+         "seg_start": torch.from_numpy(start), "seg_len": torch.from_numpy(lens.astype(np.int32)), "cap": cap}
+    now = np.full(w.n_seq, int(lens.max()), dtype=np.int32)
+    hc = host_cache(w, c)
+    score = oracle.score(hc, now)
+    budget = lens.reshape(w.n_seq, -1).sum(1) - evictions
+    keep, kept, thr = oracle.select(hc, score, budget)
+    ctx = kv.Context(w.n_seq, w.n_layers, w.n_kv_heads, w.n_q_heads, 64, cap)
+    dc = kv.Cache.from_dict(c, DEV)
+    live = live_mask(hc)
+    args = [torch.from_numpy(now).to(DEV), torch.from_numpy(budget).to(DEV), torch.zeros(cap, dtype=torch.float32, device=DEV),
+            torch.zeros(cap, dtype=torch.uint8, device=DEV), torch.zeros(w.nseg, dtype=torch.int32, device=DEV),
+            torch.zeros(w.n_seq, dtype=torch.int32, device=DEV)]
+    for call in range(1 + calls):
+        args[3].fill_(7)
+        kv.kvtrim_score_select(ctx, dc, *args, evict_hint=evictions if call else 0)
+        assert kv.kvtrim_poll_error(ctx) == 0
+        assert np.array_equal(args[2].cpu().numpy()[live].view(np.uint32), score[live].view(np.uint32))
+        k = args[3].cpu().numpy()
+        assert np.array_equal(k[live], keep[live]) and np.all(k[~live] == 7)
+        assert np.array_equal(args[4].cpu().numpy(), kept)
+        assert np.array_equal(args[5].cpu().numpy().view(np.uint32), thr)
+    return kv.kvtrim_select_path_counts(ctx)
+
+
+def test_a_hot_layer_of_a_batch_stays_on_the_candidate_list():
+    # 2048 segments, several to a scanning block; nearly all candidates (about 900 per sequence) come from the 16 neighbouring
+    # segments of one layer, which must not share one block's sub-list (256 entries)
+    w = wl(4, 32, 16, 1, 64)
+    lens = np.full(w.nseg, 9)
+    for s in range(4):
+        lens[s * 512 + 80:s * 512 + 96] = 70
+
+    def log_beta(cap, start):
+        rng = np.random.default_rng(9)
+        lb = -0.001 * rng.random(cap)
+        for s in range(4):
+            a, b = start[s * 512 + 80], start[s * 512 + 96]
+            lb[a:b] = -1.0 - rng.random(b - a)
+        return lb
+    assert select_repeatedly(w, lens, log_beta, 300, 3) == (3 * 4, 0)
+
+
+def test_one_hot_segment_stays_on_the_candidate_list():
+    # 64 segments with a block each; all candidates (some 600) come from one of them: more than its sub-list's 256 entries
+    w = wl(1, 8, 8, 1, 64)
+    lens = np.full(w.nseg, 40)
+    lens[37] = 3000
+    rng = np.random.default_rng(10)
+
+    def log_beta(cap, start):
+        lb = -0.0001 * rng.random(cap)
+        lb[start[37]:start[38]] = -1.0 - rng.random(start[38] - start[37])
+        return lb
+    assert select_repeatedly(w, lens, log_beta, 150, 3) == (3, 0)
+
+
+@pytest.mark.parametrize("S,H,evictions", [(260, 16, 490),        # about 1490 candidates per sequence: more than a block stages
+                                           (260, 16, 8)])         # ... few, but a selection from scratch leaves the bound far off
+def test_sequences_of_few_segments_stay_on_the_candidate_list(S, H, evictions):
+    w = wl(S, 1, H, 1, 64)
+    rng = np.random.default_rng(evictions)
+    lens = rng.integers(140, 161, w.nseg)
+    assert select_repeatedly(w, lens, lambda cap, start: -rng.random(cap), evictions, 3) == (3 * S, 0)
