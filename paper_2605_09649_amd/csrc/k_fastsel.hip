@@ -371,6 +371,24 @@ __device__ __forceinline__ T ld_dev(const T* p) { return __hip_atomic_load(p, __
 template <typename T>
 __device__ __forceinline__ void st_dev(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
+// Several segments to a block: a segment's own threads walk its first `limit` entries (scan_grid), and then all threads of
+// the block together what is left of the longer ones.  (With a wavefront per segment the longest of 16 lists would set
+// the time of the block, and the lists of a global budget are uneven: one of 60 K entries among 4096 of 500, 840 us with
+// the single-block select that its own sub-list's overflow brought, 230 without, now 48.)  Returns the segments of block blk
+// of a sequence's bpq (bit: their group) of which something may be left - every wavefront finds out for itself, so no
+// barrier is needed.
+template <int KIND>
+__device__ __forceinline__ uint32_t long_segments(const CacheView& c, const StepArgs& sa, const Shape& sh, int seq, int bpq, int blk,
+                                                  int spb, int limit) {
+    const int s = lane_id() * bpq + blk;
+    int64_t most = 0;                                             // entries the segment has at most
+    if (lane_id() < spb && s < sh.segs_per_seq) {
+        const int g = seq * sh.segs_per_seq + s;
+        most = KIND == SCAN_PAGED ? (int64_t)sa.pg.seg_pages[g] * KVTRIM_PAGE_SIZE : (int64_t)c.seg_len[g] + (KIND == SCAN_STEP ? sa.n_new : 0);
+    }
+    return (uint32_t)__ballot(most > limit);
+}
+
 // What the one-call decode step needs besides the scan, for the 16 segments from seg0 on, a wavefront each: the segment's
 // new tokens enter the source cache, and its part of the row mover's chunk table is written.  Both are read by the next
 // kernel only.  (A block per segment of 1024 threads was half the grid of the scoring kernel: at 4096 segments its
@@ -448,7 +466,7 @@ template <bool SCORE, int KIND, bool MULTI>
 __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const int32_t* __restrict__ now,
                                                             const float* score_in, float* score_out,
                                                             const int64_t* __restrict__ budget, Shape sh, Workspace ws,
-                                                            int bps, int spb_arg, int32_t* __restrict__ kept_out,
+                                                            int bps, int spb_arg, int limit, int32_t* __restrict__ kept_out,
                                                             uint32_t* __restrict__ thr_out, StepArgs sa) {
     constexpr bool STEP = KIND == SCAN_STEP, PAGED = KIND == SCAN_PAGED;
     static_assert(!STEP || SCORE, "the one-call step computes the scores itself");
@@ -480,7 +498,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     const int part = blk_in_seq % bps;
     const int seg_in_seq = MULTI ? group * bpq + blk_in_seq : blk_in_seq / bps;
     const bool no_seg = !tables_only && seg_in_seq >= sh.segs_per_seq;   // (a block may have a group to spare)
-    const int seg = seq * sh.segs_per_seq + min(seg_in_seq, sh.segs_per_seq - 1);
+    const int own_seg = seq * sh.segs_per_seq + min(seg_in_seq, sh.segs_per_seq - 1);
     // Device-scope atomics on one address are served one after the other (tens of nanoseconds each), so the
     // blocks of a sequence do not meet on one word: the list is kept in up to FAST_SUB sub-lists with a counter
     // each, the lowest key and the arrivals in FAST_SUB group words (then one top-level arrival per group).
@@ -495,9 +513,8 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         return;
     }
     bool bad = false, nocap = false;
-    const SegView sv0 = seg_view<KIND>(c, seg, sh.nseg, sa, &bad, &nocap);
-    const int64_t start = sv0.start;
-    const int len = no_seg ? 0 : sv0.len;
+    const SegView own = seg_view<KIND>(c, own_seg, sh.nseg, sa, &bad, &nocap);
+    const int own_len = no_seg ? 0 : own.len;
     if (gt == 0 && part == 0 && !no_seg && (bad || nocap)) atomicOr(ws.err, bad ? ERR_LAYOUT : ERR_CAP);
     const uint32_t hi = ws.fast_hi[seq];
     const uint32_t cap = (uint32_t)ws.fl_cap;
@@ -525,9 +542,14 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     // ---- every entry of this block's share: score, and onto the list if its key is below the bound
     {
         uint32_t mn = 0xFFFFFFFFu;
-        const int stride = bps * threads;
+        SegView sv0 = own;
+        int seg = own_seg, first = part * threads + gt, stride = bps * threads;
+        int len = MULTI ? min(own_len, limit) : own_len;
+        uint32_t todo = MULTI ? long_segments<KIND>(c, sa, sh, seq, bpq, blk_in_seq, spb, limit) : 0;
+        for (;;) {                                                // the threads' own segments, then (MULTI) what is left of long ones
+        const int64_t start = sv0.start;
         // batches of FAST_BATCH entries per thread: all loads of a batch are issued before any of them is used
-        for (int j0 = part * threads + gt; j0 < len; j0 += stride * FAST_BATCH) {
+        for (int j0 = first; j0 < len; j0 += stride * FAST_BATCH) {
             float sv[FAST_BATCH];
             int pv[FAST_BATCH];
             int64_t at[FAST_BATCH];                               // where the entry lies in the arrays
@@ -582,6 +604,15 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
                     }
                 }
             }
+        }
+        if (!MULTI || todo == 0) break;                           // (uniform)
+        seg = seq * sh.segs_per_seq + __builtin_ctz(todo) * bpq + blk_in_seq;
+        todo &= todo - 1;
+        bool b2 = false, n2 = false;                              // (reported by the segment's own threads)
+        sv0 = seg_view<KIND>(c, seg, sh.nseg, sa, &b2, &n2);
+        first = limit + tid;
+        stride = FAST_THREADS;
+        len = sv0.len;
         }
         mn = block_min_u32(mn, sm.red_u);                         // (its barriers also complete s_ncand and the staged entries)
         const int ncand = s_ncand;
@@ -1041,7 +1072,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
 // a live entry is marked for release (owner -2), exactly as k_pg_evict does from the mask.
 template <bool PAGED, bool EVICT, bool MULTI>
 __global__ __launch_bounds__(FAST_THREADS) void k_fast_mask(CacheView c, const float* __restrict__ score, Shape sh,
-                                                            Workspace ws, int bps, int spb_arg, uint8_t* __restrict__ keep,
+                                                            Workspace ws, int bps, int spb_arg, int limit, uint8_t* __restrict__ keep,
                                                             int32_t* __restrict__ kept_out, PagedArgs pg) {
     __shared__ int32_t lds32[17];
     // dealt as in k_fast_scan
@@ -1049,8 +1080,8 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_mask(CacheView c, const f
     const int tid = (int)threadIdx.x % threads;
     int seg, part;
     bool no_seg = false;
-    if (MULTI) {
-        const int bpq = (sh.segs_per_seq + spb - 1) / spb;        // (bps = 1)
+    const int bpq = (sh.segs_per_seq + spb - 1) / spb * bps;
+    if (MULTI) {                                                  // (bps = 1)
         const int seg_in_seq = (int)threadIdx.x / threads * bpq + (int)blockIdx.x % bpq;
         no_seg = seg_in_seq >= sh.segs_per_seq;
         seg = (int)blockIdx.x / bpq * sh.segs_per_seq + min(seg_in_seq, sh.segs_per_seq - 1);
@@ -1060,19 +1091,22 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_mask(CacheView c, const f
         part = (int)blockIdx.x % bps;
     }
     const int seq = seg / sh.segs_per_seq;
-    const int stride = bps * threads;
+    int stride = bps * threads;
     StepArgs sa{};
     sa.pg = pg;
     bool bad = false, nocap = false;
-    const SegView v = seg_view<PAGED ? SCAN_PAGED : SCAN_RAGGED>(c, seg, sh.nseg, sa, &bad, &nocap);
-    const int len = no_seg ? 0 : v.len;
+    SegView v = seg_view<PAGED ? SCAN_PAGED : SCAN_RAGGED>(c, seg, sh.nseg, sa, &bad, &nocap);
+    int len = no_seg ? 0 : v.len;
     KeySource<false, PAGED ? SCAN_PAGED : SCAN_RAGGED> ks;
     ks.bt = pg.block_table;
     ks.n_pages = pg.n_pages;
     const FastSel fs = ws.fast_sel[seq];
-    int n = 0;
+    int n = 0, first = part * threads + tid;
+    if (MULTI) len = min(len, limit);
+    uint32_t todo = MULTI ? long_segments<PAGED ? SCAN_PAGED : SCAN_RAGGED>(c, sa, sh, seq, bpq, (int)blockIdx.x % bpq, spb, limit) : 0;
+    for (;;) {                                                    // as in k_fast_scan
     const bool seg_before = seg < fs.seg_thr, seg_same = seg == fs.seg_thr;
-    for (int j0 = part * threads + tid; j0 < len; j0 += stride * FAST_BATCH) {
+    for (int j0 = first; j0 < len; j0 += stride * FAST_BATCH) {
         int64_t at[FAST_BATCH];
         bool bp = false;
 #pragma unroll
@@ -1124,14 +1158,25 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_mask(CacheView c, const f
         n = wave_sum(n);
         if (lane_id() == 0 && n) atomicAdd(&kept_out[seg], n);
     }
+    if (!MULTI || todo == 0) break;
+    seg = seq * sh.segs_per_seq + __builtin_ctz(todo) * bpq + (int)blockIdx.x % bpq;
+    todo &= todo - 1;
+    v = seg_view<PAGED ? SCAN_PAGED : SCAN_RAGGED>(c, seg, sh.nseg, sa, &bad, &nocap);
+    first = limit + (int)threadIdx.x;
+    stride = FAST_THREADS;
+    len = v.len;
+    n = 0;
+    }
 }
 
 // How the blocks of k_fast_scan and k_fast_mask are dealt: several to a segment of more than FAST_ENTRIES_PER_BLOCK
 // entries; several segments of a sequence to a block when a block each would be more than are resident at once (one of
 // k_fast_scan's per compute unit, two of k_fast_mask's) - a block of k_fast_scan lives 8 to 10 us whatever it has to do, so
 // 4096 segments of 2048 entries took sixteen rounds of the chip: 202 us, with sixteen segments to a block 43.
+// Of a long segment its own threads walk twice the mean capacity of a segment, and two batches at least; a whole number of
+// pages, so that a wavefront's entries stay in one.
 struct ScanGrid {
-    int bps, spb;
+    int bps, spb, limit;
     unsigned blocks;
 };
 static ScanGrid scan_grid(const Shape& sh, int64_t cap, int resident) {
@@ -1142,6 +1187,8 @@ static ScanGrid scan_grid(const Shape& sh, int64_t cap, int resident) {
     auto per_seq = [&](int spb) { return (int64_t)((sh.segs_per_seq + spb - 1) / spb); };
     while (bps < 1 && g.spb < FAST_THREADS / 64 && sh.n_seq * per_seq(g.spb) > resident && 2 * g.spb <= sh.segs_per_seq) g.spb *= 2;
     g.blocks = (unsigned)(sh.n_seq * per_seq(g.spb) * g.bps);
+    const int64_t mean2 = 2 * (cap / sh.nseg), batches = 2 * (FAST_THREADS / g.spb) * FAST_BATCH;
+    g.limit = (int)(((mean2 > batches ? mean2 : batches) + KVTRIM_PAGE_SIZE - 1) / KVTRIM_PAGE_SIZE * KVTRIM_PAGE_SIZE);   // (several to a block: a mean below FAST_ENTRIES_PER_BLOCK)
     return g;
 }
 constexpr int SCAN_RESIDENT = 256, MASK_RESIDENT = 512;
@@ -1157,12 +1204,12 @@ kvtrim_status launch_score_select(kvtrim_ctx* ctx, const CacheView& c, const int
     const dim3 block(FAST_THREADS);
     const ScanGrid sg = scan_grid(sh, c.cap, SCAN_RESIDENT);
     { ProfScope prof(ctx, K_FAST_SCAN, st);
-      if (sg.spb > 1) hipLaunchKernelGGL((k_fast_scan<true, SCAN_RAGGED, true>), dim3(sg.blocks), block, 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, kept, thr, StepArgs());
-      else hipLaunchKernelGGL((k_fast_scan<true, SCAN_RAGGED, false>), dim3(sg.blocks), block, 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, kept, thr, StepArgs()); }
+      if (sg.spb > 1) hipLaunchKernelGGL((k_fast_scan<true, SCAN_RAGGED, true>), dim3(sg.blocks), block, 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, sg.limit, kept, thr, StepArgs());
+      else hipLaunchKernelGGL((k_fast_scan<true, SCAN_RAGGED, false>), dim3(sg.blocks), block, 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, sg.limit, kept, thr, StepArgs()); }
     { ProfScope prof(ctx, K_FAST_MASK, st);
       const ScanGrid mg = scan_grid(sh, c.cap, MASK_RESIDENT);
-      if (mg.spb > 1) hipLaunchKernelGGL((k_fast_mask<false, false, true>), dim3(mg.blocks), block, 0, st, c, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, PagedArgs());
-      else hipLaunchKernelGGL((k_fast_mask<false, false, false>), dim3(mg.blocks), block, 0, st, c, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, PagedArgs()); }
+      if (mg.spb > 1) hipLaunchKernelGGL((k_fast_mask<false, false, true>), dim3(mg.blocks), block, 0, st, c, (const float*)score, sh, ws, mg.bps, mg.spb, mg.limit, keep, kept, PagedArgs());
+      else hipLaunchKernelGGL((k_fast_mask<false, false, false>), dim3(mg.blocks), block, 0, st, c, (const float*)score, sh, ws, mg.bps, mg.spb, mg.limit, keep, kept, PagedArgs()); }
     KVTRIM_HIP(ctx, hipGetLastError());
     return KVTRIM_OK;
 }
@@ -1179,15 +1226,15 @@ kvtrim_status launch_score_select_paged(kvtrim_ctx* ctx, const CacheView& pool, 
     StepArgs sa{};
     sa.pg = pg;
     { ProfScope prof(ctx, K_FAST_SCAN, st);
-      if (sg.spb > 1) hipLaunchKernelGGL((k_fast_scan<true, SCAN_PAGED, true>), dim3(sg.blocks), block, 0, st, pool, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, kept, thr, sa);
-      else hipLaunchKernelGGL((k_fast_scan<true, SCAN_PAGED, false>), dim3(sg.blocks), block, 0, st, pool, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, kept, thr, sa); }
+      if (sg.spb > 1) hipLaunchKernelGGL((k_fast_scan<true, SCAN_PAGED, true>), dim3(sg.blocks), block, 0, st, pool, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, sg.limit, kept, thr, sa);
+      else hipLaunchKernelGGL((k_fast_scan<true, SCAN_PAGED, false>), dim3(sg.blocks), block, 0, st, pool, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, sg.limit, kept, thr, sa); }
     { ProfScope prof(ctx, K_FAST_MASK, st);
       if (evict)
-          { if (mg.spb > 1) hipLaunchKernelGGL((k_fast_mask<true, true, true>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, pg);
-            else hipLaunchKernelGGL((k_fast_mask<true, true, false>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, pg); }
+          { if (mg.spb > 1) hipLaunchKernelGGL((k_fast_mask<true, true, true>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, mg.limit, keep, kept, pg);
+            else hipLaunchKernelGGL((k_fast_mask<true, true, false>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, mg.limit, keep, kept, pg); }
       else
-          { if (mg.spb > 1) hipLaunchKernelGGL((k_fast_mask<true, false, true>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, pg);
-            else hipLaunchKernelGGL((k_fast_mask<true, false, false>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, keep, kept, pg); } }
+          { if (mg.spb > 1) hipLaunchKernelGGL((k_fast_mask<true, false, true>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, mg.limit, keep, kept, pg);
+            else hipLaunchKernelGGL((k_fast_mask<true, false, false>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, mg.limit, keep, kept, pg); } }
     KVTRIM_HIP(ctx, hipGetLastError());
     return KVTRIM_OK;
 }
@@ -1200,9 +1247,9 @@ kvtrim_status launch_step_scan(kvtrim_ctx* ctx, const CacheView& c, const int32_
     const unsigned tables = (unsigned)((sh.nseg + FAST_THREADS / 64 - 1) / (FAST_THREADS / 64));
     ProfScope prof(ctx, K_FAST_SCAN, st);
     if (sg.spb > 1) hipLaunchKernelGGL((k_fast_scan<true, SCAN_STEP, true>), dim3(sg.blocks + tables), dim3(FAST_THREADS), 0, st, c, now,
-                       (const float*)nullptr, score, budget, sh, ctx->ws, sg.bps, sg.spb, kept, thr, sa);
+                       (const float*)nullptr, score, budget, sh, ctx->ws, sg.bps, sg.spb, sg.limit, kept, thr, sa);
     else hipLaunchKernelGGL((k_fast_scan<true, SCAN_STEP, false>), dim3(sg.blocks + tables), dim3(FAST_THREADS), 0, st, c, now,
-                       (const float*)nullptr, score, budget, sh, ctx->ws, sg.bps, sg.spb, kept, thr, sa);
+                       (const float*)nullptr, score, budget, sh, ctx->ws, sg.bps, sg.spb, sg.limit, kept, thr, sa);
     KVTRIM_HIP(ctx, hipGetLastError());
     return KVTRIM_OK;
 }

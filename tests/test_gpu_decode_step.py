@@ -317,3 +317,27 @@ def test_several_segments_to_a_scanning_block(S, L, H):                         
         assert r["status"] == 0 and r["score_equal"] and r["keep_equal"] and r["cache_equal"], (S, "score_select", r)
     check_paged(run_paged_both(w, [budget] * 3, device=DEV, cache_dict=clone(), now0=now.numpy(), hint=L * H))
     check_paged(run_paged_both(w, [budget] * 3, device=DEV, cache_dict=clone(), now0=now.numpy(), hint=L * H, one_call=True))
+
+
+@pytest.mark.parametrize("S,L,H,long_lens", [
+    (5, 13, 9, {0: 12345, 5: 4096, 35: 4097, 580: 9999, 584: 5000}),   # four segments to a block: at and over two batches of their threads; two in one block; the last of the batch
+    (260, 1, 16, {17: 1024, 18: 1025, 4159: 5000, 40: 2100, 41: 2000, 47: 4097}),   # sixteen, a wavefront each; three long ones in one block
+])
+def test_long_segments_among_several_to_a_scanning_block(S, L, H, long_lens):
+    from paged_harness import run_paged_both
+    from test_gpu_paged import check as check_paged
+    w = wl(S, L, H, 2, 64)
+    rng = np.random.default_rng(S)
+    seg_len = rng.choice([0, 1, 63, 64, 65, 130], w.nseg)
+    for g, n in long_lens.items():
+        seg_len[g] = n
+    c, now = ki.ragged_cache(w, seg_len, reserve=1, salt=S)
+    budget = [max(1, int(seg_len[s * L * H:(s + 1) * L * H].sum()) - L * H // 2) for s in range(S)]
+
+    def clone():
+        return {k: (v.clone() if torch.is_tensor(v) else v) for k, v in c.items()}
+    check(run_steps_both(w, steps=2, budget=budget, device=DEV, cache_dict=clone(), now0=now.numpy(), one_call=True, hint=L * H), (S, "step"))
+    for r in run_steps_both(w, steps=2, budget=budget, device=DEV, cache_dict=clone(), now0=now.numpy(), fused=True, hint=L * H):
+        assert r["status"] == 0 and r["score_equal"] and r["keep_equal"] and r["cache_equal"], (S, "score_select", r)
+    check_paged(run_paged_both(w, [budget] * 2, device=DEV, cache_dict=clone(), now0=now.numpy(), hint=L * H))
+    check_paged(run_paged_both(w, [budget] * 2, device=DEV, cache_dict=clone(), now0=now.numpy(), hint=L * H, one_call=True))
