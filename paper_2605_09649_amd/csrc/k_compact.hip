@@ -16,7 +16,7 @@ namespace kvtrim {
 constexpr int SCAN_THREADS = 1024;
 constexpr int SCAN_LANE = 16;          // mask bytes per lane and load: a wavefront's load covers 8 chunks
 constexpr int SCAN_GROUP = 64 * SCAN_LANE / CMP_CHUNK;
-constexpr int SCAN_BATCH = SCAN_THREADS / (SCAN_THREADS / 64) / SCAN_GROUP;   // loads with which the wavefronts cover a tile of SCAN_THREADS chunks: 8
+constexpr int SCAN_BATCH = 64 / SCAN_GROUP;   // loads with which a block's wavefronts cover a tile of as many chunks as it has threads: 8
 static_assert(SCAN_LANE * 8 == CMP_CHUNK, "eight lanes to a chunk");
 
 // bit i set where byte i of the 16 is not zero
@@ -113,19 +113,24 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_prefix(CacheView src, cons
     }
 }
 
+// Behind k_cmp_prefix (more than 1024 segments) a block of 256 threads takes a segment: the kernel needs some 80 registers,
+// with which a compute unit holds one block of 1024 threads but five of 256.
+constexpr int PRE_THREADS = 256;
+
 // PRE: k_cmp_prefix has run (segment prefixes and the checks over all segments are done).
 // gat: the table of the DESTINATION's 128-row chunks (ws.att_chunk_prefix / ws.att_desc) and the source row of every
 // destination row (ws.gat_src) are written as well, for the gathering instance of the fused kernel that follows.
-template <bool PRE>
-__global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const uint8_t* __restrict__ keep,
+template <bool PRE, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_cmp_scan(CacheView src, const uint8_t* __restrict__ keep,
                                                            const int32_t* __restrict__ kept, CacheViewMut dst,
                                                            int reserve, int align, Shape sh, Workspace ws, int inplace,
                                                            int gat) {
+    static_assert(PRE || THREADS == SCAN_THREADS, "a thread per segment sums the prefixes");
     __shared__ int64_t lds64[17];
     __shared__ int64_t lds_n[64];
     __shared__ int s_bad;                                         // 1: a segment table entry, 2: a count that no mask can have
-    __shared__ int s_cnt[SCAN_THREADS];
-    __shared__ int s_ex[SCAN_THREADS];
+    __shared__ int s_cnt[THREADS];
+    __shared__ int s_ex[THREADS];
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
     const int g = blockIdx.x;
     const int nseg = sh.nseg;
@@ -135,7 +140,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
     }
 
     // Order of the memory traffic: (1) this segment's own table entry; (2) in one round, the table entries of all
-    // segments (for the prefixes; !PRE) and the mask bytes of this segment's first SCAN_THREADS chunks; then
+    // segments (for the prefixes; !PRE) and the mask bytes of this segment's first THREADS chunks; then
     // arithmetic only; (3) the stores.  A decode-step segment is done after two dependent round trips.
     const int len_raw = src.seg_len[g];
     const int64_t start = src.seg_start[g];
@@ -158,13 +163,13 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
         chunks_before = ws.cmp_chunk_prefix[g];
         dst_before = dst.seg_start[g];
         if (gat) runs_before = ws.att_chunk_prefix[g];
-    } else if (tid < nseg) {                                      // (nseg <= SCAN_THREADS without k_cmp_prefix)
+    } else if (tid < nseg) {                                      // (nseg <= THREADS without k_cmp_prefix)
         o_len = src.seg_len[tid];
         o_st = src.seg_start[tid];
         o_kp = kept[tid];
     }
 
-    // Mask bytes of one tile of SCAN_THREADS chunks: load u of a wavefront covers the 8 chunks from (16 u + wave) * 8 on, 16
+    // Mask bytes of one tile of THREADS chunks: load u of a wavefront covers the 8 chunks from (16 u + wave) * 8 on, 16
     // bytes per lane (at any address: a segment starts anywhere), all of them asked for at once.  They stay in registers
     // as one bit per entry, for the counts and (gat) for the row numbers.  (A wavefront per chunk with two byte loads per
     // lane, twice over for the row numbers, took 46 us for the 33.5 M entries of a first eviction; now 18.)
@@ -172,7 +177,8 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
     // In two halves, the first of which - 512 chunks - is under way while the prefixes are summed.
     scan_v4 w[SCAN_BATCH / 2];
     uint32_t bits[SCAN_BATCH];
-    auto first_of = [&](int tile0, int u) { return (tile0 + (u * (SCAN_THREADS / 64) + wave) * SCAN_GROUP) * CMP_CHUNK; };   // (< 2^31 + a tile)
+    // (below 2^31: a tile starts at a multiple of THREADS chunks inside a segment of at most 2^31 - 4096 entries)
+    auto first_of = [&](int tile0, int u) { return (tile0 + (u * (THREADS / 64) + wave) * SCAN_GROUP) * CMP_CHUNK; };
     auto request = [&](int tile0, int half) {
 #pragma unroll
         for (int u = 0; u < SCAN_BATCH / 2; ++u) {
@@ -194,6 +200,10 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
         for (int i = 0; i < SCAN_BATCH / 2; ++i) {
             constexpr int first = decltype(half)::value * (SCAN_BATCH / 2);
             const int u = first + i;
+            if (first_of(tile0, u) >= len) {                      // (uniform; nothing there, and nobody reads the counts)
+                bits[u] = 0;
+                continue;
+            }
             const int64_t over = (int64_t)first_of(tile0, u) + lane * SCAN_LANE - ((int64_t)len - SCAN_LANE);   // bytes past the end
             bits[u] = nonzero_bytes(w[i]);
             if (over > 0 && len >= SCAN_LANE) bits[u] = over < SCAN_LANE ? bits[u] >> over : 0u;
@@ -201,7 +211,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
             n += __shfl_xor(n, 1, 64);
             n += __shfl_xor(n, 2, 64);
             n += __shfl_xor(n, 4, 64);
-            if ((lane & 7) == 0) s_cnt[(u * (SCAN_THREADS / 64) + wave) * SCAN_GROUP + (lane >> 3)] = n;
+            if ((lane & 7) == 0) s_cnt[(u * (THREADS / 64) + wave) * SCAN_GROUP + (lane >> 3)] = n;
         }
     };
     request(0, 0);                                                // in flight while the prefixes are summed
@@ -250,7 +260,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
         const int rlen = own_ok ? kept[g] : 0;
         const int nrun = len > 0 && rlen > 0 ? (rlen + CMP_CHUNK - 1) / CMP_CHUNK : 0;
         gat_slots = (int64_t)nrun * CMP_CHUNK;
-        for (int u = tid; u < nrun; u += SCAN_THREADS) {
+        for (int u = tid; u < nrun; u += THREADS) {
             ChunkDesc d;
             d.first = dst_before + (int64_t)u * CMP_CHUNK;
             d.n = min(CMP_CHUNK, rlen - u * CMP_CHUNK);
@@ -263,11 +273,11 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
         }
     }
 
-    // Tiles of SCAN_THREADS chunks: counts (phase 1, above), then a thread per chunk - exclusive scan of the counts,
+    // Tiles of THREADS chunks: counts (phase 1, above), then a thread per chunk - exclusive scan of the counts,
     // destination offset and descriptor of every chunk (phase 2).
     int64_t running = 0;
-    for (int tile0 = 0; tile0 < nch; tile0 += SCAN_THREADS) {
-        const int tile_n = min(SCAN_THREADS, nch - tile0);
+    for (int tile0 = 0; tile0 < nch; tile0 += THREADS) {
+        const int tile_n = min(THREADS, nch - tile0);
         __syncthreads();                                          // s_cnt of the previous tile has been read
         if (tile0 > 0) request(tile0, 0);                         // (the first one is already here)
         count(tile0, std::integral_constant<int, 0>());
@@ -296,7 +306,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
             int32_t* slots = ws.gat_src + runs_before * CMP_CHUNK;
 #pragma unroll
             for (int u = 0; u < SCAN_BATCH; ++u) {
-                const int cl = (u * (SCAN_THREADS / 64) + wave) * SCAN_GROUP + (lane >> 3);
+                const int cl = (u * (THREADS / 64) + wave) * SCAN_GROUP + (lane >> 3);
                 const int n = __popc(bits[u]);
                 int before = n;                                   // survivors of the chunk up to this lane's, then before them
                 int o = __shfl_up(before, 1, 8);
@@ -316,7 +326,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void k_cmp_scan(CacheView src, const 
     }
     if (gat) {
         // the slots behind the segment's last row, up to the end of its last chunk, name a row that exists
-        for (int64_t r = running + tid; r < gat_slots; r += SCAN_THREADS) ws.gat_src[runs_before * CMP_CHUNK + r] = (int32_t)start;
+        for (int64_t r = running + tid; r < gat_slots; r += THREADS) ws.gat_src[runs_before * CMP_CHUNK + r] = (int32_t)start;
     }
     if (tid == 0) {
         if (running != kept[g]) atomicOr(ws.err, ERR_MISMATCH);
@@ -430,10 +440,10 @@ void launch_cmp_scan_aligned(kvtrim_ctx* ctx, const CacheView& src, const uint8_
     const int g = gat ? 1 : 0;
     if (ctx->shape.nseg > 1024) {                                 // see k_cmp_prefix
         hipLaunchKernelGGL(k_cmp_prefix, dim3(1), dim3(SCAN_THREADS), 0, st, src, kept, dst, reserve, align, ctx->shape, ctx->ws, 0, g);
-        hipLaunchKernelGGL(k_cmp_scan<true>, dim3(ctx->shape.nseg), dim3(SCAN_THREADS), 0, st, src, keep, kept, dst, reserve,
+        hipLaunchKernelGGL((k_cmp_scan<true, PRE_THREADS>), dim3(ctx->shape.nseg), dim3(PRE_THREADS), 0, st, src, keep, kept, dst, reserve,
                            align, ctx->shape, ctx->ws, 0, g);
     } else {
-        hipLaunchKernelGGL(k_cmp_scan<false>, dim3(ctx->shape.nseg), dim3(SCAN_THREADS), 0, st, src, keep, kept, dst, reserve,
+        hipLaunchKernelGGL((k_cmp_scan<false, SCAN_THREADS>), dim3(ctx->shape.nseg), dim3(SCAN_THREADS), 0, st, src, keep, kept, dst, reserve,
                            align, ctx->shape, ctx->ws, 0, g);
     }
 }
@@ -447,10 +457,10 @@ void launch_cmp_scan_inplace(kvtrim_ctx* ctx, const CacheViewMut& c, const uint8
     src.seg_start = c.seg_start; src.seg_len = c.seg_len; src.cap = c.cap; src.log_tail = c.log_tail;
     if (ctx->shape.nseg > 1024) {
         hipLaunchKernelGGL(k_cmp_prefix, dim3(1), dim3(SCAN_THREADS), 0, st, src, kept, c, 0, 1, ctx->shape, ctx->ws, 1, 0);
-        hipLaunchKernelGGL(k_cmp_scan<true>, dim3(ctx->shape.nseg), dim3(SCAN_THREADS), 0, st, src, keep, kept, c, 0, 1,
+        hipLaunchKernelGGL((k_cmp_scan<true, PRE_THREADS>), dim3(ctx->shape.nseg), dim3(PRE_THREADS), 0, st, src, keep, kept, c, 0, 1,
                            ctx->shape, ctx->ws, 1, 0);
     } else {
-        hipLaunchKernelGGL(k_cmp_scan<false>, dim3(ctx->shape.nseg), dim3(SCAN_THREADS), 0, st, src, keep, kept, c, 0, 1,
+        hipLaunchKernelGGL((k_cmp_scan<false, SCAN_THREADS>), dim3(ctx->shape.nseg), dim3(SCAN_THREADS), 0, st, src, keep, kept, c, 0, 1,
                            ctx->shape, ctx->ws, 1, 0);
     }
 }

@@ -835,3 +835,26 @@ def test_more_segments_than_a_long_mask_needs_over_a_handful_of_entries(cap):
     assert np.array_equal(d_score.cpu().numpy().view(np.uint32), score.view(np.uint32))
     assert np.array_equal(d_keep.cpu().numpy(), keep) and np.array_equal(d_kept.cpu().numpy(), kept)
     assert np.array_equal(d_thr.cpu().numpy().view(np.uint32), thr)
+
+
+@pytest.mark.parametrize("keep_part", [2, 40])               # a block per source chunk / the gathering form
+def test_compaction_of_many_segments_at_the_edges_of_their_tiles(keep_part):
+    # more than 1024 segments: the scan takes a segment in tiles of 256 chunks = 32768 entries
+    w = wl(9, 8, 16, 1, 64)                                  # 1152 segments
+    rng = np.random.default_rng(keep_part)
+    seg_len = rng.choice([0, 1, 15, 16, 127, 128, 129, 300], w.nseg)
+    for g, n in {0: 32767, 3: 32768, 4: 32769, 700: 65537, 1151: 33000}.items():
+        seg_len[g] = n
+    c, _ = ki.ragged_cache(w, seg_len, reserve=1, salt=52)
+    hc = host_cache(w, c)
+    keep = np.zeros(hc.cap, np.uint8)
+    kept = np.zeros(w.nseg, np.int32)
+    for g, (s, n) in enumerate(zip(hc.seg_start, hc.seg_len)):
+        keep[s:s + n] = rng.random(n) < 1 / keep_part
+        kept[g] = keep[s:s + n].sum()
+    ctx = kv.Context(w.n_seq, w.n_layers, w.n_kv_heads, w.n_q_heads, 64, hc.cap)
+    dst = kv.Cache.empty(w.nseg, 64, int(kept.sum()) + w.nseg, DEV)
+    args = (ctx, kv.Cache.from_dict(c, DEV), torch.from_numpy(keep).to(DEV), torch.from_numpy(kept).to(DEV), dst, 1)
+    kv.kvtrim_compact(*args)
+    assert kv.kvtrim_poll_error(ctx) == 0
+    assert compare_caches(device_cache_to_host(w, dst), oracle.compact(hc, keep, dst.cap, 1))
