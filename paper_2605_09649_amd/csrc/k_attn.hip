@@ -22,9 +22,10 @@ namespace kvtrim {
 constexpr int ATT_THREADS = 256;
 constexpr int ATT_ROUND = 64;               // rows of a round: one tile for each of a block's four wavefronts
 // Segments up to which every block adds up the segments' lengths itself (in LDS) instead of reading a table that a
-// kernel before it has written.  That kernel takes 5.5 us at 256 segments; 4096 segments are 16 lengths and starts per
-// thread, 48 KB out of L2 per block, and 32 KB of LDS, with which three blocks still fit a compute unit.
-constexpr int ATT_SCAN_SEGS = 4096;
+// kernel before it has written.  That kernel and its launch cost about as much as the sums in every block at 2000 to 3000
+// segments (40 entries each, 4 heads: 1024 segments 26.3 us with it, 23.9 without, 2048 37.6 / 36, 3072 51.8 / 50.8, 4096
+// 64.6 / 69.1; 8 heads alike); 3072 lengths and starts are 24 KB of LDS, with which three blocks fit a compute unit.
+constexpr int ATT_SCAN_SEGS = 3072;
 
 typedef __attribute__((ext_vector_type(4))) float float4v;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -167,7 +168,8 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, AttPag
     if (!PLANNED) {
         if (tid == 0) s_bad = 0;
         bad = false;
-        const int each = (n_in + ATT_THREADS - 1) / ATT_THREADS;  // consecutive ordinals per thread
+        int each = (n_in + ATT_THREADS - 1) / ATT_THREADS;        // consecutive ordinals per thread
+        if (each % 8 == 0) ++each;                                // (at 8 words' distance the threads' words share a few banks: 2048 segments 38.8 us, now 36)
         int64_t mine = 0;
         for (int i = 0; i < each; ++i) {
             const int o = tid * each + i;
