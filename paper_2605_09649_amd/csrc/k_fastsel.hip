@@ -24,7 +24,7 @@ namespace kvtrim {
 constexpr int FAST_ITEMS = FL_CAP_MAX / FAST_THREADS;             // list entries a thread of the resolving block holds
 constexpr int FAST_SUB = 16;                                      // sub-lists / group words per sequence
 constexpr int FAST_STAGE = 1024;                                  // candidates a block of one segment stages in LDS
-constexpr int FAST_PIECE = 64;                                    // ... and puts on one sub-list before it goes on to the next
+constexpr int FAST_PIECE_SHIFT = 6;                               // ... 64 of which go on one sub-list before the next is taken
 constexpr int FAST_BATCH = 8;                                     // entries a thread loads before it uses any of them
 constexpr int FAST_BIN_DIRECT = 256;                              // a bin of at most this many entries is ranked directly
 static_assert(FAST_ITEMS * FAST_THREADS == FL_CAP_MAX, "list capacity must be a multiple of the block size");
@@ -616,18 +616,23 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         }
         mn = block_min_u32(mn, sm.red_u);                         // (its barriers also complete s_ncand and the staged entries)
         const int ncand = s_ncand;
-        // One reservation per FAST_PIECE candidates, in neighbouring sub-lists, so that a segment with many of them does not
-        // fill its own; a block with more candidates than it can stage makes its sub-list overflow.
-        const int piece = max(FAST_PIECE, (ncand + nsub - 1) / nsub), npiece = ncand > STAGE ? 1 : (ncand + piece - 1) / piece;
+        // One reservation per block; MULTI: one per 64 candidates (more where the sub-lists are few), in neighbouring sub-lists, so
+        // that a block with the segments of a hot layer does not fill its own.  A block with more candidates than it can
+        // stage makes its sub-list overflow.
+        int shift = MULTI ? FAST_PIECE_SHIFT : 31;
+        while (MULTI && nsub << shift < ncand) ++shift;
+        const int npiece = ncand > STAGE || !MULTI ? min(ncand, 1) : (ncand + (1 << shift) - 1) >> shift;
+        auto list_of = [&](int p) { return sub + p < nsub ? sub + p : sub + p - nsub; };
         if (tid == 0 && mn != 0xFFFFFFFFu) atomicMin(&grp_min[sub], mn);
-        if (tid < npiece) s_base[tid] = atomicAdd(&sub_count[(sub + tid) % nsub], ncand > STAGE ? cap + 1u : (uint32_t)min(piece, ncand - tid * piece));
+        if (tid < npiece)
+            s_base[tid] = atomicAdd(&sub_count[list_of(tid)], ncand > STAGE ? cap + 1u : (uint32_t)(MULTI ? min(1 << shift, ncand - (tid << shift)) : ncand));
         __syncthreads();
         if (ncand > 0 && ncand <= STAGE) {
             for (int i = tid; i < ncand; i += FAST_THREADS) {
-                const int p = i / piece;
-                const uint32_t slot = s_base[p] + (uint32_t)(i - p * piece);
+                const int p = MULTI ? i >> shift : 0;
+                const uint32_t slot = s_base[p] + (uint32_t)(MULTI ? i - (p << shift) : i);
                 if (slot < subcap) {
-                    const size_t at = (size_t)((sub + p) % nsub) * subcap + slot;
+                    const size_t at = (size_t)list_of(p) * subcap + slot;
                     st_dev(&lk[at], c_key[i]);
                     st_dev(&ls[at], c_seg[i]);
                     st_dev(&lp[at], c_pos[i]);

@@ -245,18 +245,20 @@ def test_a_hot_layer_of_a_batch_stays_on_the_candidate_list():
     assert select_repeatedly(w, lens, log_beta, 300, 3) == (3 * 4, 0)
 
 
-def test_one_hot_segment_stays_on_the_candidate_list():
-    # 64 segments with a block each; all candidates (some 600) come from one of them: more than its sub-list's 256 entries
-    w = wl(1, 8, 8, 1, 64)
+def test_one_hot_segment_of_a_batch_stays_on_the_candidate_list():
+    # 320 segments, two to a block; all candidates of a sequence (some 600) come from one segment: more than a sub-list's 256
+    # entries
+    w = wl(5, 8, 8, 1, 64)
     lens = np.full(w.nseg, 40)
-    lens[37] = 3000
+    lens[37::64] = 3000
     rng = np.random.default_rng(10)
 
     def log_beta(cap, start):
         lb = -0.0001 * rng.random(cap)
-        lb[start[37]:start[38]] = -1.0 - rng.random(start[38] - start[37])
+        for g in range(37, w.nseg, 64):
+            lb[start[g]:start[g + 1]] = -1.0 - rng.random(start[g + 1] - start[g])
         return lb
-    assert select_repeatedly(w, lens, log_beta, 150, 3) == (3, 0)
+    assert select_repeatedly(w, lens, log_beta, 150, 3) == (3 * 5, 0)
 
 
 @pytest.mark.parametrize("S,H,evictions", [(260, 16, 490),        # about 1490 candidates per sequence: more than a block stages
