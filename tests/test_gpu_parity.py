@@ -858,3 +858,44 @@ def test_compaction_of_many_segments_at_the_edges_of_their_tiles(keep_part):
     kv.kvtrim_compact(*args)
     assert kv.kvtrim_poll_error(ctx) == 0
     assert compare_caches(device_cache_to_host(w, dst), oracle.compact(hc, keep, dst.cap, 1))
+
+
+@pytest.mark.parametrize("shift", [0, 1])                    # the mask kernel's long form / a score array it cannot load 16 bytes from
+def test_long_mask_over_uneven_segments(shift):
+    # 8400 segments, so that a block walks runs of chunks: across empty, tiny and longer ones (2049: two chunks) and from
+    # sequence to sequence - one with an ordinary threshold, one that keeps nothing, one with ties to rank inside the runs,
+    # one that keeps everything; the last group of four entries ends behind the arrays
+    w = wl(4, 30, 70, 1, 64)
+    rng = np.random.default_rng(53)
+    seg_len = rng.choice([0, 1, 3, 4, 5, 7, 2049], w.nseg, p=[.2, .2, .2, .1, .1, .19, .01])
+    seg_len[-1] = 7
+    seg_len[0] += (3 - int((seg_len + 1).sum())) % 4
+    start = np.concatenate([[0], np.cumsum(seg_len + 1)[:-1]])
+    cap = int((seg_len + 1).sum())
+    assert cap % 4 == 3
+    log_beta = -rng.random(cap).astype(np.float32)
+    log_beta[start[2 * 2100]:start[3 * 2100]] = -0.25 * rng.integers(1, 3, start[3 * 2100] - start[2 * 2100])
+    c = {"k": torch.zeros(cap, 64, dtype=torch.bfloat16), "v": torch.zeros(cap, 64, dtype=torch.bfloat16),
+         "log_beta": torch.from_numpy(log_beta), "pos": torch.from_numpy((np.arange(cap) - np.repeat(start, seg_len + 1)).astype(np.int32)),
+         "seg_start": torch.from_numpy(start), "seg_len": torch.from_numpy(seg_len.astype(np.int32)), "cap": cap}
+    hc = host_cache(w, c)
+    per_seq = seg_len.reshape(4, -1).sum(1)
+    budget = np.array([per_seq[0] // 3, 0, per_seq[2] // 2, per_seq[3]], dtype=np.int64)
+    score = oracle.score(hc, np.full(4, 3000, dtype=np.int32))
+    keep, kept, thr = oracle.select(hc, score, budget)
+    live = live_mask(hc)
+    d_score = torch.zeros(cap + shift, dtype=torch.float32, device=DEV)
+    d_score[shift:].copy_(torch.from_numpy(score))
+    ctx = kv.Context(w.n_seq, w.n_layers, w.n_kv_heads, w.n_q_heads, 64, cap)
+    d_keep = torch.full((cap,), 7, dtype=torch.uint8, device=DEV)
+    d_kept = torch.zeros(w.nseg, dtype=torch.int32, device=DEV)
+    d_thr = torch.zeros(4, dtype=torch.int32, device=DEV)
+    kv.kvtrim_select_global(ctx, kv.Cache.from_dict(c, DEV), d_score[shift:], torch.from_numpy(budget).to(DEV), d_keep, d_kept, d_thr)
+    assert kv.kvtrim_poll_error(ctx) == 0
+    k = d_keep.cpu().numpy()
+    assert np.array_equal(k[live], keep[live]) and np.all(k[~live] == 7)
+    assert np.array_equal(d_kept.cpu().numpy(), kept)
+    assert np.array_equal(d_thr.cpu().numpy().view(np.uint32), thr)
+    tied = score[live & (np.arange(cap) >= start[2 * 2100]) & (np.arange(cap) < start[3 * 2100])]
+    last = np.sort(tied)[::-1][budget[2] - 1]
+    assert (tied == last).sum() > 1 and (tied >= last).sum() > budget[2]   # (fewer survive than tie at the threshold)
