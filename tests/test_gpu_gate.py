@@ -51,23 +51,23 @@ def rel_err(got, ref):
 
 
 @pytest.mark.parametrize("L,H,d_model,d_g,d_p,n_tok", [
-    (2, 2, 256, 64, 1, 1),            # smallest legal sizes, scalar projection
-    (3, 2, 512, 128, 7, 5),           # d_p not a multiple of the 16-row tile
-    (2, 4, 1024, 512, 128, 16),       # the paper's hidden width, one full token tile
-    (2, 2, 256, 576, 40, 17),         # hidden width beyond one staged chunk, token tail of one
-    (1, 2, 512, 64, 33, 20),          # two token tiles per block
-    (1, 2, 512, 64, 33, 64),          # four token tiles in one block
-    (1, 2, 512, 64, 33, 150),         # four token tiles per block, three blocks along the tokens, ragged tail
-    (2, 2, 256, 192, 16, 300),        # LDS-tiled first layer (hidden width not a multiple of 128): 1.5 row tiles, 2.3 token tiles
-    (1, 2, 256, 576, 8, 256),         # ... hidden width above 512
-    (1, 1, 1024, 512, 128, 257),      # folded prefill path: the paper's hidden width, one token beyond two 128-token tiles
-    (2, 3, 512, 128, 20, 300),        # ... one 16-row tile per wavefront, three heads
+    (2, 2, 256, 64, 1, 1),            # smallest legal sizes, scalar projection: per-token kernels
+    (3, 2, 512, 128, 7, 5),           # ... d_p not a multiple of the 16-row tile
+    (2, 4, 1024, 512, 128, 16),       # ... the paper's hidden width, one full token tile
+    (2, 2, 256, 576, 40, 17),         # folded, sliced kernel: hidden width above 512, token tail of one
+    (1, 2, 512, 64, 33, 20),          # ... two token tiles per block
+    (1, 2, 512, 64, 33, 64),          # ... four token tiles in one block
+    (1, 2, 512, 64, 33, 150),         # ... three blocks along the tokens, ragged tail
+    (2, 2, 256, 192, 16, 300),        # ... hidden width not a multiple of 128
+    (1, 2, 256, 576, 8, 256),         # ... full token tiles, hidden width above 512
+    (1, 1, 1024, 512, 128, 257),      # ... the paper's hidden width, one token beyond four 64-token blocks
+    (2, 3, 512, 128, 20, 300),        # folded prefill kernel: one 16-row tile per wavefront, three heads, W1 from its copy in the scratch
     (9, 2, 256, 256, 16, 260),        # ... nine layers: the second round of the layer-to-XCD dealing is partly empty
-    (1, 8, 256, 384, 5, 513),         # ... eight heads, three tiles per wavefront, token tail of one
-    (3, 2, 256, 512, 1, 256),         # ... exactly two full token tiles, scalar projection
-    (2, 2, 512, 128, 9, 129),         # ... just above the switch-over: 32-token blocks, a tail of one
-    (2, 2, 256, 512, 16, 300),        # ... the paper's hidden width from the tiled copy of W1 (short rows: the copy fits the scratch)
-    (32, 2, 1280, 128, 8, 520),       # ... 64-token blocks (32 layers x 9 tiles), W1 straight from its rows
+    (1, 8, 256, 384, 5, 513),         # sliced kernel: eight heads, token tail of one
+    (3, 2, 256, 512, 1, 256),         # ... scalar projection
+    (2, 2, 512, 128, 9, 129),         # folded prefill kernel: 32-token blocks, a tail of one, W1 straight from its rows
+    (2, 2, 256, 512, 16, 300),        # sliced kernel: the paper's hidden width, short rows
+    (32, 2, 1280, 128, 8, 520),       # folded prefill kernel: 64-token blocks (32 layers x 9 tiles), W1 straight from its rows
 ])
 def test_gate_forward_matches_the_oracle(L, H, d_model, d_g, d_p, n_tok):
     z_ref, lb_ref, _, lb, _ = run_both(L, H, d_model, d_g, d_p, n_tok, salt=d_p)
@@ -94,7 +94,7 @@ def test_horizon_tail_constant(horizon):
 
 
 def test_prefill_sized_call_with_a_layer_range_and_a_horizon():
-    # the folded path (128 tokens and more): layers outside the range stay untouched, the tail constant follows log beta
+    # the folded prefill kernel: layers outside the range stay untouched, the tail constant follows log beta
     _, lb_ref, lt_ref, lb, lt = run_both(5, 2, 256, 128, 12, 300, b_g=1.0, layer_begin=1, layer_end=4, horizon=2)
     assert np.isnan(lb[:, 0, :]).all() and np.isnan(lb[:, 4, :]).all()
     assert np.isnan(lt[:, 0, :]).all() and np.isnan(lt[:, 4, :]).all()
@@ -103,7 +103,7 @@ def test_prefill_sized_call_with_a_layer_range_and_a_horizon():
 
 
 def test_both_paths_agree_across_the_token_threshold():
-    # 127 tokens run the per-token kernels, 128 the folded ones: the shared 127 tokens get the same gates to rounding
+    # 16 tokens run the per-token kernels, more the folded ones: the shared tokens get the same gates to rounding
     L, H, d_model, d_g, d_p = 2, 2, 512, 256, 24
     w = ki.gate_weights(L, H, d_model, d_g, d_p, b_g=3.5, seed=77)
     x = ki.gate_inputs(L, 128, d_model, salt=3)
@@ -112,7 +112,7 @@ def test_both_paths_agree_across_the_token_threshold():
     ctx = kv.Context(1, L, H, H, 64, 1024)
     gate = kv.Gate.from_dict(w, DEV)
     got = {}
-    for n_tok in (127, 128):
+    for n_tok in (16, 17, 127, 128):
         xd = x[:, :n_tok].contiguous().to(DEV)
         scratch = torch.empty(kv.kvtrim_gate_scratch_bytes(gate, n_tok, L) // 4, dtype=torch.float32, device=DEV)
         lb = torch.full((n_tok, L, H), float("nan"), dtype=torch.float32, device=DEV)
@@ -120,7 +120,8 @@ def test_both_paths_agree_across_the_token_threshold():
         assert kv.kvtrim_poll_error(ctx) == 0
         got[n_tok] = lb.cpu().numpy()
         assert rel_err(got[n_tok], lb_ref[:n_tok]) <= RTOL
-    assert np.max(np.abs(got[127] - got[128][:127]) / np.abs(lb_ref[:127])) <= RTOL
+    for n_tok in (16, 17, 127):
+        assert np.max(np.abs(got[n_tok] - got[128][:n_tok]) / np.abs(lb_ref[:n_tok])) <= RTOL
 
 
 @pytest.mark.parametrize("d_g,n_tok", [(64, 4), (128, 130)])     # per-token kernels; folded kernel
@@ -149,12 +150,12 @@ def test_full_size_gate_prefill_chunk_on_sampled_tokens():
 
 
 @pytest.mark.parametrize("L,H,d_model,d_g,d_p,n_toks", [
-    (3, 2, 256, 64, 7, (1, 5, 20, 150)),          # per-token first layer + dot-product readout; hidden width not for the folded kernel
-    (2, 3, 512, 128, 20, (16, 23, 24, 127, 300)),  # across the switch-over at 24 tokens: 32-token blocks read W1 from the prepared tiles
+    (3, 2, 256, 64, 7, (1, 5, 20, 150)),          # sliced kernel; hidden width not for the prefill kernel
+    (2, 3, 512, 128, 20, (16, 23, 24, 127, 300)),  # sliced kernel, then the prefill kernel's 32-token blocks from the prepared tiles
     (32, 2, 1280, 128, 8, (520,)),                 # 64-token blocks from the prepared tiles
-    (2, 8, 256, 512, 16, (1, 7, 16, 64, 513, 1100)),   # the paper's hidden width, eight heads: one kernel with the readout inside up to 16 tokens, 128-token blocks
-    (2, 17, 256, 64, 4, (3,)),                     # more than 16 heads: the readout's parts do not fit the scratch buffer, two kernels
-    (2, 2, 256, 576, 8, (256,)),                   # hidden width above 512: LDS-tiled first layer + dot-product readout
+    (2, 8, 256, 512, 16, (1, 7, 16, 64, 513, 1100)),   # the paper's hidden width, eight heads: slices, then prefill blocks
+    (2, 17, 256, 64, 4, (3,)),                     # more than 16 heads: slices of 32 units, whose parts fit the scratch buffer
+    (2, 2, 256, 576, 8, (256,)),                   # hidden width above 512
 ])
 def test_prepared_gate_matches_the_oracle_and_is_reusable(L, H, d_model, d_g, d_p, n_toks):
     w = ki.gate_weights(L, H, d_model, d_g, d_p, b_g=3.5, seed=99 + d_p)
@@ -227,6 +228,15 @@ def test_host_side_argument_checks_of_the_gate():
     (2, 9, 768, 192, 15, True, "k_gate_slice"),      # twelve steps in eight shares, more heads than wavefronts
     (2, 32, 256, 128, 16, True, "k_gate_slice"),     # the most heads, a full token tile
     (2, 33, 256, 128, 16, True, "k_gate_hidden"),    # ... one more: the two-kernel path
+    (1, 33, 512, 64, 20, True, "k_gate_hidden"),     # ... with two token tiles per block
+    (1, 33, 512, 64, 64, True, "k_gate_hidden"),     # ... with four
+    (1, 33, 512, 64, 150, True, "k_gate_hidden"),    # ... three blocks along the tokens
+    (2, 33, 256, 192, 300, True, "k_gate_hidden"),   # ... its LDS-tiled first layer: 1.5 row tiles, 2.3 token tiles
+    (1, 33, 512, 64, 20, False, "k_gate_hidden"),    # the same without prepared weights, second layer on the matrix cores
+    (1, 33, 512, 64, 64, False, "k_gate_hidden"),
+    (1, 33, 512, 64, 150, False, "k_gate_hidden"),
+    (2, 33, 256, 192, 300, False, "k_gate_hidden"),
+    (1, 33, 256, 576, 256, False, "k_gate_hidden"),  # hidden width beyond one staged chunk of the readout
     (6, 2, 256, 512, 33, True, "k_gate_slice"),      # four token tiles, slices of 32 units
     (9, 2, 512, 512, 31, True, "k_gate_slice"),      # two token tiles, slices of 32 units
     (33, 2, 256, 512, 17, True, "k_gate_slice"),     # two token tiles, slices of 64 units, more blocks than compute units
