@@ -883,18 +883,16 @@ struct GatePlan {
 static GatePlan gate_plan(const kvtrim_ctx* ctx, const GateView& g, int n_tok, int nl, bool prepared) {
     const int n_heads = ctx->shape.n_kv_heads;
     auto tiles = [&](int tt) { return (int64_t)((n_tok + 16 * tt - 1) / (16 * tt)); };
-    auto rounds = [](int64_t blocks) { return (double)((blocks + 255) / 256); };   // of one block per compute unit
-    const double r = g.d_model / 4096.0;
-    // Both kernels' times are a fixed part (launch, first loads, readout) and one that grows with d_model per round of
-    // blocks; measured (us, fixed + per round at d_model 4096): k_gate_slice with 64 tokens 8 + 24 - or 8 + 12 with slices
-    // of 32 units - with 128 tokens 15 + 27, whatever the number of hidden units; k_gate_prefill with 32 / 64 / 128
-    // tokens and 512 units 7 + 71 / 80 / 120, or 7 + 40 / 50 / 110 while the weights of the call stay in the chip's
-    // last-level cache (256 MB).
-    const int64_t slices = g.d_g / 64;
-    // Row tiles of a k_gate_slice block with tt token tiles, 0 if such blocks cannot run: there is a counter for GSL_TILES_MAX
-    // token tiles, and the parts of the sums must fit the scratch buffer, behind the folded vectors when those are made in
-    // the call.  Slices of 64 units, halved while that still is one round of blocks (1 layer, 1 token: 15.6 / 11.5 / 9.4 us
-    // with 64 / 32 / 16 units; 20 layers: 64 units 19.4 us, 32 units - two rounds - 22.6) and the parts fit.
+    // The choice is by time, estimated (us) from a fixed part and one per round of blocks - one block per compute unit - of
+    // either kernel: least-squares fits to 5200 measured calls (1 to 40 layers, d_model 1024 to 4096, 128 to 512 units, 33
+    // to 4096 tokens, weights not in any cache, as between two steps of a model), mostly within 5 to 10 %.
+    // r, k: widths, in units of the paper's gate on a 4096-wide model.
+    const double r = g.d_model / 4096.0, k = g.d_g / 512.0;
+
+    // k_gate_slice.  Row tiles of a block with tt token tiles, 0 if such blocks cannot run: there is a counter for
+    // GSL_TILES_MAX token tiles, and the parts of the sums must fit the scratch buffer, behind the folded vectors when those
+    // are made in the call.  Slices of 64 units, halved while that still is one round of blocks (1 layer, 1 token: 15.6 /
+    // 11.5 / 9.4 us with 64 / 32 / 16 units; 20 layers: 64 units 19.4 us, 32 units - two rounds - 22.6) and the parts fit.
     auto row_tiles = [&](int tt) {
         const size_t room = (size_t)n_tok * nl * g.d_g, taken = prepared ? 0 : folded_floats(g, nl, n_heads);
         auto fits = [&](int mt) { return (size_t)nl * (g.d_g / (16 * mt)) * n_heads * n_tok + taken <= room; };
@@ -903,30 +901,56 @@ static GatePlan gate_plan(const kvtrim_ctx* ctx, const GateView& g, int n_tok, i
         while (tt < 8 && mt > (tt < 4 ? 1 : 2) && nl * (g.d_g / (8 * mt)) * tiles(tt) <= 256 && fits(mt / 2)) mt >>= 1;
         return mt;
     };
-    const double s8 = 15 + 27 * r * rounds(nl * slices * tiles(8)), s4 = row_tiles(4) == 2 ? 8 + 12 * r : 8 + 24 * r * rounds(nl * slices * tiles(4));
+    auto slice_time = [&](int tt) {
+        const int mt = row_tiles(tt);
+        if (mt == 0) return 1e30;
+        const double rounds = (double)((nl * (g.d_g / (16 * mt)) * tiles(tt) + 255) / 256);
+        if (tt == 8) return prepared ? 9 + rounds * (2.5 + 27 * r) : 11 + rounds * (2.5 + 34.5 * r);   // (without prepared weights: W1 from its rows, and the fold)
+        if (mt == 2) return prepared ? 8.5 + 9.5 * r : 11.7 + 13.3 * r;
+        return prepared ? 6.5 + rounds * (0.5 + 19 * r) : 9 + rounds * (1 + 28 * r);
+    };
     int tt = n_tok <= 16 ? 1 : (n_tok <= 32 ? 2 : 4);
-    if (n_tok > 64 && (!row_tiles(4) || (row_tiles(8) && s8 < s4))) tt = 8;
+    if (n_tok > 64 && slice_time(8) < slice_time(4)) tt = 8;
     const int mt = row_tiles(tt);
     const bool slice_ok = mt > 0 && (prepared || tt > 1);
+
+    // k_gate_prefill.  A layer's blocks run on one of the eight XCDs (32 compute units), so what counts is the rounds of the
+    // XCD with most layers.  Its W1 comes from the prepared copy, from the one made in the scratch buffer - whose making is
+    // the larger `weights` term - or from its rows, which takes a round as long for 32 tokens as for 128.
     const bool prefill_shape = g.d_g % 128 == 0 && g.d_g <= 512 && n_heads <= GP_HEADS_MAX;
     const bool prefill_ok = prefill_shape && (prepared || n_tok >= GP_MIN_TOK);
+    struct Cost { double fixed, fixed_rk, round, round_r, round_rk, weights; };
+    static const Cost costs[3][3] = {                                // 32, 64, 128 tokens per block
+        {{4.5, 2, 0.5, 6, 40, 35}, {5.5, -16, 0.5, 9, 56, 35}, {-2, -30, 11, 17, 85, 20}},      // prepared
+        {{13, -7, -1, 7, 38, 74}, {13, -20, 0, 9, 59, 66}, {7, -19, 8, 17, 78, 67}},            // copied in the call
+        {{8.5, 0, 1.5, -1, 118, 10}, {8, -6, 2.5, 1, 124, 15}, {-8, 9, 21, 5, 114, 18}}};       // rows
+    const bool tiled = prepared || tiled_fits(g, n_tok, nl, n_heads);
+    auto prefill_time = [&](int t) {
+        const double x = ((nl + 7) / 8) * tiles(t) / 32.0;
+        double rounds = (double)(((nl + 7) / 8 * tiles(t) + 31) / 32);
+        // (128 units: a compute unit holds three blocks of 32 tokens - 75 registers, 26 KB of LDS - which run side by side,
+        // narrow models' nearly for nothing)
+        if (g.d_g == 128 && tiled && t == 2 && x > 1 && x <= 3) {
+            const double beside = g.d_model <= 2048 ? 0.65 * x : 1.1 * x, least = g.d_model <= 2048 ? 1.1 : 1.3;
+            rounds = beside > least ? beside : least;
+        }
+        const Cost& c = costs[prepared ? 0 : (tiled ? 1 : 2)][t == 2 ? 0 : (t == 4 ? 1 : 2)];
+        return c.fixed + c.fixed_rk * r * k + rounds * (c.round + c.round_r * r + c.round_rk * r * k) + c.weights * r * k * nl / 32;
+    };
+    int ptt = 8;                                                     // (more than 256 blocks of 128 tokens: their rate per token counts, and that is the best)
+    if (nl * tiles(8) <= 256 || g.d_g == 128)
+        for (int t = 4; t >= 2; t >>= 1)
+            if (prefill_time(t) <= prefill_time(ptt)) ptt = t;
+
     // A pre-activation is summed in four chains or more wherever the kernels that would take the call otherwise
     // (k_gate_hidden: four) do so; k_gate_prefill and the first layer of 256 tokens and more sum in one.  Slices of 64
     // units have two shares of the contraction, so two chains in each: free with up to two token tiles, 2 to 25 % with more
     // (32 layers, d_model 4096, 512 units, 32 heads: 64 tokens 42.7 -> 43.9 us, 130 tokens 104 -> 131).  Relative error of
     // log beta there 3.9e-7 with two chains in all, 3.0e-7 with four, 5.5e-7 with one.
     const int ch = mt == 4 && (tt <= 2 || (prepared && n_tok < 256 && !prefill_shape)) ? 2 : 1;
-    const bool cached = (size_t)nl * g.d_g * g.d_model * 2 <= (size_t)100 << 20;
-    const double share = r * g.d_g / 512;
-    // (128 units with W1 in operand order: a compute unit holds three blocks of 32 tokens - 75 registers, 26 KB of LDS - and
-    // up to half a round more of them costs next to nothing: 4 layers, d_model 1024, 264 / 376 blocks 17.8 / 18.9 us, with
-    // 64 tokens a block 19.6 / 20.8; 512 blocks 24.8 against 21.6)
-    const bool narrow = g.d_g == 128 && (prepared || tiled_fits(g, n_tok, nl, n_heads));
-    const double p2 = (narrow && nl * tiles(2) <= 384 ? 1 : rounds(nl * tiles(2))) * (cached ? 40 : 71), p4 = rounds(nl * tiles(4)) * (cached ? 50 : 80),
-                 p8 = rounds(nl * tiles(8)) * (cached ? 110 : 120);
-    // (more than a round of 128-token blocks: their rate per token counts, and that is the best)
-    const int ptt = nl * tiles(8) > 256 ? 8 : (p2 < p4 && p2 < p8 ? 2 : (p4 < p8 ? 4 : 8));
-    if (slice_ok && (!prefill_ok || tt < 4 || (tt == 8 ? s8 : s4) <= 7 + share * (ptt == 2 ? p2 : (ptt == 4 ? p4 : p8)))) return {GATE_SLICE, tt, mt, ch};
+    // (below d_model 512 both are launch and latency: the slices, whose sums are in shorter chains)
+    const double near = g.d_model < 512 ? 1 : 0;
+    if (slice_ok && (!prefill_ok || tt < 4 || slice_time(tt) <= prefill_time(ptt) + near)) return {GATE_SLICE, tt, mt, ch};
     if (prefill_ok) return {GATE_PREFILL, ptt, 0, 0};
     return {GATE_PER_TOKEN, 0, 0, 0};
 }
