@@ -97,7 +97,8 @@ typedef struct {
  * workspace on the current device; kvtrim_workspace_bytes says how large it is.
  * One tuning knob is read from the environment at creation: KVTRIM_ATT_BLOCKS = most blocks
  * among which the stand-alone attention kernel shares its rows (1 .. 65536, default 768).
- * It changes the order of floating-point sums in attention, nothing else. */
+ * It changes the order of floating-point sums in attention, nothing else.  (KVTRIM_ATT_CHUNK, the rows
+ * per chunk of an earlier attention kernel, has nothing left to set and is not read.) */
 kvtrim_status kvtrim_create(kvtrim_ctx **out, const kvtrim_config *cfg);
 kvtrim_status kvtrim_destroy(kvtrim_ctx *ctx);
 size_t kvtrim_workspace_bytes(const kvtrim_config *cfg);
@@ -301,9 +302,9 @@ kvtrim_status kvtrim_decode_step(kvtrim_ctx *ctx, kvtrim_cache *src, const void 
  *     kvtrim_append(c, new tokens) -> kvtrim_score_select(c, now, budget, evict_hint)
  *     -> kvtrim_compact_attn_inplace(c, spare, q)
  * leave there; arguments and the rules for `spare` as in those calls (every segment needs free slots for its new
- * tokens behind it: kvtrim_min_room).  Under the conditions of kvtrim_decode_step it is FOUR kernels: the scoring
- * kernel leaves every segment's start where it is, the row mover touches only the rows behind an eviction, a small
- * kernel puts the rows it had to park in `spare` in place, and one merges the partial attention results. */
+ * tokens behind it: kvtrim_min_room).  Under the conditions of kvtrim_decode_step it is THREE kernels: the scoring
+ * kernel leaves every segment's start where it is, the row mover touches only the rows behind an eviction, and one
+ * merges the partial attention results and puts the rows that the mover had to park in `spare` in place. */
 kvtrim_status kvtrim_decode_step_inplace(kvtrim_ctx *ctx, kvtrim_cache *c, const void *k_new, const void *v_new,
                                          const float *log_beta_new, const float *log_tail_new, const int32_t *pos_new,
                                          int32_t n_new, const int32_t *now, const int64_t *budget, float *score_out,
@@ -473,9 +474,10 @@ typedef struct {
 } kvtrim_gate;
 
 /* Bytes of scratch kvtrim_gate_forward needs for n_tok tokens and n_layers layers of a range:
- * n_tok * n_layers * d_g floats (short calls keep the hidden activations u there in fp32, longer ones the folded
- * readout vectors and the blocks' parts of the readout sums or, where it fits - from about d_model / 2 tokens on -
- * a copy of W1 in matrix-core operand order); 0 for invalid arguments.  Host-only, no GPU call. */
+ * n_tok * n_layers * d_g floats.  What is kept there depends on how the call is run: the hidden activations u in
+ * fp32 (per-token kernels); without prepared weights the folded readout vectors; the blocks' parts of the readout
+ * sums; and, where it fits - from about d_model / 2 tokens on - a copy of W1 in matrix-core operand order.  A way of
+ * running the call whose data would not fit is not taken.  0 for invalid arguments.  Host-only, no GPU call. */
 size_t kvtrim_gate_scratch_bytes(const kvtrim_gate *g, int32_t n_tok, int32_t n_layers);
 
 /* x: bf16 [layer_end - layer_begin][n_tok][d_model], 16-byte aligned, the representation of each
@@ -489,7 +491,9 @@ size_t kvtrim_gate_scratch_bytes(const kvtrim_gate *g, int32_t n_tok, int32_t n_
  * bf16 products accumulated in fp32 on the matrix cores.  Calls of up to 16 tokens carry u to 16 mantissa
  * bits into the second layer; longer calls use that the second layer and the readout are both linear
  * (z = (W2^T w_g) . u + w_g . c2 + b_g), fold them into one fp32 vector per (layer, head) first and keep u
- * in fp32 (unless there are many KV heads and few tokens: then as the short ones).  Results agree with an fp64
+ * in fp32 - unless that way does not fit (more than 32 KV heads; many heads and few tokens, whose folded vectors fill
+ * the scratch buffer; thousands of tokens of a gate whose d_g is not 128, 256, 384 or 512, or of more than 8 heads):
+ * then as the short ones.  Results agree with an fp64
  * evaluation to about 1e-5 relative in log beta either way.  Some calls keep arrival counters in the context's
  * workspace: as for every call on a context, two gate calls on one context must not run at the same time. */
 kvtrim_status kvtrim_gate_forward(kvtrim_ctx *ctx, const kvtrim_gate *g, const void *x, int32_t n_tok,
@@ -505,8 +509,11 @@ kvtrim_status kvtrim_gate_forward(kvtrim_ctx *ctx, const kvtrim_gate *g, const v
  * the stream.  The buffer is valid for as long as the weights it was made from are unchanged.
  * kvtrim_gate_forward_prepared: same arguments, outputs and arithmetic contract as kvtrim_gate_forward (g must
  * be the gate the buffer was prepared from; scratch as for kvtrim_gate_forward); calls of every length then read
- * the readout as one dot product per (token, layer, head) and W1 from the operand-order copy.  Calls are one kernel
- * (more than 32 KV heads: two), whose blocks split the hidden units or the tokens, by the number of tokens. */
+ * the readout as one dot product per (token, layer, head).  A call is one kernel, which reads W1 from the
+ * operand-order copy and whose blocks split the hidden units or the tokens, by what takes less time.  It is two
+ * kernels, the first layer and the readout, with more than 32 KV heads, and with more tokens than the first of those
+ * forms takes (1024 in blocks of 64 or 2048 in blocks of 128) where the second does not apply (d_g not 128, 256, 384
+ * or 512, or more than 8 heads); above 64 tokens these read W1 itself. */
 size_t kvtrim_gate_prepared_bytes(const kvtrim_gate *g, int32_t n_layers, int32_t n_kv_heads);
 kvtrim_status kvtrim_gate_prepare(kvtrim_ctx *ctx, const kvtrim_gate *g, void *prepared, void *hip_stream);
 kvtrim_status kvtrim_gate_forward_prepared(kvtrim_ctx *ctx, const kvtrim_gate *g, const void *prepared, const void *x,

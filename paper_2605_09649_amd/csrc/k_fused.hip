@@ -714,8 +714,8 @@ kvtrim_status launch_decode_step(kvtrim_ctx* ctx, const CacheViewMut& srcm, cons
     return launch_combine(ctx, ws.cmp_chunk_prefix, layer_begin, layer_end, out, lse, max_chunks, st);
 }
 
-// The decode step in one call with stages 3 + 4 inside the cache: four kernels (score + resolve, move + attend, the
-// rows parked in `stage` put in place, merge) when this is a decode step the candidate list can carry; otherwise the
+// The decode step in one call with stages 3 + 4 inside the cache: three kernels (score + resolve, move + attend, merge
+// with the rows parked in `stage` put in place) when this is a decode step the candidate list can carry; otherwise the
 // calls it stands for, one after the other.
 kvtrim_status launch_decode_step_inplace(kvtrim_ctx* ctx, const CacheViewMut& c, const StepArgs& sa, const CacheViewMut& stage,
                                          const int32_t* now, const int64_t* budget, float* score, int32_t* kept, uint32_t* thr,
@@ -727,9 +727,9 @@ kvtrim_status launch_decode_step_inplace(kvtrim_ctx* ctx, const CacheViewMut& c,
     src.k = c.k; src.v = c.v; src.log_beta = c.log_beta; src.pos = c.pos;
     src.seg_start = c.seg_start; src.seg_len = c.seg_len; src.cap = c.cap; src.log_tail = c.log_tail;
     const int64_t max_chunks = src.cap / CMP_CHUNK + sh.nseg;    // <= ws.max_att_chunks, checked by the caller
-    const bool four = evict_hint > 0 && 8 * (evict_hint + 1) <= (int64_t)ws.fl_cap && sh.segs_per_seq <= STEP_MAX_SEGS &&
+    const bool three = evict_hint > 0 && 8 * (evict_hint + 1) <= (int64_t)ws.fl_cap && sh.segs_per_seq <= STEP_MAX_SEGS &&
                       sh.n_seq <= STEP_MAX_SEQS && sa.n_new <= STEP_MAX_NEW && max_chunks <= ws.max_cmp_chunks;
-    if (!four) {
+    if (!three) {
         kvtrim_status rc = launch_append(ctx, c, sa.k_new, sa.v_new, sa.lb_new, sa.lt_new, sa.pos_new, sa.n_new, true, nullptr, st);
         if (rc != KVTRIM_OK) return rc;
         rc = launch_score_select(ctx, src, now, budget, score, sa.keep_out, kept, thr, evict_hint, st);

@@ -1139,8 +1139,10 @@ extern "C" {
 
 size_t kvtrim_gate_scratch_bytes(const kvtrim_gate* g, int32_t n_tok, int32_t n_layers) {
     if (!g || n_tok < 1 || n_layers < 1 || g->d_g < 1) return 0;
-    // u for the per-token kernels; the prefill kernels keep (heads <= 8) * (d_g + 1) numbers per layer there and
-    // run only from GP_MIN_TOK tokens on, so they always fit
+    // u for the per-token kernels.  k_gate_slice keeps its parts of the sums there, behind the folded vectors when those are
+    // made in the call: gate_plan takes it only if they fit.  k_gate_prefill without prepared weights keeps the folded
+    // vectors - at most 8 heads of d_g + 1 numbers per layer, and GP_MIN_TOK tokens or more, so they fit - and the copy
+    // of W1 if there is room behind them.
     return (size_t)n_tok * (size_t)n_layers * (size_t)g->d_g * sizeof(float);
 }
 

@@ -260,7 +260,7 @@ kvtrim_status launch_decode_step(kvtrim_ctx*, const CacheViewMut& src, const Ste
                                  const int64_t* budget, float* score, int32_t* kept, uint32_t* thr, const uint16_t* q,
                                  int32_t layer_begin, int32_t layer_end, float scale, float* out, float* lse,
                                  int64_t evict_hint, hipStream_t);
-// The same with stages 3 + 4 inside the cache (four kernels: the row mover is followed by k_cmp_unstage).
+// The same with stages 3 + 4 inside the cache (three kernels: the merge kernel also puts the mover's parked rows in place).
 kvtrim_status launch_decode_step_inplace(kvtrim_ctx*, const CacheViewMut& c, const StepArgs& sa, const CacheViewMut& stage,
                                          const int32_t* now, const int64_t* budget, float* score, int32_t* kept, uint32_t* thr,
                                          const uint16_t* q, int32_t layer_begin, int32_t layer_end, float scale, float* out,
