@@ -620,7 +620,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         // that a block with the segments of a hot layer does not fill its own.  A block with more candidates than it can
         // stage makes its sub-list overflow.
         int shift = MULTI ? FAST_PIECE_SHIFT : 31;
-        while (MULTI && nsub << shift < ncand) ++shift;
+        while (MULTI && nsub << shift < min(ncand, STAGE)) ++shift;
         const int npiece = ncand > STAGE || !MULTI ? min(ncand, 1) : (ncand + (1 << shift) - 1) >> shift;
         auto list_of = [&](int p) { return sub + p < nsub ? sub + p : sub + p - nsub; };
         if (tid == 0 && mn != 0xFFFFFFFFu) atomicMin(&grp_min[sub], mn);
@@ -1192,8 +1192,9 @@ static ScanGrid scan_grid(const Shape& sh, int64_t cap, int resident) {
     auto per_seq = [&](int spb) { return (int64_t)((sh.segs_per_seq + spb - 1) / spb); };
     while (bps < 1 && g.spb < FAST_THREADS / 64 && sh.n_seq * per_seq(g.spb) > resident && 2 * g.spb <= sh.segs_per_seq) g.spb *= 2;
     g.blocks = (unsigned)(sh.n_seq * per_seq(g.spb) * g.bps);
+    // (several to a block: a mean below FAST_ENTRIES_PER_BLOCK, so the limit is below 2^15)
     const int64_t mean2 = 2 * (cap / sh.nseg), batches = 2 * (FAST_THREADS / g.spb) * FAST_BATCH;
-    g.limit = (int)(((mean2 > batches ? mean2 : batches) + KVTRIM_PAGE_SIZE - 1) / KVTRIM_PAGE_SIZE * KVTRIM_PAGE_SIZE);   // (several to a block: a mean below FAST_ENTRIES_PER_BLOCK)
+    g.limit = g.spb == 1 ? 0 : (int)(((mean2 > batches ? mean2 : batches) + KVTRIM_PAGE_SIZE - 1) / KVTRIM_PAGE_SIZE * KVTRIM_PAGE_SIZE);
     return g;
 }
 constexpr int SCAN_RESIDENT = 256, MASK_RESIDENT = 512;
