@@ -13,7 +13,8 @@
 //          what the Q.K^T accumulator of lane (b, c) holds - the other operand, as two bf16 terms.
 // A wavefront keeps one online-softmax stream per query head (the maximum over the tile's 16
 // rows) for as long as the block stays inside one segment; then the four wavefronts are merged
-// through LDS, and the partial results of a segment by k_att_combine.  Logits are kept in base-2
+// through LDS, and the partial results of a segment by k_att_combine (in small calls by the last of the segment's blocks
+// to finish).  Logits are kept in base-2
 // units.
 #include "kvtrim_paged_device.h"
 
@@ -26,6 +27,14 @@ constexpr int ATT_ROUND = 64;               // rows of a round: one tile for eac
 // segments (40 entries each, 4 heads: 1024 segments 26.3 us with it, 23.9 without, 2048 37.6 / 36, 3072 51.8 / 50.8, 4096
 // 64.6 / 69.1; 8 heads alike); 3072 lengths and starts are 24 KB of LDS, with which three blocks fit a compute unit.
 constexpr int ATT_SCAN_SEGS = 3072;
+// How a call of the attention kernel finds its segments and who merges its partial results:
+//   ATT_PLANNED  k_att_plan has written the rows before each segment; k_att_combine merges
+//   ATT_SUMMED   every block adds the lengths up itself; k_att_combine merges
+//   ATT_ONE      every block adds the lengths up itself, and the last block of a segment to finish merges: one launch
+constexpr int ATT_PLANNED = 0, ATT_SUMMED = 1, ATT_ONE = 2;
+constexpr int ATT_ONE_THREADS = 512, ATT_ONE_LOG = 7;             // eight wavefronts, rounds of 128 rows
+constexpr int ATT_ONE_SEGS = 1024;                                // every block looks at all segments' table entries
+constexpr int att_threads(int mode) { return mode == ATT_ONE ? ATT_ONE_THREADS : ATT_THREADS; }
 
 typedef __attribute__((ext_vector_type(4))) float float4v;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
@@ -123,6 +132,127 @@ __global__ __launch_bounds__(1024) void k_att_plan(CacheView c, AttPages pt, Sha
     if (threadIdx.x == 0) ws.att_row_prefix[n_in] = carry;
 }
 
+// op over the four rows of 16 lanes, in every lane: two register swaps, where shuffles through LDS take 100 cycles each.
+template <typename Op>
+__device__ __forceinline__ float rows4(float v, Op op) {
+    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);   // rows (0, 0, 2, 2) and (1, 1, 3, 3)
+    v = op(__uint_as_float(a[0]), __uint_as_float(a[1]));
+    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return op(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// The first query head (row of q, out and lse) of segment seg.
+template <int G>
+__device__ __forceinline__ int64_t q_row_of(int seg, const Shape& sh) {
+    const int seq = seg / sh.segs_per_seq, lh = seg - seq * sh.segs_per_seq;
+    const int layer = lh / sh.n_kv_heads, head = lh - layer * sh.n_kv_heads;
+    return ((int64_t)seq * sh.n_layers + layer) * sh.n_q_heads + (int64_t)head * G;
+}
+
+// Maximum and sum over the wavefront, in every lane: by DPP inside the rows of 16 lanes and then across them, without LDS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_or(float v, float other) {   // `other` where there is no such lane
+    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(other), __float_as_int(v), CTRL, ROWS, 0xF, false));
+}
+__device__ __forceinline__ float wave_max(float v) {
+    v = fmaxf(v, dpp_or<0x111, 0xF>(v, -INFINITY));
+    v = fmaxf(v, dpp_or<0x112, 0xF>(v, -INFINITY));
+    v = fmaxf(v, dpp_or<0x114, 0xF>(v, -INFINITY));
+    v = fmaxf(v, dpp_or<0x118, 0xF>(v, -INFINITY));
+    v = fmaxf(v, dpp_or<0x142, 0xA>(v, -INFINITY));
+    v = fmaxf(v, dpp_or<0x143, 0xC>(v, -INFINITY));
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+__device__ __forceinline__ float wave_total(float v) {
+    v += dpp_or<0x111, 0xF>(v, 0.f);
+    v += dpp_or<0x112, 0xF>(v, 0.f);
+    v += dpp_or<0x114, 0xF>(v, 0.f);
+    v += dpp_or<0x118, 0xF>(v, 0.f);
+    v += dpp_or<0x142, 0xA>(v, 0.f);
+    v += dpp_or<0x143, 0xC>(v, 0.f);
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
+}
+
+// ATT_ONE: the n partial results at `part` become the segment's output.  A thread owns two columns of a head and every
+// RG-th partial result; their loads and those of the (m, l) pairs, a lane per result, go out together, so a tile of results
+// costs one round trip.  The results come past the caches that are not coherent across the chip (eight bytes a load).
+template <int D, int G, int THREADS>
+__device__ __forceinline__ void merge_shared(const float* __restrict__ part, int n, int64_t hq, float* lds, float* __restrict__ out,
+                                             float* __restrict__ lse) {
+    constexpr int PAIRS = G * D / 2;                              // 32 .. 512
+    constexpr int RG = THREADS / PAIRS > 4 ? 4 : THREADS / PAIRS; // groups of threads that share the results
+    constexpr int LOADS = 16, TILE = RG * LOADS;                  // 16 .. 64 results
+    static_assert(RG >= 1 && TILE <= 64 && THREADS / 64 >= G, "a wavefront for every head, a lane for every result of a tile");
+    float2* s_acc = reinterpret_cast<float2*>(lds);               // [RG - 1][PAIRS]
+    float* s_w = lds + 2 * (RG - 1) * PAIRS;                      // [G][TILE] weights of a tile's results
+    float* s_scale = s_w + G * TILE;                              // [G] what the sums so far are scaled by
+    float* s_ml = s_scale + G;                                    // [G][2] maximum and denominator
+    static_assert(2 * (RG - 1) * PAIRS + G * TILE + 3 * G <= THREADS / 64 * G * (D + 8), "fits the wavefronts' partial results");
+    const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rg = tid / PAIRS, pair = tid - rg * PAIRS, g = pair / (D / 2), col = 2 * (pair - g * (D / 2));
+    const bool mine = rg < RG;
+    auto ld2 = [](const float* p) {
+        return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    };
+    constexpr size_t stride = (size_t)G * (D + 2);
+    float2 acc = make_float2(0.f, 0.f);
+    float M = -INFINITY, L = 0.f;                                 // of head `wave`
+    for (int t0 = 0; t0 < n; t0 += TILE) {
+        float2 x[LOADS];
+        float2 ml = make_float2(-INFINITY, 0.f);
+        if (wave < G && lane < TILE && t0 + lane < n) ml = ld2(part + (t0 + lane) * stride + (size_t)wave * (D + 2));
+#pragma unroll
+        for (int u = 0; u < LOADS; ++u) {
+            const int e = t0 + u * RG + rg;
+            x[u] = make_float2(0.f, 0.f);
+            if (mine && e < n) x[u] = ld2(part + e * stride + (size_t)g * (D + 2) + 2 + col);
+        }
+        if (wave < G) {
+            const float Mn = fmaxf(M, wave_max(ml.x)), ms = Mn == -INFINITY ? 0.f : Mn;
+            const float alpha = __builtin_amdgcn_exp2f(M - ms), w = __builtin_amdgcn_exp2f(ml.x - ms);   // (2^-inf = 0)
+            L = L * alpha + wave_total(ml.y * w);
+            M = Mn;
+            if (lane < TILE) s_w[wave * TILE + lane] = w;
+            if (lane == 0) {
+                s_scale[wave] = alpha;
+                s_ml[2 * wave] = M;
+                s_ml[2 * wave + 1] = L;
+            }
+        }
+        __syncthreads();
+        if (mine) {
+            const float a = s_scale[g];
+            acc.x *= a;
+            acc.y *= a;
+#pragma unroll
+            for (int u = 0; u < LOADS; ++u) {
+                const float w = s_w[g * TILE + u * RG + rg];
+                acc.x = fmaf(x[u].x, w, acc.x);
+                acc.y = fmaf(x[u].y, w, acc.y);
+            }
+        }
+        __syncthreads();
+    }
+    if (RG > 1) {
+        if (mine && rg > 0) s_acc[(rg - 1) * PAIRS + pair] = acc;
+        __syncthreads();
+        if (rg == 0) {
+#pragma unroll
+            for (int k = 0; k < RG - 1; ++k) {
+                const float2 o = s_acc[k * PAIRS + pair];
+                acc.x += o.x;
+                acc.y += o.y;
+            }
+        }
+    }
+    if (rg == 0) {
+        const float l = s_ml[2 * g + 1];
+        *reinterpret_cast<float2*>(out + (hq + g) * D + col) = l > 0.f ? make_float2(acc.x / l, acc.y / l) : make_float2(0.f, 0.f);
+        if (col == 0 && lse) lse[hq + g] = l > 0.f ? (s_ml[2 * g] + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
+    }
+    __syncthreads();                                              // (LDS may be used again)
+}
+
 // partial layout: [slot][G][D + 2] = (m in base-2 units, l, o[D] unnormalised)
 // SOFT: retention-gated attention of Sec. 2.2 - the logit of entry i gets the bias (t - i) log(beta_i),
 // t = now[seq] (the weights beta^(t-i) e^z of the soft form); otherwise hard eviction, no bias.
@@ -136,39 +266,82 @@ __global__ __launch_bounds__(1024) void k_att_plan(CacheView c, AttPages pt, Sha
 // block, so all of the call's rows are in flight at once and the call is a chain of latencies: lengths -> scan in LDS ->
 // rows -> partial result.  (It used to be a kernel that built a table of 512-row chunks, then seven dependent loads in
 // front of the first row: 42 us a layer with the merge, 32 layers of 8 KV heads, 1.05 M entries; now 14.4 us.)
+// ATT_ONE: the call is one launch of blocks of 128-row rounds (shares of 64, 32 or 16 rows where the segments are shorter).
+// With two, the second took 4.5 us to be launched and to find 8 to 70 results, and the first 3 us before its first row was
+// asked for.  Timestamps inside (8 segments of 4096 rows, D = 128, 4 heads; us): table 1.6
+// (3.1 with sums in LDS and 64-bit divisions), rows 3.2, partial result 0.6, its acknowledgement 0.4, the counter 0.5 (1.4
+// while the segments' counters shared a line), merge 3.3 (2.1 with 8 results instead of 32).  A block whose run is a whole
+// segment writes the result itself, and segments of one round are not divided, so short segments need no second step.
 // A block keeps ONE online-softmax state for as long as its rows belong to the same segment: a partial result is
 // written per (block, segment) run, at slot block + ordinal (a step to the next run advances one of the two).
 // On this GPU a stream of reads slows down by far more than the bytes suggest when result writes are mixed into
 // it (8.5 MB of writes in a 1.1 GB read stream cost 12 us of 170), so the fewer partial results the better.
-template <int D, int G, bool SOFT, bool PAGED, bool PLANNED>
-__global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, AttPages pt, const uint16_t* __restrict__ q,
-                                                             Shape sh, Workspace ws, float scale_log2,
-                                                             const int32_t* __restrict__ now, int layer_begin, int per, int n_in) {
+template <int D, int G, bool SOFT, bool PAGED, int MODE>
+__global__ __launch_bounds__(att_threads(MODE)) void k_att_partial(CacheView c, AttPages pt, const uint16_t* __restrict__ q,
+                                                                   Shape sh, Workspace ws, float scale_log2,
+                                                                   const int32_t* __restrict__ now, int layer_begin, int per, int n_in,
+                                                                   float* __restrict__ out, float* __restrict__ lse) {
     typedef Frag<D> F;
     typedef typename F::vec vec;
+    constexpr bool PLANNED = MODE == ATT_PLANNED, ONE = MODE == ATT_ONE;
     constexpr int E = F::E;
-    constexpr int NSTREAM = ATT_THREADS / 64;
+    constexpr int THREADS = att_threads(MODE);
+    constexpr int NSTREAM = THREADS / 64;
+    constexpr int ROUND = 16 * NSTREAM;
     __shared__ float s_m[NSTREAM][G], s_l[NSTREAM][G];
     constexpr int SO = D + 8;                                     // a 32-byte skew between heads
     __shared__ __attribute__((aligned(16))) float s_o[NSTREAM][G][SO];
     __shared__ int64_t s_scan[17];
-    __shared__ int s_bad;
+    __shared__ int s_bad[NSTREAM], s_merge[2];
     extern __shared__ int32_t s_tab[];                            // !PLANNED: [n_in + 1] rows before each ordinal, [n_in] starts
 
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int32_t* s_start = s_tab + n_in + 1;
     bool bad = false;
-    // the segments outside the range are looked at as well: a call on a cache with an unusable table gives no result
-    for (int g = (int)blockIdx.x * ATT_THREADS + tid; g < sh.nseg; g += (int)gridDim.x * ATT_THREADS) {
-        int64_t st;
-        (void)att_rows<PAGED>(c, pt, g, sh.nseg, &st, &bad);
-    }
-    if (bad) atomicOr(ws.err, ERR_LAYOUT);
     int64_t N;
-    if (!PLANNED) {
-        if (tid == 0) s_bad = 0;
+    int err = 0, unit_log = ONE ? ATT_ONE_LOG : 6;                // shares start at multiples of 2^unit_log rows of their segment
+    static_assert(ROUND == 1 << (ONE ? ATT_ONE_LOG : 6), "a round of rows");
+    int rows_of = 0, start_of = 0, ex_of = 0;                     // ONE: rows, start and rows before of ordinal `lane`
+    if (ONE) {
+        // At most 64 ordinals: every wavefront holds the table in its lanes, a lane per ordinal, and needs no other wavefront
+        // to know where its rows are.  What only decides whether the call has a result - the sticky flag, the segments
+        // outside the range, the pages of the others - is asked for with the rows and looked at before anything is written.
+        err = __hip_atomic_load(ws.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (lane < n_in) {
+            int64_t st;
+            rows_of = att_rows<PAGED>(c, pt, seg_of_ordinal(lane, per, layer_begin, sh), sh.nseg, &st, &bad);
+            start_of = (int32_t)st;                               // (below 2^31: cap is, and an entry beyond it is bad; PAGED not used)
+        }
+        const int inc = wave_incl_scan(rows_of);
+        ex_of = inc - rows_of;
+        N = __builtin_amdgcn_readlane(inc, 63);                   // (usable segments do not overlap and the capacity is below 2^31; PAGED: see the launch)
+        if (__any(bad)) {                                         // the same in every wavefront of the grid
+            if (tid == 0) atomicOr(ws.err, ERR_LAYOUT);
+            return;
+        }
+        while (unit_log > 4 && N < (int64_t)n_in << unit_log) --unit_log;
+        for (int g = tid; g < sh.nseg; g += THREADS) {
+            int64_t st;
+            (void)att_rows<PAGED>(c, pt, g, sh.nseg, &st, &bad);
+        }
+        if (PAGED) {
+            for (int o = wave; o < n_in; o += NSTREAM) {
+                const int npg = __builtin_amdgcn_readlane(rows_of, o) / KVTRIM_PAGE_SIZE;
+                const int32_t* bt = pt.block_table + (int64_t)seg_of_ordinal(o, per, layer_begin, sh) * pt.max_pps;
+                for (int i = lane; i < npg; i += 64) bad |= bt[i] < 0 || bt[i] >= pt.n_pages;
+            }
+        }
+    } else {
+        for (int g = (int)blockIdx.x * THREADS + tid; g < sh.nseg; g += (int)gridDim.x * THREADS) {
+            int64_t st;
+            (void)att_rows<PAGED>(c, pt, g, sh.nseg, &st, &bad);
+        }
+        if (bad) atomicOr(ws.err, ERR_LAYOUT);
+    }
+    if (MODE == ATT_SUMMED) {
+        if (tid == 0) s_bad[0] = 0;
         bad = false;
-        int each = (n_in + ATT_THREADS - 1) / ATT_THREADS;        // consecutive ordinals per thread
+        int each = (n_in + THREADS - 1) / THREADS;        // consecutive ordinals per thread
         if (each % 8 == 0) ++each;                                // (at 8 words' distance the threads' words share a few banks: 2048 segments 38.8 us, now 36)
         int64_t mine = 0;
         for (int i = 0; i < each; ++i) {
@@ -181,7 +354,7 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, AttPag
             mine += rows;
         }
         int64_t ex = block_excl_scan<int64_t>(mine, s_scan, &N);
-        if (bad) s_bad = 1;
+        if (bad) s_bad[0] = 1;
         for (int i = 0; i < each; ++i) {
             const int o = tid * each + i;
             if (o >= n_in) break;
@@ -191,39 +364,81 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, AttPag
         }
         if (tid == 0) s_tab[n_in] = (int32_t)N;
         __syncthreads();
-        if (s_bad || N > ((int64_t)1 << 31) - ATT_ROUND) {
+        if (s_bad[0] || N > ((int64_t)1 << 31) - ROUND) {
             if (tid == 0) atomicOr(ws.err, ERR_LAYOUT);
             return;
         }
         // the merge kernel reads the same prefix from memory (by then a paged cache's tables may be in change)
-        for (int o = (int)blockIdx.x * ATT_THREADS + tid; o <= n_in; o += (int)gridDim.x * ATT_THREADS) ws.att_row_prefix[o] = s_tab[o];
-    } else {
+        for (int o = (int)blockIdx.x * THREADS + tid; o <= n_in; o += (int)gridDim.x * THREADS) ws.att_row_prefix[o] = s_tab[o];
+    } else if (PLANNED) {
         N = ws.att_row_prefix[n_in];
     }
-    auto rp = [&](int o) -> int64_t { return PLANNED ? ws.att_row_prefix[o] : (int64_t)s_tab[o]; };
-    const int nb = (int)min((int64_t)gridDim.x, max(N / ATT_ROUND, (int64_t)1));
+    auto rp = [&](int o) -> int64_t {
+        if (ONE) return o < n_in ? (int64_t)__builtin_amdgcn_readlane(ex_of, o) : N;
+        return PLANNED ? ws.att_row_prefix[o] : (int64_t)s_tab[o];
+    };
+    const int nb = (int)min((int64_t)gridDim.x, max(N >> unit_log, (int64_t)1));
+    // ONE: true for every thread, or for none of any block of the grid (behind a barrier of the block)
+    auto no_result = [&]() {
+        int any = 0;
+#pragma unroll
+        for (int w = 0; w < NSTREAM; ++w) any |= s_bad[w];
+        return any != 0;
+    };
+    if (ONE) {
+        const bool wave_bad = __any(bad);
+        if (lane == 0) {
+            s_bad[wave] = wave_bad || err != 0;
+            if (wave_bad) atomicOr(ws.err, ERR_LAYOUT);
+        }
+        const uint64_t empty = __ballot(lane < n_in && rows_of == 0);
+        if (empty) {                                              // segments without rows: nothing retained
+            __syncthreads();
+            if (no_result()) return;
+            for (int o = (int)blockIdx.x; o < n_in; o += (int)gridDim.x) {
+                if (!(empty >> o & 1)) continue;
+                const int64_t hq = q_row_of<G>(seg_of_ordinal(o, per, layer_begin, sh), sh);
+                for (int i = tid; i < G * D; i += THREADS) out[hq * D + i] = 0.f;
+                if (lse && tid < G) lse[hq + tid] = -INFINITY;
+            }
+        }
+    }
     if ((int)blockIdx.x >= nb || N == 0) return;
+    // ONE: block b starts at row b share + min(b, rest) (32-bit divisions; a 64-bit one takes half a microsecond)
+    const uint32_t share = ONE ? (uint32_t)N / (uint32_t)nb : 0u, rest = ONE ? (uint32_t)N - share * (uint32_t)nb : 0u;
+    auto first_row = [&](int b) -> int64_t {
+        return ONE ? (int64_t)((uint32_t)b * share + min((uint32_t)b, rest)) : (int64_t)b * N / nb;
+    };
     // where the rows e0 <= e1 of the concatenation lie: the ordinal s with rp(s) <= e < rp(s + 1) (n_in behind the last row)
     // and the round of rows inside it.  A 64-way search, both rows at once: every lane looks at one point of each
     // remaining range, so 4096 segments take two rounds instead of twelve reads one after the other.
     int seg_b, row_b, seg_e, row_e;
     {
-        const int64_t e0 = (int64_t)blockIdx.x * N / nb, e1 = (int64_t)(blockIdx.x + 1) * N / nb;
+        const int64_t e0 = first_row((int)blockIdx.x), e1 = first_row((int)blockIdx.x + 1);
         int lo0 = 0, hi0 = n_in, lo1 = 0, hi1 = n_in;              // invariant: rp(lo) <= e < rp(hi)   (rp(0) = 0, rp(n_in) = N)
-        while (hi0 - lo0 > 1 || hi1 - lo1 > 1) {
-            const int st0 = (hi0 - lo0 + 63) / 64, st1 = (hi1 - lo1 + 63) / 64;   // lane l probes lo + (l + 1) stride
-            const int i0 = lo0 + (lane + 1) * st0, i1 = lo1 + (lane + 1) * st1;
-            const bool in0 = i0 < hi0 && rp(min(i0, n_in)) <= e0, in1 = i1 < hi1 && rp(min(i1, n_in)) <= e1;
-            const int n0 = __popcll(__ballot(in0)), n1 = __popcll(__ballot(in1));   // (monotone: the first n lanes)
-            hi0 = min(hi0, lo0 + (n0 + 1) * st0);
-            lo0 += n0 * st0;
-            hi1 = min(hi1, lo1 + (n1 + 1) * st1);
-            lo1 += n1 * st1;
+        if (ONE) {
+            lo0 = __popcll(__ballot(lane < n_in && ex_of <= (int)e0)) - 1;
+            lo1 = __popcll(__ballot(lane < n_in && ex_of <= (int)e1)) - 1;
+        } else {
+            while (hi0 - lo0 > 1 || hi1 - lo1 > 1) {
+                const int st0 = (hi0 - lo0 + 63) / 64, st1 = (hi1 - lo1 + 63) / 64;   // lane l probes lo + (l + 1) stride
+                const int i0 = lo0 + (lane + 1) * st0, i1 = lo1 + (lane + 1) * st1;
+                const bool in0 = i0 < hi0 && rp(min(i0, n_in)) <= e0, in1 = i1 < hi1 && rp(min(i1, n_in)) <= e1;
+                const int n0 = __popcll(__ballot(in0)), n1 = __popcll(__ballot(in1));   // (monotone: the first n lanes)
+                hi0 = min(hi0, lo0 + (n0 + 1) * st0);
+                lo0 += n0 * st0;
+                hi1 = min(hi1, lo1 + (n1 + 1) * st1);
+                lo1 += n1 * st1;
+            }
         }
         seg_b = e0 >= N ? n_in : lo0;
-        row_b = e0 >= N ? 0 : (int)(e0 - rp(lo0)) / ATT_ROUND * ATT_ROUND;
+        row_b = e0 >= N ? 0 : (int)(e0 - rp(lo0)) >> unit_log << unit_log;
         seg_e = e1 >= N ? n_in : lo1;
-        row_e = e1 >= N ? 0 : (int)(e1 - rp(lo1)) / ATT_ROUND * ATT_ROUND;
+        row_e = e1 >= N ? 0 : (int)(e1 - rp(lo1)) >> unit_log << unit_log;
+        if (ONE) {                                                // a segment that is one round of rows is not divided
+            if (row_b && rp(seg_b + 1) - rp(seg_b) <= ROUND) row_b = 0;
+            if (row_e && rp(seg_e + 1) - rp(seg_e) <= ROUND) row_e = 0;
+        }
     }
     const int c16 = lane & 15, b4 = lane >> 4;
     const vec* kp = reinterpret_cast<const vec*>(c.k);
@@ -243,10 +458,9 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, AttPag
     };
     // the run's partial result goes to slot `slot`: the wavefronts' partials (the MFMAs have summed over a wavefront's
     // row groups already) meet in LDS, s_o[wave][head][(4 i + b4) E + e] = column E (4 b4 + i) + e, and are merged
-    auto flush = [&](int slot) {
-        float l_all = l;
-        l_all += __shfl_xor(l_all, 16, 64);
-        l_all += __shfl_xor(l_all, 32, 64);
+    // whole: the run is all of its segment, so what leaves is the result itself
+    auto flush = [&](int slot, bool whole, int64_t hq) {
+        const float l_all = rows4(l, [](float a, float b) { return a + b; });
         if (c16 < G) {
             if (b4 == 0) {
                 s_m[wave][c16] = m;
@@ -261,8 +475,9 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, AttPag
             }
         }
         __syncthreads();
+        if (ONE && no_result()) return false;
         float* part = ws.att_partial + (size_t)slot * G * (D + 2);
-        for (int idx = tid; idx < G * D; idx += ATT_THREADS) {
+        for (int idx = tid; idx < G * D; idx += THREADS) {
             const int g = idx / D, d = idx % D;
             const int cb = d / E;
             const int so_at = (4 * (cb & 3) + (cb >> 2)) * E + d % E;
@@ -277,30 +492,40 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, AttPag
                 accd += s_o[s2][g][so_at] * w;
                 lsum += s_l[s2][g] * w;
             }
-            part[g * (D + 2) + 2 + d] = accd;
+            if (ONE && whole) {
+                out[(hq + g) * D + d] = lsum > 0.f ? accd / lsum : 0.f;
+                if (d == 0 && lse) lse[hq + g] = lsum > 0.f ? (M + __builtin_amdgcn_logf(lsum)) * 0.6931471805599453f : -INFINITY;
+                continue;
+            }
+            auto put = [](float* p, float v) {                    // ONE: past the caches that are not coherent across the chip
+                if (ONE) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                else *p = v;
+            };
+            put(&part[g * (D + 2) + 2 + d], accd);
             if (d == 0) {
-                part[g * (D + 2)] = M;
-                part[g * (D + 2) + 1] = lsum;
+                put(&part[g * (D + 2)], M);
+                put(&part[g * (D + 2) + 1], lsum);
             }
         }
         __syncthreads();                                          // (the next run's partials may overwrite LDS)
+        return true;
     };
+    int64_t hq_first = 0, hq_last = 0;
+    int shared_first = -1, shared_last = -1;                      // ONE: the segments this block shares with others (the first and the last at most)
     for (int ord = seg_b; ord <= seg_e && ord < n_in; ++ord) {
     const int seg_rows = (int)(rp(ord + 1) - rp(ord));
     const int run_lo = ord == seg_b ? row_b : 0;                  // this block's rows of the segment: [run_lo, run_hi)
     const int run_hi = ord == seg_e ? row_e : seg_rows;           // (a multiple of 64, or the segment's end)
     if (run_lo >= run_hi) continue;                               // (uniform over the block)
     const int seg = seg_of_ordinal(ord, per, layer_begin, sh);
-    const int64_t seg_start = PAGED ? (int64_t)seg * pt.max_pps : (PLANNED ? c.seg_start[seg] : (int64_t)s_start[ord]);
+    const int64_t seg_start = PAGED ? (int64_t)seg * pt.max_pps : (PLANNED ? c.seg_start[seg] : (ONE ? (int64_t)__builtin_amdgcn_readlane(start_of, ord) : (int64_t)s_start[ord]));
     reset();
+    const int64_t hq = q_row_of<G>(seg, sh);
     {   // query fragments: lane (query c16, k-group b4), MFMA step j covers elements (4j + b4)*E ..
-        const int seq = seg / sh.segs_per_seq, lh = seg % sh.segs_per_seq;
-        const int layer = lh / sh.n_kv_heads, head = lh % sh.n_kv_heads;
-        const int64_t qrow = ((int64_t)seq * sh.n_layers + layer) * sh.n_q_heads + (int64_t)head * G + c16;
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            qf[j] = c16 < G ? reinterpret_cast<const vec*>(q + qrow * D)[4 * j + b4] : F::zero();
-        t_now = SOFT ? now[seq] : 0;
+            qf[j] = c16 < G ? reinterpret_cast<const vec*>(q + (hq + c16) * D)[4 * j + b4] : F::zero();
+        t_now = SOFT ? now[seg / sh.segs_per_seq] : 0;
     }
     const int last = seg_rows - 1;
     // PAGED: lane l holds the pool page of the segment's page win / 128 + l, so that no load of a tile waits for a look-up in
@@ -315,7 +540,7 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, AttPag
         pg_mine = min(max(pg, 0), pt.n_pages - 1);                // (clamped: no reader leaves the pool)
         if (pg != pg_mine) atomicOr(ws.err, ERR_LAYOUT);
     }
-    for (int r0 = max(run_lo, win) + wave * 16; r0 < win_hi; r0 += ATT_ROUND) {
+    for (int r0 = max(run_lo, win) + wave * 16; r0 < win_hi; r0 += ROUND) {
         int64_t rbase = seg_start;                                // entry of row 0 in this 16-row group's numbering
         if (PAGED) {                                              // 16 | page size: the group lies in one page, the same for all lanes
             const int pg = __builtin_amdgcn_readlane(pg_mine, (r0 - win) / KVTRIM_PAGE_SIZE);
@@ -358,8 +583,7 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, AttPag
             z[i] = valid ? zi : -INFINITY;
             tmax = fmaxf(tmax, z[i]);
         }
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-        tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));             // over the tile's 16 rows: P.V sums over all of them
+        tmax = rows4(tmax, [](float a, float b) { return fmaxf(a, b); });   // over the tile's 16 rows: P.V sums over all of them
         const float m_new = fmaxf(m, tmax);
         const float m_safe = m_new == -INFINITY ? 0.f : m_new;
         const float alpha = __builtin_amdgcn_exp2f(m - m_safe);   // m = -inf gives 0; l and o are 0 then
@@ -400,8 +624,53 @@ __global__ __launch_bounds__(ATT_THREADS) void k_att_partial(CacheView c, AttPag
     }
     win += WINDOW;
     } while (PAGED && win < run_hi);                              // (windows of the run)
-    flush((int)blockIdx.x + ord);
+    const bool whole = run_lo == 0 && run_hi == seg_rows;
+    if (!flush((int)blockIdx.x + ord, whole, hq)) return;
+    if (ONE && !whole) {
+        if (ord == seg_b) {
+            shared_first = ord;
+            hq_first = hq;
+        } else {
+            shared_last = ord;
+            hq_last = hq;
+        }
+    }
     }                                                             // (segments of the block)
+    if constexpr (ONE) {
+    if (shared_first < 0 && shared_last < 0) return;
+
+    // The blocks of a shared segment count themselves when their partial result has been acknowledged; the last one merges.
+    // The blocks with rows of segment ord are b0 - the last one that starts at or before its first row (a start below
+    // unit rows into it rounds down to it) - to the last one that starts inside it.
+    auto starts_below = [&](uint32_t x) {                         // blocks b with first_row(b) < x; x > 0
+        const uint32_t t = rest * (share + 1);
+        return x <= t ? (x + share) / (share + 1) : rest + (x - t + share - 1) / share;
+    };
+    int b0[2] = {0, 0}, n[2] = {0, 0};
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int ord = k == 0 ? shared_first : shared_last;
+        if (ord < 0) continue;
+        const uint32_t r0s = (uint32_t)rp(ord), r1s = (uint32_t)rp(ord + 1);
+        b0[k] = (int)starts_below(min(r0s + (1u << unit_log), r1s)) - 1;
+        n[k] = (int)starts_below(r1s) - b0[k];
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid < 2) {
+        const int ord = tid == 0 ? shared_first : shared_last;
+        s_merge[tid] = ord >= 0 && atomicAdd(&ws.att_done[ord * ATT_DONE_STRIDE], 1u) == (unsigned)(tid == 0 ? n[0] : n[1]) - 1u;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int k = 0; k < 2; ++k) {
+        if (!s_merge[k]) continue;                                // (uniform)
+        const int ord = k == 0 ? shared_first : shared_last;
+        if (tid == 0) __hip_atomic_store(&ws.att_done[ord * ATT_DONE_STRIDE], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const float* part = ws.att_partial + (size_t)((k == 0 ? b0[0] : b0[1]) + ord) * G * (D + 2);
+        merge_shared<D, G, THREADS>(part, k == 0 ? n[0] : n[1], k == 0 ? hq_first : hq_last, &s_o[0][0][0], out, lse);
+    }
+    }
 }
 
 // Merges the partial results of every segment of the layer range.  A block of 512 threads is 512 / D groups of D threads;
@@ -545,43 +814,60 @@ __global__ __launch_bounds__(COMB_THREADS) void k_att_combine(Shape sh, Workspac
 // What a call of the attention kernel needs: the segments of its layer range, the grid, the LDS for the row prefix.
 struct AttCall {
     int layer_begin, per, n_in, nb;
-    bool planned;
+    int mode;
     size_t lds;
 };
-static AttCall att_call(const kvtrim_ctx* ctx, int64_t cap, int32_t layer_begin, int32_t layer_end, bool paged) {
+// One launch (ATT_ONE) for the small calls a model makes layer by layer.  Per call (us; 8 KV heads, 4 query heads each,
+// D = 128, against two launches): 52 rows a segment 8.2 / 11.9, 4096 rows 12.7 / 13.9, 6500 rows 14.7 / 15.8, but 9000
+// rows 20 / 17.5: beyond two blocks of 128 rows per compute unit the two launches' smaller blocks spread better.  And
+// the one block that merges a segment reads all of its partial results: 64 KB still cost less than the launch of
+// k_att_combine, whose blocks share them (12.7 / 13.9), 128 KB as much (4000 rows, 8 heads: 13.3 / 13.3), 200 KB more (2
+// heads of 15 K rows, 7 query heads each: 24 / 17).
+constexpr int64_t ATT_ONE_ROWS = 2 * 256 * 128, ATT_ONE_MERGE_BYTES = 1 << 17;
+static bool att_one(const kvtrim_ctx* ctx, int64_t cap, const AttPages* pages, int32_t layer_begin, int32_t layer_end) {
+    const Shape& sh = ctx->shape;
+    const int64_t n_in = (int64_t)sh.n_seq * (layer_end - layer_begin) * sh.n_kv_heads;
+    const int64_t rows = cap * (layer_end - layer_begin) / sh.n_layers;   // of the range, if the layers' segments are alike
+    if (n_in > ATT_ONE_ORDS || sh.nseg > ATT_ONE_SEGS || rows > ATT_ONE_ROWS) return false;
+    if (pages && n_in * pages->max_pps >= 1 << 24) return false;  // (the rows of the range are added up in 32 bits)
+    return (rows / n_in / (16 * ATT_ONE_THREADS / 64) + 1) * sh.group * (sh.head_dim + 2) * (int64_t)sizeof(float) <= ATT_ONE_MERGE_BYTES;
+}
+
+static AttCall att_call(const kvtrim_ctx* ctx, int64_t cap, int32_t layer_begin, int32_t layer_end, bool paged, bool one) {
     AttCall a;
     a.layer_begin = layer_begin;
     a.per = (layer_end - layer_begin) * ctx->shape.n_kv_heads;
     a.n_in = ctx->shape.n_seq * a.per;
+    a.mode = one ? ATT_ONE : (a.n_in > ATT_SCAN_SEGS ? ATT_PLANNED : ATT_SUMMED);
     // a block per round of 64 rows at most, and a slot per block and segment in the partial-result buffer
     int64_t nb = cap / ATT_ROUND + 1;
     if (nb > ctx->att_blocks) nb = ctx->att_blocks;
     if (nb > ctx->ws.att_slots - a.n_in) nb = ctx->ws.att_slots - a.n_in;
     a.nb = (int)nb;
-    a.planned = a.n_in > ATT_SCAN_SEGS;
-    a.lds = a.planned ? 0 : ((size_t)(paged ? 1 : 2) * a.n_in + 1) * sizeof(int32_t);
+    a.lds = a.mode != ATT_SUMMED ? 0 : ((size_t)(paged ? 1 : 2) * a.n_in + 1) * sizeof(int32_t);
     return a;
 }
 
 template <int D, int G, bool SOFT, bool PAGED>
 static void launch_partial(const AttCall& a, const CacheView& c, const AttPages& pt, const uint16_t* q, const Shape& sh,
-                           const Workspace& ws, float scale_log2, const int32_t* now, hipStream_t st) {
-    if (a.planned)
-        hipLaunchKernelGGL((k_att_partial<D, G, SOFT, PAGED, true>), dim3(a.nb), dim3(ATT_THREADS), a.lds, st, c, pt, q, sh, ws, scale_log2, now, a.layer_begin, a.per, a.n_in);
-    else
-        hipLaunchKernelGGL((k_att_partial<D, G, SOFT, PAGED, false>), dim3(a.nb), dim3(ATT_THREADS), a.lds, st, c, pt, q, sh, ws, scale_log2, now, a.layer_begin, a.per, a.n_in);
+                           const Workspace& ws, float scale_log2, const int32_t* now, float* out, float* lse, hipStream_t st) {
+#define KVTRIM_MODE(m) hipLaunchKernelGGL((k_att_partial<D, G, SOFT, PAGED, m>), dim3(a.nb), dim3(att_threads(m)), a.lds, st, c, pt, q, sh, ws, scale_log2, now, a.layer_begin, a.per, a.n_in, out, lse)
+    if (a.mode == ATT_PLANNED) KVTRIM_MODE(ATT_PLANNED);
+    else if (a.mode == ATT_SUMMED) KVTRIM_MODE(ATT_SUMMED);
+    else KVTRIM_MODE(ATT_ONE);
+#undef KVTRIM_MODE
 }
 
 template <int D>
 static bool dispatch_partial(const AttCall& a, const CacheView& c, const AttPages* pages, const uint16_t* q, const Shape& sh,
-                             const Workspace& ws, float scale_log2, const int32_t* now, hipStream_t st) {
+                             const Workspace& ws, float scale_log2, const int32_t* now, float* out, float* lse, hipStream_t st) {
     const AttPages pt = pages ? *pages : AttPages{};
     switch (sh.group) {
 #define KVTRIM_CASE(g)                                                                                          \
     case g:                                                                                                     \
-        if (pages) launch_partial<D, g, false, true>(a, c, pt, q, sh, ws, scale_log2, now, st);                 \
-        else if (now) launch_partial<D, g, true, false>(a, c, pt, q, sh, ws, scale_log2, now, st);              \
-        else launch_partial<D, g, false, false>(a, c, pt, q, sh, ws, scale_log2, now, st);                      \
+        if (pages) launch_partial<D, g, false, true>(a, c, pt, q, sh, ws, scale_log2, now, out, lse, st);       \
+        else if (now) launch_partial<D, g, true, false>(a, c, pt, q, sh, ws, scale_log2, now, out, lse, st);    \
+        else launch_partial<D, g, false, false>(a, c, pt, q, sh, ws, scale_log2, now, out, lse, st);            \
         return true;
         KVTRIM_CASE(1) KVTRIM_CASE(2) KVTRIM_CASE(3) KVTRIM_CASE(4) KVTRIM_CASE(5) KVTRIM_CASE(6) KVTRIM_CASE(7) KVTRIM_CASE(8)
 #undef KVTRIM_CASE
@@ -626,9 +912,10 @@ kvtrim_status launch_attn(kvtrim_ctx* ctx, const CacheView& c, const AttPages* p
                           int32_t layer_begin, int32_t layer_end, float scale, float* out, float* lse, hipStream_t st,
                           const PagedView* tidy) {
     const Shape& sh = ctx->shape;
-    const AttCall a = att_call(ctx, c.cap, layer_begin, layer_end, pages != nullptr);
+    const bool one = !tidy && att_one(ctx, c.cap, pages, layer_begin, layer_end);
+    const AttCall a = att_call(ctx, c.cap, layer_begin, layer_end, pages != nullptr, one);
     const float scale_log2 = scale * 1.4426950408889634f;
-    if (a.planned) {
+    if (a.mode == ATT_PLANNED) {
         ProfScope prof(ctx, pages ? K_PG_ATT_PLAN : K_ATT_PLAN, st);
         if (pages)
             hipLaunchKernelGGL(k_att_plan<true>, dim3(1), dim3(1024), 0, st, c, *pages, sh, ctx->ws, a.layer_begin, a.per, a.n_in);
@@ -638,10 +925,14 @@ kvtrim_status launch_attn(kvtrim_ctx* ctx, const CacheView& c, const AttPages* p
     bool ok;
     {
         ProfScope prof(ctx, K_ATT_PARTIAL, st);
-        ok = sh.head_dim == 128 ? dispatch_partial<128>(a, c, pages, q, sh, ctx->ws, scale_log2, soft_now, st)
-                                : dispatch_partial<64>(a, c, pages, q, sh, ctx->ws, scale_log2, soft_now, st);
+        ok = sh.head_dim == 128 ? dispatch_partial<128>(a, c, pages, q, sh, ctx->ws, scale_log2, soft_now, out, lse, st)
+                                : dispatch_partial<64>(a, c, pages, q, sh, ctx->ws, scale_log2, soft_now, out, lse, st);
     }
     if (!ok) return KVTRIM_EINVAL;
+    if (a.mode == ATT_ONE) {
+        KVTRIM_HIP(ctx, hipGetLastError());
+        return KVTRIM_OK;
+    }
     if (!tidy) return launch_merge<EXTRA_NONE, true>(ctx, nullptr, layer_begin, layer_end, out, lse, a.nb, CombineExtra{}, 0, a.nb, st);
     CombineExtra ex{};
     ex.tidy = *tidy;

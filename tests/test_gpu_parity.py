@@ -772,6 +772,60 @@ def test_attention_on_a_bad_table_outside_the_layer_range_gives_no_result():
     assert torch.all(out == 99.0)
 
 
+# Rounds of 128 rows, shares that start at multiples of 128 to 16 rows, segments of one round undivided, merges in tiles of
+# RG * 16 results (16 at 8 heads and D = 128, 64 at one head), at most 64 segments and 128 KB of results a segment in one
+# launch: lengths on both sides of each, 64 and 65 segments, and the same call again on counters that the first left behind.
+@pytest.mark.parametrize("S,H,G,D,lens,soft", [
+    (1, 16, 4, 128, [0, 1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 130, 255, 256, 257, 2100], False),
+    (1, 2, 8, 128, [5000, 100], False),                           # 40 results to merge: three tiles of 16
+    (1, 1, 1, 64, [9000], True),                                  # 71 results: a tile of 64 and the rest
+    (1, 3, 3, 128, [0, 0, 4097], True),
+    (4, 16, 2, 64, [40, 0, 300, 16], False),                      # 64 segments, most shorter than a round
+    (5, 13, 2, 64, [40, 0, 300, 16], False),                      # 65: two launches
+    (2, 2, 4, 128, [0], False)])                                  # nothing retained at all
+def test_attention_of_small_calls_at_the_edges_of_their_shares(S, H, G, D, lens, soft):
+    w = wl(S, 2, H, G, D)
+    seg_len = [lens[g % len(lens)] for g in range(w.nseg)]
+    c, now = ki.ragged_cache(w, seg_len, reserve=1, salt=50 + G)
+    hc = host_cache(w, c)
+    dc = kv.Cache.from_dict(c, DEV)
+    ctx = kv.Context(S, 2, H, H * G, D, hc.cap)
+    q = ki.decode_inputs(w, 1)["q"]
+    now_np = now.numpy() + 2
+    ref, ref_lse = oracle.attend(hc, bf16_bits(q), 0.1, soft_now=now_np if soft else None)
+    out = torch.full(ref.shape, 99.0, dtype=torch.float32, device=DEV)
+    lse = torch.full(ref_lse.shape, 99.0, dtype=torch.float32, device=DEV)
+    now_dev, qd = torch.from_numpy(now_np).to(DEV), q.to(DEV)
+
+    def call(cache, layer, lse=lse):
+        if soft:
+            kv.kvtrim_decode_attn_soft(ctx, cache, qd, now_dev, layer, layer + 1, 0.1, out, lse)
+        else:
+            kv.kvtrim_decode_attn(ctx, cache, qd, layer, layer + 1, 0.1, out, lse)
+
+    # a table that is unusable, and the sticky flag it leaves: no result, and nothing counted
+    bad_len = dc.seg_len.clone()
+    bad_len[w.nseg - 1] = 10 ** 6
+    call(kv.Cache(dc.k, dc.v, dc.log_beta, dc.pos, dc.seg_start, bad_len), 0)
+    call(dc, 1)
+    assert torch.all(out == 99.0) and torch.all(lse == 99.0)
+    assert kv.kvtrim_poll_error(ctx) == -6                               # KVTRIM_ELAYOUT
+    got = []
+    for again in range(3):
+        out.fill_(99.0)
+        for layer in range(2):
+            call(dc, layer, lse if again < 2 else None)
+        assert kv.kvtrim_poll_error(ctx) == 0
+        got.append(out.cpu().numpy())
+    assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+    fin = np.isfinite(ref_lse)
+    l = lse.cpu().numpy()
+    assert np.array_equal(np.isneginf(l), ~fin) and np.all(got[0][~fin] == 0.0)
+    if fin.any():
+        assert attn_error(got[0], ref) <= ATTN_TOL
+        assert np.abs(l[fin] - ref_lse[fin]).max() <= 2e-3
+
+
 @pytest.mark.parametrize("reserve,lens", [
     (3, [0, 1, 15, 16, 17, 127, 128, 129]),                  # under, at and over a lane's 16 mask bytes and a chunk; every start misaligned differently
     (1, [1023, 1024, 1025, 2047, 2048, 2049, 4095, 8]),      # ... a wavefront's load (8 chunks) and a selection chunk
