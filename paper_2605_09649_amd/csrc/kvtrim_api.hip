@@ -34,7 +34,7 @@ static bool config_ok(const kvtrim_config* c) {
 
 struct Layout {
     size_t off[42];
-    int32_t fl_cap;
+    int32_t fl_cap, fast_stride;
     size_t total;
     int64_t max_sel_chunks, max_cmp_chunks, max_att_chunks, att_slots, gat_slots;
 };
@@ -90,9 +90,10 @@ static Layout layout_of(const kvtrim_config* c, bool select_only) {
     fl = fl > FL_CAP_MAX ? FL_CAP_MAX : (fl < FL_CAP_MIN ? FL_CAP_MIN : fl);
     l.fl_cap = select_only ? 0 : (int32_t)fl;
     l.off[24] = bump(cur, seg_tables * (size_t)c->n_seq * sizeof(uint32_t));   // fast_hi
-    l.off[25] = bump(cur, seg_tables * (size_t)c->n_seq * 16 * sizeof(uint32_t));   // fast_min: 16 group words per sequence
-    l.off[26] = bump(cur, seg_tables * (size_t)c->n_seq * 17 * sizeof(uint32_t));   // fast_done: top-level + 16 group counters
-    l.off[27] = bump(cur, seg_tables * (size_t)c->n_seq * 16 * sizeof(uint32_t));   // fl_count: one per sub-list
+    l.fast_stride = c->n_seq <= FAST_WORD_SEQS ? FAST_WORD_STRIDE : 1;
+    l.off[25] = bump(cur, seg_tables * (size_t)c->n_seq * l.fast_stride * 16 * sizeof(uint32_t));   // fast_min: 16 group words per sequence
+    l.off[26] = bump(cur, seg_tables * (size_t)c->n_seq * l.fast_stride * 17 * sizeof(uint32_t));   // fast_done: top-level + 16 group counters
+    l.off[27] = bump(cur, seg_tables * (size_t)c->n_seq * l.fast_stride * 16 * sizeof(uint32_t));   // fl_count: one per sub-list
     l.off[28] = bump(cur, seg_tables * (size_t)c->n_seq * sizeof(FastSel));    // fast_sel
     l.off[29] = bump(cur, (size_t)c->n_seq * l.fl_cap * sizeof(uint32_t));     // fl_key
     l.off[30] = bump(cur, (size_t)c->n_seq * l.fl_cap * sizeof(int32_t));      // fl_seg
@@ -155,6 +156,7 @@ static void bind(const Layout& l, char* b, Workspace& w) {
     w.att_done = (uint32_t*)(b + l.off[41]);
     w.gat_slots = l.gat_slots;
     w.fl_cap = l.fl_cap;
+    w.fast_stride = l.fast_stride;
     w.max_sel_chunks = l.max_sel_chunks;
     w.max_cmp_chunks = l.max_cmp_chunks;
     w.max_att_chunks = l.max_att_chunks;
@@ -268,7 +270,7 @@ kvtrim_status kvtrim_create(kvtrim_ctx** out, const kvtrim_config* cfg) {
     }
     if ((e = hipHostMalloc((void**)&ctx->err_host, sizeof(int32_t), hipHostMallocDefault)) != hipSuccess ||
         (e = hipMemset(ctx->ws_base, 0, l.total)) != hipSuccess ||
-        (e = hipMemset((char*)ctx->ws_base + l.off[25], 0xFF, (size_t)cfg->n_seq * 16 * sizeof(uint32_t))) != hipSuccess ||   // fast_min: "no key seen"
+        (e = hipMemset((char*)ctx->ws_base + l.off[25], 0xFF, (size_t)cfg->n_seq * l.fast_stride * 16 * sizeof(uint32_t))) != hipSuccess ||   // fast_min: "no key seen"
         (e = hipDeviceSynchronize()) != hipSuccess) {
         snprintf(g_create_error, sizeof g_create_error, "kvtrim_create: setting up the workspace: %s", hipGetErrorString(e));
         (void)hipGetLastError();

@@ -28,6 +28,7 @@ constexpr int HIST_REPLICAS = 8;     // copies of the merged histogram (spreads 
 // Decode-step selection (k_fastsel.hip): candidates below the carried bound are listed per sequence.
 constexpr int FL_CAP_MAX = 4096;     // list entries per sequence (fewer when the context has many sequences)
 constexpr int FL_CAP_MIN = 64;
+constexpr int FAST_WORD_STRIDE = 64, FAST_WORD_SEQS = 32;   // words between two counters that the blocks of a sequence meet on (256 bytes); next to each other for more sequences, which have fewer blocks each
 constexpr int FAST_THREADS = 1024;
 constexpr int FAST_ENTRIES_PER_BLOCK = 8192;   // entries of a segment one block covers (blocks per segment from the capacity)
 
@@ -194,6 +195,7 @@ struct alignas(64) Workspace {
     int64_t* chunk_tie_base;     // [max_sel_chunks] ties of the sequence before the chunk
     // decode-step selection: state carried from call to call, and the per-call candidate lists
     uint32_t* fast_hi;           // [n_seq] entries with key < fast_hi are listed (0: nothing known yet)
+    // (word i of the 16 or 17 of sequence s at (16 s + i) * fast_stride; fast_done: 17 s + i)
     uint32_t* fast_min;          // [n_seq][16] smallest key seen in the call, per group of blocks (0xFFFFFFFF between calls)
     uint32_t* fast_done;         // [n_seq][17] arrivals: top level, 16 groups of blocks (0 between calls)
     uint32_t* fl_count;          // [n_seq][16] candidates per sub-list (beyond its capacity: the list is incomplete; 0 between calls)
@@ -204,6 +206,7 @@ struct alignas(64) Workspace {
     int32_t* fl_pos;             // [n_seq][fl_cap]
     int32_t* fl_idx;             // [n_seq][fl_cap] index of the entry in its segment (one-call decode step)
     int32_t fl_cap;
+    int32_t fast_stride;         // words from one of them to the next
     // one-call decode step
     int32_t* step_len;           // [nseg] segment lengths with the step's new tokens
     int64_t* att_row_prefix;     // [nseg+1] attention: rows (paged: slots) before each segment of the layer range, counted inside the range
