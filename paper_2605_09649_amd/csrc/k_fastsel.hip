@@ -55,6 +55,7 @@ struct SegView {
     int live;
 };
 
+constexpr int DEAL_SEGMENT = 0, DEAL_MULTI = 1, DEAL_WHOLE = 2;   // a segment or a part of one / several segments / a whole sequence to a block of k_fast_scan
 constexpr int SCAN_RAGGED = 0, SCAN_STEP = 1, SCAN_PAGED = 2;     // what k_fast_scan walks over
 
 template <int KIND>
@@ -462,25 +463,32 @@ static_assert(STEP_MAX_NEW <= 64, "a lane per new token");
 // writer waits for before it arrives, and read with device-scope loads - so no block needs a fence, which on this
 // chip means a write-back of a whole L2.  The scores written here are read by the NEXT kernel only; the
 // single-block select, which has to look at every entry, recomputes them from the call's inputs.
-template <bool SCORE, int KIND, bool MULTI>
+template <bool SCORE, int KIND, int DEAL>
 __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const int32_t* __restrict__ now,
                                                             const float* score_in, float* score_out,
                                                             const int64_t* __restrict__ budget, Shape sh, Workspace ws,
                                                             int bps, int spb_arg, int limit, int32_t* __restrict__ kept_out,
                                                             uint32_t* __restrict__ thr_out, StepArgs sa) {
-    constexpr bool STEP = KIND == SCAN_STEP, PAGED = KIND == SCAN_PAGED;
+    constexpr bool STEP = KIND == SCAN_STEP, PAGED = KIND == SCAN_PAGED, MULTI = DEAL == DEAL_MULTI, WHOLE = DEAL == DEAL_WHOLE;
     static_assert(!STEP || SCORE, "the one-call step computes the scores itself");
     __shared__ ResolveShared sm;
     __shared__ int s_last, s_ncand;
     __shared__ uint32_t s_base[FAST_SUB];
     // This block's candidates, before they go to the list; the last block of a sequence reuses the space (STEP).  A block of
     // several segments, which may be all of its sequence, stages as many as the list holds.
-    constexpr int STAGE = MULTI ? FL_CAP_MAX : FAST_STAGE;
-    __shared__ int32_t s_pool[(STEP ? 4 : 3) * STAGE];
-    uint32_t* c_key = reinterpret_cast<uint32_t*>(s_pool);
-    int32_t* c_pos = s_pool + STAGE;
-    int32_t* c_seg = s_pool + 2 * STAGE;
-    int32_t* c_idx = s_pool + (STEP ? 3 : 2) * STAGE;
+    constexpr int STAGE = DEAL == DEAL_SEGMENT ? FAST_STAGE : FL_CAP_MAX;
+    constexpr int STAGE_AT = WHOLE ? 5 * FAST_STAGE : 0;          // (WHOLE: behind the tables, which it needs from the beginning)
+    __shared__ int32_t s_pool[STAGE_AT + (STEP ? 4 : 3) * STAGE];
+    uint32_t* c_key = reinterpret_cast<uint32_t*>(s_pool + STAGE_AT);
+    int32_t* c_pos = s_pool + STAGE_AT + STAGE;
+    int32_t* c_seg = s_pool + STAGE_AT + 2 * STAGE;
+    int32_t* c_idx = s_pool + STAGE_AT + (STEP ? 3 : 2) * STAGE;
+    // tables of the sequence's segments (STEP, WHOLE): entries before it, length, chunks before it, start, entries in the cache
+    uint32_t* s_before = reinterpret_cast<uint32_t*>(s_pool);
+    uint32_t* s_len = reinterpret_cast<uint32_t*>(s_pool) + FAST_STAGE;
+    uint32_t* s_chb = reinterpret_cast<uint32_t*>(s_pool) + 2 * FAST_STAGE;
+    uint32_t* s_start = reinterpret_cast<uint32_t*>(s_pool) + 3 * FAST_STAGE;
+    uint32_t* s_old = reinterpret_cast<uint32_t*>(s_pool) + (WHOLE ? 4 : 0) * FAST_STAGE;
     __shared__ int s_ev[STEP ? STEP_MAX_SEGS : 1], s_off[STEP ? STEP_MAX_SEGS : 1];
     __shared__ int s_seqcnt[STEP ? STEP_MAX_SEQS + 1 : 1];        // entries before each sequence
     static_assert(STEP_MAX_EVICT < 1 << 16 && STEP_MAX_SEGS <= FAST_STAGE && STEP_MAX_SEGS <= FAST_THREADS && STEP_MAX_EVICT <= FAST_STAGE, "the step's tables reuse the staging space, one segment per thread");
@@ -489,8 +497,9 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     // each (whole wavefronts).  A block takes every bpq-th segment, so that neighbouring segments - a layer's, whose
     // candidates come in the same steps - are staged by different blocks.  STEP: behind the scanning blocks the grid has blocks
     // that only write the segments' tables, a wavefront per segment.
+    // WHOLE: a block walks all segments of its sequence.
     const int spb = MULTI ? spb_arg : 1;
-    const int bpq = (sh.segs_per_seq + spb - 1) / spb * bps;      // scanning blocks per sequence
+    const int bpq = WHOLE ? 1 : (sh.segs_per_seq + spb - 1) / spb * bps;   // scanning blocks per sequence
     const bool tables_only = STEP && (int)blockIdx.x >= sh.n_seq * bpq;
     const int threads = FAST_THREADS / spb, group = tid / threads, gt = tid % threads;
     const int seq = tables_only ? 0 : (int)blockIdx.x / bpq;
@@ -514,9 +523,10 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         return;
     }
     bool bad = false, nocap = false;
-    const SegView own = seg_view<KIND>(c, own_seg, sh.nseg, sa, &bad, &nocap);
+    SegView own{};
+    if (!WHOLE) own = seg_view<KIND>(c, own_seg, sh.nseg, sa, &bad, &nocap);
     const int own_len = no_seg ? 0 : own.len;
-    if (gt == 0 && part == 0 && !no_seg && (bad || nocap)) atomicOr(ws.err, bad ? ERR_LAYOUT : ERR_CAP);
+    if (!WHOLE && gt == 0 && part == 0 && !no_seg && (bad || nocap)) atomicOr(ws.err, bad ? ERR_LAYOUT : ERR_CAP);
     const uint32_t hi = ws.fast_hi[seq];
     const uint32_t cap = (uint32_t)ws.fl_cap;
     const uint32_t subcap = cap / (uint32_t)nsub;                 // entries per sub-list
@@ -541,8 +551,147 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     ks.n_new = sa.n_new;
     ks.t1 = SCORE ? now[seq] + 1 : 0;
 
+    const int g0 = seq * sh.segs_per_seq;
+    // STEP: one scan over the segments of the batch (1024 at a time): entries and chunks before each, so the entries of every
+    // sequence (the destination of a sequence starts behind all earlier ones) and this sequence's part of the tables
+    // fall out of it.  (The staging space is free once the block has arrived; entries of a cache are below 2^31.)
+    auto step_tables = [&]() {
+        uint64_t carry = 0;                                       // entries in the upper, chunks in the lower 28 bits
+        for (int base = 0; base < sh.nseg; base += FAST_THREADS) {
+            const int g = base + tid;
+            uint64_t v = 0;
+            SegView sv{};
+            bool b2 = false, n2 = false;
+            if (g < sh.nseg) {
+                sv = seg_view<KIND>(c, g, sh.nseg, sa, &b2, &n2);
+                v = (uint64_t)sv.len << 28 | (uint64_t)((sv.len + CMP_CHUNK - 1) / CMP_CHUNK);
+            }
+            uint64_t tot;
+            const uint64_t ex = carry + block_excl_scan<uint64_t>(v, reinterpret_cast<uint64_t*>(sm.lds64), &tot);
+            carry += tot;
+            if (g < sh.nseg && g % sh.segs_per_seq == 0) s_seqcnt[g / sh.segs_per_seq] = (int)(uint32_t)(ex >> 28);
+            if (g >= g0 && g < g0 + sh.segs_per_seq) {
+                kept_out[g] = 0;
+                s_start[g - g0] = (uint32_t)sv.start;
+                s_len[g - g0] = (uint32_t)sv.len;
+                s_chb[g - g0] = (uint32_t)(ex & 0xFFFFFFFu);
+                if (WHOLE) {
+                    s_before[g - g0] = (uint32_t)(ex >> 28);
+                    s_old[g - g0] = (uint32_t)sv.len_old;
+                    if (b2 || n2) atomicOr(ws.err, b2 ? ERR_LAYOUT : ERR_CAP);
+                }
+            }
+        }
+        if (tid == 0) s_seqcnt[sh.n_seq] = (int)(uint32_t)(carry >> 28);
+        __syncthreads();
+    };
+
+    int64_t cnt = 0;                                              // entries of the sequence (not STEP: of this thread's segments)
+    uint32_t key[FAST_ITEMS];
+    int sg[FAST_ITEMS], ps[FAST_ITEMS], ix[FAST_ITEMS];
+    bool valid[FAST_ITEMS], listed[FAST_ITEMS];
+    bool sub_overflow = false;
+    uint32_t n_list = 0, min_key = 0xFFFFFFFFu;
+    if constexpr (WHOLE) {
+        // ---- the whole sequence: its entries as one flat range, in equal shares of whole 64s to the wavefronts, so that it
+        // does not matter how they are spread over the segments; a lane follows the table from entry to entry
+        uint32_t total;
+        if (STEP) {
+            step_tables();
+            total = (uint32_t)s_seqcnt[seq + 1] - (uint32_t)s_seqcnt[seq];
+        } else {
+            SegView sv{};
+            bool b2 = false, n2 = false;
+            if (tid < sh.segs_per_seq) {
+                sv = seg_view<KIND>(c, g0 + tid, sh.nseg, sa, &b2, &n2);
+                if (b2) atomicOr(ws.err, ERR_LAYOUT);
+                kept_out[g0 + tid] = 0;                           // the mask kernel adds its counts
+                cnt = sv.live;
+            }
+            int32_t tot;
+            const int32_t ex = block_excl_scan<int32_t>(sv.len, sm.lds32, &tot);
+            if (tid < sh.segs_per_seq) {
+                s_before[tid] = (uint32_t)ex;
+                s_len[tid] = (uint32_t)sv.len;
+                s_start[tid] = (uint32_t)sv.start;
+            }
+            total = (uint32_t)tot;
+            __syncthreads();
+        }
+        const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        constexpr uint32_t NW = FAST_THREADS / 64;
+        const uint32_t first_before = STEP ? (uint32_t)s_seqcnt[seq] : 0u;
+        const uint32_t share = (total + NW * 64 - 1) / (NW * 64) * 64;
+        const uint32_t i0 = first_before + min(total, (uint32_t)wave * share), i1 = first_before + min(total, ((uint32_t)wave + 1) * share);
+        int sl = -1;                                              // the segment of this lane's entry
+        for (int base = 0; base < sh.segs_per_seq; base += 64)
+            sl += __popcll(__ballot(base + lane < sh.segs_per_seq && s_before[min(base + lane, sh.segs_per_seq - 1)] <= i0));
+        sl = max(sl, 0);
+        uint32_t mn = 0xFFFFFFFFu;
+        for (uint32_t b0 = i0; b0 < i1; b0 += 64 * FAST_BATCH) {
+            float sv[FAST_BATCH];
+            int pv[FAST_BATCH], seg[FAST_BATCH], jj[FAST_BATCH];
+            int64_t at[FAST_BATCH], sat[FAST_BATCH];              // where the entry lies in the arrays, and its score
+            bool isnew[FAST_BATCH], in[FAST_BATCH];
+            bool bad_page = false;
+#pragma unroll
+            for (int u = 0; u < FAST_BATCH; ++u) {
+                const uint32_t i = b0 + u * 64 + lane;
+                in[u] = i < i1;
+                if (in[u])
+                    while (i >= s_before[sl] + s_len[sl]) ++sl;
+                seg[u] = sl;
+                jj[u] = in[u] ? (int)(i - s_before[sl]) : 0;
+                isnew[u] = STEP && in[u] && jj[u] >= (int)s_old[sl];
+                SegView v{};
+                v.start = PAGED ? (int64_t)(g0 + sl) * sa.pg.max_pps : (int64_t)s_start[sl];
+                sat[u] = in[u] ? ks.place(v, jj[u], &bad_page) : 0;
+                at[u] = isnew[u] ? (int64_t)(g0 + sl) * sa.n_new + (jj[u] - (int)s_old[sl]) : sat[u];
+            }
+            if (PAGED && bad_page) atomicOr(ws.err, ERR_LAYOUT);
+            float lbv[FAST_BATCH], ltv[FAST_BATCH];
+#pragma unroll
+            for (int u = 0; u < FAST_BATCH; ++u) {
+                pv[u] = in[u] ? (isnew[u] ? sa.pos_new : c.pos)[at[u]] : 0;
+                lbv[u] = in[u] ? (isnew[u] ? sa.lb_new : c.log_beta)[at[u]] : 0.f;
+                ltv[u] = (in[u] && c.log_tail) ? (isnew[u] ? sa.lt_new : c.log_tail)[at[u]] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < FAST_BATCH; ++u) {
+                const float dt = (float)(ks.t1 - pv[u]);
+                sv[u] = c.log_tail ? __fmaf_rn(dt, lbv[u], ltv[u]) : __fmul_rn(dt, lbv[u]);
+                if (PAGED && pv[u] < 0) sv[u] = 0.f;              // an empty slot's score reads 0
+                if (in[u]) score_out[sat[u]] = sv[u];
+                const uint32_t k2 = key_of_score(sv[u]);
+                const bool live = in[u] && (!PAGED || pv[u] >= 0);
+                if (live) mn = min(mn, k2);
+                if (live && k2 < hi) {
+                    const int slot = atomicAdd(&s_ncand, 1);
+                    if (slot < STAGE) {
+                        c_key[slot] = k2;
+                        c_pos[slot] = pv[u];
+                        c_seg[slot] = g0 + seg[u];
+                        if (STEP) c_idx[slot] = jj[u];
+                    }
+                }
+            }
+        }
+        min_key = block_min_u32(mn, sm.red_u);                    // (its barriers also complete s_ncand and the staged entries)
+        n_list = (uint32_t)s_ncand;
+        sub_overflow = n_list > (uint32_t)STAGE;
+#pragma unroll
+        for (int u = 0; u < FAST_ITEMS; ++u) {
+            const int i = u * FAST_THREADS + tid;
+            valid[u] = !sub_overflow && (uint32_t)i < n_list;
+            listed[u] = valid[u];
+            key[u] = valid[u] ? c_key[i] : 0u;
+            sg[u] = valid[u] ? c_seg[i] : 0;
+            ps[u] = valid[u] ? c_pos[i] : 0;
+            ix[u] = STEP && valid[u] ? c_idx[i] : 0;
+        }
+    }
     // ---- every entry of this block's share: score, and onto the list if its key is below the bound
-    {
+    if constexpr (!WHOLE) {
         uint32_t mn = 0xFFFFFFFFu;
         SegView sv0 = own;
         int seg = own_seg, first = part * threads + gt, stride = bps * threads;
@@ -643,6 +792,20 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
             }
         }
     }
+    uint32_t slot_sub[FAST_ITEMS], slot_idx[FAST_ITEMS], word = 0;
+    const int lane = lane_id();
+    // slot i of the flat list buffer; a wavefront takes 256 in a row - one sub-list of a full-size list, of which the first
+    // 128 are asked for before its counter is known and the rest only if it reaches them
+    auto load_slot = [&](int u) {
+        const uint32_t i = (uint32_t)((tid >> 6) * (64 * FAST_ITEMS) + u * 64 + lane);
+        if (i < cap && slot_sub[u] < (uint32_t)nsub) {
+            key[u] = ld_dev(&lk[i]);
+            sg[u] = ld_dev(&ls[i]);
+            ps[u] = ld_dev(&lp[i]);
+            if (STEP) ix[u] = ld_dev(&li[i]);
+        }
+    };
+    if constexpr (!WHOLE) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");              // this thread's list entries are acknowledged ...
     __syncthreads();                                              // ... and so are the whole block's, before it arrives
     if (tid == 0) {
@@ -667,24 +830,9 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     // and one for the destination, the counters a lane per word, no reduction for the key range (256 segments of 4096
     // entries, the whole kernel: 28.6 -> 22.8 us; 16 segments of 65: 21.5 -> 15.6).
     // (a lane per word: 0..15 the sub-lists' counters, 16..31 the groups' lowest keys)
-    const int lane = lane_id();
-    uint32_t word = 0xFFFFFFFFu;
+    word = 0xFFFFFFFFu;
     if (lane < FAST_SUB) word = lane < nsub ? ld_dev(&sub_count[lane * wstride]) : 0u;
     else if (lane < 2 * FAST_SUB) word = ld_dev(&grp_min[(lane - FAST_SUB) * wstride]);
-    uint32_t key[FAST_ITEMS];
-    int sg[FAST_ITEMS], ps[FAST_ITEMS], ix[FAST_ITEMS];
-    uint32_t slot_sub[FAST_ITEMS], slot_idx[FAST_ITEMS];
-    // slot i of the flat list buffer; a wavefront takes 256 in a row - one sub-list of a full-size list, of which the first
-    // 128 are asked for before its counter is known and the rest only if it reaches them
-    auto load_slot = [&](int u) {
-        const uint32_t i = (uint32_t)((tid >> 6) * (64 * FAST_ITEMS) + u * 64 + lane);
-        if (i < cap && slot_sub[u] < (uint32_t)nsub) {
-            key[u] = ld_dev(&lk[i]);
-            sg[u] = ld_dev(&ls[i]);
-            ps[u] = ld_dev(&lp[i]);
-            if (STEP) ix[u] = ld_dev(&li[i]);
-        }
-    };
 #pragma unroll
     for (int u = 0; u < FAST_ITEMS; ++u) {
         const uint32_t i = (uint32_t)((tid >> 6) * (64 * FAST_ITEMS) + u * 64 + lane);
@@ -694,46 +842,16 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         sg[u] = ps[u] = ix[u] = 0;
         if (u < FAST_ITEMS / 2) load_slot(u);
     }
+    }
     int64_t bud = budget[seq];
     const int64_t bud_other = STEP && tid < sh.n_seq ? budget[tid] : 0;   // (n_seq <= FAST_THREADS in a STEP)
-    const int g0 = seq * sh.segs_per_seq;
-    int64_t cnt = 0;
     int64_t step_before = 0, step_total = 0;                      // STEP: destination entries before this sequence / of all sequences
     int step_chunks_before = 0;                                   // STEP: chunks of the sequences before this one
     int my_len = 0;                                               // STEP: length and start of segment g0 + tid (one segment of the sequence per thread)
     uint32_t my_start = 0;
     int32_t step_cex = 0, step_ctot = 0;                          // STEP: chunks of the sequence's segments before that one / of all of them
     if (STEP) {
-        // One scan over the segments of the batch (1024 at a time): entries and chunks before each, so the entries of every
-        // sequence (the destination of a sequence starts behind all earlier ones) and this sequence's part of the tables
-        // fall out of it.  (The staging space is free once the block has arrived; entries of a cache are below 2^31.)
-        uint32_t* s_len = reinterpret_cast<uint32_t*>(s_pool) + FAST_STAGE;   // per segment of this sequence
-        uint32_t* s_chb = reinterpret_cast<uint32_t*>(s_pool) + 2 * FAST_STAGE;
-        uint32_t* s_start = reinterpret_cast<uint32_t*>(s_pool) + 3 * FAST_STAGE;
-        uint64_t carry = 0;                                       // entries in the upper, chunks in the lower 28 bits
-        for (int base = 0; base < sh.nseg; base += FAST_THREADS) {
-            const int g = base + tid;
-            uint64_t v = 0;
-            int vlen = 0;
-            if (g < sh.nseg) {
-                bool b2 = false, n2 = false;
-                const SegView sv = seg_view<KIND>(c, g, sh.nseg, sa, &b2, &n2);
-                vlen = sv.len;
-                if (g >= g0 && g < g0 + sh.segs_per_seq) s_start[g - g0] = (uint32_t)sv.start;
-                v = (uint64_t)vlen << 28 | (uint64_t)((vlen + CMP_CHUNK - 1) / CMP_CHUNK);
-            }
-            uint64_t tot;
-            const uint64_t ex = carry + block_excl_scan<uint64_t>(v, reinterpret_cast<uint64_t*>(sm.lds64), &tot);
-            carry += tot;
-            if (g < sh.nseg && g % sh.segs_per_seq == 0) s_seqcnt[g / sh.segs_per_seq] = (int)(uint32_t)(ex >> 28);
-            if (g >= g0 && g < g0 + sh.segs_per_seq) {
-                kept_out[g] = 0;
-                s_len[g - g0] = (uint32_t)vlen;
-                s_chb[g - g0] = (uint32_t)(ex & 0xFFFFFFFu);
-            }
-        }
-        if (tid == 0) s_seqcnt[sh.n_seq] = (int)(uint32_t)(carry >> 28);
-        __syncthreads();
+        if (!WHOLE) step_tables();
         step_chunks_before = (int)s_chb[0];
         if (tid < sh.segs_per_seq) {
             my_len = (int)s_len[tid];
@@ -761,7 +879,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         // (write-through: the counts are added with device-scope atomics) complete while the candidates are ranked.
         if (sa.inplace || step_total <= sa.dst.cap)
             for (int i = tid; i < step_ctot; i += FAST_THREADS) st_dev(&ws.step_chunk_ev[step_chunks_before + i], 0u);
-    } else {
+    } else if (!WHOLE) {
         for (int g = g0 + tid; g < g0 + sh.segs_per_seq; g += FAST_THREADS) {
             bool b2 = false, n2 = false;
             cnt += seg_view<KIND>(c, g, sh.nseg, sa, &b2, &n2).live;
@@ -769,8 +887,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         }
     }
     if (bud < 0) bud = 0;
-    bool sub_overflow = false;
-    uint32_t n_list = 0, min_key = 0xFFFFFFFFu;
+    if constexpr (!WHOLE) {
 #pragma unroll
     for (int i = 0; i < FAST_SUB; ++i) {
         const uint32_t n = (uint32_t)__builtin_amdgcn_readlane((int)word, i);
@@ -778,7 +895,6 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         n_list += n > subcap ? subcap : n;
         min_key = min(min_key, (uint32_t)__builtin_amdgcn_readlane((int)word, FAST_SUB + i));
     }
-    bool valid[FAST_ITEMS], listed[FAST_ITEMS];
 #pragma unroll
     for (int u = 0; u < FAST_ITEMS; ++u) {
         const uint32_t n_here = (uint32_t)__shfl((int)word, (int)min(slot_sub[u], (uint32_t)FAST_SUB - 1), 64);
@@ -786,10 +902,11 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         listed[u] = valid[u];
         if (u >= FAST_ITEMS / 2 && __any(valid[u])) load_slot(u);
     }
+    }
     // every listed key lies in [lowest key of the sequence, bound): no reduction over the list is needed
     uint32_t lo = min_key, hi_k = hi - 1u;
     __syncthreads();                                              // every thread has read the per-call words
-    if (tid <= FAST_SUB) {                                        // ... which go back to "between calls"
+    if (!WHOLE && tid <= FAST_SUB) {                              // ... which go back to "between calls"
         atomicExch(&done[tid * wstride], 0u);
         if (tid < FAST_SUB) {
             atomicExch(&sub_count[tid * wstride], 0u);
@@ -1183,23 +1300,46 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_mask(CacheView c, const f
 // Of a long segment its own threads walk twice the mean capacity of a segment, and two batches at least; a whole number of
 // pages, so that a wavefront's entries stay in one.
 struct ScanGrid {
-    int bps, spb, limit;
+    int deal, bps, spb, limit;
     unsigned blocks;
 };
-static ScanGrid scan_grid(const Shape& sh, int64_t cap, int resident) {
+// A whole sequence to a block, which then neither lists its candidates in memory nor meets other blocks: up to a batch of
+// FAST_BATCH entries for every lane of its wavefronts.  One-call steps in us, against a block per segment or several
+// segments to a block: 16 lists of 65 entries 24.2 / 26.6, 64 of 101 27.2 / 29.2, 4 of 1901 25.9 / 29.4, eight sequences
+// of 16 lists of 501 38.5 / 40.9; but with two batches the walk has no other blocks to hide behind: 2 x 18 lists of 1152
+// 38.3 / 34.9, 88 lists of 297 35.2 / 28.8.  The capacity in all is bounded because nothing says that a batch's
+// sequences are alike: the longest may be all of it.
+constexpr int64_t WHOLE_ENTRIES = FAST_THREADS * FAST_BATCH, WHOLE_CAP = 8 * WHOLE_ENTRIES;
+static bool scan_whole(const Shape& sh, int64_t cap, int64_t max_pps) {
+    if (sh.segs_per_seq > STEP_MAX_SEGS || sh.n_seq > STEP_MAX_SEQS || cap / sh.n_seq > WHOLE_ENTRIES || cap > WHOLE_CAP) return false;
+    return sh.segs_per_seq * max_pps < 1 << 24;                   // (a sequence's slots are counted in 32 bits)
+}
+static ScanGrid scan_grid(const Shape& sh, int64_t cap, int resident, bool whole, int64_t max_pps = 0) {
     ScanGrid g;
+    if (whole && scan_whole(sh, cap, max_pps)) return ScanGrid{DEAL_WHOLE, 1, 1, 0, (unsigned)sh.n_seq};
     const int64_t bps = cap / ((int64_t)sh.nseg * FAST_ENTRIES_PER_BLOCK);
     g.bps = (int)(bps < 1 ? 1 : (bps > 64 ? 64 : bps));
     g.spb = 1;
     auto per_seq = [&](int spb) { return (int64_t)((sh.segs_per_seq + spb - 1) / spb); };
     while (bps < 1 && g.spb < FAST_THREADS / 64 && sh.n_seq * per_seq(g.spb) > resident && 2 * g.spb <= sh.segs_per_seq) g.spb *= 2;
     g.blocks = (unsigned)(sh.n_seq * per_seq(g.spb) * g.bps);
+    g.deal = g.spb > 1 ? DEAL_MULTI : DEAL_SEGMENT;
     // (several to a block: a mean below FAST_ENTRIES_PER_BLOCK, so the limit is below 2^15)
     const int64_t mean2 = 2 * (cap / sh.nseg), batches = 2 * (FAST_THREADS / g.spb) * FAST_BATCH;
     g.limit = g.spb == 1 ? 0 : (int)(((mean2 > batches ? mean2 : batches) + KVTRIM_PAGE_SIZE - 1) / KVTRIM_PAGE_SIZE * KVTRIM_PAGE_SIZE);
     return g;
 }
 constexpr int SCAN_RESIDENT = 256, MASK_RESIDENT = 512;
+
+template <int KIND>
+static void launch_scan(const ScanGrid& g, const CacheView& c, const int32_t* now, float* score, const int64_t* budget, const Shape& sh,
+                        const Workspace& ws, int32_t* kept, uint32_t* thr, const StepArgs& sa, unsigned more_blocks, hipStream_t st) {
+#define KVTRIM_DEAL(d) hipLaunchKernelGGL((k_fast_scan<true, KIND, d>), dim3(g.blocks + more_blocks), dim3(FAST_THREADS), 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, g.bps, g.spb, g.limit, kept, thr, sa)
+    if (g.deal == DEAL_WHOLE) KVTRIM_DEAL(DEAL_WHOLE);
+    else if (g.deal == DEAL_MULTI) KVTRIM_DEAL(DEAL_MULTI);
+    else KVTRIM_DEAL(DEAL_SEGMENT);
+#undef KVTRIM_DEAL
+}
 
 kvtrim_status launch_score_select(kvtrim_ctx* ctx, const CacheView& c, const int32_t* now, const int64_t* budget,
                                   float* score, uint8_t* keep, int32_t* kept, uint32_t* thr, int64_t evict_hint,
@@ -1210,12 +1350,11 @@ kvtrim_status launch_score_select(kvtrim_ctx* ctx, const CacheView& c, const int
     if (evict_hint <= 0 || 8 * (evict_hint + 1) > (int64_t)ws.fl_cap)
         return launch_score_select_general(ctx, c, now, budget, score, keep, kept, thr, st);
     const dim3 block(FAST_THREADS);
-    const ScanGrid sg = scan_grid(sh, c.cap, SCAN_RESIDENT);
+    const ScanGrid sg = scan_grid(sh, c.cap, SCAN_RESIDENT, true);
     { ProfScope prof(ctx, K_FAST_SCAN, st);
-      if (sg.spb > 1) hipLaunchKernelGGL((k_fast_scan<true, SCAN_RAGGED, true>), dim3(sg.blocks), block, 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, sg.limit, kept, thr, StepArgs());
-      else hipLaunchKernelGGL((k_fast_scan<true, SCAN_RAGGED, false>), dim3(sg.blocks), block, 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, sg.limit, kept, thr, StepArgs()); }
+      launch_scan<SCAN_RAGGED>(sg, c, now, score, budget, sh, ws, kept, thr, StepArgs(), 0, st); }
     { ProfScope prof(ctx, K_FAST_MASK, st);
-      const ScanGrid mg = scan_grid(sh, c.cap, MASK_RESIDENT);
+      const ScanGrid mg = scan_grid(sh, c.cap, MASK_RESIDENT, false);
       if (mg.spb > 1) hipLaunchKernelGGL((k_fast_mask<false, false, true>), dim3(mg.blocks), block, 0, st, c, (const float*)score, sh, ws, mg.bps, mg.spb, mg.limit, keep, kept, PagedArgs());
       else hipLaunchKernelGGL((k_fast_mask<false, false, false>), dim3(mg.blocks), block, 0, st, c, (const float*)score, sh, ws, mg.bps, mg.spb, mg.limit, keep, kept, PagedArgs()); }
     KVTRIM_HIP(ctx, hipGetLastError());
@@ -1230,12 +1369,11 @@ kvtrim_status launch_score_select_paged(kvtrim_ctx* ctx, const CacheView& pool, 
     const Shape& sh = ctx->shape;
     const Workspace& ws = ctx->ws;
     const dim3 block(FAST_THREADS);
-    const ScanGrid sg = scan_grid(sh, pool.cap, SCAN_RESIDENT), mg = scan_grid(sh, pool.cap, MASK_RESIDENT);
+    const ScanGrid sg = scan_grid(sh, pool.cap, SCAN_RESIDENT, true, pg.max_pps), mg = scan_grid(sh, pool.cap, MASK_RESIDENT, false);
     StepArgs sa{};
     sa.pg = pg;
     { ProfScope prof(ctx, K_FAST_SCAN, st);
-      if (sg.spb > 1) hipLaunchKernelGGL((k_fast_scan<true, SCAN_PAGED, true>), dim3(sg.blocks), block, 0, st, pool, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, sg.limit, kept, thr, sa);
-      else hipLaunchKernelGGL((k_fast_scan<true, SCAN_PAGED, false>), dim3(sg.blocks), block, 0, st, pool, now, (const float*)nullptr, score, budget, sh, ws, sg.bps, sg.spb, sg.limit, kept, thr, sa); }
+      launch_scan<SCAN_PAGED>(sg, pool, now, score, budget, sh, ws, kept, thr, sa, 0, st); }
     { ProfScope prof(ctx, K_FAST_MASK, st);
       if (evict)
           { if (mg.spb > 1) hipLaunchKernelGGL((k_fast_mask<true, true, true>), dim3(mg.blocks), block, 0, st, pool, (const float*)score, sh, ws, mg.bps, mg.spb, mg.limit, keep, kept, pg);
@@ -1251,13 +1389,10 @@ kvtrim_status launch_score_select_paged(kvtrim_ctx* ctx, const CacheView& pool, 
 kvtrim_status launch_step_scan(kvtrim_ctx* ctx, const CacheView& c, const int32_t* now, const int64_t* budget, float* score,
                                int32_t* kept, uint32_t* thr, const StepArgs& sa, hipStream_t st) {
     const Shape& sh = ctx->shape;
-    const ScanGrid sg = scan_grid(sh, c.cap, SCAN_RESIDENT);
+    const ScanGrid sg = scan_grid(sh, c.cap, SCAN_RESIDENT, true);
     const unsigned tables = (unsigned)((sh.nseg + FAST_THREADS / 64 - 1) / (FAST_THREADS / 64));
     ProfScope prof(ctx, K_FAST_SCAN, st);
-    if (sg.spb > 1) hipLaunchKernelGGL((k_fast_scan<true, SCAN_STEP, true>), dim3(sg.blocks + tables), dim3(FAST_THREADS), 0, st, c, now,
-                       (const float*)nullptr, score, budget, sh, ctx->ws, sg.bps, sg.spb, sg.limit, kept, thr, sa);
-    else hipLaunchKernelGGL((k_fast_scan<true, SCAN_STEP, false>), dim3(sg.blocks + tables), dim3(FAST_THREADS), 0, st, c, now,
-                       (const float*)nullptr, score, budget, sh, ctx->ws, sg.bps, sg.spb, sg.limit, kept, thr, sa);
+    launch_scan<SCAN_STEP>(sg, c, now, score, budget, sh, ctx->ws, kept, thr, sa, tables, st);
     KVTRIM_HIP(ctx, hipGetLastError());
     return KVTRIM_OK;
 }

@@ -341,3 +341,43 @@ def test_long_segments_among_several_to_a_scanning_block(S, L, H, long_lens):
         assert r["status"] == 0 and r["score_equal"] and r["keep_equal"] and r["cache_equal"], (S, "score_select", r)
     check_paged(run_paged_both(w, [budget] * 2, device=DEV, cache_dict=clone(), now0=now.numpy(), hint=L * H))
     check_paged(run_paged_both(w, [budget] * 2, device=DEV, cache_dict=clone(), now0=now.numpy(), hint=L * H, one_call=True))
+
+
+# A sequence to a block up to 8192 entries of capacity per sequence and 65536 in all: both sides of the line, everything in
+# one segment, empty segments first and last, uneven sequences (several batches of a wavefront), as many segments as a step
+# may have.
+@pytest.mark.parametrize("S,L,H,lens,cap", [
+    (1, 2, 4, [0, 7000, 1, 63, 0, 64, 65, 0], 8192), (1, 2, 4, [0, 7000, 1, 63, 0, 64, 65, 0], 8193),
+    (3, 1, 5, [0, 0, 19000, 700, 30] + [1, 0, 2, 3, 0] + [0, 0, 0, 0, 130], 3 * 8192),
+    (1, 64, 16, [0, 1, 7, 13, 2, 5, 0, 3], 8192), (8, 2, 2, [300, 129, 128, 127], 65536), (8, 2, 2, [300, 129, 128, 127], 65537)])
+def test_a_sequence_to_a_scanning_block(S, L, H, lens, cap):
+    from paged_harness import run_paged_both
+    from test_gpu_paged import check as check_paged
+    w = wl(S, L, H, 2, 64)
+    seg_len = np.resize(np.array(lens), w.nseg)
+    c, now = ki.ragged_cache(w, seg_len, reserve=1, salt=S + cap)
+    for name in ("k", "v", "log_beta", "pos"):                    # free entries behind the last segment: the capacity decides
+        pad = torch.zeros((cap - c["cap"],) + c[name].shape[1:], dtype=c[name].dtype)
+        c[name] = torch.cat([c[name], pad])
+    c["cap"] = cap
+    budget = [max(1, int(seg_len[s * L * H:(s + 1) * L * H].sum()) - L * H // 2) for s in range(S)]
+
+    def clone():
+        return {k: (v.clone() if torch.is_tensor(v) else v) for k, v in c.items()}
+    check(run_steps_both(w, steps=4, budget=budget, device=DEV, cache_dict=clone(), now0=now.numpy(), one_call=True, hint=min(400, L * H)), (S, "step"))
+    for r in run_steps_both(w, steps=3, budget=budget, device=DEV, cache_dict=clone(), now0=now.numpy(), fused=True, hint=min(400, L * H)):
+        assert r["status"] == 0 and r["score_equal"] and r["keep_equal"] and r["cache_equal"], (S, "score_select", r)
+    check_paged(run_paged_both(w, [budget] * 3, device=DEV, cache_dict=clone(), now0=now.numpy(), hint=min(400, L * H)))
+    check_paged(run_paged_both(w, [budget] * 3, device=DEV, cache_dict=clone(), now0=now.numpy(), hint=min(400, L * H), one_call=True))
+
+
+@pytest.mark.parametrize("evictions,listed", [(490, True), (490, False)])
+def test_many_candidates_of_a_sequence_in_a_scanning_block(evictions, listed):
+    # about 1490 candidates in the block's LDS; with all scores alike the list is of no use and the single-block select runs
+    from test_gpu_score_select import select_repeatedly
+    w = wl(3, 1, 16, 1, 64)
+    lens = np.random.default_rng(3).integers(300, 400, w.nseg)
+    rng = np.random.default_rng(4)
+    log_beta = (lambda cap, start: -rng.random(cap)) if listed else (lambda cap, start: np.zeros(cap))
+    counts = select_repeatedly(w, lens, log_beta, evictions, 3)
+    assert sum(counts) == 9 and (counts == (9, 0) or not listed)
