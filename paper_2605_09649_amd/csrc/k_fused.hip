@@ -23,7 +23,7 @@
 // The same kernel has an instance that compacts INSIDE the cache (segments keep their starts; only the rows
 // behind an eviction move), followed by k_cmp_unstage; k_cmp_move_inplace is that instance without the
 // attention (it is bracketed under the row mover's name, k_cmp_copy, when kernels are timed).
-#include "kvtrim_device.h"
+#include "kvtrim_merge_device.h"
 
 namespace kvtrim {
 
@@ -102,12 +102,16 @@ __device__ __forceinline__ float row16_sum(float x) {
 // the source row of every destination row (ws.gat_src, 128 slots per chunk, the slots behind a ragged chunk's last
 // row naming a live row), so a block asks for its row numbers at once, together with its descriptor, and for the
 // rows as soon as the numbers are there; neither the mask nor the source's chunk table is read.
-template <int D, int G, bool INPLACE, bool STEP = false, bool GATHER = false>
+// MERGE (out of place): the last chunk of a segment to finish merges the segment's partial results, and a
+// segment of one chunk has none: no launch of k_att_combine.
+template <int D, int G, bool INPLACE, bool STEP = false, bool GATHER = false, bool MERGE = false>
 __global__ __launch_bounds__(FUS_THREADS) void k_cmp_attn(CacheView src, const uint8_t* keep,
                                                           CacheViewMut dst, CacheViewMut stage,
                                                           const uint16_t* __restrict__ q,
                                                           Shape sh, Workspace ws, float scale_log2,
-                                                          int layer_begin, int layer_end, int32_t* step_seg_len = nullptr) {
+                                                          int layer_begin, int layer_end, int32_t* step_seg_len = nullptr,
+                                                          float* __restrict__ out = nullptr, float* __restrict__ lse = nullptr) {
+    static_assert(!MERGE || !INPLACE, "in place the rows parked by the mover need another launch anyway");
     static_assert(!(GATHER && (INPLACE || STEP)), "the gathering instance compacts out of place, from a keep mask");
     typedef Row<D> R;
     typedef typename R::vec vec;
@@ -137,7 +141,16 @@ __global__ __launch_bounds__(FUS_THREADS) void k_cmp_attn(CacheView src, const u
         if (tid < CMP_CHUNK) gat_md = slots[tid];
     }
     if (__hip_atomic_load(ws.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
-    if (ch >= (GATHER ? ws.att_chunk_prefix : ws.cmp_chunk_prefix)[sh.nseg]) return;
+    const int32_t* chunk_prefix = GATHER ? ws.att_chunk_prefix : ws.cmp_chunk_prefix;
+    if (MERGE && ch < sh.nseg) {                                  // (the grid has a block for every segment at least) no chunk: nothing retained
+        const int lh0 = ch % sh.segs_per_seq;
+        if (chunk_prefix[ch] == chunk_prefix[ch + 1] && lh0 >= layer_begin * sh.n_kv_heads && lh0 < layer_end * sh.n_kv_heads) {
+            const int64_t hq = q_row_of<G>(ch, sh);
+            for (int i = tid; i < G * D; i += FUS_THREADS) out[hq * D + i] = 0.f;
+            if (lse && tid < G) lse[hq + tid] = -INFINITY;
+        }
+    }
+    if (ch >= chunk_prefix[sh.nseg]) return;
     const int64_t sbase = GATHER ? 0 : cd.first;                  // (GATHER: row numbers are absolute)
     // STEP: the scoring kernel leaves no destination per chunk (one block would write 16 K of them) but a record per
     // SEGMENT - where the segment's survivors start and which of its entries go - from which the chunk's block
@@ -240,6 +253,7 @@ __global__ __launch_bounds__(FUS_THREADS) void k_cmp_attn(CacheView src, const u
     const int seq = seg / sh.segs_per_seq, lh = seg % sh.segs_per_seq;
     const int layer = lh / sh.n_kv_heads, head = lh % sh.n_kv_heads;
     const bool attend = layer >= layer_begin && layer < layer_end;   // uniform over the block
+    const int first_ch = MERGE ? chunk_prefix[seg] : 0, n_ch = MERGE ? chunk_prefix[seg + 1] - first_ch : 0;
     const int sub = lane >> 4, col = lane & 15;
     const int r0 = wave * CMP_WAVE_ROWS;                          // this wavefront's rows of the survivor list
     const bool has_rows = r0 < cnt;                               // uniform over the wavefront
@@ -422,21 +436,45 @@ __global__ __launch_bounds__(FUS_THREADS) void k_cmp_attn(CacheView src, const u
                 lsum += s_l[s][g] * w;
             }
         }
-        part[g * (D + 2) + 2 + d] = accd;
-        if (d == 0) {
-            part[g * (D + 2)] = M;
-            part[g * (D + 2) + 1] = lsum;
+        if (MERGE && n_ch == 1) {
+            const int64_t hq = q_row_of<G>(seg, sh) + g;
+            out[hq * D + d] = lsum > 0.f ? accd / lsum : 0.f;
+            if (d == 0 && lse) lse[hq] = lsum > 0.f ? (M + __builtin_amdgcn_logf(lsum)) * 0.6931471805599453f : -INFINITY;
+            continue;
         }
+        auto put = [](float* p, float v) {
+            if (MERGE) put_shared(p, v);
+            else *p = v;
+        };
+        put(&part[g * (D + 2) + 2 + d], accd);
+        if (d == 0) {
+            put(&part[g * (D + 2)], M);
+            put(&part[g * (D + 2) + 1], lsum);
+        }
+    }
+    if constexpr (MERGE) {
+        if (n_ch == 1) return;
+        __shared__ int s_last;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this thread's part of the result has been acknowledged ...
+        __syncthreads();                                          // ... and so has the block's
+        if (tid == 0) s_last = atomicAdd(&ws.att_done[seg * ATT_DONE_STRIDE], 1u) == (unsigned)n_ch - 1u;
+        __syncthreads();
+        if (!s_last) return;
+        if (tid == 0) __hip_atomic_store(&ws.att_done[seg * ATT_DONE_STRIDE], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        merge_shared<D, G, FUS_THREADS>(ws.att_partial + (size_t)first_ch * G * (D + 2), n_ch, q_row_of<G>(seg, sh), &s_o[0][0][0], out, lse);
     }
 }
 
 template <int D, bool INPLACE>
 static bool dispatch_fused(int G, dim3 grid, hipStream_t st, const CacheView& src, const uint8_t* keep,
                            const CacheViewMut& dst, const CacheViewMut& stage, const uint16_t* q, const Shape& sh,
-                           const Workspace& ws, float scale_log2, int lb, int le) {
+                           const Workspace& ws, float scale_log2, int lb, int le, bool merge = false, float* out = nullptr, float* lse = nullptr) {
     switch (G) {
 #define KVTRIM_CASE(g) \
-    case g: hipLaunchKernelGGL((k_cmp_attn<D, g, INPLACE>), grid, dim3(FUS_THREADS), 0, st, src, keep, dst, stage, q, sh, ws, scale_log2, lb, le); return true;
+    case g: \
+        if (!INPLACE && merge) hipLaunchKernelGGL((k_cmp_attn<D, g, false, false, false, !INPLACE>), grid, dim3(FUS_THREADS), 0, st, src, keep, dst, stage, q, sh, ws, scale_log2, lb, le, nullptr, out, lse); \
+        else hipLaunchKernelGGL((k_cmp_attn<D, g, INPLACE>), grid, dim3(FUS_THREADS), 0, st, src, keep, dst, stage, q, sh, ws, scale_log2, lb, le); \
+        return true;
         KVTRIM_CASE(1) KVTRIM_CASE(2) KVTRIM_CASE(3) KVTRIM_CASE(4) KVTRIM_CASE(5) KVTRIM_CASE(6) KVTRIM_CASE(7) KVTRIM_CASE(8)
 #undef KVTRIM_CASE
         default: return false;
@@ -444,11 +482,14 @@ static bool dispatch_fused(int G, dim3 grid, hipStream_t st, const CacheView& sr
 }
 
 template <int D>
-static bool dispatch_gather(int G, dim3 grid, hipStream_t st, const CacheView& src, const CacheViewMut& dst,
-                            const uint16_t* q, const Shape& sh, const Workspace& ws, float scale_log2, int lb, int le) {
+static bool dispatch_gather(int G, dim3 grid, hipStream_t st, const CacheView& src, const CacheViewMut& dst, const uint16_t* q,
+                            const Shape& sh, const Workspace& ws, float scale_log2, int lb, int le, bool merge, float* out, float* lse) {
     switch (G) {
 #define KVTRIM_CASE(g) \
-    case g: hipLaunchKernelGGL((k_cmp_attn<D, g, false, false, true>), grid, dim3(FUS_THREADS), 0, st, src, nullptr, dst, dst, q, sh, ws, scale_log2, lb, le); return true;
+    case g: \
+        if (merge) hipLaunchKernelGGL((k_cmp_attn<D, g, false, false, true, true>), grid, dim3(FUS_THREADS), 0, st, src, nullptr, dst, dst, q, sh, ws, scale_log2, lb, le, nullptr, out, lse); \
+        else hipLaunchKernelGGL((k_cmp_attn<D, g, false, false, true>), grid, dim3(FUS_THREADS), 0, st, src, nullptr, dst, dst, q, sh, ws, scale_log2, lb, le); \
+        return true;
         KVTRIM_CASE(1) KVTRIM_CASE(2) KVTRIM_CASE(3) KVTRIM_CASE(4) KVTRIM_CASE(5) KVTRIM_CASE(6) KVTRIM_CASE(7) KVTRIM_CASE(8)
 #undef KVTRIM_CASE
         default: return false;
@@ -596,6 +637,18 @@ kvtrim_status launch_compact_inplace(kvtrim_ctx* ctx, const CacheViewMut& c, con
     return KVTRIM_OK;
 }
 
+// The row mover merges its partial results itself (MERGE) where that costs less than the launch of k_att_combine: a grid that
+// is on the chip at once - a block then lives 1.5 us longer, which more blocks would wait for (4 x 28 x 2 lists of 2048,
+// 3800 blocks: 114 -> 127 us a step) - and segments of few chunks, which one block reads back.  One-call steps in us, against
+// the launch: one chunk a segment 24.2 -> 21.2 (16 lists of 65, 2 heads, D = 64), 24.3 -> 22.3 (24 of 68, 7 heads); 7 chunks
+// 26.0 -> 24.8 (13 KB of results), 10 chunks 35.1 -> 33.9; 34 chunks, 8 heads (67 KB) 37.9 -> 39.6, a first eviction into
+// 32 such chunks 52.8 -> 62.  (What a segment longer than the others costs here it costs k_att_combine's block too.)
+constexpr int64_t MERGE_BLOCKS = 1024, MERGE_BYTES = 16384;
+static bool merges_itself(const Shape& sh, int64_t chunks) {
+    return sh.nseg <= ATT_MERGE_SEGS && chunks <= MERGE_BLOCKS &&
+           chunks / sh.nseg * sh.group * (sh.head_dim + 2) * (int64_t)sizeof(float) <= MERGE_BYTES;
+}
+
 kvtrim_status launch_compact_attn(kvtrim_ctx* ctx, const CacheView& src, const uint8_t* keep, const int32_t* kept,
                                   const CacheViewMut& dst, int32_t reserve, const uint16_t* q, int32_t layer_begin,
                                   int32_t layer_end, float scale, float* out, float* lse, hipStream_t st,
@@ -616,15 +669,20 @@ kvtrim_status launch_compact_attn(kvtrim_ctx* ctx, const CacheView& src, const u
         // (a block per source chunk would write one partial result per 128 source entries for a handful of survivors
         // each).  The compaction scan lists the destination's chunks and the source row of each of their rows.
         launch_cmp_scan_aligned(ctx, src, keep, kept, dst, reserve, 1, st, true);
+        const bool merge = merges_itself(sh, dst_chunks);
         bool ok;
         {
             ProfScope prof(ctx, K_CMP_ATTN, st);
             const float scale_log2 = scale * 1.4426950408889634f;
             ok = sh.head_dim == 128
-                     ? dispatch_gather<128>(sh.group, dim3((unsigned)dst_chunks), st, src, dst, q, sh, ws, scale_log2, layer_begin, layer_end)
-                     : dispatch_gather<64>(sh.group, dim3((unsigned)dst_chunks), st, src, dst, q, sh, ws, scale_log2, layer_begin, layer_end);
+                     ? dispatch_gather<128>(sh.group, dim3((unsigned)dst_chunks), st, src, dst, q, sh, ws, scale_log2, layer_begin, layer_end, merge, out, lse)
+                     : dispatch_gather<64>(sh.group, dim3((unsigned)dst_chunks), st, src, dst, q, sh, ws, scale_log2, layer_begin, layer_end, merge, out, lse);
         }
         if (!ok) return KVTRIM_EINVAL;
+        if (merge) {
+            KVTRIM_HIP(ctx, hipGetLastError());
+            return KVTRIM_OK;
+        }
         return launch_combine(ctx, ws.att_chunk_prefix, layer_begin, layer_end, out, lse, dst_chunks, st);
     }
     if (max_chunks > ws.max_att_chunks || sparse) {
@@ -638,15 +696,20 @@ kvtrim_status launch_compact_attn(kvtrim_ctx* ctx, const CacheView& src, const u
         return launch_attn(ctx, d, nullptr, q, nullptr, layer_begin, layer_end, scale, out, lse, st);
     }
     launch_cmp_scan(ctx, src, keep, kept, dst, reserve, st);
+    const bool merge = merges_itself(sh, max_chunks);
     bool ok;
     {
         ProfScope prof(ctx, K_CMP_ATTN, st);
         const float scale_log2 = scale * 1.4426950408889634f;
         ok = sh.head_dim == 128
-                 ? dispatch_fused<128, false>(sh.group, dim3((unsigned)max_chunks), st, src, keep, dst, dst, q, sh, ws, scale_log2, layer_begin, layer_end)
-                 : dispatch_fused<64, false>(sh.group, dim3((unsigned)max_chunks), st, src, keep, dst, dst, q, sh, ws, scale_log2, layer_begin, layer_end);
+                 ? dispatch_fused<128, false>(sh.group, dim3((unsigned)max_chunks), st, src, keep, dst, dst, q, sh, ws, scale_log2, layer_begin, layer_end, merge, out, lse)
+                 : dispatch_fused<64, false>(sh.group, dim3((unsigned)max_chunks), st, src, keep, dst, dst, q, sh, ws, scale_log2, layer_begin, layer_end, merge, out, lse);
     }
     if (!ok) return KVTRIM_EINVAL;
+    if (merge) {
+        KVTRIM_HIP(ctx, hipGetLastError());
+        return KVTRIM_OK;
+    }
     return launch_combine(ctx, ws.cmp_chunk_prefix, layer_begin, layer_end, out, lse, max_chunks, st);
 }
 
@@ -696,6 +759,7 @@ kvtrim_status launch_decode_step(kvtrim_ctx* ctx, const CacheViewMut& srcm, cons
         return launch_compact_attn(ctx, src, sa.keep_out, kept, sa.dst, sa.reserve, q, layer_begin, layer_end, scale, out, lse, st,
                                    evict_hint);
     }
+    const bool merge = merges_itself(sh, max_chunks);
     kvtrim_status rc = launch_step_scan(ctx, src, now, budget, score, kept, thr, sa, st);
     if (rc != KVTRIM_OK) return rc;
     {
@@ -704,12 +768,19 @@ kvtrim_status launch_decode_step(kvtrim_ctx* ctx, const CacheViewMut& srcm, cons
         const dim3 grid((unsigned)max_chunks), block(FUS_THREADS);
         switch (sh.head_dim * 16 + sh.group) {
 #define KVTRIM_CASE(d, g) \
-    case d * 16 + g: hipLaunchKernelGGL((k_cmp_attn<d, g, false, true>), grid, block, 0, st, src, (const uint8_t*)sa.keep_out, sa.dst, sa.dst, q, sh, ws, scale_log2, layer_begin, layer_end, srcm.seg_len); break;
+    case d * 16 + g: \
+        if (merge) hipLaunchKernelGGL((k_cmp_attn<d, g, false, true, false, true>), grid, block, 0, st, src, (const uint8_t*)sa.keep_out, sa.dst, sa.dst, q, sh, ws, scale_log2, layer_begin, layer_end, srcm.seg_len, out, lse); \
+        else hipLaunchKernelGGL((k_cmp_attn<d, g, false, true>), grid, block, 0, st, src, (const uint8_t*)sa.keep_out, sa.dst, sa.dst, q, sh, ws, scale_log2, layer_begin, layer_end, srcm.seg_len); \
+        break;
             KVTRIM_CASE(128, 1) KVTRIM_CASE(128, 2) KVTRIM_CASE(128, 3) KVTRIM_CASE(128, 4) KVTRIM_CASE(128, 5) KVTRIM_CASE(128, 6) KVTRIM_CASE(128, 7) KVTRIM_CASE(128, 8)
             KVTRIM_CASE(64, 1) KVTRIM_CASE(64, 2) KVTRIM_CASE(64, 3) KVTRIM_CASE(64, 4) KVTRIM_CASE(64, 5) KVTRIM_CASE(64, 6) KVTRIM_CASE(64, 7) KVTRIM_CASE(64, 8)
 #undef KVTRIM_CASE
             default: return KVTRIM_EINVAL;
         }
+    }
+    if (merge) {
+        KVTRIM_HIP(ctx, hipGetLastError());
+        return KVTRIM_OK;
     }
     return launch_combine(ctx, ws.cmp_chunk_prefix, layer_begin, layer_end, out, lse, max_chunks, st);
 }

@@ -108,7 +108,8 @@ static Layout layout_of(const kvtrim_config* c, bool select_only) {
     l.off[38] = bump(cur, (size_t)l.gat_slots * sizeof(int32_t));              // gat_src
     l.off[39] = bump(cur, seg_tables * (size_t)(nseg + 1) * sizeof(int64_t));  // att_row_prefix
     l.off[40] = bump(cur, (size_t)c->n_layers * GATE_TOKEN_TILES * sizeof(uint32_t));   // gate_done
-    l.off[41] = bump(cur, seg_tables * (size_t)ATT_ONE_ORDS * ATT_DONE_STRIDE * sizeof(uint32_t));   // att_done
+    const int64_t done_segs = nseg < ATT_ONE_ORDS ? ATT_ONE_ORDS : (nseg < ATT_MERGE_SEGS ? nseg : ATT_MERGE_SEGS);
+    l.off[41] = bump(cur, seg_tables * (size_t)done_segs * ATT_DONE_STRIDE * sizeof(uint32_t));   // att_done
     l.total = (cur + 255) & ~(size_t)255;
     return l;
 }

@@ -381,3 +381,48 @@ def test_many_candidates_of_a_sequence_in_a_scanning_block(evictions, listed):
     log_beta = (lambda cap, start: -rng.random(cap)) if listed else (lambda cap, start: np.zeros(cap))
     counts = select_repeatedly(w, lens, log_beta, evictions, 3)
     assert sum(counts) == 9 and (counts == (9, 0) or not listed)
+
+
+# Small grids: the row mover's last block of a segment merges, a segment of one chunk (128 entries) has nothing to merge and
+# one without entries no block.  Up to 1024 blocks and 16 KB of results a segment on average (3 chunks at 8 heads, D = 128):
+# chunk counts on both sides, one long segment among short ones (four tiles of 16 results), a layer that is not attended.
+@pytest.mark.parametrize("S,L,H,G,D,lens,steps", [
+    (1, 2, 2, 8, 128, [128, 129, 256, 0], 4), (1, 2, 2, 8, 128, [300, 301, 250, 390], 3), (1, 1, 8, 8, 128, [0, 7500, 0, 0, 1, 2, 0, 40], 4),
+    (2, 1, 3, 4, 128, [127, 0, 128, 260, 1, 640], 5), (1, 1, 7, 3, 64, [0, 127, 126, 125, 1, 2, 0], 6), (5, 10, 20, 1, 64, [0, 40, 3, 130], 2)])
+def test_attention_merged_by_the_row_mover(S, L, H, G, D, lens, steps):
+    w = wl(S, L, H, G, D)
+    seg_len = np.resize(np.array(lens), w.nseg)
+    c, now = ki.ragged_cache(w, seg_len, reserve=1, salt=G + D)
+    budget = [max(1, int(seg_len[s * L * H:(s + 1) * L * H].sum()) - 3) for s in range(S)]
+    small = [max(1, n // 6) for n in budget]                      # the first eviction keeps few: the gathering form merges too
+
+    def clone():
+        return {k: (v.clone() if torch.is_tensor(v) else v) for k, v in c.items()}
+    check(run_steps_both(w, steps=steps, budget=budget, device=DEV, cache_dict=clone(), now0=now.numpy(), one_call=True, hint=L * H))
+    for b in (budget, small):
+        for r in run_steps_both(w, steps=steps, budget=b, device=DEV, cache_dict=clone(), now0=now.numpy(), fused=True, hint=0):
+            assert r["status"] == 0 and r["keep_equal"] and r["cache_equal"] and r["attn_err"] <= ATTN_TOL and r["lse_inf_equal"], r
+
+
+@pytest.mark.parametrize("layers", [(0, 1), (1, 3)])
+def test_the_row_mover_merges_the_layers_it_attends_only(layers):
+    w = wl(1, 3, 2, 4, 128)
+    c, now = ki.ragged_cache(w, [200, 0, 129, 60, 0, 300], reserve=1, salt=8)
+    hc = host_cache(w, c)
+    ctx = kv.Context(1, 3, 2, 8, 128, hc.cap)
+    src, dst = kv.Cache.from_dict(c, DEV), kv.Cache.empty(w.nseg, 128, hc.cap, DEV)
+    q = ki.decode_inputs(w, 0)["q"]
+    ref, ref_lse = oracle.attend(hc, bf16_bits(q), 0.1)
+    keep = torch.ones(hc.cap, dtype=torch.uint8, device=DEV)
+    kept = torch.tensor([200, 0, 129, 60, 0, 300], dtype=torch.int32, device=DEV)
+    out = torch.full(ref.shape, 99.0, dtype=torch.float32, device=DEV)
+    lse = torch.full(ref_lse.shape, 99.0, dtype=torch.float32, device=DEV)
+    for again in range(2):
+        kv.kvtrim_compact_attn(ctx, src, keep, kept, dst, 0, q.to(DEV), layers[0], layers[1], 0.1, out, lse)
+        assert kv.kvtrim_poll_error(ctx) == 0
+    o, l = out.cpu().numpy(), lse.cpu().numpy()
+    inside = list(range(*layers))
+    outside = [x for x in range(3) if x not in inside]
+    assert np.all(o[:, outside] == 99.0) and np.all(l[:, outside] == 99.0)
+    assert attn_error(o[:, inside], ref[:, inside]) <= ATTN_TOL
+    assert np.array_equal(np.isneginf(l[:, inside]), np.isneginf(ref_lse[:, inside]))
