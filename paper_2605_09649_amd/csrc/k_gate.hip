@@ -470,7 +470,19 @@ constexpr int GP_THREADS = 512, GP_HEADS_MAX = 8;
 constexpr int GP_MIN_TOK = 128;          // k_gate_prefill with the weight-only work in the call: below this it does not pay
 constexpr int GP_GROUP_BYTES = 272, GP_HALF_BYTES = 4 * GP_GROUP_BYTES, GP_TILE_BYTES = 2 * GP_HALF_BYTES;   // 272, 1088, 2176
 
-template <int HT, int TT, bool TILED>
+// Token rows are read once.  STREAM: past the caches, which then keep W1 (a layer's 4 MB are as much as an XCD's L2 holds); for
+// calls whose rows do not fit the 256 MB cache in front of the memory anyway.  32 layers of 512 units, d_model 4096: 4096
+// tokens (1.07 GB of rows) 491 -> 455 us, 2048 tokens 250 -> 230, 20 layers of 384 units 281 -> 247; but rows that a call
+// finds there are lost to it: 512 tokens (134 MB) 66 -> 71, 32 layers of 128 units at d_model 1024 (268 MB) 66 -> 81.
+constexpr size_t GP_STREAM_BYTES = 300u << 20;
+template <bool STREAM>
+__device__ __forceinline__ uint4 row_piece(const char* p) {
+    if (!STREAM) return *reinterpret_cast<const uint4*>(p);
+    const gate_u4 t = __builtin_nontemporal_load(reinterpret_cast<const gate_u4*>(p));
+    return make_uint4(t.x, t.y, t.z, t.w);
+}
+
+template <int HT, int TT, bool TILED, bool STREAM>
 __global__ __launch_bounds__(GP_THREADS) void k_gate_prefill(GateView g, const uint16_t* __restrict__ x, int n_tok,
                                                              int layer_begin, int nl, int n_layers, int n_heads, int horizon,
                                                              const uint4* __restrict__ tiled, const float* __restrict__ v,
@@ -543,10 +555,10 @@ __global__ __launch_bounds__(GP_THREADS) void k_gate_prefill(GateView g, const u
     auto load_x = [&](int kt) {                                      // the token rows of steps kt and kt + 1
         if (TT == 8 || loader) {
             const char* p = xbase + (size_t)kt * 128;
-            xr[0][0] = *reinterpret_cast<const uint4*>(p + xoff_a);
-            xr[0][1] = *reinterpret_cast<const uint4*>(p + xoff_b);
-            xr[1][0] = *reinterpret_cast<const uint4*>(p + xoff_a + 128);
-            xr[1][1] = *reinterpret_cast<const uint4*>(p + xoff_b + 128);
+            xr[0][0] = row_piece<STREAM>(p + xoff_a);
+            xr[0][1] = row_piece<STREAM>(p + xoff_b);
+            xr[1][0] = row_piece<STREAM>(p + xoff_a + 128);
+            xr[1][1] = row_piece<STREAM>(p + xoff_b + 128);
         }
     };
     auto park_x = [&](int buf) {                                     // buf: one of the three pair buffers
@@ -645,12 +657,25 @@ __global__ __launch_bounds__(GP_THREADS) void k_gate_prefill(GateView g, const u
 #pragma unroll
                 for (int r = 0; r < 4; ++r) zp[j] = fmaf(ww[r], acc[i][j][r], zp[j]);
         }
+        // sums over the four lane groups, two (then four) token tiles to a register: a swap of rows puts two tiles' values for the
+        // same token beside each other, so an addition serves both (shuffles through LDS, two for each tile, and a store of 16
+        // lanes for each: 4096 tokens 502 us, now 491; 32 layers of 128 units at d_model 1024 74, now 66)
+        float two[TT / 2];
 #pragma unroll
-        for (int j = 0; j < TT; ++j) {
-            float t = zp[j];
-            t += __shfl_xor(t, 16, 64);
-            t += __shfl_xor(t, 32, 64);
-            if (g4 == 0) s_z[(wave * GP_HEADS_MAX + h) * GP_TOK + 16 * j + r16] = t;
+        for (int j = 0; j < TT; j += 2) {
+            const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(zp[j]), __float_as_uint(zp[j + 1]), false, false);
+            two[j / 2] = __uint_as_float(p[0]) + __uint_as_float(p[1]);   // rows 0 and 2: tile j, rows 1 and 3: tile j + 1
+        }
+        float* zh = s_z + (wave * GP_HEADS_MAX + h) * GP_TOK;
+        if constexpr (TT == 2) {
+            const float t = two[0] + __shfl_xor(two[0], 32, 64);
+            if (g4 < 2) zh[16 * g4 + r16] = t;
+        } else {
+#pragma unroll
+            for (int j = 0; j < TT / 2; j += 2) {
+                const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(two[j]), __float_as_uint(two[j + 1]), false, false);
+                zh[32 * j + lane] = __uint_as_float(p[0]) + __uint_as_float(p[1]);   // lane group g4: tile 2 j + g4
+            }
         }
     }
     __syncthreads();
@@ -1072,12 +1097,18 @@ kvtrim_status launch_gate(kvtrim_ctx* ctx, const GateView& g, const float* prepa
             const int tt = plan.tt;
             const int tiles = (n_tok + 16 * tt - 1) / (16 * tt);
             const dim3 grid(8u * (unsigned)((nl + 7) / 8) * (unsigned)tiles);
+            const bool stream = 2 * (size_t)n_tok * nl * g.d_model > GP_STREAM_BYTES;
 #define KVTRIM_GATE_PREFILL(HT, TT, TILED)                                                                                    \
-    hipLaunchKernelGGL((k_gate_prefill<HT, TT, TILED>), grid, dim3(GP_THREADS), 0, st, g, x, n_tok, layer_begin, nl, L,       \
+    hipLaunchKernelGGL((k_gate_prefill<HT, TT, TILED, false>), grid, dim3(GP_THREADS), 0, st, g, x, n_tok, layer_begin, nl, L,       \
+                       n_heads, horizon, tiled, v, sconst, log_beta_out, log_tail_out)
+#define KVTRIM_GATE_PREFILL_STREAM(HT, TILED)                                                                                 \
+    hipLaunchKernelGGL((k_gate_prefill<HT, 8, TILED, true>), grid, dim3(GP_THREADS), 0, st, g, x, n_tok, layer_begin, nl, L,  \
                        n_heads, horizon, tiled, v, sconst, log_beta_out, log_tail_out)
 #define KVTRIM_GATE_PREFILL_TT(HT)                                                                                            \
     do {                                                                                                                      \
-        if (use_tiled && tt == 8) KVTRIM_GATE_PREFILL(HT, 8, true);                                                           \
+        if (use_tiled && tt == 8 && stream) KVTRIM_GATE_PREFILL_STREAM(HT, true);                                             \
+        else if (tt == 8 && stream) KVTRIM_GATE_PREFILL_STREAM(HT, false);                                                    \
+        else if (use_tiled && tt == 8) KVTRIM_GATE_PREFILL(HT, 8, true);                                                      \
         else if (use_tiled && tt == 4) KVTRIM_GATE_PREFILL(HT, 4, true);                                                      \
         else if (use_tiled) KVTRIM_GATE_PREFILL(HT, 2, true);                                                                 \
         else if (tt == 8) KVTRIM_GATE_PREFILL(HT, 8, false);                                                                  \
@@ -1091,6 +1122,7 @@ kvtrim_status launch_gate(kvtrim_ctx* ctx, const GateView& g, const float* prepa
                 default: KVTRIM_GATE_PREFILL_TT(4); break;
             }
 #undef KVTRIM_GATE_PREFILL_TT
+#undef KVTRIM_GATE_PREFILL_STREAM
 #undef KVTRIM_GATE_PREFILL
         }
         KVTRIM_HIP(ctx, hipGetLastError());

@@ -319,3 +319,35 @@ def test_sliced_kernel_is_as_exact_as_the_two_kernels(n_tok):
         err[H] = np.linalg.norm(d) / np.linalg.norm(ref[:, :, :32])
     print(f"two kernels {err[33]:.2e}, sliced {err[32]:.2e}")
     assert err[32] <= 1.1 * err[33]
+
+
+@pytest.mark.parametrize("L,n_tok,d_model,d_g,prepared", [(24, 4090, 2048, 512, True), (24, 3585, 2048, 128, False), (34, 1205, 4096, 256, False)])
+def test_calls_whose_rows_bypass_the_caches_give_the_same_bits(L, n_tok, d_model, d_g, prepared):
+    # more than 300 MB of token rows are loaded past the caches (W1 from its copy, made in the call or straight from its rows);
+    # the same layers in two calls are not.  At least 257 blocks of 128 tokens in either, so the tiles are the same.
+    g = torch.Generator(device=DEV).manual_seed(n_tok)
+    H = 2
+    w = {k: v.to(DEV) for k, v in ki.gate_weights(L, H, d_model, d_g, 4, b_g=3.5, seed=9).items() if torch.is_tensor(v)}
+    gate = kv.Gate(w["w1"], w["c1"], w["w2"], w["c2"], w["w_g"], 3.5)
+    x = torch.randn(L, n_tok, d_model, generator=g, device=DEV, dtype=torch.bfloat16)
+    assert x.numel() * 2 > 300 << 20 and x[:L // 2].numel() * 2 <= 300 << 20
+    ctx = kv.Context(1, L, H, H, 64, 1024)
+    scratch = torch.empty(kv.kvtrim_gate_scratch_bytes(gate, n_tok, L), dtype=torch.uint8, device=DEV)
+    prep = torch.empty(kv.kvtrim_gate_prepared_bytes(gate, L, H), dtype=torch.uint8, device=DEV)
+    kv.kvtrim_gate_prepare(ctx, gate, prep)
+    one, two = (torch.full((n_tok, L, H), float("nan"), device=DEV) for _ in range(2))
+    for out, ranges in ((one, [(0, L)]), (two, [(0, L // 2), (L // 2, L)])):
+        for lo, hi in ranges:
+            part = x[lo:hi].contiguous()
+            if prepared:
+                kv.kvtrim_gate_forward_prepared(ctx, gate, prep, part, n_tok, lo, hi, 1, scratch, out, None)
+            else:
+                kv.kvtrim_gate_forward(ctx, gate, part, n_tok, lo, hi, 1, scratch, out, None)
+    assert kv.kvtrim_poll_error(ctx) == 0 and torch.isfinite(one).all()
+    assert torch.equal(one, two)
+    pick = torch.tensor([0, 15, 16, n_tok - 1], device=DEV)
+    for layer in (0, L - 1):
+        u = x[layer, pick].double() @ w["w1"][layer].double().t() + w["c1"][layer].double()
+        p = torch.einsum("tu,hpu->thp", u * torch.sigmoid(u), w["w2"][layer].double()) + w["c2"][layer].double()
+        ref = torch.nn.functional.logsigmoid(p @ w["w_g"].double() + 3.5)
+        assert rel_err(one[pick, layer].cpu().numpy(), ref.cpu().numpy()) <= RTOL
