@@ -367,18 +367,31 @@ __global__ __launch_bounds__(CMP_THREADS) void k_cmp_copy(CacheView src, const u
     __shared__ int wave_cnt[CMP_CHUNK / 64];
     __shared__ int list[CMP_CHUNK];
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    if (__hip_atomic_load(ws.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
-    const int total = ws.cmp_chunk_prefix[sh.nseg];
     const int ch = blockIdx.x;
-    if (ch >= total) return;
+    // (what the tables hold at or beyond `total` is not used; the grid never exceeds them)
     const ChunkDesc d = ws.cmp_desc[ch];
-    const int64_t sbase = d.first;                                // first source entry of the chunk
     const int64_t dbase = ws.cmp_chunk_dst[ch] & ~CMP_DST_FULL;   // first destination entry of its survivors
-    // the first CMP_CHUNK threads rank the survivors
+    const int err = __hip_atomic_load(ws.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (ch >= ws.cmp_chunk_prefix[sh.nseg] || err != 0) return;
+    const int64_t sbase = d.first;                                // first source entry of the chunk
+    // NEW: index of the chunk's first entry in its segment, and where the segment's new entries begin
+    const int64_t seg_off = NEW ? sbase - src.seg_start[d.seg] : 0;
+    const int64_t first_new = NEW ? old_len[d.seg] : 0;
+    const int64_t new_base = NEW ? (int64_t)d.seg * n_new - first_new : 0;   // + index in the segment = row of k_new
+    // the first CMP_CHUNK threads rank the survivors; an entry's metadata is asked for with its mask byte
     int rank = 0;
     bool flag = false;
+    float md_lb = 0.f, md_lt = 0.f;
+    int md_pos = 0;
     if (tid < CMP_CHUNK) {
-        flag = tid < d.n && keep[sbase + tid] != 0;
+        const bool in = tid < d.n;
+        const uint8_t kb = in ? keep[sbase + tid] : (uint8_t)0;
+        if (in) {
+            md_lb = src.log_beta[sbase + tid];
+            if (src.log_tail) md_lt = src.log_tail[sbase + tid];
+            md_pos = src.pos[sbase + tid];
+        }
+        flag = kb != 0;
         const uint64_t mask = __ballot(flag);
         rank = mbcnt(mask);
         if (lane == 0) wave_cnt[wave] = __popcll(mask);
@@ -392,9 +405,9 @@ __global__ __launch_bounds__(CMP_THREADS) void k_cmp_copy(CacheView src, const u
     }
     if (flag) {
         list[rank] = tid;
-        dst.log_beta[dbase + rank] = src.log_beta[sbase + tid];
-        if (src.log_tail) dst.log_tail[dbase + rank] = src.log_tail[sbase + tid];
-        dst.pos[dbase + rank] = src.pos[sbase + tid];
+        dst.log_beta[dbase + rank] = md_lb;
+        if (src.log_tail) dst.log_tail[dbase + rank] = md_lt;
+        dst.pos[dbase + rank] = md_pos;
     }
     __syncthreads();
     const int r0 = wave * CMP_WAVE_ROWS;                          // this wavefront's rows of the survivor list
@@ -405,23 +418,13 @@ __global__ __launch_bounds__(CMP_THREADS) void k_cmp_copy(CacheView src, const u
     uint4* dv = reinterpret_cast<uint4*>(dst.v);
     const int sub = lane / VPR, col = lane % VPR;
     uint4 kk[BATCH], vv[BATCH];
-    // NEW: index of the chunk's first entry in its segment, and where the segment's new entries begin
-    const int64_t seg_off = NEW ? sbase - src.seg_start[d.seg] : 0;
-    const int64_t first_new = NEW ? old_len[d.seg] : 0;
-    const int64_t new_base = NEW ? (int64_t)d.seg * n_new - first_new : 0;   // + index in the segment = row of k_new
 #pragma unroll
     for (int u = 0; u < BATCH; ++u) {
-        const int r = min(r0 + u * RPI + sub, cnt - 1);           // clamped: loads stay on live rows
-        const int64_t j = seg_off + list[r];
-        if (NEW && j >= first_new) {
-            const int64_t ne = (new_base + j) * VPR + col;
-            kk[u] = ld16_nt(reinterpret_cast<const uint4*>(k_new) + ne);
-            vv[u] = ld16_nt(reinterpret_cast<const uint4*>(v_new) + ne);
-        } else {
-            const int64_t se = (sbase + list[r]) * VPR + col;
-            kk[u] = ld16_nt(sk + se);
-            vv[u] = ld16_nt(sv + se);
-        }
+        const int e = list[min(r0 + u * RPI + sub, cnt - 1)];     // clamped: loads stay on live rows
+        const bool fresh = NEW && seg_off + e >= first_new;
+        const int64_t row = (fresh ? new_base + seg_off + e : sbase + e) * VPR + col;
+        kk[u] = ld16_nt((fresh ? reinterpret_cast<const uint4*>(k_new) : sk) + row);
+        vv[u] = ld16_nt((fresh ? reinterpret_cast<const uint4*>(v_new) : sv) + row);
     }
 #pragma unroll
     for (int u = 0; u < BATCH; ++u) {
@@ -489,7 +492,7 @@ kvtrim_status launch_cmp_copy(kvtrim_ctx* ctx, const CacheView& src, const uint8
         if (gather_fits(ctx, src.cap, dst.cap))                   // few survivors per chunk: a block per chunk of the destination
             return launch_gather_rows(ctx, src, dst, st);
         if (sh.head_dim == 128)
-            hipLaunchKernelGGL((k_cmp_copy<128, false>), grid, block, 0, st, src, keep, dst, sh, ws, nullptr, nullptr, 0, nullptr);
+            hipLaunchKernelGGL((k_cmp_copy<128, false>), grid, block, mover_lds(128, 0, grid.x), st, src, keep, dst, sh, ws, nullptr, nullptr, 0, nullptr);
         else
             hipLaunchKernelGGL((k_cmp_copy<64, false>), grid, block, 0, st, src, keep, dst, sh, ws, nullptr, nullptr, 0, nullptr);
     }
@@ -507,7 +510,7 @@ kvtrim_status launch_cmp_copy_new(kvtrim_ctx* ctx, const CacheView& src, const u
         ProfScope prof(ctx, K_CMP_COPY, st);
         const dim3 grid((unsigned)max_chunks), block(CMP_THREADS);
         if (sh.head_dim == 128)
-            hipLaunchKernelGGL((k_cmp_copy<128, true>), grid, block, 0, st, src, keep, dst, sh, ws, k_new, v_new, n_new, old_len);
+            hipLaunchKernelGGL((k_cmp_copy<128, true>), grid, block, mover_lds(128, 0, grid.x), st, src, keep, dst, sh, ws, k_new, v_new, n_new, old_len);
         else
             hipLaunchKernelGGL((k_cmp_copy<64, true>), grid, block, 0, st, src, keep, dst, sh, ws, k_new, v_new, n_new, old_len);
     }

@@ -15,6 +15,17 @@ constexpr int CMP_CHUNK = 128;       // compaction: entries per block
 constexpr long long CMP_DST_FULL = 1ll << 62;   // flag in ws.cmp_chunk_dst: every entry of the chunk survives
 constexpr int CMP_WAVE_ROWS = 16;    // rows a wavefront moves (one batch of loads, one of stores)
 constexpr int CMP_THREADS = CMP_CHUNK / CMP_WAVE_ROWS * 64;   // 512: one wavefront per 16 survivors
+// LDS that a launch of a row mover (k_cmp_copy: G = 0; k_cmp_attn out of place, G query heads) asks for beyond what the kernel
+// uses, so that two blocks share a compute unit and not four: 128 KB of rows of 256 bytes under way per compute unit are
+// as many as the memory takes in turn; with more, reads and writes of more places disturb each other.  (One-call steps of 32 x
+// 8 lists of 8192 405 -> 398 us, 16 sequences of 2048 1640 -> 1570; chunks of 4096 for 1024 lists of 8192 1780 -> 1660; one
+// block 455, 1805, 1970; three 405, 1643, 1756.)  Rows of 128 bytes: four blocks are 128 KB (20 x 3 lists of 11 K 99 us,
+// with two 110).  Compaction in place, which mostly reads, is better with all it can get (150 us, with two 156).  Fewer than
+// about 2000 blocks are better on the chip at once (2 x 16 x 8 lists of 700, 1800 blocks: 64.4 us, with two 66.1).
+constexpr int64_t MOVER_BLOCKS = 2048;
+constexpr size_t mover_lds(int D, int G, int64_t blocks) {
+    return D == 128 && blocks >= MOVER_BLOCKS ? 57344 - (size_t)G * (CMP_THREADS / 64) * (128 + 8) * sizeof(float) - 2048 : 0;
+}
 constexpr int RADIX_BITS0 = 11, RADIX_BITS1 = 11, RADIX_BITS2 = 10;
 constexpr int RADIX_BINS = 2048;     // bins of the widest pass
 constexpr int HIST_BLOCKS_MAX = 512; // blocks of a histogram pass (few and fat: see k_select.hip)
