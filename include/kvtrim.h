@@ -288,7 +288,7 @@ kvtrim_status kvtrim_append(kvtrim_ctx *ctx, kvtrim_cache *c, const void *k_new,
  * indices of its evicted entries (further blocks of the same launch append the new tokens); one moves every
  * surviving row while using it for the attention of its segment (no mask pass, no compaction scan: a block derives
  * its chunk's destination from its segment's record and writes the chunk's mask bytes itself); one merges the
- * partial attention results.  Any other shape or hint runs the three calls one after the other.  Device-side errors as in
+ * partial attention results (small caches: the second does that, too, and the step is two).  Any other shape or hint runs the three calls one after the other.  Device-side errors as in
  * the three calls. */
 kvtrim_status kvtrim_decode_step(kvtrim_ctx *ctx, kvtrim_cache *src, const void *k_new, const void *v_new,
                                  const float *log_beta_new, const float *log_tail_new, const int32_t *pos_new,

@@ -492,7 +492,7 @@ kvtrim_status launch_cmp_copy(kvtrim_ctx* ctx, const CacheView& src, const uint8
         if (gather_fits(ctx, src.cap, dst.cap))                   // few survivors per chunk: a block per chunk of the destination
             return launch_gather_rows(ctx, src, dst, st);
         if (sh.head_dim == 128)
-            hipLaunchKernelGGL((k_cmp_copy<128, false>), grid, block, mover_lds(128, 0, grid.x), st, src, keep, dst, sh, ws, nullptr, nullptr, 0, nullptr);
+            hipLaunchKernelGGL((k_cmp_copy<128, false>), grid, block, mover_lds(128, 0, dense_blocks(src.cap, dst.cap, grid.x)), st, src, keep, dst, sh, ws, nullptr, nullptr, 0, nullptr);
         else
             hipLaunchKernelGGL((k_cmp_copy<64, false>), grid, block, 0, st, src, keep, dst, sh, ws, nullptr, nullptr, 0, nullptr);
     }
@@ -510,7 +510,7 @@ kvtrim_status launch_cmp_copy_new(kvtrim_ctx* ctx, const CacheView& src, const u
         ProfScope prof(ctx, K_CMP_COPY, st);
         const dim3 grid((unsigned)max_chunks), block(CMP_THREADS);
         if (sh.head_dim == 128)
-            hipLaunchKernelGGL((k_cmp_copy<128, true>), grid, block, mover_lds(128, 0, grid.x), st, src, keep, dst, sh, ws, k_new, v_new, n_new, old_len);
+            hipLaunchKernelGGL((k_cmp_copy<128, true>), grid, block, mover_lds(128, 0, dense_blocks(src.cap, dst.cap, grid.x)), st, src, keep, dst, sh, ws, k_new, v_new, n_new, old_len);
         else
             hipLaunchKernelGGL((k_cmp_copy<64, true>), grid, block, 0, st, src, keep, dst, sh, ws, k_new, v_new, n_new, old_len);
     }

@@ -18,7 +18,8 @@
 //   p.v   one MFMA per column of the slice: the lane's 4 rows are 4 consecutive slots of the
 //         reduction dimension, and the MFMA sums over the wavefront's 16 rows for all query heads
 // A wavefront takes one softmax partial per query head over its 16 rows; the wavefronts of the
-// block are merged through LDS, and the chunks of a segment by k_att_combine.
+// block are merged through LDS, and the chunks of a segment by k_att_combine (in small grids by the last of them to
+// finish).
 //
 // The same kernel has an instance that compacts INSIDE the cache (segments keep their starts; only the rows
 // behind an eviction move), followed by k_cmp_unstage; k_cmp_move_inplace is that instance without the
@@ -473,7 +474,7 @@ static bool dispatch_fused(int G, dim3 grid, hipStream_t st, const CacheView& sr
 #define KVTRIM_CASE(g) \
     case g: \
         if (!INPLACE && merge) hipLaunchKernelGGL((k_cmp_attn<D, g, false, false, false, !INPLACE>), grid, dim3(FUS_THREADS), 0, st, src, keep, dst, stage, q, sh, ws, scale_log2, lb, le, nullptr, out, lse); \
-        else hipLaunchKernelGGL((k_cmp_attn<D, g, INPLACE>), grid, dim3(FUS_THREADS), INPLACE ? 0 : mover_lds(D, g, grid.x), st, src, keep, dst, stage, q, sh, ws, scale_log2, lb, le); \
+        else hipLaunchKernelGGL((k_cmp_attn<D, g, INPLACE>), grid, dim3(FUS_THREADS), INPLACE ? 0 : mover_lds(D, g, dense_blocks(src.cap, dst.cap, grid.x)), st, src, keep, dst, stage, q, sh, ws, scale_log2, lb, le); \
         return true;
         KVTRIM_CASE(1) KVTRIM_CASE(2) KVTRIM_CASE(3) KVTRIM_CASE(4) KVTRIM_CASE(5) KVTRIM_CASE(6) KVTRIM_CASE(7) KVTRIM_CASE(8)
 #undef KVTRIM_CASE
@@ -748,7 +749,7 @@ kvtrim_status launch_decode_step(kvtrim_ctx* ctx, const CacheViewMut& srcm, cons
     src.k = srcm.k; src.v = srcm.v; src.log_beta = srcm.log_beta; src.pos = srcm.pos;
     src.seg_start = srcm.seg_start; src.seg_len = srcm.seg_len; src.cap = srcm.cap; src.log_tail = srcm.log_tail;
     const int64_t max_chunks = src.cap / CMP_CHUNK + sh.nseg;
-    // Three kernels (score + resolve, move + attend, merge) when this is a decode step the candidate list can carry;
+    // Three kernels (score + resolve, move + attend, merge; small grids merge in the second) when this is a decode step the candidate list can carry;
     // otherwise the calls it stands for, one after the other.
     const bool three = evict_hint > 0 && 8 * (evict_hint + 1) <= (int64_t)ws.fl_cap &&
                        sh.segs_per_seq <= STEP_MAX_SEGS && sh.n_seq <= STEP_MAX_SEQS && sa.n_new <= STEP_MAX_NEW &&

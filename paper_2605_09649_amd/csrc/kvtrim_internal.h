@@ -21,8 +21,11 @@ constexpr int CMP_THREADS = CMP_CHUNK / CMP_WAVE_ROWS * 64;   // 512: one wavefr
 // 8 lists of 8192 405 -> 398 us, 16 sequences of 2048 1640 -> 1570; chunks of 4096 for 1024 lists of 8192 1780 -> 1660; one
 // block 455, 1805, 1970; three 405, 1643, 1756.)  Rows of 128 bytes: four blocks are 128 KB (20 x 3 lists of 11 K 99 us,
 // with two 110).  Compaction in place, which mostly reads, is better with all it can get (150 us, with two 156).  Fewer than
-// about 2000 blocks are better on the chip at once (2 x 16 x 8 lists of 700, 1800 blocks: 64.4 us, with two 66.1).
+// about 2000 blocks are better on the chip at once (2 x 16 x 8 lists of 700, 1800 blocks: 64.4 us, with two 66.1), and so are
+// blocks of whose entries few survive (a quarter of 3400 chunks: 60 us, with two 64): a destination under three quarters of
+// the source.
 constexpr int64_t MOVER_BLOCKS = 2048;
+inline int64_t dense_blocks(int64_t src_cap, int64_t dst_cap, int64_t blocks) { return 4 * dst_cap >= 3 * src_cap ? blocks : 0; }
 constexpr size_t mover_lds(int D, int G, int64_t blocks) {
     return D == 128 && blocks >= MOVER_BLOCKS ? 57344 - (size_t)G * (CMP_THREADS / 64) * (128 + 8) * sizeof(float) - 2048 : 0;
 }
