@@ -115,7 +115,9 @@ __device__ __forceinline__ void merge_shared(const float* __restrict__ part, int
     }
     if (rg == 0) {
         const float l = s_ml[2 * g + 1];
-        *reinterpret_cast<float2*>(out + (hq + g) * D + col) = l > 0.f ? make_float2(acc.x / l, acc.y / l) : make_float2(0.f, 0.f);
+        float* o = out + (hq + g) * D + col;                      // (one by one: the caller's array need not be 8-byte aligned)
+        o[0] = l > 0.f ? acc.x / l : 0.f;
+        o[1] = l > 0.f ? acc.y / l : 0.f;
         if (col == 0 && lse) lse[hq + g] = l > 0.f ? (s_ml[2 * g] + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
     }
     __syncthreads();                                              // (LDS may be used again)

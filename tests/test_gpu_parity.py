@@ -826,6 +826,45 @@ def test_attention_of_small_calls_at_the_edges_of_their_shares(S, H, G, D, lens,
         assert np.abs(l[fin] - ref_lse[fin]).max() <= 2e-3
 
 
+# out and lse are arrays of floats and need no more than their alignment, also where the last block of a segment merges:
+# attention of a small call (2200 and 40 rows a list), of the row mover (18 chunks and 1), of segments that one block writes
+@pytest.mark.parametrize("G,D", [(4, 128), (3, 64)])
+def test_attention_results_may_lie_at_any_float(G, D):
+    w = wl(1, 2, 2, G, D)
+    lens = [2200, 40, 1100, 130]
+    c, now = ki.ragged_cache(w, lens, reserve=1, salt=60 + G)
+    hc = host_cache(w, c)
+    dc, dst = kv.Cache.from_dict(c, DEV), kv.Cache.empty(w.nseg, D, hc.cap, DEV)
+    ctx = kv.Context(1, 2, 2, 2 * G, D, hc.cap)
+    q = ki.decode_inputs(w, 1)["q"]
+    ref, ref_lse = oracle.attend(hc, bf16_bits(q), 0.1)
+    qd = q.to(DEV)
+    keep = torch.ones(hc.cap, dtype=torch.uint8, device=DEV)
+    kept = torch.tensor(lens, dtype=torch.int32, device=DEV)
+
+    def layers(out, lse):
+        for layer in range(2):
+            kv.kvtrim_decode_attn(ctx, dc, qd, layer, layer + 1, 0.1, out, lse)
+
+    def mover(out, lse):
+        kv.kvtrim_compact_attn(ctx, dc, keep, kept, dst, 0, qd, 0, 2, 0.1, out, lse)
+    for call in (layers, mover):
+        first = None
+        for off in range(4):
+            bufs = [torch.full((r.size + 8,), 99.0, device=DEV) for r in (ref, ref_lse)]
+            out, lse = (b[off:off + r.size].view(r.shape) for b, r in zip(bufs, (ref, ref_lse)))
+            assert out.data_ptr() % 16 == 4 * off
+            call(out, lse)
+            assert kv.kvtrim_poll_error(ctx) == 0
+            got = [b.cpu().numpy() for b in bufs]
+            for g, r in zip(got, (ref, ref_lse)):
+                assert np.all(g[:off] == 99.0) and np.all(g[off + r.size:] == 99.0), (call.__name__, off)
+            got = [g[off:off + r.size].reshape(r.shape) for g, r in zip(got, (ref, ref_lse))]
+            assert attn_error(got[0], ref) <= ATTN_TOL and np.abs(got[1] - ref_lse).max() <= 2e-3
+            first = first or got
+            assert all(np.array_equal(a, b) for a, b in zip(first, got)), (call.__name__, off)
+
+
 @pytest.mark.parametrize("reserve,lens", [
     (3, [0, 1, 15, 16, 17, 127, 128, 129]),                  # under, at and over a lane's 16 mask bytes and a chunk; every start misaligned differently
     (1, [1023, 1024, 1025, 2047, 2048, 2049, 4095, 8]),      # ... a wavefront's load (8 chunks) and a selection chunk
