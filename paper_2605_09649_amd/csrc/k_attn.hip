@@ -181,7 +181,7 @@ __global__ __launch_bounds__(att_threads(MODE)) void k_att_partial(CacheView c, 
     constexpr int SO = D + 8;                                     // a 32-byte skew between heads
     __shared__ __attribute__((aligned(16))) float s_o[NSTREAM][G][SO];
     __shared__ int64_t s_scan[17];
-    __shared__ int s_bad[NSTREAM], s_merge[2];
+    __shared__ int s_bad[NSTREAM], s_merge[2], s_last;
     extern __shared__ int32_t s_tab[];                            // !PLANNED: [n_in + 1] rows before each ordinal, [n_in] starts
 
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -536,6 +536,7 @@ __global__ __launch_bounds__(att_threads(MODE)) void k_att_partial(CacheView c, 
         return x <= t ? (x + share) / (share + 1) : rest + (x - t + share - 1) / share;
     };
     int b0[2] = {0, 0}, n[2] = {0, 0};
+    MergeCount mc[2] = {};                                        // (before the wait, which it does not lengthen)
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
         const int ord = k == 0 ? shared_first : shared_last;
@@ -543,21 +544,21 @@ __global__ __launch_bounds__(att_threads(MODE)) void k_att_partial(CacheView c, 
         const uint32_t r0s = (uint32_t)rp(ord), r1s = (uint32_t)rp(ord + 1);
         b0[k] = (int)starts_below(min(r0s + (1u << unit_log), r1s)) - 1;
         n[k] = (int)starts_below(r1s) - b0[k];
+        mc[k] = merge_count<MergeShape<D, G, THREADS>>(ws, ord, b0[k] + ord, (int)blockIdx.x - b0[k], n[k]);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (tid < 2) {
         const int ord = tid == 0 ? shared_first : shared_last;
-        s_merge[tid] = ord >= 0 && atomicAdd(&ws.att_done[ord * ATT_DONE_STRIDE], 1u) == (unsigned)(tid == 0 ? n[0] : n[1]) - 1u;
+        s_merge[tid] = ord >= 0 && atomicAdd(tid == 0 ? mc[0].word : mc[1].word, 1u) == (unsigned)(tid == 0 ? mc[0].of : mc[1].of) - 1u;
     }
     __syncthreads();
 #pragma unroll 1
     for (int k = 0; k < 2; ++k) {
         if (!s_merge[k]) continue;                                // (uniform)
         const int ord = k == 0 ? shared_first : shared_last;
-        if (tid == 0) __hip_atomic_store(&ws.att_done[ord * ATT_DONE_STRIDE], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const float* part = ws.att_partial + (size_t)((k == 0 ? b0[0] : b0[1]) + ord) * G * (D + 2);
-        merge_shared<D, G, THREADS>(part, k == 0 ? n[0] : n[1], k == 0 ? hq_first : hq_last, &s_o[0][0][0], out, lse);
+        merge_last<D, G, THREADS>(ws, k == 0 ? mc[0] : mc[1], ord, (k == 0 ? b0[0] : b0[1]) + ord, k == 0 ? n[0] : n[1], k == 0 ? hq_first : hq_last,
+                                  &s_o[0][0][0], &s_last, out, lse);
     }
     }
 }
@@ -711,8 +712,14 @@ struct AttCall {
 // rows 20 / 17.5: beyond two blocks of 128 rows per compute unit the two launches' smaller blocks spread better.  And
 // the one block that merges a segment reads all of its partial results: 64 KB still cost less than the launch of
 // k_att_combine, whose blocks share them (12.7 / 13.9), 128 KB as much (4000 rows, 8 heads: 13.3 / 13.3), 200 KB more (2
-// heads of 15 K rows, 7 query heads each: 24 / 17).
+// heads of 15 K rows, 7 query heads each: 24 / 17).  Both are means: the host knows the capacity, not how it is spread over
+// layers and lists.  A longer list is merged in groups (see merge_last), and the grid - two blocks a compute unit, which are on
+// the chip at once - does not grow with the other layers' capacity: 8 layers of 8 lists, 63000 rows a layer, the layer with
+// twice that 19.2 us, with nine tenths of all 46.4, all of that in one list 47.5 (two launches 20.7, 44.6, 56.0; with 768
+// blocks and one block to merge 27.9, 55.6, 90.7).
 constexpr int64_t ATT_ONE_ROWS = 2 * 256 * 128, ATT_ONE_MERGE_BYTES = 1 << 17;
+constexpr int ATT_ONE_BLOCKS = 2 * 256;                           // of 128 rows: two for every compute unit
+static_assert(ATT_ONE_BLOCKS + ATT_ONE_ORDS <= ATT_MERGE_SLOTS, "counters for the groups of its results");
 static bool att_one(const kvtrim_ctx* ctx, int64_t cap, const AttPages* pages, int32_t layer_begin, int32_t layer_end) {
     const Shape& sh = ctx->shape;
     const int64_t n_in = (int64_t)sh.n_seq * (layer_end - layer_begin) * sh.n_kv_heads;
@@ -731,6 +738,7 @@ static AttCall att_call(const kvtrim_ctx* ctx, int64_t cap, int32_t layer_begin,
     // a block per round of 64 rows at most, and a slot per block and segment in the partial-result buffer
     int64_t nb = cap / ATT_ROUND + 1;
     if (nb > ctx->att_blocks) nb = ctx->att_blocks;
+    if (one && nb > ATT_ONE_BLOCKS) nb = ATT_ONE_BLOCKS;
     if (nb > ctx->ws.att_slots - a.n_in) nb = ctx->ws.att_slots - a.n_in;
     a.nb = (int)nb;
     a.lds = a.mode != ATT_SUMMED ? 0 : ((size_t)(paged ? 1 : 2) * a.n_in + 1) * sizeof(int32_t);

@@ -462,7 +462,7 @@ __global__ __launch_bounds__(FUS_THREADS) void k_cmp_attn(CacheView src, const u
         __syncthreads();
         if (!s_last) return;
         if (tid == 0) __hip_atomic_store(&ws.att_done[seg * ATT_DONE_STRIDE], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        merge_shared<D, G, FUS_THREADS>(ws.att_partial + (size_t)first_ch * G * (D + 2), n_ch, q_row_of<G>(seg, sh), &s_o[0][0][0], out, lse);
+        merge_shared<D, G, FUS_THREADS, MergeShape<D, G, FUS_THREADS>::LOADS>(ws.att_partial + (size_t)first_ch * G * (D + 2), n_ch, G * (D + 2), true, q_row_of<G>(seg, sh), &s_o[0][0][0], out, lse);
     }
 }
 

@@ -33,7 +33,7 @@ static bool config_ok(const kvtrim_config* c) {
 }
 
 struct Layout {
-    size_t off[42];
+    size_t off[43];
     int32_t fl_cap, fast_stride;
     size_t total;
     int64_t max_sel_chunks, max_cmp_chunks, max_att_chunks, att_slots, gat_slots;
@@ -110,6 +110,7 @@ static Layout layout_of(const kvtrim_config* c, bool select_only) {
     l.off[40] = bump(cur, (size_t)c->n_layers * GATE_TOKEN_TILES * sizeof(uint32_t));   // gate_done
     const int64_t done_segs = nseg < ATT_ONE_ORDS ? ATT_ONE_ORDS : (nseg < ATT_MERGE_SEGS ? nseg : ATT_MERGE_SEGS);
     l.off[41] = bump(cur, seg_tables * (size_t)done_segs * ATT_DONE_STRIDE * sizeof(uint32_t));   // att_done
+    l.off[42] = bump(cur, seg_tables * (size_t)(done_segs + ATT_MERGE_SLOTS / ATT_MERGE_GROUP) * ATT_DONE_STRIDE * sizeof(uint32_t));   // att_group
     l.total = (cur + 255) & ~(size_t)255;
     return l;
 }
@@ -155,6 +156,7 @@ static void bind(const Layout& l, char* b, Workspace& w) {
     w.att_row_prefix = (int64_t*)(b + l.off[39]);
     w.gate_done = (uint32_t*)(b + l.off[40]);
     w.att_done = (uint32_t*)(b + l.off[41]);
+    w.att_group = (uint32_t*)(b + l.off[42]);
     w.gat_slots = l.gat_slots;
     w.fl_cap = l.fl_cap;
     w.fast_stride = l.fast_stride;

@@ -35,6 +35,8 @@ constexpr int HIST_BLOCKS_MAX = 512; // blocks of a histogram pass (few and fat:
 constexpr int ATT_BLOCKS = 768;       // most blocks of the attention kernel: three per compute unit
 constexpr int ATT_ONE_ORDS = 64;      // most segments of a layer range that the attention takes in one launch: a lane each
 constexpr int ATT_MERGE_SEGS = 1024;  // most segments whose partial results the row mover merges itself
+constexpr int ATT_MERGE_SLOTS = 1024; // most partial results of such a call
+constexpr int ATT_MERGE_GROUP = 32;   // results of a group, where a segment has too many for one block to merge
 constexpr int ATT_DONE_STRIDE = 64;   // words between two of its counters: atomics on one line are served one after the other
 constexpr int GATE_TOKEN_TILES = 16;  // token tiles of a gate call that finishes inside its first-layer kernel
 constexpr int DONE_WORDS = 128;      // 4 sets of 32 counters (three histogram passes, the tie count)
@@ -226,6 +228,7 @@ struct alignas(64) Workspace {
     int32_t* step_len;           // [nseg] segment lengths with the step's new tokens
     int64_t* att_row_prefix;     // [nseg+1] attention: rows (paged: slots) before each segment of the layer range, counted inside the range
     uint32_t* att_done;          // [max(ATT_ONE_ORDS, min(nseg, ATT_MERGE_SEGS))][ATT_DONE_STRIDE] blocks that have left their partial result of a segment that the last of them merges (zero between calls)
+    uint32_t* att_group;         // [as many + ATT_MERGE_SLOTS / ATT_MERGE_GROUP][ATT_DONE_STRIDE] ... of a group of a long segment's results (zero between calls)
     uint32_t* gate_done;         // [n_layers][GATE_TOKEN_TILES] gate forward: blocks of a layer and token tile that have left their part of the readout (zero between calls)
     int64_t gat_slots;
     int64_t max_sel_chunks, max_cmp_chunks, max_att_chunks;

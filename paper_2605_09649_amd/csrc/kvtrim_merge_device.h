@@ -40,16 +40,23 @@ __device__ __forceinline__ float wave_total(float v) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 63));
 }
 
-// The last block of a segment to finish merges: the n partial results at `part` ([n][G][D + 2] = (m in base-2 units, l,
-// o[D] unnormalised)) become the segment's output.  A thread owns two columns of a head and every
+template <int D, int G, int THREADS>
+struct MergeShape {
+    static constexpr int PAIRS = G * D / 2;                              // 32 .. 512
+    static constexpr int RG = THREADS / PAIRS > 4 ? 4 : THREADS / PAIRS; // groups of threads that share the results
+    static constexpr int LOADS = 16, GROUP_LOADS = 8;                    // results under way per thread: of a segment, of a group
+    static constexpr int AT_ONCE = 2 * RG * LOADS;                       // most results of a segment that one block merges (see merge_last)
+    static constexpr uint32_t RESULT = G * (D + 2);                      // floats of a partial result
+};
+
+// The n partial results at part, part + step, ... ([G][D + 2] = (m in base-2 units, l, o[D] unnormalised)) become the
+// segment's output, or (not final) one partial result in the place of the first.  A thread owns two columns of a head and every
 // RG-th partial result; their loads and those of the (m, l) pairs, a lane per result, go out together, so a tile of results
 // costs one round trip.  The results come past the caches that are not coherent across the chip (eight bytes a load).
-template <int D, int G, int THREADS>
-__device__ __forceinline__ void merge_shared(const float* __restrict__ part, int n, int64_t hq, float* lds, float* __restrict__ out,
-                                             float* __restrict__ lse) {
-    constexpr int PAIRS = G * D / 2;                              // 32 .. 512
-    constexpr int RG = THREADS / PAIRS > 4 ? 4 : THREADS / PAIRS; // groups of threads that share the results
-    constexpr int LOADS = 16, TILE = RG * LOADS;                  // 16 .. 64 results
+template <int D, int G, int THREADS, int LOADS>
+__device__ __forceinline__ void merge_shared(float* part, int n, uint32_t step, bool final, int64_t hq, float* lds,
+                                             float* __restrict__ out, float* __restrict__ lse) {
+    constexpr int PAIRS = MergeShape<D, G, THREADS>::PAIRS, RG = MergeShape<D, G, THREADS>::RG, TILE = RG * LOADS;   // (tiles of 8 to 64 results)
     static_assert(RG >= 1 && TILE <= 64 && THREADS / 64 >= G, "a wavefront for every head, a lane for every result of a tile");
     float2* s_acc = reinterpret_cast<float2*>(lds);               // [RG - 1][PAIRS]
     float* s_w = lds + 2 * (RG - 1) * PAIRS;                      // [G][TILE] weights of a tile's results
@@ -59,21 +66,21 @@ __device__ __forceinline__ void merge_shared(const float* __restrict__ part, int
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rg = tid / PAIRS, pair = tid - rg * PAIRS, g = pair / (D / 2), col = 2 * (pair - g * (D / 2));
     const bool mine = rg < RG;
-    auto ld2 = [](const float* p) {
-        return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    auto ld2 = [&](uint32_t at) {                                 // (a uniform base and 32-bit offsets: ATT_MERGE_SLOTS results of at most 4160 bytes)
+        const uint64_t* p = reinterpret_cast<const uint64_t*>(reinterpret_cast<const char*>(part) + 4u * at);
+        return __builtin_bit_cast(float2, __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     };
-    constexpr size_t stride = (size_t)G * (D + 2);
     float2 acc = make_float2(0.f, 0.f);
     float M = -INFINITY, L = 0.f;                                 // of head `wave`
     for (int t0 = 0; t0 < n; t0 += TILE) {
         float2 x[LOADS];
         float2 ml = make_float2(-INFINITY, 0.f);
-        if (wave < G && lane < TILE && t0 + lane < n) ml = ld2(part + (t0 + lane) * stride + (size_t)wave * (D + 2));
+        if (wave < G && lane < TILE && t0 + lane < n) ml = ld2((uint32_t)(t0 + lane) * step + (uint32_t)(wave * (D + 2)));
 #pragma unroll
         for (int u = 0; u < LOADS; ++u) {
             const int e = t0 + u * RG + rg;
             x[u] = make_float2(0.f, 0.f);
-            if (mine && e < n) x[u] = ld2(part + e * stride + (size_t)g * (D + 2) + 2 + col);
+            if (mine && e < n) x[u] = ld2((uint32_t)e * step + (uint32_t)(g * (D + 2) + 2 + col));
         }
         if (wave < G) {
             const float Mn = fmaxf(M, wave_max(ml.x)), ms = Mn == -INFINITY ? 0.f : Mn;
@@ -114,13 +121,78 @@ __device__ __forceinline__ void merge_shared(const float* __restrict__ part, int
         }
     }
     if (rg == 0) {
-        const float l = s_ml[2 * g + 1];
-        float* o = out + (hq + g) * D + col;                      // (one by one: the caller's array need not be 8-byte aligned)
-        o[0] = l > 0.f ? acc.x / l : 0.f;
-        o[1] = l > 0.f ? acc.y / l : 0.f;
-        if (col == 0 && lse) lse[hq + g] = l > 0.f ? (s_ml[2 * g] + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
+        const float m = s_ml[2 * g], l = s_ml[2 * g + 1];
+        if (final) {
+            float* o = out + (hq + g) * D + col;                  // (one by one: the caller's array need not be 8-byte aligned)
+            o[0] = l > 0.f ? acc.x / l : 0.f;
+            o[1] = l > 0.f ? acc.y / l : 0.f;
+            if (col == 0 && lse) lse[hq + g] = l > 0.f ? (m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f : -INFINITY;
+        } else {                                                  // (every result has been read: the barriers above)
+            float* p = part + g * (D + 2);
+            put_shared(p + 2 + col, acc.x);
+            put_shared(p + 3 + col, acc.y);
+            if (col == 0) {
+                put_shared(p, m);
+                put_shared(p + 1, l);
+            }
+        }
     }
     __syncthreads();                                              // (LDS may be used again)
+}
+
+// Result i of the n of segment seg (its number among the call's, below ATT_MERGE_SEGS), which lie at the slots slot0, slot0 +
+// 1, ... : the counter its block counts itself on once the result has been acknowledged, and the number of results
+// that meet there.  With more than AT_ONCE results they meet in groups of ATT_MERGE_GROUP first.
+struct MergeCount {
+    uint32_t* word;
+    int group, of;
+};
+template <typename MS>
+__device__ __forceinline__ MergeCount merge_count(const Workspace& ws, int seg, int slot0, int i, int n) {
+    if (n <= MS::AT_ONCE) return {ws.att_done + (size_t)seg * ATT_DONE_STRIDE, 0, n};
+    const int group = i / ATT_MERGE_GROUP, first = group * ATT_MERGE_GROUP;
+    // (groups begin ATT_MERGE_GROUP slots apart inside a segment, and a segment adds one: every group has a word of its own)
+    return {ws.att_group + ((size_t)(slot0 + first) / ATT_MERGE_GROUP + seg) * ATT_DONE_STRIDE, group, min(ATT_MERGE_GROUP, n - first)};
+}
+
+// For the block that was the last at merge_count's counter, all threads; lds as for merge_shared.  One block reads AT_ONCE
+// results in two round trips.  A list that is much longer than the others of its call - the launches decide by means - can
+// have hundreds: then the last block of each group makes one of the group's, and the last of those the segment's
+// output.  (A call on 8 lists, one with nine tenths of 30000 rows, 8 heads, D = 128, 211 results: in one block 32.7 us, so
+// 14.9, with a launch of k_att_combine 19.0; 62000 rows, 4 heads 35.5 / 15.0 / 27.0; a list of 62000 rows, 1 head, D = 64 24.2
+// / 12.0 / 18.3.  With sixteen loads a thread for the groups as well the kernel took 20 to 30 more registers and calls
+// that merge at once lost 2 %.)
+template <int D, int G, int THREADS>
+__device__ __forceinline__ void merge_last(const Workspace& ws, const MergeCount& mc, int seg, int slot0, int n, int64_t hq, float* lds,
+                                           int* s_last, float* __restrict__ out, float* __restrict__ lse) {
+    typedef MergeShape<D, G, THREADS> MS;
+    uint32_t* done = ws.att_done + (size_t)seg * ATT_DONE_STRIDE;
+    float* part = ws.att_partial + (size_t)slot0 * MS::RESULT;   // (uniform)
+    if (threadIdx.x == 0) __hip_atomic_store(mc.word, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (n <= MS::AT_ONCE) {
+        merge_shared<D, G, THREADS, MS::LOADS>(part, n, MS::RESULT, true, hq, lds, out, lse);
+        return;
+    }
+    bool final = false;
+    float* p = part + (uint32_t)(mc.group * ATT_MERGE_GROUP) * MS::RESULT;
+    int cnt = mc.of;
+    uint32_t step = MS::RESULT;
+#pragma unroll 1
+    for (;;) {
+        merge_shared<D, G, THREADS, MS::GROUP_LOADS>(p, cnt, step, final, hq, lds, out, lse);
+        if (final) return;
+        const int groups = (n + ATT_MERGE_GROUP - 1) / ATT_MERGE_GROUP;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this thread's part of the group's result has been acknowledged ...
+        __syncthreads();                                          // ... and so has the block's
+        if (threadIdx.x == 0) *s_last = atomicAdd(done, 1u) == (unsigned)groups - 1u;
+        __syncthreads();
+        if (!*s_last) return;
+        if (threadIdx.x == 0) __hip_atomic_store(done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        final = true;
+        p = part;
+        cnt = groups;
+        step = MS::RESULT * ATT_MERGE_GROUP;
+    }
 }
 
 }  // namespace kvtrim

@@ -826,6 +826,42 @@ def test_attention_of_small_calls_at_the_edges_of_their_shares(S, H, G, D, lens,
         assert np.abs(l[fin] - ref_lse[fin]).max() <= 2e-3
 
 
+# One launch goes by the mean list; a list far longer than that has more results than one block merges (four tiles of 16 at 8
+# heads and D = 128): groups of 32 meet first.  64 and 65 results (one group more, of one result), two long lists that
+# share a block, several wide groups, tiles of 64 results, a longest list that is all of the call; hard, soft and on pages.
+@pytest.mark.parametrize("H,G,D,lens", [
+    (4, 8, 128, [8319, 0, 0, 0]), (4, 8, 128, [0, 8320, 0, 0]), (8, 8, 128, [0, 9000, 9001, 0, 0, 1, 0, 0]),
+    (16, 4, 128, [30000] + [17] * 15), (32, 1, 64, [3] * 31 + [34000]), (16, 3, 64, [0] * 8 + [26001, 129] + [0] * 6)])
+def test_attention_of_a_list_that_outgrows_the_others(H, G, D, lens):
+    w = wl(1, 1, H, G, D)
+    c, now = ki.ragged_cache(w, lens, reserve=1, salt=70 + G)
+    hc = host_cache(w, c)
+    dc = kv.Cache.from_dict(c, DEV)
+    n_pages = sum((n + 127) // 128 for n in lens)
+    pages = kv.PagedCache(H, D, n_pages + 3, (max(lens) + 127) // 128, DEV)
+    ctx = kv.Context(1, 1, H, H * G, D, max(hc.cap, pages.slots))
+    q = ki.decode_inputs(w, 1)["q"]
+    qd, now_np = q.to(DEV), now.numpy() + 2
+    now_dev = torch.from_numpy(now_np).to(DEV)
+    kv.kvtrim_paged_build(ctx, dc, torch.ones(hc.cap, dtype=torch.uint8, device=DEV), dc.seg_len, pages)
+    assert kv.kvtrim_poll_error(ctx) == 0
+    for soft, call in ((False, lambda o, l: kv.kvtrim_decode_attn(ctx, dc, qd, 0, 1, 0.1, o, l)),
+                       (True, lambda o, l: kv.kvtrim_decode_attn_soft(ctx, dc, qd, now_dev, 0, 1, 0.1, o, l)),
+                       (False, lambda o, l: kv.kvtrim_paged_attn(ctx, pages, qd, 0, 1, 0.1, o, l))):
+        ref, ref_lse = oracle.attend(hc, bf16_bits(q), 0.1, soft_now=now_np if soft else None)
+        fin = np.isfinite(ref_lse)
+        got = []
+        for again in range(3):                                    # on the counters that the call before left
+            out, lse = (torch.full(r.shape, 99.0, device=DEV) for r in (ref, ref_lse))
+            call(out, lse)
+            assert kv.kvtrim_poll_error(ctx) == 0
+            got.append((out.cpu().numpy(), lse.cpu().numpy()))
+        assert all(np.array_equal(x, y) for g in got[1:] for x, y in zip(g, got[0]))
+        o, l = got[0]
+        assert attn_error(o, ref) <= ATTN_TOL and np.abs(l[fin] - ref_lse[fin]).max() <= 2e-3
+        assert np.array_equal(np.isneginf(l), ~fin) and np.all(o[~fin] == 0.0)
+
+
 # out and lse are arrays of floats and need no more than their alignment, also where the last block of a segment merges:
 # attention of a small call (2200 and 40 rows a list), of the row mover (18 chunks and 1), of segments that one block writes
 @pytest.mark.parametrize("G,D", [(4, 128), (3, 64)])
