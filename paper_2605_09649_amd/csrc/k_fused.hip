@@ -456,13 +456,12 @@ __global__ __launch_bounds__(FUS_THREADS) void k_cmp_attn(CacheView src, const u
     if constexpr (MERGE) {
         if (n_ch == 1) return;
         __shared__ int s_last;
+        const MergeCount mc = merge_count<MergeShape<D, G, FUS_THREADS>>(ws, seg, first_ch, ch - first_ch, n_ch);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // this thread's part of the result has been acknowledged ...
         __syncthreads();                                          // ... and so has the block's
-        if (tid == 0) s_last = atomicAdd(&ws.att_done[seg * ATT_DONE_STRIDE], 1u) == (unsigned)n_ch - 1u;
+        if (tid == 0) s_last = atomicAdd(mc.word, 1u) == (unsigned)mc.of - 1u;
         __syncthreads();
-        if (!s_last) return;
-        if (tid == 0) __hip_atomic_store(&ws.att_done[seg * ATT_DONE_STRIDE], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        merge_shared<D, G, FUS_THREADS, MergeShape<D, G, FUS_THREADS>::LOADS>(ws.att_partial + (size_t)first_ch * G * (D + 2), n_ch, G * (D + 2), true, q_row_of<G>(seg, sh), &s_o[0][0][0], out, lse);
+        if (s_last) merge_last<D, G, FUS_THREADS>(ws, mc, seg, first_ch, n_ch, q_row_of<G>(seg, sh), &s_o[0][0][0], &s_last, out, lse);
     }
 }
 
@@ -645,7 +644,8 @@ kvtrim_status launch_compact_inplace(kvtrim_ctx* ctx, const CacheViewMut& c, con
 // 3800 blocks: 114 -> 127 us a step) - and segments of few chunks, which one block reads back.  One-call steps in us, against
 // the launch: one chunk a segment 24.2 -> 21.2 (16 lists of 65, 2 heads, D = 64), 24.3 -> 22.3 (24 of 68, 7 heads); 7 chunks
 // 26.0 -> 24.8 (13 KB of results), 10 chunks 35.1 -> 33.9; 34 chunks, 8 heads (67 KB) 37.9 -> 39.6, a first eviction into
-// 32 such chunks 52.8 -> 62.  (What a segment longer than the others costs here it costs k_att_combine's block too.)
+// 32 such chunks 52.8 -> 62.  These are means; the chunks of a list that is much longer than the others meet in groups (see
+// merge_last): 16 lists, one with nine tenths of 464 chunks, D = 64, 2 heads 55.4 us, merged by one block 56.5, so 55.0.
 constexpr int64_t MERGE_BLOCKS = 1024, MERGE_BYTES = 16384;
 static bool merges_itself(const Shape& sh, int64_t chunks) {
     return sh.nseg <= ATT_MERGE_SEGS && chunks <= MERGE_BLOCKS &&

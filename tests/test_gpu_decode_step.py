@@ -385,10 +385,12 @@ def test_many_candidates_of_a_sequence_in_a_scanning_block(evictions, listed):
 
 # Small grids: the row mover's last block of a segment merges, a segment of one chunk (128 entries) has nothing to merge and
 # one without entries no block.  Up to 1024 blocks and 16 KB of results a segment on average (3 chunks at 8 heads, D = 128):
-# chunk counts on both sides, one long segment among short ones (four tiles of 16 results), a layer that is not attended.
+# chunk counts on both sides, one long segment among short ones (more than two tiles of 16 or 64 results: groups of 32 meet
+# first, with a last group of one), a layer that is not attended.
 @pytest.mark.parametrize("S,L,H,G,D,lens,steps", [
     (1, 2, 2, 8, 128, [128, 129, 256, 0], 4), (1, 2, 2, 8, 128, [300, 301, 250, 390], 3), (1, 1, 8, 8, 128, [0, 7500, 0, 0, 1, 2, 0, 40], 4),
-    (2, 1, 3, 4, 128, [127, 0, 128, 260, 1, 640], 5), (1, 1, 7, 3, 64, [0, 127, 126, 125, 1, 2, 0], 6), (5, 10, 20, 1, 64, [0, 40, 3, 130], 2)])
+    (2, 1, 3, 4, 128, [127, 0, 128, 260, 1, 640], 5), (1, 1, 7, 3, 64, [0, 127, 126, 125, 1, 2, 0], 6), (5, 10, 20, 1, 64, [0, 40, 3, 130], 2),
+    (1, 2, 20, 8, 128, [12400, 200, 0] + [5] * 37, 3), (1, 1, 20, 1, 64, [3] * 19 + [30000], 3)])
 def test_attention_merged_by_the_row_mover(S, L, H, G, D, lens, steps):
     w = wl(S, L, H, G, D)
     seg_len = np.resize(np.array(lens), w.nseg)
