@@ -55,8 +55,10 @@ struct SegView {
     int live;
 };
 
-constexpr int DEAL_SEGMENT = 0, DEAL_MULTI = 1, DEAL_WHOLE = 2;   // a segment or a part of one / several segments / a whole sequence to a block of k_fast_scan
+// What a block of k_fast_scan walks: a segment or a part of one / several segments / a whole sequence / one too, or a part of a long one
+constexpr int DEAL_SEGMENT = 0, DEAL_MULTI = 1, DEAL_WHOLE = 2, DEAL_PARTS = 3;
 constexpr int SCAN_RAGGED = 0, SCAN_STEP = 1, SCAN_PAGED = 2;     // what k_fast_scan walks over
+constexpr int WHOLE_ENTRIES = FAST_THREADS * FAST_BATCH;          // a batch for every lane of a block
 
 template <int KIND>
 __device__ __forceinline__ SegView seg_view(const CacheView& c, int g, int nseg, const StepArgs& sa, bool* bad, bool* nocap) {
@@ -469,7 +471,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
                                                             const int64_t* __restrict__ budget, Shape sh, Workspace ws,
                                                             int bps, int spb_arg, int limit, int32_t* __restrict__ kept_out,
                                                             uint32_t* __restrict__ thr_out, StepArgs sa) {
-    constexpr bool STEP = KIND == SCAN_STEP, PAGED = KIND == SCAN_PAGED, MULTI = DEAL == DEAL_MULTI, WHOLE = DEAL == DEAL_WHOLE;
+    constexpr bool STEP = KIND == SCAN_STEP, PAGED = KIND == SCAN_PAGED, MULTI = DEAL == DEAL_MULTI, WHOLE = DEAL >= DEAL_WHOLE, PARTS = DEAL == DEAL_PARTS;
     static_assert(!STEP || SCORE, "the one-call step computes the scores itself");
     __shared__ ResolveShared sm;
     __shared__ int s_last, s_ncand;
@@ -497,7 +499,8 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     // each (whole wavefronts).  A block takes every bpq-th segment, so that neighbouring segments - a layer's, whose
     // candidates come in the same steps - are staged by different blocks.  STEP: behind the scanning blocks the grid has blocks
     // that only write the segments' tables, a wavefront per segment.
-    // WHOLE: a block walks all segments of its sequence.
+    // WHOLE: a block walks all segments of its sequence; PARTS: of a sequence of more than a batch up to bps (= gridDim.y)
+    // blocks walk a part each, and a shorter one's other blocks have nothing to do.
     const int spb = MULTI ? spb_arg : 1;
     const int bpq = WHOLE ? 1 : (sh.segs_per_seq + spb - 1) / spb * bps;   // scanning blocks per sequence
     const bool tables_only = STEP && (int)blockIdx.x >= sh.n_seq * bpq;
@@ -519,6 +522,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     __syncthreads();
     // the tables-only blocks take no part in the scan, so a sequence's last block never waits for them
     if (tables_only) {
+        if (PARTS && blockIdx.y > 0) return;
         write_step_tables(c, sh, ws, sa, ((int)blockIdx.x - sh.n_seq * bpq) * (FAST_THREADS / 64), sm.lds32);
         return;
     }
@@ -571,7 +575,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
             carry += tot;
             if (g < sh.nseg && g % sh.segs_per_seq == 0) s_seqcnt[g / sh.segs_per_seq] = (int)(uint32_t)(ex >> 28);
             if (g >= g0 && g < g0 + sh.segs_per_seq) {
-                kept_out[g] = 0;
+                if (!PARTS) kept_out[g] = 0;
                 s_start[g - g0] = (uint32_t)sv.start;
                 s_len[g - g0] = (uint32_t)sv.len;
                 s_chb[g - g0] = (uint32_t)(ex & 0xFFFFFFFu);
@@ -605,7 +609,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
             if (tid < sh.segs_per_seq) {
                 sv = seg_view<KIND>(c, g0 + tid, sh.nseg, sa, &b2, &n2);
                 if (b2) atomicOr(ws.err, ERR_LAYOUT);
-                kept_out[g0 + tid] = 0;                           // the mask kernel adds its counts
+                if (!PARTS) kept_out[g0 + tid] = 0;               // the mask kernel adds its counts
                 cnt = sv.live;
             }
             int32_t tot;
@@ -621,8 +625,16 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         constexpr uint32_t NW = FAST_THREADS / 64;
         const uint32_t first_before = STEP ? (uint32_t)s_seqcnt[seq] : 0u;
-        const uint32_t share = (total + NW * 64 - 1) / (NW * 64) * 64;
-        const uint32_t i0 = first_before + min(total, (uint32_t)wave * share), i1 = first_before + min(total, ((uint32_t)wave + 1) * share);
+        uint32_t share = (total + NW * 64 - 1) / (NW * 64) * 64, w = (uint32_t)wave, parts = 1;
+        if (PARTS) {
+            if (total > WHOLE_ENTRIES) {
+                parts = min((uint32_t)bps, (total - 1) / WHOLE_ENTRIES + 1);
+                share = (total + parts * NW * 64 - 1) / (parts * NW * 64) * 64;
+                w += blockIdx.y * NW;
+            }
+            if (blockIdx.y >= parts) return;                      // (the whole block: there is no part for it)
+        }
+        const uint32_t i0 = first_before + min(total, w * share), i1 = first_before + min(total, (w + 1) * share);
         int sl = -1;                                              // the segment of this lane's entry
         for (int base = 0; base < sh.segs_per_seq; base += 64)
             sl += __popcll(__ballot(base + lane < sh.segs_per_seq && s_before[min(base + lane, sh.segs_per_seq - 1)] <= i0));
@@ -677,6 +689,58 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
             }
         }
         min_key = block_min_u32(mn, sm.red_u);                    // (its barriers also complete s_ncand and the staged entries)
+        if (PARTS && parts > 1) {
+            // The blocks of a long sequence meet on its list in memory, each with one place for all it has staged (they are 8 at
+            // most), and the last takes the list into its LDS, as if it had walked the sequence alone.
+            const int ncand = s_ncand;
+            uint32_t* k_list = ws.fl_key + (size_t)seq * cap;
+            int32_t* s_list = ws.fl_seg + (size_t)seq * cap;
+            int32_t* p_list = ws.fl_pos + (size_t)seq * cap;
+            int32_t* i_list = ws.fl_idx + (size_t)seq * cap;
+            const size_t at_word = (size_t)seq * (uint32_t)ws.fast_stride;
+            uint32_t* count = ws.fl_count + FAST_SUB * at_word;
+            uint32_t* lowest = ws.fast_min + FAST_SUB * at_word;
+            uint32_t* arrived = ws.fast_done + (FAST_SUB + 1) * at_word;
+            if (tid == 0) {
+                if (min_key != 0xFFFFFFFFu) atomicMin(lowest, min_key);
+                s_base[0] = ncand ? atomicAdd(count, ncand > STAGE ? cap + 1u : (uint32_t)ncand) : 0u;
+            }
+            __syncthreads();
+            for (int i = tid; i < ncand && ncand <= STAGE; i += FAST_THREADS) {
+                const uint32_t slot = s_base[0] + (uint32_t)i;
+                if (slot < cap) {
+                    st_dev(&k_list[slot], c_key[i]);
+                    st_dev(&s_list[slot], c_seg[i]);
+                    st_dev(&p_list[slot], c_pos[i]);
+                    if (STEP) st_dev(&i_list[slot], c_idx[i]);
+                }
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // this thread's list entries are acknowledged ...
+            __syncthreads();                                      // ... and so are the whole block's, before it arrives
+            if (tid == 0) {
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");   // (thread 0's own atomics above have returned)
+                s_last = atomicAdd(arrived, 1u) == parts - 1u;
+            }
+            __syncthreads();
+            if (!s_last) return;
+            const uint32_t n = ld_dev(count);
+            min_key = ld_dev(lowest);
+            for (uint32_t i = tid; i < n && n <= cap; i += FAST_THREADS) {   // (cap <= STAGE)
+                c_key[i] = ld_dev(&k_list[i]);
+                c_seg[i] = ld_dev(&s_list[i]);
+                c_pos[i] = ld_dev(&p_list[i]);
+                if (STEP) c_idx[i] = ld_dev(&i_list[i]);
+            }
+            __syncthreads();                                      // every thread has read the per-call words ...
+            if (tid == 0) {                                       // ... which go back to "between calls"
+                s_ncand = n <= cap ? (int)n : STAGE + 1;
+                atomicExch(arrived, 0u);
+                atomicExch(count, 0u);
+                atomicExch(lowest, 0xFFFFFFFFu);
+            }
+            __syncthreads();
+        }
+        if (PARTS && tid < sh.segs_per_seq) kept_out[g0 + tid] = 0;   // (here: by the block that will write the counts, no other)
         n_list = (uint32_t)s_ncand;
         sub_overflow = n_list > (uint32_t)STAGE;
 #pragma unroll
@@ -1301,22 +1365,29 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_mask(CacheView c, const f
 // pages, so that a wavefront's entries stay in one.
 struct ScanGrid {
     int deal, bps, spb, limit;
-    unsigned blocks;
+    unsigned blocks, parts = 1;
 };
 // A whole sequence to a block, which then neither lists its candidates in memory nor meets other blocks: up to a batch of
 // FAST_BATCH entries for every lane of its wavefronts.  One-call steps in us, against a block per segment or several
 // segments to a block: 16 lists of 65 entries 24.2 / 26.6, 64 of 101 27.2 / 29.2, 4 of 1901 25.9 / 29.4, eight sequences
 // of 16 lists of 501 38.5 / 40.9; but with two batches the walk has no other blocks to hide behind: 2 x 18 lists of 1152
-// 38.3 / 34.9, 88 lists of 297 35.2 / 28.8.  The capacity in all is bounded because nothing says that a batch's
-// sequences are alike: the longest may be all of it.
-constexpr int64_t WHOLE_ENTRIES = FAST_THREADS * FAST_BATCH, WHOLE_CAP = 8 * WHOLE_ENTRIES;
-static bool scan_whole(const Shape& sh, int64_t cap, int64_t max_pps) {
-    if (sh.segs_per_seq > STEP_MAX_SEGS || sh.n_seq > STEP_MAX_SEQS || cap / sh.n_seq > WHOLE_ENTRIES || cap > WHOLE_CAP) return false;
-    return sh.segs_per_seq * max_pps < 1 << 24;                   // (a sequence's slots are counted in 32 bits)
+// 38.3 / 34.9, 88 lists of 297 35.2 / 28.8.  That is a mean: nothing says that a batch's sequences are alike, the longest may be
+// all of it.  Beyond two batches in all the grid therefore has more blocks for each sequence, as many as the longest could
+// use and a compute unit each has (for more than 128 sequences none: those are better off with a block each whatever their
+// lengths, 200 sequences of 288 entries, nine tenths of all in one 75.5 / 100.6).  Lists of 500 for four sequences, alike / one
+// with nine tenths / with half: 27.7, 29.0, 29.8 us, dealt by segments 31.0, 30.8, 31.0, a block for each whatever its length 27.4,
+// 36.1, 30.6; for eight 31.9, 33.6, 34.6 (34.5, 34.9, 34.4; 31.5, 52.9, 34.5).  The separate instance, because what a sequence of
+// one block never needs costs it 0.5 us all the same.
+constexpr int64_t WHOLE_CAP = 8 * WHOLE_ENTRIES;
+static int whole_parts(const Shape& sh, int64_t cap, int resident, int64_t max_pps) {   // blocks for a sequence; 0: dealt in another way
+    if (sh.segs_per_seq > STEP_MAX_SEGS || sh.n_seq > STEP_MAX_SEQS || cap / sh.n_seq > WHOLE_ENTRIES || cap > WHOLE_CAP) return 0;
+    if (sh.segs_per_seq * max_pps >= 1 << 24) return 0;           // (a sequence's slots are counted in 32 bits)
+    const int64_t most = (cap + WHOLE_ENTRIES - 1) / WHOLE_ENTRIES, room = resident / sh.n_seq;
+    return cap <= 2 * WHOLE_ENTRIES || room < 2 ? 1 : (int)(most < room ? most : room);
 }
 static ScanGrid scan_grid(const Shape& sh, int64_t cap, int resident, bool whole, int64_t max_pps = 0) {
     ScanGrid g;
-    if (whole && scan_whole(sh, cap, max_pps)) return ScanGrid{DEAL_WHOLE, 1, 1, 0, (unsigned)sh.n_seq};
+    if (const int parts = whole ? whole_parts(sh, cap, resident, max_pps) : 0) return ScanGrid{parts > 1 ? DEAL_PARTS : DEAL_WHOLE, parts, 1, 0, (unsigned)sh.n_seq, (unsigned)parts};
     const int64_t bps = cap / ((int64_t)sh.nseg * FAST_ENTRIES_PER_BLOCK);
     g.bps = (int)(bps < 1 ? 1 : (bps > 64 ? 64 : bps));
     g.spb = 1;
@@ -1334,8 +1405,9 @@ constexpr int SCAN_RESIDENT = 256, MASK_RESIDENT = 512;
 template <int KIND>
 static void launch_scan(const ScanGrid& g, const CacheView& c, const int32_t* now, float* score, const int64_t* budget, const Shape& sh,
                         const Workspace& ws, int32_t* kept, uint32_t* thr, const StepArgs& sa, unsigned more_blocks, hipStream_t st) {
-#define KVTRIM_DEAL(d) hipLaunchKernelGGL((k_fast_scan<true, KIND, d>), dim3(g.blocks + more_blocks), dim3(FAST_THREADS), 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, g.bps, g.spb, g.limit, kept, thr, sa)
+#define KVTRIM_DEAL(d) hipLaunchKernelGGL((k_fast_scan<true, KIND, d>), dim3(g.blocks + more_blocks, g.parts), dim3(FAST_THREADS), 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, g.bps, g.spb, g.limit, kept, thr, sa)
     if (g.deal == DEAL_WHOLE) KVTRIM_DEAL(DEAL_WHOLE);
+    else if (g.deal == DEAL_PARTS) KVTRIM_DEAL(DEAL_PARTS);
     else if (g.deal == DEAL_MULTI) KVTRIM_DEAL(DEAL_MULTI);
     else KVTRIM_DEAL(DEAL_SEGMENT);
 #undef KVTRIM_DEAL

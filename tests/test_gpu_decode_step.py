@@ -344,12 +344,16 @@ def test_long_segments_among_several_to_a_scanning_block(S, L, H, long_lens):
 
 
 # A sequence to a block up to 8192 entries of capacity per sequence and 65536 in all: both sides of the line, everything in
-# one segment, empty segments first and last, uneven sequences (several batches of a wavefront), as many segments as a step
-# may have.
+# one segment, empty segments first and last, uneven sequences, as many segments as a step may have.  Beyond 16384 in
+# all up to eight blocks share a sequence of more than 8192: just under and over, all of them and fewer, with
+# segments of every length at the borders of their parts; 128 sequences have two blocks at most, 129 one.
 @pytest.mark.parametrize("S,L,H,lens,cap", [
     (1, 2, 4, [0, 7000, 1, 63, 0, 64, 65, 0], 8192), (1, 2, 4, [0, 7000, 1, 63, 0, 64, 65, 0], 8193),
     (3, 1, 5, [0, 0, 19000, 700, 30] + [1, 0, 2, 3, 0] + [0, 0, 0, 0, 130], 3 * 8192),
-    (1, 64, 16, [0, 1, 7, 13, 2, 5, 0, 3], 8192), (8, 2, 2, [300, 129, 128, 127], 65536), (8, 2, 2, [300, 129, 128, 127], 65537)])
+    (1, 64, 16, [0, 1, 7, 13, 2, 5, 0, 3], 8192), (8, 2, 2, [300, 129, 128, 127], 65536), (8, 2, 2, [300, 129, 128, 127], 65537),
+    (3, 2, 2, [2000, 2096, 4095, 1] + [8191, 1, 0, 1] + [0, 0, 0, 5], 3 * 8192), (2, 2, 2, [8100, 0, 0, 1] + [8230, 0, 1, 0], 16384),
+    (8, 1, 4, [60000, 1, 0, 3500] + [7, 0, 2, 1] * 7, 65536), (4, 3, 5, [(17 * i * i) % 4001 for i in range(15)] + [3] * 45, 32768),
+    (128, 1, 2, [17000, 1] + [20, 3] * 127, 32768), (129, 1, 2, [17000, 1] + [20, 3] * 128, 32768)])
 def test_a_sequence_to_a_scanning_block(S, L, H, lens, cap):
     from paged_harness import run_paged_both
     from test_gpu_paged import check as check_paged
