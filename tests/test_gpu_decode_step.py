@@ -384,7 +384,33 @@ def test_many_candidates_of_a_sequence_in_a_scanning_block(evictions, listed):
     rng = np.random.default_rng(4)
     log_beta = (lambda cap, start: -rng.random(cap)) if listed else (lambda cap, start: np.zeros(cap))
     counts = select_repeatedly(w, lens, log_beta, evictions, 3)
-    assert sum(counts) == 9 and (counts == (9, 0) or not listed)
+    assert counts == ((9, 0) if listed else (0, 9))
+
+
+# As many candidates as the list holds, and one more: 400 scattered ones and a cluster that one bin of the ranking holds, so the
+# bound that a call leaves lists all of it in the next.  One more, and that call takes the single-block select, which leaves
+# a bound of its own.  A sequence to a block (what it holds in LDS), several blocks to a sequence (what they meet on), and 300
+# sequences, whose lists are shorter (3456).
+@pytest.mark.parametrize("S,n,many,short,evictions,listed", [
+    (3, 6000, 4096, 0, 490, 9), (3, 6000, 4097, 0, 490, 6), (4, 20000, 4096, 3, 490, 3), (4, 20000, 4097, 3, 490, 2),
+    (300, 4992, 3456, 299, 400, 3), (300, 4992, 3457, 299, 400, 2)])
+def test_a_full_candidate_list_and_one_more(S, n, many, short, evictions, listed):
+    from test_gpu_score_select import select_repeatedly
+    w = wl(S, 1, 16, 1, 64)
+    lens = np.full(w.nseg, 1)                                     # (short sequences retain nothing: no threshold, not counted)
+    lens[:(S - short) * 16] = n // 16
+    top = int(lens.max())
+
+    def log_beta(cap, start):
+        rng = np.random.default_rng(many)
+        lb = np.full(cap, -0.1 / (top + 1))                       # scores above -0.1
+        for s in range(S - short):
+            pick = rng.permutation(n)[:many]                      # entries of the sequence
+            target = np.concatenate([-rng.uniform(2, 1000, 400), -1.0 - 1e-4 * rng.random(many - 400)])
+            at, pos = start[s * 16 + pick // (n // 16)] + pick % (n // 16), pick % (n // 16)
+            lb[at] = target / (top + 1 - pos)
+        return lb
+    assert select_repeatedly(w, lens, log_beta, evictions, 3) == (listed, 3 * (S - short) - listed)
 
 
 # Small grids: the row mover's last block of a segment merges, a segment of one chunk (128 entries) has nothing to merge and
