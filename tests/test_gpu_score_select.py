@@ -268,3 +268,41 @@ def test_sequences_of_few_segments_stay_on_the_candidate_list(S, H, evictions):
     rng = np.random.default_rng(evictions)
     lens = rng.integers(140, 161, w.nseg)
     assert select_repeatedly(w, lens, lambda cap, start: -rng.random(cap), evictions, 3) == (3 * S, 0)
+
+
+@pytest.mark.parametrize("cap,offset", [(1 << 21, 0), ((1 << 21) + 5, 0), ((1 << 21) - 1, 0), ((1 << 21) + 3, 1)])
+def test_tails_enter_the_scores_of_large_caches(cap, offset):
+    # from 2097152 entries on the first pass loads log beta, positions and tails past the caches, four entries at a time where
+    # the arrays are 16-byte aligned; segments that begin and end at any entry, one of them empty, free entries behind the last
+    w = wl(2, 2, 3, 1, 64)
+    rng = np.random.default_rng(cap % 1000 + offset)
+    lens = rng.integers(100000, 170001, w.nseg)
+    lens[[1, 7]] = [0, 3]
+    lens[11] += cap - 9 - w.nseg - int(lens.sum())
+    start = np.concatenate([[0], np.cumsum(lens + 1)[:-1]])
+    c = {"k": torch.zeros(cap, 64, dtype=torch.bfloat16), "v": torch.zeros(cap, 64, dtype=torch.bfloat16),
+         "log_beta": torch.from_numpy(-np.log1p(np.exp(-(rng.standard_normal(cap) * 1.5 + 3)))).float(),
+         "pos": torch.from_numpy((np.arange(cap) - np.repeat(np.append(start, cap - 9), np.append(lens + 1, 9))).astype(np.int32)),
+         "seg_start": torch.from_numpy(start), "seg_len": torch.from_numpy(lens.astype(np.int32)), "cap": cap}
+    c["log_tail"] = ki.log_tail_of(c["log_beta"], 2)
+    now = np.array([int(lens[:6].max()), int(lens[6:].max())], dtype=np.int32)
+    hc = host_cache(w, c)
+    score = oracle.score(hc, now)
+    budget = np.array([int(lens[:6].sum()) // 9, int(lens[6:].sum()) // 2])
+    keep, kept, thr = oracle.select(hc, score, budget)
+
+    def on_gpu(t):
+        b = torch.zeros(t.numel() + offset, dtype=t.dtype, device=DEV)[offset:]
+        return b.copy_(t)
+    dc = kv.Cache(c["k"].to(DEV), c["v"].to(DEV), on_gpu(c["log_beta"]), on_gpu(c["pos"]), c["seg_start"].to(DEV),
+                  c["seg_len"].to(DEV), on_gpu(c["log_tail"]))
+    ctx = kv.Context(2, 2, 3, 3, 64, cap)
+    live = live_mask(hc)
+    s = torch.full((cap,), 7.0, device=DEV)
+    k = torch.full((cap,), 7, dtype=torch.uint8, device=DEV)
+    n, t = torch.zeros(w.nseg, dtype=torch.int32, device=DEV), torch.zeros(2, dtype=torch.int32, device=DEV)
+    kv.kvtrim_score_select(ctx, dc, torch.from_numpy(now).to(DEV), torch.from_numpy(budget).to(DEV), s, k, n, t)
+    assert kv.kvtrim_poll_error(ctx) == 0
+    assert np.array_equal(s.cpu().numpy()[live].view(np.uint32), score[live].view(np.uint32))
+    assert np.array_equal(k.cpu().numpy()[live], keep[live]) and np.array_equal(n.cpu().numpy(), kept)
+    assert np.array_equal(t.cpu().numpy().view(np.uint32), thr)
