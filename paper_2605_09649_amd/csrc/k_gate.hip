@@ -913,8 +913,7 @@ constexpr int GATE_PER_TOKEN = 0, GATE_SLICE = 1, GATE_PREFILL = 2;
 struct GatePlan {
     int kind, tt, mt, ch;
 };
-static GatePlan gate_plan(const kvtrim_ctx* ctx, const GateView& g, int n_tok, int nl, bool prepared) {
-    const int n_heads = ctx->shape.n_kv_heads;
+static GatePlan gate_plan(int n_heads, const GateView& g, int n_tok, int nl, bool prepared) {
     auto tiles = [&](int tt) { return (int64_t)((n_tok + 16 * tt - 1) / (16 * tt)); };
     // The choice is by time, estimated (us) from a fixed part and one per round of blocks - one block per compute unit - of
     // either kernel: least-squares fits to 5200 measured calls (1 to 40 layers, d_model 1024 to 4096, 128 to 512 units, 33
@@ -988,6 +987,22 @@ static GatePlan gate_plan(const kvtrim_ctx* ctx, const GateView& g, int n_tok, i
     return {GATE_PER_TOKEN, 0, 0, 0};
 }
 
+// k_gate_prefill's token rows past the caches: calls whose rows no cache holds, which run in blocks of 128 tokens.
+static bool gate_streams(const GatePlan& plan, const GateView& g, int n_tok, int nl) {
+    return plan.kind == GATE_PREFILL && plan.tt == 8 && 2 * (size_t)n_tok * nl * g.d_model > GP_STREAM_BYTES;
+}
+
+// Which instance of k_gate_prefill such a call runs: tokens per block, + 1000 with W1 in operand order, + 2000 with the token rows
+// past the caches; 0: another kernel.  Host-only and no part of the API; the tests ask it whether a case reaches what it is for.
+extern "C" int32_t kvtrim_internal_gate_prefill(int32_t n_heads, int32_t d_model, int32_t d_g, int32_t n_tok, int32_t nl, int32_t prepared) {
+    GateView g{};
+    g.d_model = d_model;
+    g.d_g = d_g;
+    const GatePlan plan = gate_plan(n_heads, g, n_tok, nl, prepared != 0);
+    if (plan.kind != GATE_PREFILL) return 0;
+    return 16 * plan.tt + (prepared || tiled_fits(g, n_tok, nl, n_heads) ? 1000 : 0) + (gate_streams(plan, g, n_tok, nl) ? 2000 : 0);
+}
+
 // Readout from folded vectors for calls that went through the per-token first-layer kernels: one wavefront
 // per (token, layer, head) forms z = v . u + s - every dot product is one trip to memory, all of them at once.
 constexpr int GD_THREADS = 256;
@@ -1049,7 +1064,7 @@ kvtrim_status launch_gate(kvtrim_ctx* ctx, const GateView& g, const float* prepa
     const uint4* ptiled = prepared ? reinterpret_cast<const uint4*>(prepared + folded_floats(g, L, n_heads)) +
                                          (size_t)layer_begin * (g.d_g >> 4) * (g.d_model >> 6) * 128
                                    : nullptr;
-    const GatePlan plan = gate_plan(ctx, g, n_tok, nl, prepared != nullptr);
+    const GatePlan plan = gate_plan(n_heads, g, n_tok, nl, prepared != nullptr);
     if (plan.kind != GATE_PER_TOKEN) {
         const float* v = pv;
         const float* sconst = ps;
@@ -1105,7 +1120,7 @@ kvtrim_status launch_gate(kvtrim_ctx* ctx, const GateView& g, const float* prepa
             const int tt = plan.tt;
             const int tiles = (n_tok + 16 * tt - 1) / (16 * tt);
             const dim3 grid(8u * (unsigned)((nl + 7) / 8) * (unsigned)tiles);
-            const bool stream = 2 * (size_t)n_tok * nl * g.d_model > GP_STREAM_BYTES;
+            const bool stream = gate_streams(plan, g, n_tok, nl);
 #define KVTRIM_GATE_PREFILL(HT, TT, TILED)                                                                                    \
     hipLaunchKernelGGL((k_gate_prefill<HT, TT, TILED, false>), grid, dim3(GP_THREADS), 0, st, g, x, n_tok, layer_begin, nl, L,       \
                        n_heads, horizon, tiled, v, sconst, log_beta_out, log_tail_out)
@@ -1114,8 +1129,8 @@ kvtrim_status launch_gate(kvtrim_ctx* ctx, const GateView& g, const float* prepa
                        n_heads, horizon, tiled, v, sconst, log_beta_out, log_tail_out)
 #define KVTRIM_GATE_PREFILL_TT(HT)                                                                                            \
     do {                                                                                                                      \
-        if (use_tiled && tt == 8 && stream) KVTRIM_GATE_PREFILL_STREAM(HT, true);                                             \
-        else if (tt == 8 && stream) KVTRIM_GATE_PREFILL_STREAM(HT, false);                                                    \
+        if (use_tiled && stream) KVTRIM_GATE_PREFILL_STREAM(HT, true);                                                        \
+        else if (stream) KVTRIM_GATE_PREFILL_STREAM(HT, false);                                                               \
         else if (use_tiled && tt == 8) KVTRIM_GATE_PREFILL(HT, 8, true);                                                      \
         else if (use_tiled && tt == 4) KVTRIM_GATE_PREFILL(HT, 4, true);                                                      \
         else if (use_tiled) KVTRIM_GATE_PREFILL(HT, 2, true);                                                                 \

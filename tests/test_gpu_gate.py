@@ -321,10 +321,15 @@ def test_sliced_kernel_is_as_exact_as_the_two_kernels(n_tok):
     assert err[32] <= 1.1 * err[33]
 
 
-@pytest.mark.parametrize("L,n_tok,d_model,d_g,prepared", [(24, 4090, 2048, 512, True), (24, 3585, 2048, 128, False), (34, 1205, 4096, 256, False)])
-def test_calls_whose_rows_bypass_the_caches_give_the_same_bits(L, n_tok, d_model, d_g, prepared):
-    # more than 300 MB of token rows are loaded past the caches (W1 from its copy, made in the call or straight from its rows);
-    # the same layers in two calls are not.  At least 257 blocks of 128 tokens in either, so the tiles are the same.
+# W1 prepared or copied in the call (+ 1000), or straight from its rows; every width that the kernel has
+@pytest.mark.parametrize("L,n_tok,d_model,d_g,prepared,w1", [
+    (24, 4090, 2048, 512, True, 1000), (16, 3113, 4096, 128, False, 1000), (32, 1577, 4096, 128, False, 0), (34, 1205, 4096, 256, False, 0),
+    (22, 3001, 3072, 384, False, 1000)])
+def test_calls_whose_rows_bypass_the_caches_give_the_same_bits(L, n_tok, d_model, d_g, prepared, w1):
+    # more than 300 MB of token rows are loaded past the caches; the same layers in two calls are not.  Both in blocks of 128
+    # tokens, as the library's own plan says.
+    for layers, rows in ((L, 2000), (L // 2, 0)):
+        assert kv.load_library().kvtrim_internal_gate_prefill(2, d_model, d_g, n_tok, layers, int(prepared)) == 128 + w1 + rows
     g = torch.Generator(device=DEV).manual_seed(n_tok)
     H = 2
     w = {k: v.to(DEV) for k, v in ki.gate_weights(L, H, d_model, d_g, 4, b_g=3.5, seed=9).items() if torch.is_tensor(v)}
