@@ -282,14 +282,14 @@ kvtrim_status kvtrim_append(kvtrim_ctx *ctx, kvtrim_cache *c, const void *k_new,
  * leave there (bit for bit in everything but out / lse, which agree within the attention tolerance: the split of
  * the softmax sums is the same, so in practice they are equal too).  Arguments as in those three calls; keep_out is
  * required.  With a small evict_hint (see kvtrim_score_select), at most 1024 segments per sequence, 1024 sequences
- * and 16 new tokens per segment the step is THREE kernels:
+ * and 16 new tokens per segment the step is two or three kernels:
  * one scores, lists the eviction candidates and - in each sequence's last block - ranks them, counts the evicted
  * entries per segment and per chunk of 128 entries and leaves the destination's segment table and, per segment, the
  * indices of its evicted entries (further blocks of the same launch append the new tokens); one moves every
  * surviving row while using it for the attention of its segment (no mask pass, no compaction scan: a block derives
- * its chunk's destination from its segment's record and writes the chunk's mask bytes itself); one merges the
- * partial attention results (small caches: the second does that, too, and the step is two).  Any other shape or hint runs the three calls one after the other.  Device-side errors as in
- * the three calls. */
+ * its chunk's destination from its segment's record and writes the chunk's mask bytes itself); a third merges
+ * the partial attention results, unless the cache is small and the second did so itself.  Any other shape or hint runs
+ * the three calls one after the other.  Device-side errors as in the three calls. */
 kvtrim_status kvtrim_decode_step(kvtrim_ctx *ctx, kvtrim_cache *src, const void *k_new, const void *v_new,
                                  const float *log_beta_new, const float *log_tail_new, const int32_t *pos_new,
                                  int32_t n_new, const int32_t *now, const int64_t *budget, float *score_out,

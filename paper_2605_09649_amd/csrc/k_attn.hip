@@ -404,7 +404,7 @@ __global__ __launch_bounds__(att_threads(MODE)) void k_att_partial(CacheView c, 
     for (int ord = seg_b; ord <= seg_e && ord < n_in; ++ord) {
     const int seg_rows = (int)(rp(ord + 1) - rp(ord));
     const int run_lo = ord == seg_b ? row_b : 0;                  // this block's rows of the segment: [run_lo, run_hi)
-    const int run_hi = ord == seg_e ? row_e : seg_rows;           // (a multiple of 64, or the segment's end)
+    const int run_hi = ord == seg_e ? row_e : seg_rows;           // (a multiple of 2^unit_log rows, or the segment's end)
     if (run_lo >= run_hi) continue;                               // (uniform over the block)
     const int seg = seg_of_ordinal(ord, per, layer_begin, sh);
     const int64_t seg_start = PAGED ? (int64_t)seg * pt.max_pps : (PLANNED ? c.seg_start[seg] : (ONE ? (int64_t)__builtin_amdgcn_readlane(start_of, ord) : (int64_t)s_start[ord]));

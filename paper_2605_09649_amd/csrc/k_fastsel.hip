@@ -1376,7 +1376,8 @@ struct ScanGrid {
 // use and a compute unit each has (for more than 128 sequences none: those are better off with a block each whatever their
 // lengths, 200 sequences of 288 entries, nine tenths of all in one 75.5 / 100.6).  Lists of 500 for four sequences, alike / one
 // with nine tenths / with half: 27.7, 29.0, 29.8 us, dealt by segments 31.0, 30.8, 31.0, a block for each whatever its length 27.4,
-// 36.1, 30.6; for eight 31.9, 33.6, 34.6 (34.5, 34.9, 34.4; 31.5, 52.9, 34.5).  The separate instance, because what a sequence of
+// 36.1, 30.6; for eight 31.9, 33.6, 34.6 (34.5, 34.9, 34.4; 31.5, 52.9, 34.5); 64 sequences of 16 lists of 60, four blocks for each at most,
+// 34.6, 44.9, 34.8 (40.2, 42.7, 40.8; 34.0, 57.0, 34.1).  The separate instance, because what a sequence of
 // one block never needs costs it 0.5 us all the same.
 constexpr int64_t WHOLE_CAP = 8 * WHOLE_ENTRIES;
 static int whole_parts(const Shape& sh, int64_t cap, int resident, int64_t max_pps) {   // blocks for a sequence; 0: dealt in another way

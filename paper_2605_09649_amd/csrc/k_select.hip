@@ -172,9 +172,10 @@ __device__ __forceinline__ void reload_quad_tail(const T* __restrict__ base, con
 }
 
 // STREAM (with SCORE): log beta, positions and tails, which the call's passes do not read again, are loaded past the caches and
-// leave those to the scores, which they do.  That pays once all of it is more than the caches hold: a 128 K prefill of 256
-// lists (33.5 M entries) 630 -> 622 us a first eviction, chunks of 4096 for 1024 lists of 8192 (12.6 M) 1765 -> 1720, 256 lists of
-// 15 K (3.9 M) 606 -> 597; but 98 x 8 lists of 1 K (0.8 M) 151 -> 154.
+// leave those to the scores, which they do.  That pays where the scores are what the caches can hold: chunks of 4096 for 1024 lists of
+// 8192 (12.6 M entries) 1700 -> 1657 us (both in one process, taking turns), 256 lists of 15 K (3.9 M) 606 -> 597; a first
+// eviction behind a 128 K prefill of 256 lists (33.5 M, 134 MB of scores) is the same, 614 to 621 either way; and 98 x 8 lists of
+// 1 K (0.8 M) 151 -> 154.
 constexpr int64_t SEL_STREAM = 2 << 20;
 template <int PASS, int SHIFT, bool PAGED, bool SCORE = false, bool STREAM = false>
 __global__ __launch_bounds__(HIST_THREADS, 8) void k_sel_hist(const float* __restrict__ score, Shape sh,

@@ -45,7 +45,11 @@ constexpr int HIST_REPLICAS = 8;     // copies of the merged histogram (spreads 
 // Decode-step selection (k_fastsel.hip): candidates below the carried bound are listed per sequence.
 constexpr int FL_CAP_MAX = 4096;     // list entries per sequence (fewer when the context has many sequences)
 constexpr int FL_CAP_MIN = 64;
-constexpr int FAST_WORD_STRIDE = 64, FAST_WORD_SEQS = 32;   // words between two counters that the blocks of a sequence meet on (256 bytes); next to each other for more sequences, which have fewer blocks each
+// Words between two counters that the blocks of a sequence meet on (256 bytes); next to each other for more sequences, which have
+// fewer blocks each.  Against words next to each other, both in one process and taking turns, the mean of either order: a
+// step of 256 lists in place 1.0 % faster, on pages 0.8, 16 sequences 1.2, 2 x 112 lists 0.5, 256 lists of 8192 0.5; steps of few
+// blocks the same.
+constexpr int FAST_WORD_STRIDE = 64, FAST_WORD_SEQS = 32;
 constexpr int FAST_THREADS = 1024;
 constexpr int FAST_ENTRIES_PER_BLOCK = 8192;   // entries of a segment one block covers (blocks per segment from the capacity)
 

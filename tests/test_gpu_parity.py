@@ -777,8 +777,8 @@ def test_attention_on_a_bad_table_outside_the_layer_range_gives_no_result():
 # launch: lengths on both sides of each, 64 and 65 segments, and the same call again on counters that the first left behind.
 @pytest.mark.parametrize("S,H,G,D,lens,soft", [
     (1, 16, 4, 128, [0, 1, 15, 16, 17, 63, 64, 65, 127, 128, 129, 130, 255, 256, 257, 2100], False),
-    (1, 2, 8, 128, [5000, 100], False),                           # 40 results to merge: three tiles of 16
-    (1, 1, 1, 64, [9000], True),                                  # 71 results: a tile of 64 and the rest
+    (1, 2, 8, 128, [5000, 100], False),                           # 39 results to merge, more than two tiles of 16: in groups of 32
+    (1, 1, 1, 64, [9000], True),                                  # 70 results: a tile of 64 and the rest
     (1, 3, 3, 128, [0, 0, 4097], True),
     (4, 16, 2, 64, [40, 0, 300, 16], False),                      # 64 segments, most shorter than a round
     (5, 13, 2, 64, [40, 0, 300, 16], False),                      # 65: two launches
