@@ -468,12 +468,12 @@ __global__ __launch_bounds__(FUS_THREADS) void k_cmp_attn(CacheView src, const u
 template <int D, bool INPLACE>
 static bool dispatch_fused(int G, dim3 grid, hipStream_t st, const CacheView& src, const uint8_t* keep,
                            const CacheViewMut& dst, const CacheViewMut& stage, const uint16_t* q, const Shape& sh,
-                           const Workspace& ws, float scale_log2, int lb, int le, bool merge = false, float* out = nullptr, float* lse = nullptr) {
+                           const Workspace& ws, float scale_log2, int lb, int le, bool most_stay = false, bool merge = false, float* out = nullptr, float* lse = nullptr) {
     switch (G) {
 #define KVTRIM_CASE(g) \
     case g: \
         if (!INPLACE && merge) hipLaunchKernelGGL((k_cmp_attn<D, g, false, false, false, !INPLACE>), grid, dim3(FUS_THREADS), 0, st, src, keep, dst, stage, q, sh, ws, scale_log2, lb, le, nullptr, out, lse); \
-        else hipLaunchKernelGGL((k_cmp_attn<D, g, INPLACE>), grid, dim3(FUS_THREADS), INPLACE ? 0 : mover_lds(D, g, dense_blocks(src.cap, dst.cap, grid.x)), st, src, keep, dst, stage, q, sh, ws, scale_log2, lb, le); \
+        else hipLaunchKernelGGL((k_cmp_attn<D, g, INPLACE>), grid, dim3(FUS_THREADS), !INPLACE && most_stay ? mover_lds(D, g, grid.x) : 0, st, src, keep, dst, stage, q, sh, ws, scale_log2, lb, le); \
         return true;
         KVTRIM_CASE(1) KVTRIM_CASE(2) KVTRIM_CASE(3) KVTRIM_CASE(4) KVTRIM_CASE(5) KVTRIM_CASE(6) KVTRIM_CASE(7) KVTRIM_CASE(8)
 #undef KVTRIM_CASE
@@ -705,8 +705,8 @@ kvtrim_status launch_compact_attn(kvtrim_ctx* ctx, const CacheView& src, const u
         ProfScope prof(ctx, K_CMP_ATTN, st);
         const float scale_log2 = scale * 1.4426950408889634f;
         ok = sh.head_dim == 128
-                 ? dispatch_fused<128, false>(sh.group, dim3((unsigned)max_chunks), st, src, keep, dst, dst, q, sh, ws, scale_log2, layer_begin, layer_end, merge, out, lse)
-                 : dispatch_fused<64, false>(sh.group, dim3((unsigned)max_chunks), st, src, keep, dst, dst, q, sh, ws, scale_log2, layer_begin, layer_end, merge, out, lse);
+                 ? dispatch_fused<128, false>(sh.group, dim3((unsigned)max_chunks), st, src, keep, dst, dst, q, sh, ws, scale_log2, layer_begin, layer_end, evict_hint > 0, merge, out, lse)
+                 : dispatch_fused<64, false>(sh.group, dim3((unsigned)max_chunks), st, src, keep, dst, dst, q, sh, ws, scale_log2, layer_begin, layer_end, evict_hint > 0, merge, out, lse);
     }
     if (!ok) return KVTRIM_EINVAL;
     if (merge) {

@@ -22,10 +22,12 @@ constexpr int CMP_THREADS = CMP_CHUNK / CMP_WAVE_ROWS * 64;   // 512: one wavefr
 // block 455, 1805, 1970; three 405, 1643, 1756.)  Rows of 128 bytes: four blocks are 128 KB (20 x 3 lists of 11 K 99 us,
 // with two 110).  Compaction in place, which mostly reads, is better with all it can get (150 us, with two 156).  Fewer than
 // about 2000 blocks are better on the chip at once (2 x 16 x 8 lists of 700, 1800 blocks: 64.4 us, with two 66.1), and so are
-// blocks of whose entries few survive (a quarter of 3400 chunks: 60 us, with two 64): a destination under three quarters of
-// the source.
+// blocks of whose entries few survive, which have few rows under way.  So only calls ask for it that say that most stay: decode
+// steps (by their hint of the evictions) and chunks (see launch_cmp_copy_new); the rows of a gathering block are all
+// there (10 M entries to 2.1 M 491 us, with four 504).  The capacities do not say it: 256 lists of 8192 into a cache of that size, of
+// which 3 % / 25 % / 75 % / 99.9 % survive, kvtrim_compact_attn 110 / 147 / 293 / 379 us, with two blocks 145 / 191 / 309 / 378,
+// kvtrim_compact 44 / 96 / 287 / 390, with two 72 / 118 / 279 / 396.
 constexpr int64_t MOVER_BLOCKS = 2048;
-inline int64_t dense_blocks(int64_t src_cap, int64_t dst_cap, int64_t blocks) { return 4 * dst_cap >= 3 * src_cap ? blocks : 0; }
 constexpr size_t mover_lds(int D, int G, int64_t blocks) {
     return D == 128 && blocks >= MOVER_BLOCKS ? 57344 - (size_t)G * (CMP_THREADS / 64) * (128 + 8) * sizeof(float) - 2048 : 0;
 }
