@@ -155,14 +155,12 @@ __device__ __forceinline__ Quad quad_of(const ChunkDesc& d, int q, int64_t cap) 
     r.whole = r.a + 4 <= cap;
     return r;
 }
-typedef unsigned sel_u4 __attribute__((ext_vector_type(4)));
-template <bool STREAM = false, typename T>
+template <typename T>
 __device__ __forceinline__ void load_quad(const T* __restrict__ base, const Quad& q, T (&v)[4]) {
+    struct alignas(16) T4 { T x, y, z, w; };
     // (a group with nothing of the chunk, or reaching past the arrays, loads the arrays' first four entries instead)
-    const sel_u4* p = reinterpret_cast<const sel_u4*>(base + ((q.whole && q.lo < q.hi) ? q.a : 0));
-    const sel_u4 x = STREAM ? __builtin_nontemporal_load(p) : *p;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = __builtin_bit_cast(T, (unsigned)x[i]);
+    const T4 x = *reinterpret_cast<const T4*>(base + ((q.whole && q.lo < q.hi) ? q.a : 0));
+    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
 }
 template <typename T>
 __device__ __forceinline__ void reload_quad_tail(const T* __restrict__ base, const Quad& q, T (&v)[4]) {
@@ -171,13 +169,7 @@ __device__ __forceinline__ void reload_quad_tail(const T* __restrict__ base, con
         if (i >= q.lo && i < q.hi) v[i] = base[q.a + i];
 }
 
-// STREAM (with SCORE): log beta, positions and tails, which the call's passes do not read again, are loaded past the caches and
-// leave those to the scores, which they do.  That pays where the scores are what the caches can hold: chunks of 4096 for 1024 lists of
-// 8192 (12.6 M entries) 1700 -> 1657 us (both in one process, taking turns), 256 lists of 15 K (3.9 M) 606 -> 597; a first
-// eviction behind a 128 K prefill of 256 lists (33.5 M, 134 MB of scores) is the same, 614 to 621 either way; and 98 x 8 lists of
-// 1 K (0.8 M) 151 -> 154.
-constexpr int64_t SEL_STREAM = 2 << 20;
-template <int PASS, int SHIFT, bool PAGED, bool SCORE = false, bool STREAM = false>
+template <int PASS, int SHIFT, bool PAGED, bool SCORE = false>
 __global__ __launch_bounds__(HIST_THREADS, 8) void k_sel_hist(const float* __restrict__ score, Shape sh,
                                                            Workspace ws, SelTables tb,
                                                            CacheView c, const int32_t* __restrict__ now,
@@ -262,9 +254,9 @@ __global__ __launch_bounds__(HIST_THREADS, 8) void k_sel_hist(const float* __res
                             if (qi >= nt * QPC) d.n = 0;
                             qd[u] = quad_of(d, qi - cidx * QPC, c.cap);
                             if (SCORE) {
-                                load_quad<STREAM>(c.pos, qd[u], pv[u]);
-                                load_quad<STREAM>(c.log_beta, qd[u], lbv[u]);
-                                if (c.log_tail) load_quad<STREAM>(c.log_tail, qd[u], ltv[u]);
+                                load_quad(c.pos, qd[u], pv[u]);
+                                load_quad(c.log_beta, qd[u], lbv[u]);
+                                if (c.log_tail) load_quad(c.log_tail, qd[u], ltv[u]);
                             } else {
                                 load_quad(score, qd[u], sv[u]);
                             }
@@ -650,9 +642,7 @@ static kvtrim_status launch_select_impl(kvtrim_ctx* ctx, const CacheView& c, con
     { ProfScope prof(ctx, K_SEL_PLAN, st);
       hipLaunchKernelGGL(k_sel_plan, dim3(PLAN_TABLE_BLOCKS + PLAN_ZERO_BLOCKS), dim3(1024), 0, st, c, sh, budget, ws, kept, thr, hist_blocks); }
     { ProfScope prof(ctx, K_SEL_HIST0, st);
-      if (now && c.cap >= SEL_STREAM)
-          hipLaunchKernelGGL((k_sel_hist<0, SEL_SHIFT, false, true, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, (const float*)nullptr, sh, ws, tb, c, now, score_w, vec);
-      else if (now)
+      if (now)
           hipLaunchKernelGGL((k_sel_hist<0, SEL_SHIFT, false, true>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, (const float*)nullptr, sh, ws, tb, c, now, score_w, vec);
       else
           hipLaunchKernelGGL((k_sel_hist<0, SEL_SHIFT, false>), dim3(hist_blocks), dim3(HIST_THREADS), 0, st, score, sh, ws, tb, c, nullptr, nullptr, vec); }

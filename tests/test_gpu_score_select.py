@@ -272,8 +272,8 @@ def test_sequences_of_few_segments_stay_on_the_candidate_list(S, H, evictions):
 
 @pytest.mark.parametrize("cap,offset", [(1 << 21, 0), ((1 << 21) + 5, 0), ((1 << 21) - 1, 0), ((1 << 21) + 3, 1)])
 def test_tails_enter_the_scores_of_large_caches(cap, offset):
-    # from 2097152 entries on the first pass loads log beta, positions and tails past the caches, four entries at a time where
-    # the arrays are 16-byte aligned; segments that begin and end at any entry, one of them empty, free entries behind the last
+    # the first pass loads log beta, positions and tails four entries at a time where the arrays are 16-byte aligned; segments that
+    # begin and end at any entry, one of them empty, free entries behind the last
     w = wl(2, 2, 3, 1, 64)
     rng = np.random.default_rng(cap % 1000 + offset)
     lens = rng.integers(100000, 170001, w.nseg)
