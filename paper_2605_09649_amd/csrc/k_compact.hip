@@ -500,6 +500,7 @@ kvtrim_status launch_cmp_copy(kvtrim_ctx* ctx, const CacheView& src, const uint8
     return KVTRIM_OK;
 }
 
+constexpr size_t THREE_BLOCKS_LDS = 40960;                        // and what the kernel itself uses: three blocks to a compute unit's 160 KB
 kvtrim_status launch_cmp_copy_new(kvtrim_ctx* ctx, const CacheView& src, const uint8_t* keep, const CacheViewMut& dst,
                                   const uint16_t* k_new, const uint16_t* v_new, int32_t n_new, const int32_t* old_len,
                                   hipStream_t st) {
@@ -511,12 +512,15 @@ kvtrim_status launch_cmp_copy_new(kvtrim_ctx* ctx, const CacheView& src, const u
         const dim3 grid((unsigned)max_chunks), block(CMP_THREADS);
         // Two blocks a compute unit where most entries stay (mover_lds): a cache at its budget keeps as many as it held, half of all
         // if the new ones are not more than those.  256 lists, chunks of 1024 into 8192 440 us (with four blocks 448), 4096 into
-        // 4096 251 (253); but four sequences, 4096 into 2048 547, with four 498.
-        const bool most_stay = src.cap >= 2 * (int64_t)sh.nseg * n_new;
+        // 4096 251 (253); but four sequences, 4096 into 2048 547, with four 498.  Rows of 128 bytes: three blocks where two
+        // thirds stay: 1024 into 8192 239 us (with four blocks 249, two 240), 4096 into four times 8192 883 (913, 936); 4000 into
+        // 4000 164 (158, 178).
+        const int64_t fresh = (int64_t)sh.nseg * n_new;
+        const bool most_stay = src.cap >= (sh.head_dim == 128 ? 2 : 3) * fresh;
         if (sh.head_dim == 128)
             hipLaunchKernelGGL((k_cmp_copy<128, true>), grid, block, most_stay ? mover_lds(128, 0, max_chunks) : 0, st, src, keep, dst, sh, ws, k_new, v_new, n_new, old_len);
         else
-            hipLaunchKernelGGL((k_cmp_copy<64, true>), grid, block, 0, st, src, keep, dst, sh, ws, k_new, v_new, n_new, old_len);
+            hipLaunchKernelGGL((k_cmp_copy<64, true>), grid, block, most_stay && max_chunks >= MOVER_BLOCKS ? THREE_BLOCKS_LDS : 0, st, src, keep, dst, sh, ws, k_new, v_new, n_new, old_len);
     }
     KVTRIM_HIP(ctx, hipGetLastError());
     return KVTRIM_OK;
