@@ -647,6 +647,7 @@ kvtrim_status launch_compact_inplace(kvtrim_ctx* ctx, const CacheViewMut& c, con
 // 32 such chunks 52.8 -> 62.  These are means; the chunks of a list that is much longer than the others meet in groups (see
 // merge_last): 16 lists, one with nine tenths of 464 chunks, D = 64, 2 heads 55.4 us, merged by one block 56.5, so 55.0.
 constexpr int64_t MERGE_BLOCKS = 1024, MERGE_BYTES = 16384;
+static_assert(MERGE_BLOCKS <= ATT_MERGE_SLOTS, "counters for the groups of its results");
 static bool merges_itself(const Shape& sh, int64_t chunks) {
     return sh.nseg <= ATT_MERGE_SEGS && chunks <= MERGE_BLOCKS &&
            chunks / sh.nseg * sh.group * (sh.head_dim + 2) * (int64_t)sizeof(float) <= MERGE_BYTES;
