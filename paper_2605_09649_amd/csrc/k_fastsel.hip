@@ -9,7 +9,7 @@
 // that is not listed has a key >= hi > every listed key.  The last block to finish a sequence ("last block done",
 // one arrival counter per sequence) ranks the list - a few hundred entries - and publishes the last retained
 // entry of the order as (key, segment, position); the mask kernel compares every entry with that triple (on pages the scanning
-// blocks write the mask of what is not listed and the last block the rest: one kernel).
+// blocks write the mask as if all survived and the last block clears what goes: one kernel).
 //
 // The bound adapts by itself: the next bound is the key of about the 3(k+1)-th lowest entry of the current
 // list.  Scores only decay from step to step (beta <= 1, Eq. global_score) and new tokens enter with the highest
@@ -706,7 +706,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
                 if (in[u]) score_out[sat[u]] = sv[u];
                 const uint32_t k2 = key_of_score(sv[u]);
                 const bool live = in[u] && (!PAGED || pv[u] >= 0);
-                if (PAGED && in[u] && !(live && k2 < hi)) st_dev(&sa.keep_out[sat[u]], (uint8_t)live);
+                if (PAGED && in[u]) st_dev(&sa.keep_out[sat[u]], (uint8_t)live);
                 if (live) mn = min(mn, k2);
                 if (live && k2 < hi) {
                     const int slot = atomicAdd(&s_ncand, 1);
@@ -840,7 +840,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
                 const int j = j0 + u * stride;
                 const uint32_t key = key_of_score(sv[u]);
                 const bool live = j < len && (!PAGED || pv[u] >= 0);
-                if (PAGED && j < len && !(live && key < hi)) st_dev(&sa.keep_out[at[u]], (uint8_t)live);
+                if (PAGED && j < len) st_dev(&sa.keep_out[at[u]], (uint8_t)live);
                 if (live) mn = min(mn, key);
                 if (live && key < hi) {                           // rare: a few hundred entries per sequence and call
                     const int slot = atomicAdd(&s_ncand, 1);
@@ -889,8 +889,9 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
             }
         }
     }
-    // ---- PAGED: the mask (all but the listed entries have theirs from the scanning blocks), the survivors' counts and, in the decode
-    // step in one call, the eviction: a slot that goes becomes empty, the live counts of its page and segment go down, and
+    // ---- PAGED: the scanning blocks have written the mask as if everything survived (a byte for every slot, listed or not: a list
+    // may hold fewer than lie below the bound).  Here the bytes of what goes are cleared, the survivors counted and, in the decode
+    // step in one call, the eviction applied: a slot that goes becomes empty, the live counts of its page and segment go down, and
     // a page left without a live entry goes back to the free list.  No other block reads this sequence's tables any more.
     // What the scanning blocks wrote of the mask has left their caches (st_dev, and acknowledged before they arrived),
     // so it does not come back over what is written here.  (A mask kernel that also evicted, and the tidying in the
@@ -911,16 +912,14 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         __builtin_amdgcn_s_waitcnt(VMCNT_0);                      // (the live counts; after a ranking they are long here)
         if (tid == 0) s_nrel = 0;
         __syncthreads();
-        if (o.mode == FSEL_ALL || (o.mode == FSEL_THRESHOLD && from_list)) {
+        if (o.mode == FSEL_ALL) return;
+        if (o.mode == FSEL_THRESHOLD && from_list) {
 #pragma unroll
             for (int u = 0; u < FAST_ITEMS; ++u) {
-                if (!listed[u]) continue;
-                const bool gone = o.mode == FSEL_THRESHOLD && evicted_before(key[u], sg[u], ps[u], o.key_thr, o.seg_thr, o.pos_thr);
-                sa.keep_out[ix[u]] = !gone;
-                if (gone) {
-                    atomicSub(&kept_out[sg[u]], 1);
-                    if (sa.pg.evict) evict(sg[u], ix[u]);
-                }
+                if (!listed[u] || !evicted_before(key[u], sg[u], ps[u], o.key_thr, o.seg_thr, o.pos_thr)) continue;
+                sa.keep_out[ix[u]] = 0;
+                atomicSub(&kept_out[sg[u]], 1);
+                if (sa.pg.evict) evict(sg[u], ix[u]);
             }
         } else {                                                  // not listed: one more pass over the sequence
             for (int g = g0; g < g0 + sh.segs_per_seq; ++g) {

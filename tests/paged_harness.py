@@ -195,6 +195,7 @@ def run_paged_both(w, budgets, device="cuda:0", cache_dict=None, now0=None, n_pa
         now_dev, pos_dev = torch.from_numpy(now).to(device), torch.from_numpy(pos_new).to(device)
         budget_dev = torch.from_numpy(budget_np).to(device)
         res = {"step": step}
+        keep.fill_(7)                                             # (a byte that is not written is seen)
         if step == 0:
             kv.kvtrim_append(ctx, src, d["k_new"], d["v_new"], d["log_beta_new"], pos_dev, 1,
                              log_tail_new=d.get("log_tail_new"))

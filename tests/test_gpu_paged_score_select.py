@@ -247,3 +247,83 @@ def test_one_call_frees_any_number_of_pages_at_once(S, L, H, lens):
     res = run_paged_both(w, budgets, device=DEV, cache_dict=c, now0=now.numpy(), hint=per, one_call=True)
     check(res)
     assert res[3]["pages_in_use"] == 0 and res[4]["pages_in_use"] == w.nseg
+
+
+# More entries below the carried bound than a list holds, in every way in which the scan is dealt: the bound comes from a selection
+# down to 200 entries, then the budget is above all there is (nothing goes, whatever was listed) and one below it (the single-block
+# select).  Every slot of a segment's pages gets its mask byte, whatever the mask held before.
+DEALS = [(1, 2, 2, [1900, 0, 2200, 1700]),                        # a block for the sequence
+         (4, 1, 2, [9000, 9000, 20, 30, 0, 40, 50, 60]),          # up to three blocks for a sequence
+         (1, 2, 2, [20000, 9000, 40000, 129]),                    # blocks for a segment
+         (2, 40, 8, [130, 70])]                                   # several segments to a block
+
+
+def _pages_of(S, L, H, lens, G=1, D=64):
+    import paper_2605_09649_amd as kv
+    w = wl(S, L, H, G, D)
+    seg_len = [lens[g % len(lens)] for g in range(w.nseg)]
+    c, now = ki.ragged_cache(w, seg_len, reserve=1, salt=S + L)
+    src = kv.Cache.from_dict(c, DEV)
+    n_pages = sum((n + P - 1) // P for n in seg_len) + w.nseg + 2
+    pc = kv.PagedCache(w.nseg, D, n_pages, max(seg_len) // P + 4, DEV)
+    ctx = kv.Context(S, L, H, G * H, D, max(src.cap, n_pages * P))
+    kv.kvtrim_paged_build(ctx, src, torch.ones(src.cap, dtype=torch.uint8, device=DEV), src.seg_len, pc)
+    per = L * H
+    total = torch.tensor([sum(seg_len[s * per:(s + 1) * per]) for s in range(S)], dtype=torch.int64, device=DEV)
+    return kv, w, c, ctx, pc, now.to(DEV), total
+
+
+def _slots_of(pc):                                               # every slot of the segments' pages
+    pages = torch.cat([pc.block_table[g, :int(n)] for g, n in enumerate(pc.seg_pages.tolist())]).long()
+    return (pages[:, None] * P + torch.arange(P, device=DEV)).reshape(-1)
+
+
+@pytest.mark.parametrize("S,L,H,lens", DEALS)
+def test_every_slot_has_its_mask_byte_when_a_list_overflows(S, L, H, lens):
+    kv, w, c, ctx, pc, now, total = _pages_of(S, L, H, lens)
+    slots, at = pc.n_pages * P, _slots_of(pc)
+    big = int((total > 5000).sum())
+
+    def select(cx, budget, hint, fill):
+        score = torch.full((slots,), 99.0, device=DEV)
+        keep = torch.full((slots,), fill, dtype=torch.uint8, device=DEV)
+        kept, thr = torch.full((w.nseg,), 9, dtype=torch.int32, device=DEV), torch.full((S,), 9, dtype=torch.int32, device=DEV)
+        kv.kvtrim_paged_score_select(cx, pc, now, budget, score, keep, kept, thr, evict_hint=hint)
+        assert kv.kvtrim_poll_error(cx) == 0
+        return score[at], keep[at], kept, thr, keep
+
+    other = kv.Context(S, L, H, H, 64, slots)
+    for budget in (total + 5, total - 1, total * 0 - 3, total // 2):
+        want = select(other, budget, 0, 3)
+        for fill in (0, 7):
+            select(ctx, torch.full_like(total, 200), 0, 0)        # (leaves the bound)
+            before = kv.kvtrim_select_path_counts(ctx)[1]
+            got = select(ctx, budget, 4, fill)
+            for a, b in zip(got[:4], want[:4]):
+                assert torch.equal(a, b)
+            if int((budget - total).max()) == -1:                 # (the list is no use to the select either)
+                assert kv.kvtrim_select_path_counts(ctx)[1] - before >= big
+    select(ctx, torch.full_like(total, 200), 0, 0)
+    live = pc.seg_live.clone()
+    kv.kvtrim_paged_evict(ctx, pc, select(ctx, total + 5, 4, 0)[4])
+    assert kv.kvtrim_poll_error(ctx) == 0 and torch.equal(pc.seg_live, live)
+
+
+@pytest.mark.parametrize("fill", [0, 7])
+@pytest.mark.parametrize("S,L,H,lens", DEALS)
+def test_one_call_keeps_all_when_a_list_overflows(S, L, H, lens, fill):
+    kv, w, c, ctx, pc, now, total = _pages_of(S, L, H, lens)
+    score, keep = torch.zeros(pc.n_pages * P, device=DEV), torch.zeros(pc.n_pages * P, dtype=torch.uint8, device=DEV)
+    kept = torch.zeros(w.nseg, dtype=torch.int32, device=DEV)
+    kv.kvtrim_paged_score_select(ctx, pc, now, torch.full_like(total, 200), score, keep, kept, None, evict_hint=0)
+    keep.fill_(fill)
+    live = pc.seg_live.clone()
+    d = {k: v.to(DEV) for k, v in ki.decode_inputs(w, 0).items()}
+    out = torch.zeros(S, L, H, 64, device=DEV)
+    pos = (now + 1).repeat_interleave(L * H)
+    kv.kvtrim_paged_decode_step(ctx, pc, d["k_new"], d["v_new"], d["log_beta_new"], pos, now + 1, total * 2 + 10000, score, keep, kept, d["q"],
+                                0, L, 0.125, out, None, evict_hint=4)
+    assert kv.kvtrim_poll_error(ctx) == 0
+    at = _slots_of(pc)
+    assert torch.equal(keep[at], (pc.pos.reshape(-1)[at] >= 0).to(torch.uint8))
+    assert torch.equal(pc.seg_live, live + 1) and torch.equal(kept, live + 1)
