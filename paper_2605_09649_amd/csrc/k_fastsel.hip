@@ -637,7 +637,10 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
             bool b2 = false, n2 = false;
             if (tid < sh.segs_per_seq) {
                 sv = seg_view<KIND>(c, g0 + tid, sh.nseg, sa, &b2, &n2);
-                if (b2) atomicOr(ws.err, ERR_LAYOUT);
+                // (a sequence's first block always takes part.  One without a part is not waited for: it may read the tables while the
+                // resolving block shortens them, and see a page count and a live count that do not belong together.  It
+                // then counts fewer entries than there were, and still finds no part for itself)
+                if (b2 && (!PARTS || blockIdx.y == 0)) atomicOr(ws.err, ERR_LAYOUT);
                 if (!PAGED && !PARTS) kept_out[g0 + tid] = 0;     // the mask kernel adds its counts
                 if (PAGED) live_mine = sv.live;
                 cnt = sv.live;
@@ -892,7 +895,8 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     // ---- PAGED: the scanning blocks have written the mask as if everything survived (a byte for every slot, listed or not: a list
     // may hold fewer than lie below the bound).  Here the bytes of what goes are cleared, the survivors counted and, in the decode
     // step in one call, the eviction applied: a slot that goes becomes empty, the live counts of its page and segment go down, and
-    // a page left without a live entry goes back to the free list.  No other block reads this sequence's tables any more.
+    // a page left without a live entry goes back to the free list.  Of the other blocks only those without a part (PARTS) may still
+    // read this sequence's tables, and they report nothing.
     // What the scanning blocks wrote of the mask has left their caches (st_dev, and acknowledged before they arrived),
     // so it does not come back over what is written here.  (A mask kernel that also evicted, and the tidying in the
     // attention's merge kernel, took 4 to 9 us: on pages 256 lists of 8192 entries 204.1 -> 201.4 us a step, 20 of 756 31.9 -> 27.9.)

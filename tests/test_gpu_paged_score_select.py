@@ -327,3 +327,31 @@ def test_one_call_keeps_all_when_a_list_overflows(S, L, H, lens, fill):
     at = _slots_of(pc)
     assert torch.equal(keep[at], (pc.pos.reshape(-1)[at] >= 0).to(torch.uint8))
     assert torch.equal(pc.seg_live, live + 1) and torch.equal(kept, live + 1)
+
+
+def test_parts_of_sequences_report_bad_tables_and_no_others():
+    # Three sequences of up to three blocks each, of which short ones need one.  The blocks without a part may see a table that
+    # the resolving block is shortening and must not report it: steps that free pages leave no error.  A table that is
+    # unusable is reported, whichever sequence it is in.
+    S, L, H = 4, 1, 2
+    kv, w, c, ctx, pc, now, total = _pages_of(S, L, H, [9000, 4000, 700, 300, 0, 600, 1290, 128])
+    slots = pc.n_pages * P
+    assert 2 * 8192 < slots <= 4 * 8192                           # (in parts)
+    score, keep = torch.zeros(slots, device=DEV), torch.zeros(slots, dtype=torch.uint8, device=DEV)
+    kept = torch.zeros(w.nseg, dtype=torch.int32, device=DEV)
+    out = torch.zeros(S, L, H, 64, device=DEV)
+    for step in range(12):
+        d = {k: v.to(DEV) for k, v in ki.decode_inputs(w, step).items()}
+        total -= torch.tensor([150, 140, 60, 130], device=DEV)
+        kv.kvtrim_paged_decode_step(ctx, pc, d["k_new"], d["v_new"], d["log_beta_new"], (now + 1 + step).repeat_interleave(L * H), now + 1 + step,
+                                    total.clamp(min=5), score, keep, kept, d["q"], 0, L, 0.125, out, None, evict_hint=150)
+        assert kv.kvtrim_poll_error(ctx) == 0, step
+    assert torch.equal(pc.seg_live.view(S, -1).sum(1), total.clamp(min=5))
+    for g in (0, 3, 7):
+        was = int(pc.seg_pages[g])
+        pc.seg_pages[g] = pc.max_pages_per_seg + 1
+        kv.kvtrim_paged_score_select(ctx, pc, now + 20, total, score, keep, kept, None, evict_hint=4)
+        assert kv.kvtrim_poll_error(ctx) == -6, g
+        pc.seg_pages[g] = was
+        kv.kvtrim_paged_score_select(ctx, pc, now + 20, total, score, keep, kept, None, evict_hint=4)
+        assert kv.kvtrim_poll_error(ctx) == 0
