@@ -151,8 +151,8 @@ kvtrim_status kvtrim_select_global(kvtrim_ctx *ctx, const kvtrim_cache *c, const
  *     k + 1 entries of the order are among them and are ranked directly; then the mask pass.  Two kernels.  The
  *     bound follows the threshold from call to call by itself.  A sequence whose list comes up short (no previous
  *     selection on this context, a jump in the budget or the workload) or overflows is selected by a slow single-
- *     block fallback inside the same kernel - correct, but about as slow as a millisecond per 2 M entries, so pass
- *     0 when the number of evictions is not small.
+ *     block fallback inside the same kernel - correct, but slow, some 2.5 ms per million entries, so pass 0 when the
+ *     number of evictions is not small.
  * Device-side error: KVTRIM_ELAYOUT for a segment table that does not fit cap_entries or overlaps. */
 kvtrim_status kvtrim_score_select(kvtrim_ctx *ctx, const kvtrim_cache *c, const int32_t *now, const int64_t *budget,
                                   float *score_out, uint8_t *keep_out, int32_t *kept_out, uint32_t *thr_key_out,

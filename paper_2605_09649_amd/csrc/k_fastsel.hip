@@ -27,7 +27,8 @@ constexpr int FAST_ITEMS = FL_CAP_MAX / FAST_THREADS;             // list entrie
 constexpr int FAST_SUB = 16;                                      // sub-lists / group words per sequence
 constexpr int FAST_STAGE = 1024;                                  // candidates a block of one segment stages in LDS
 constexpr int FAST_PIECE_SHIFT = 6;                               // ... 64 of which go on one sub-list before the next is taken
-constexpr int FAST_BATCH = 8;                                     // entries a thread loads before it uses any of them
+constexpr int FAST_BATCH = 8;                                     // entries a thread loads before it uses any of them ...
+constexpr int SLOW_BATCH = 4;                                     // ... in the single-block select (eight took the scoring kernel's registers from 72 to 86)
 constexpr int FAST_BIN_DIRECT = 256;                              // a bin of at most this many entries is ranked directly
 static_assert(FAST_ITEMS * FAST_THREADS == FL_CAP_MAX, "list capacity must be a multiple of the block size");
 
@@ -239,48 +240,99 @@ struct KeySource {
         *s_out = lt ? __fmaf_rn(dt, b, t) : __fmul_rn(dt, b);
         return true;
     }
+    // the same for entries j0, j0 + stride, ... of a batch (those behind the segment's end are not live): all loads of a kind are
+    // under way together
+    __device__ __forceinline__ void batch_at(int g, const SegView& v, int j0, int stride, int (&slot)[SLOW_BATCH], bool (&live)[SLOW_BATCH],
+                                             int (&p)[SLOW_BATCH], float (&s)[SLOW_BATCH]) const {
+        float b[SLOW_BATCH], t[SLOW_BATCH];
+        bool bp = false;
+#pragma unroll
+        for (int u = 0; u < SLOW_BATCH; ++u) {                    // (places are below 2^31 - and those of new tokens, at most STEP_MAX_NEW of 2^20 segments)
+            const int j = j0 + u * stride;
+            slot[u] = STEP && j >= v.len_old ? g * n_new + (j - v.len_old) : (j < v.len ? (int)place(v, j, &bp) : 0);
+        }
+#pragma unroll
+        for (int u = 0; u < SLOW_BATCH; ++u) {
+            const int j = j0 + u * stride;
+            const bool in = j < v.len, isnew = STEP && j >= v.len_old;
+            p[u] = in ? (isnew ? pos_new : pos)[slot[u]] : 0;
+            b[u] = in ? (isnew ? lb_new : lb)[slot[u]] : 0.f;
+            t[u] = in && lt ? (isnew ? lt_new : lt)[slot[u]] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < SLOW_BATCH; ++u) {
+            const float dt = (float)(t1 - p[u]);
+            s[u] = lt ? __fmaf_rn(dt, b[u], t[u]) : __fmul_rn(dt, b[u]);
+            live[u] = j0 + u * stride < v.len && (!PAGED || p[u] >= 0);
+        }
+    }
 };
 
-// One digit of a most-significant-digit radix select over all entries of the sequence, by this block alone.
-template <int PASS, bool SCORE, int KIND>
+// What a pass does with the entries besides counting them: nothing, or what the function does with a batch of a segment's entries
+// (a wavefront's 64 of a place in the batch lie next to one another, on pages in one page).
+struct NoVisit {
+    static constexpr bool ANY = false;
+    __device__ __forceinline__ void operator()(int, const int*, const bool*, const int*, const float*) const {}
+};
+template <typename F>
+struct Visit {
+    static constexpr bool ANY = true;
+    const F& f;
+    __device__ __forceinline__ void operator()(int g, const int* slot, const bool* live, const int* pos, const float* score) const { f(g, slot, live, pos, score); }
+};
+
+// One digit of a most-significant-digit radix select over all entries of the sequence, by this block alone: sixteen segments
+// at a time, a wavefront to each if they are all short, else all wavefronts to one after the other.  (The chain of loads
+// to a list's first entry is a microsecond, and a batch's loads must not wait for one another: kvtrim_paged_score_select with
+// a list that is no use, 256 lists of 1000 entries 1690 us -> 548, 4 of 500 K 10.2 ms -> 5.1.)
+constexpr int SLOW_SHORT = 8192;
+template <int PASS, bool SCORE, int KIND, typename V = NoVisit>
 __device__ __forceinline__ void slow_pass(const KeySource<SCORE, KIND>& ks, const CacheView& c, const Shape& sh,
-                                          const StepArgs& sa, int seq, uint32_t prefix, ResolveShared* sm) {
-    constexpr int NB = PASS == 2 ? 1024 : 2048;
-    const int tid = threadIdx.x;
+                                          const StepArgs& sa, int seq, uint32_t prefix, ResolveShared* sm, const V& visit = V()) {
+    constexpr int NB = PASS == 2 ? 1024 : 2048, NW = FAST_THREADS / 64;
+    const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     __syncthreads();
     for (int i = tid; i < NB; i += FAST_THREADS) sm->h[i] = 0;
     __syncthreads();
-    for (int g = seq * sh.segs_per_seq; g < (seq + 1) * sh.segs_per_seq; ++g) {
+    auto walk = [&](int g, int first, int stride) {
         bool bad = false, nocap = false;
         const SegView v = seg_view<KIND>(c, g, sh.nseg, sa, &bad, &nocap);
         const int len = v.len;
-        for (int j0 = tid; j0 < len; j0 += FAST_THREADS * FAST_BATCH) {
-            float sv[FAST_BATCH];
-            bool lv[FAST_BATCH];
+        for (int j0 = first; j0 < len; j0 += stride * SLOW_BATCH) {
+            float sv[SLOW_BATCH];
+            bool lv[SLOW_BATCH];
+            int pv[SLOW_BATCH], slot[SLOW_BATCH];
+            ks.batch_at(g, v, j0, stride, slot, lv, pv, sv);
 #pragma unroll
-            for (int u = 0; u < FAST_BATCH; ++u) {
-                const int j = j0 + u * FAST_THREADS;
-                int p;
-                sv[u] = 0.f;
-                lv[u] = j < len && ks.entry_at(g, v, j, &p, &sv[u]);
-            }
-#pragma unroll
-            for (int u = 0; u < FAST_BATCH; ++u) {
+            for (int u = 0; u < SLOW_BATCH; ++u) {
                 int bin;
                 if (lv[u] && digit_of<PASS>(key_of_score(sv[u]), prefix, &bin)) atomicAdd(&sm->h[bin], 1u);
             }
+            if (V::ANY) visit(g, slot, lv, pv, sv);
+        }
+    };
+    const int g0 = seq * sh.segs_per_seq, g1 = g0 + sh.segs_per_seq;
+    for (int g = g0; g < g1; g += NW) {
+        bool bad = false, nocap = false;
+        int len = 0;
+        if (lane < NW && g + lane < g1) len = KIND == SCAN_PAGED ? sa.pg.seg_pages[g + lane] * KVTRIM_PAGE_SIZE : seg_view<KIND>(c, g + lane, sh.nseg, sa, &bad, &nocap).len;
+        if (!__any(len > SLOW_SHORT)) {
+            if (g + wave < g1) walk(g + wave, lane, 64);
+        } else {
+            for (int i = 0; i < NW && g + i < g1; ++i) walk(g + i, tid, FAST_THREADS);
         }
     }
     __syncthreads();
 }
 
 // Key of the entry of rank `rank` (1-based, descending key order) of the sequence; *rank_in = its rank among the
-// entries with that key, *ties = how many entries have that key.
-template <bool SCORE, int KIND>
+// entries with that key, *ties = how many entries have that key.  The first pass shows every entry to `visit`, which may
+// empty slots of entries that come behind the one looked for.
+template <bool SCORE, int KIND, typename V = NoVisit>
 __device__ __forceinline__ uint32_t slow_radix(const KeySource<SCORE, KIND>& ks, const CacheView& c, const Shape& sh,
                                                const StepArgs& sa, int seq, int64_t rank, ResolveShared* sm,
-                                               int64_t* rank_in, uint32_t* ties) {
-    slow_pass<0>(ks, c, sh, sa, seq, 0, sm);
+                                               int64_t* rank_in, uint32_t* ties, const V& visit = V()) {
+    slow_pass<0>(ks, c, sh, sa, seq, 0, sm, visit);
     walk_from_top<2048>(sm, rank);
     uint32_t prefix = (uint32_t)sm->digit;
     rank = sm->rank_in;
@@ -570,6 +622,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     ks.pos_new = sa.pos_new;
     ks.n_new = sa.n_new;
     ks.t1 = SCORE ? now[seq] + 1 : 0;
+    const bool none_stays = PAGED && budget[seq] <= 0;            // (the mask and the slots then need no selection)
 
     const int g0 = seq * sh.segs_per_seq;
     // STEP: one scan over the segments of the batch (1024 at a time): entries and chunks before each, so the entries of every
@@ -709,7 +762,8 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
                 if (in[u]) score_out[sat[u]] = sv[u];
                 const uint32_t k2 = key_of_score(sv[u]);
                 const bool live = in[u] && (!PAGED || pv[u] >= 0);
-                if (PAGED && in[u]) st_dev(&sa.keep_out[sat[u]], (uint8_t)live);
+                if (PAGED && in[u]) st_dev(&sa.keep_out[sat[u]], (uint8_t)(live && !none_stays));
+                if (PAGED && sa.pg.evict && none_stays && live) sa.pg.pos[sat[u]] = -1;
                 if (live) mn = min(mn, k2);
                 if (live && k2 < hi) {
                     const int slot = atomicAdd(&s_ncand, 1);
@@ -843,7 +897,8 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
                 const int j = j0 + u * stride;
                 const uint32_t key = key_of_score(sv[u]);
                 const bool live = j < len && (!PAGED || pv[u] >= 0);
-                if (PAGED && j < len) st_dev(&sa.keep_out[at[u]], (uint8_t)live);
+                if (PAGED && j < len) st_dev(&sa.keep_out[at[u]], (uint8_t)(live && !none_stays));
+                if (PAGED && sa.pg.evict && none_stays && live) sa.pg.pos[at[u]] = -1;
                 if (live) mn = min(mn, key);
                 if (live && key < hi) {                           // rare: a few hundred entries per sequence and call
                     const int slot = atomicAdd(&s_ncand, 1);
@@ -893,65 +948,44 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         }
     }
     // ---- PAGED: the scanning blocks have written the mask as if everything survived (a byte for every slot, listed or not: a list
-    // may hold fewer than lie below the bound).  Here the bytes of what goes are cleared, the survivors counted and, in the decode
-    // step in one call, the eviction applied: a slot that goes becomes empty, the live counts of its page and segment go down, and
-    // a page left without a live entry goes back to the free list.  Of the other blocks only those without a part (PARTS) may still
-    // read this sequence's tables, and they report nothing.
+    // may hold fewer than lie below the bound), or nothing where the budget is zero.  Here the bytes of what goes are cleared, the
+    // survivors counted and, in the decode step in one call, the eviction applied: a slot that goes becomes empty, the live counts
+    // of its page and segment go down, and a page left without a live entry goes back to the free list.  Of the other blocks
+    // only those without a part (PARTS) may still read this sequence's tables, and they report nothing.
     // What the scanning blocks wrote of the mask has left their caches (st_dev, and acknowledged before they arrived),
     // so it does not come back over what is written here.  (A mask kernel that also evicted, and the tidying in the
     // attention's merge kernel, took 4 to 9 us: on pages 256 lists of 8192 entries 204.1 -> 201.4 us a step, 20 of 756 31.9 -> 27.9.)
-    auto apply_paged = [&](const FastSel& o, bool from_list) {
-        __shared__ int s_nrel, s_rel[PAGED ? FAST_BIN_DIRECT : 1];
-        auto evict = [&](int g, int64_t slot) {
-            sa.pg.pos[slot] = -1;
-            const int page = (int)(slot / KVTRIM_PAGE_SIZE);
-            const int left = atomicSub(&sa.pg.page_live[page], 1) - 1;
-            atomicSub(&sa.pg.seg_live[g], 1);
-            if (left <= 0) {
-                sa.pg.page_owner[page] = -2;
-                const int i = atomicAdd(&s_nrel, 1);
-                if (i < FAST_BIN_DIRECT) s_rel[i] = g;
-            }
-        };
-        __builtin_amdgcn_s_waitcnt(VMCNT_0);                      // (the live counts; after a ranking they are long here)
+    __shared__ int s_nrel, s_rel[PAGED ? FAST_BIN_DIRECT : 1];    // segments that lost pages (one may be there more than once)
+    // n live entries of segment g go (mask bytes, positions and the page's live count are the caller's)
+    auto take_out = [&](int g, int n) {
+        atomicSub(&kept_out[g], n);
+        if (sa.pg.evict) atomicSub(&sa.pg.seg_live[g], n);
+    };
+    auto release_page = [&](int g, int page) {
+        sa.pg.page_owner[page] = -2;
+        const int i = atomicAdd(&s_nrel, 1);
+        if (i < FAST_BIN_DIRECT) s_rel[i] = g;
+    };
+    // before the first entry is taken out: the live counts stored as survivors and the scanning blocks' bytes are in place
+    auto take_out_begin = [&]() {
+        __builtin_amdgcn_s_waitcnt(VMCNT_0);
         if (tid == 0) s_nrel = 0;
         __syncthreads();
-        if (o.mode == FSEL_ALL) return;
-        if (o.mode == FSEL_THRESHOLD && from_list) {
-#pragma unroll
-            for (int u = 0; u < FAST_ITEMS; ++u) {
-                if (!listed[u] || !evicted_before(key[u], sg[u], ps[u], o.key_thr, o.seg_thr, o.pos_thr)) continue;
-                sa.keep_out[ix[u]] = 0;
-                atomicSub(&kept_out[sg[u]], 1);
-                if (sa.pg.evict) evict(sg[u], ix[u]);
-            }
-        } else {                                                  // not listed: one more pass over the sequence
-            for (int g = g0; g < g0 + sh.segs_per_seq; ++g) {
-                bool b2 = false, n2 = false;
-                const SegView v = seg_view<KIND>(c, g, sh.nseg, sa, &b2, &n2);
-                int n = 0;
-                for (int j = tid; j < v.len; j += FAST_THREADS) {
-                    bool bp = false, kf = false;
-                    const int64_t at = ks.place(v, j, &bp);
-                    int p;
-                    float sc;
-                    if (ks.entry_at(g, v, j, &p, &sc)) {
-                        kf = o.mode == FSEL_THRESHOLD && !evicted_before(key_of_score(sc), g, p, o.key_thr, o.seg_thr, o.pos_thr);
-                        if (!kf && sa.pg.evict) evict(g, at);
-                    }
-                    sa.keep_out[at] = kf;
-                    n += kf;
-                }
-                n = block_sum<int32_t>(n, sm.lds32);
-                if (tid == 0) kept_out[g] = n;
-            }
-        }
-        if (!sa.pg.evict) return;
+    };
+    // a wavefront to a segment
+    auto tidy_paged = [&]() {
         __syncthreads();
-        const int nrel = s_nrel;
-        for (int i = 0; i < (nrel <= FAST_BIN_DIRECT ? nrel : sh.segs_per_seq); ++i) {   // (a segment that comes up again has nothing more to give)
-            tidy_segment<FAST_THREADS>(sa.pg, nrel <= FAST_BIN_DIRECT ? s_rel[i] : g0 + i, ws.err);
-            __syncthreads();
+        const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int nrel = none_stays ? FAST_BIN_DIRECT + 1 : s_nrel;
+        if (nrel > FAST_BIN_DIRECT) {
+            for (int i = wave; i < sh.segs_per_seq; i += FAST_THREADS / 64) tidy_segment_by_wave(sa.pg, g0 + i, none_stays, ws.err);
+            return;
+        }
+        for (int i = wave; i < nrel; i += FAST_THREADS / 64) {
+            const int g = s_rel[i];
+            bool twice = false;                                   // (whoever comes first in the list does it)
+            for (int b = 0; b < i; b += 64) twice |= __any(b + lane < i && s_rel[min(b + lane, FAST_BIN_DIRECT - 1)] == g);
+            if (!twice) tidy_segment_by_wave(sa.pg, g, false, ws.err);
         }
     };
     uint32_t word = 0;
@@ -1218,8 +1252,32 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
             const int64_t above = seed_distance(k, sh.segs_per_seq, ws.fl_cap);
             const int64_t rank_b = want - above >= 1 ? want - above : 1;
             int64_t unused_r;
-            uint32_t unused_t;
-            const uint32_t key_b = slow_radix(ks, c, sh, sa, seq, rank_b, &sm, &unused_r, &unused_t);
+            uint32_t unused_t, key_b;
+            if constexpr (PAGED) {
+                // what goes is taken out on the way
+                take_out_begin();
+                auto visit = [&](int g, const int* slot, const bool* live, const int* pos, const float* score) {
+                    int page_left[SLOW_BATCH], n[SLOW_BATCH], all = 0;
+#pragma unroll
+                    for (int u = 0; u < SLOW_BATCH; ++u) {        // (counters that are waited for are asked for together)
+                        const bool gone = live[u] && evicted_before(key_of_score(score[u]), g, pos[u], out.key_thr, out.seg_thr, out.pos_thr);
+                        const uint64_t m = __ballot(gone);
+                        n[u] = gone && (m & ((1ull << lane) - 1ull)) == 0 ? __popcll(m) : 0;   // (in the first of them)
+                        all += __popcll(m);
+                        if (gone) sa.keep_out[slot[u]] = 0;
+                        if (gone && sa.pg.evict) sa.pg.pos[slot[u]] = -1;
+                        page_left[u] = 1;
+                        if (n[u] && sa.pg.evict) page_left[u] = atomicSub(&sa.pg.page_live[slot[u] / KVTRIM_PAGE_SIZE], n[u]) - n[u];
+                    }
+                    if (all && lane == 0) take_out(g, all);       // (lane 0 has an entry of every batch)
+#pragma unroll
+                    for (int u = 0; u < SLOW_BATCH; ++u)
+                        if (page_left[u] <= 0) release_page(g, slot[u] / KVTRIM_PAGE_SIZE);
+                };
+                key_b = slow_radix(ks, c, sh, sa, seq, rank_b, &sm, &unused_r, &unused_t, Visit<decltype(visit)>{visit});
+            } else {
+                key_b = slow_radix(ks, c, sh, sa, seq, rank_b, &sm, &unused_r, &unused_t);
+            }
             next_hi = key_b == 0xFFFFFFFFu ? key_b : key_b + 1u;
         }
     }
@@ -1238,7 +1296,29 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
         if (out.mode == FSEL_THRESHOLD) ws.fast_hi[seq] = next_hi;
     }
     if constexpr (PAGED) {
-        apply_paged(out, !used_fallback);
+        if (out.mode == FSEL_ALL) return;
+        if (out.mode == FSEL_NONE) {
+            __builtin_amdgcn_s_waitcnt(VMCNT_0);                  // (the live counts of other threads)
+            __syncthreads();
+            for (int i = tid; i < sh.segs_per_seq; i += FAST_THREADS) {
+                kept_out[g0 + i] = 0;
+                if (sa.pg.evict) sa.pg.seg_live[g0 + i] = 0;
+            }
+            if (!none_stays) return;                              // (there was nothing)
+        } else if (!used_fallback) {
+            take_out_begin();
+#pragma unroll
+            for (int u = 0; u < FAST_ITEMS; ++u) {
+                if (!listed[u] || !evicted_before(key[u], sg[u], ps[u], out.key_thr, out.seg_thr, out.pos_thr)) continue;
+                sa.keep_out[ix[u]] = 0;
+                take_out(sg[u], 1);
+                if (!sa.pg.evict) continue;
+                sa.pg.pos[ix[u]] = -1;
+                const int page = ix[u] / KVTRIM_PAGE_SIZE;
+                if (atomicSub(&sa.pg.page_live[page], 1) <= 1) release_page(sg[u], page);
+            }
+        }
+        if (sa.pg.evict) tidy_paged();
         return;
     }
     if (!STEP) return;

@@ -137,4 +137,46 @@ __device__ __forceinline__ void tidy_segment(const PagedView& pc, int g, int32_t
     if (tid == 0) pc.seg_pages[g] = out;
 }
 
+// The same by a wavefront, a few tiles of 64 pages at a time.  all: every page goes, whatever it is marked as.
+__device__ __forceinline__ void tidy_segment_by_wave(const PagedView& pc, int g, bool all, int32_t* err) {
+    constexpr int TILES = 4;
+    const int lane = lane_id(), npg = pc.seg_pages[g];
+    if (npg < 0 || npg > pc.max_pps) {
+        if (lane == 0) atomicOr(err, ERR_LAYOUT);
+        return;
+    }
+    int32_t* bt = pc.block_table + (int64_t)g * pc.max_pps;
+    const uint64_t below = (1ull << lane) - 1ull;
+    int out = 0;
+    for (int base = 0; base < npg; base += 64 * TILES) {                 // read a tile, then write it: out <= base
+        int page[TILES], owner[TILES];
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            const int i = base + 64 * t + lane;
+            page[t] = i < npg ? bt[i] : -1;
+            if (page[t] >= pc.n_pages) page[t] = -1;
+        }
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) owner[t] = page[t] < 0 ? -1 : all ? -2 : pc.page_owner[page[t]];
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) {
+            const bool goes = owner[t] == -2, stays = owner[t] == g;
+            const uint64_t mg = __ballot(goes), ms = __ballot(stays);
+            if (mg) {
+                int at = 0;
+                if (lane == 0) at = atomicAdd(pc.n_free, __popcll(mg));
+                at = __builtin_amdgcn_readfirstlane(at) + __popcll(mg & below);
+                if (goes) {
+                    pc.page_owner[page[t]] = -1;
+                    pc.page_live[page[t]] = 0;
+                    if (at >= 0 && at < pc.n_pages) pc.free_list[at] = page[t];
+                }
+            }
+            if (stays) bt[out + __popcll(ms & below)] = page[t];
+            out += __popcll(ms);
+        }
+    }
+    if (lane == 0) pc.seg_pages[g] = out;
+}
+
 }  // namespace kvtrim

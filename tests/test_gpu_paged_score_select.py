@@ -355,3 +355,20 @@ def test_parts_of_sequences_report_bad_tables_and_no_others():
         pc.seg_pages[g] = was
         kv.kvtrim_paged_score_select(ctx, pc, now + 20, total, score, keep, kept, None, evict_hint=4)
         assert kv.kvtrim_poll_error(ctx) == 0
+
+
+# The one-call step where its list is no use: budgets that fall by half and more (the single-block select takes the entries out on its
+# way), to zero (everything goes without a selection), and up again; pages by the hundred go back, in every way the scan is dealt.
+@pytest.mark.parametrize("S,L,H,lens", DEALS)
+def test_one_call_evicts_what_no_list_holds(S, L, H, lens):
+    w = wl(S, L, H, 1, 64)
+    seg_len = [lens[g % len(lens)] for g in range(w.nseg)]
+    c, now = ki.ragged_cache(w, seg_len, reserve=1, salt=3)
+    per = L * H
+    full = [sum(seg_len[s * per:(s + 1) * per]) for s in range(S)]
+    budgets = [full, [n // 2 for n in full], [n // 2 - 3 for n in full], [n // 16 + 1 for n in full], [1 + 10 ** 6 * (s % 2) for s in range(S)],
+               [10 ** 6] * S, [0] * S, [10 ** 6] * S, [-5] * S]
+    res = run_paged_both(w, budgets, device=DEV, cache_dict=c, now0=now.numpy(), n_pages=sum((n + P - 1) // P for n in seg_len) + w.nseg,
+                         hint=min(per, 60), one_call=True)
+    check(res)
+    assert res[-1]["path_counts"][1] >= 2 and res[6]["pages_in_use"] == 0 and res[7]["pages_in_use"] == w.nseg
