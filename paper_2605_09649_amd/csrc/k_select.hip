@@ -608,24 +608,28 @@ __global__ __launch_bounds__(SEL_THREADS) void k_sel_mask(const float* __restric
 // have.
 // What this replaces is seven dependent launches of 2 to 8 us each, whatever the size.
 //
-// The blocks wait for one another, so all of them have to be on the chip together: SMALL_BLOCKS of 1024 threads, two to a
-// compute unit (which costs a few spilled registers, 0.5 us).  The 256 compute units hold 32 such calls at a time, as many as the
-// hardware queues that a process can have, and whatever else takes their place ends by itself.  Should a block be alone for
-// some seconds all the same, it goes on and leaves the sticky error.
+// Nothing says that the blocks of a launch are on the chip together (they are not on a stream that may use a few compute units
+// only, or beside kernels that fill the chip), so a block waits for none that may not have started.  Where the blocks of a
+// sequence meet first, one that has looked sel_wait times without seeing all of them takes the sequence over: it does the
+// whole selection itself, as a sequence of one block is done, and those that come to the meeting behind its mark leave.  Once all
+// have met without such a mark all are running, and the later meetings end by themselves.
 constexpr int SMALL_THREADS = 1024, SMALL_ITEMS = 8, SMALL_SEGS = 1024;
 constexpr int SMALL_ONE = SMALL_THREADS * SMALL_ITEMS;            // entries up to which a sequence is one block's
 // Most entries a block may have to walk when one sequence has them all: two tiles of its wavefronts.  us a call of kvtrim_score_select, in
-// seven launches / in one: 1500 entries 30.1 / 8.7, 17.6 K 30.9 / 15.5, 88 K 31.8 / 17.4, 130 K 32.4 / 18.1, 200 K 32.1 / 27.3, but
-// 400 K 36.8 / 47.7; 2 sequences of 85 K each 32.3 / 26.1, one with nine tenths 31.5 / 26.9; 4 of 25 K 31.4 / 17.4; 8 of
-// 15 K 39.3 / 25.4, one with nine tenths 40.0 / 28.2 (a fixed two blocks for each: 17 and 70); all scores equal, 88 K 47.2 / 38.2.
+// seven launches / in one: 1500 entries 30.2 / 8.0, 17.6 K 30.9 / 16.0, 88 K 32.5 / 17.2, 130 K 31.9 / 17.3, 200 K 32.4 / 24.9, but
+// 400 K 36.8 / 47.7; 2 sequences of 85 K each 32.6 / 24.8; 4 of 25 K 32.7 / 17.6; 8 of 15 K 32.9 / 22.3, one with nine tenths 33.3 /
+// 25.3 (a fixed two blocks for each: 17 and 70); 1024 lists of 4 entries 37.6 / 23.1, of 16 37.8 / 24.7; all scores equal, 88 K 48.8 / 38.3.
+// A block that takes a sequence over: 100 K 43, 200 K 240.
 constexpr int64_t SMALL_MOST = 2 * SMALL_ONE;
-constexpr uint32_t SMALL_SPINS = 1u << 22;
+constexpr uint32_t SMALL_TAKEN = 1u << 31;                        // in a sequence's arrivals: one block does it all
 
-template <bool SCORE>
-__global__ __launch_bounds__(SMALL_THREADS, 8) void k_sel_small(const float* __restrict__ score_in, CacheView c, const int32_t* __restrict__ now,
+// ONE: a grid of a block for each sequence, which meet nobody: half the registers (two of 64 to a compute unit; the others take
+// 106 to 115, and held to 64 they spill: 88 K entries 26.8 us for 17.4).
+template <bool SCORE, bool ONE>
+__global__ __launch_bounds__(SMALL_THREADS, ONE ? 8 : 4) void k_sel_small(const float* __restrict__ score_in, CacheView c, const int32_t* __restrict__ now,
                                                              float* __restrict__ score_out, const int64_t* __restrict__ budget, Shape sh,
                                                              uint32_t* __restrict__ meet, uint32_t* __restrict__ hist, uint32_t* __restrict__ fast_hi,
-                                                             int fl_cap, int32_t* __restrict__ err, uint8_t* __restrict__ keep,
+                                                             int fl_cap, uint32_t wait, int32_t* __restrict__ err, uint8_t* __restrict__ keep,
                                                              int32_t* __restrict__ kept_out, uint32_t* __restrict__ thr_out) {
     constexpr int NW = SMALL_THREADS / 64;
     __shared__ uint32_t h[RADIX_BINS];
@@ -634,7 +638,7 @@ __global__ __launch_bounds__(SMALL_THREADS, 8) void k_sel_small(const float* __r
     __shared__ int32_t lds32[17];
     __shared__ int64_t s_rank[3][2];                              // per digit: rank inside the bin, of the threshold / of the bound
     __shared__ uint32_t s_bin[3][2], s_cnt;
-    __shared__ int s_bad, s_total[SMALL_BLOCKS];
+    __shared__ int s_bad, s_met, s_total[SMALL_BLOCKS];
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int segs = sh.segs_per_seq;
     auto len_of = [&](int g, int64_t* start, bool* bad) {
@@ -648,12 +652,16 @@ __global__ __launch_bounds__(SMALL_THREADS, 8) void k_sel_small(const float* __r
     bool bad = false;
     int len = 0;
     int64_t start = 0;
-    if (tid < segs) len = len_of(tid, &start, &bad);              // (of the first sequence; usually the only one)
+    int seq = ONE ? (int)blockIdx.x : 0, part = ONE ? 0 : (int)blockIdx.x, bpq = ONE ? 1 : (int)gridDim.x;
+    if (tid < segs) len = len_of(seq * segs + tid, &start, &bad);   // (of the first sequence; usually the only one)
     if (tid == 0) s_bad = 0;
     if (tid < SMALL_BLOCKS) s_total[tid] = 0;
     for (int i = tid; i < RADIX_BINS; i += SMALL_THREADS) h[i] = 0;
-    int seq = 0, part = (int)blockIdx.x, bpq = (int)gridDim.x;
-    if (sh.n_seq > 1) {
+    if (ONE && sh.n_seq > 1) {
+        int64_t st;
+        for (int g = tid; g < sh.nseg; g += SMALL_THREADS) len_of(g, &st, &bad);
+    }
+    if (!ONE && sh.n_seq > 1) {
         // the grid's blocks are dealt out by the sequences' lengths: one each, the others in proportion, none for fewer than SMALL_ONE entries
         __syncthreads();
         for (int g = tid; g < sh.nseg; g += SMALL_THREADS) {
@@ -685,20 +693,27 @@ __global__ __launch_bounds__(SMALL_THREADS, 8) void k_sel_small(const float* __r
         s_len[tid] = (uint32_t)len;
         s_start[tid] = (uint32_t)start;
         s_kept[tid] = 0;
-        if (part == 0) __hip_atomic_store(&kept_out[g0 + tid], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (the survivors are added by all blocks)
     }
+    auto clear_kept = [&]() {                                     // (the survivors are added by all blocks)
+        if (part == 0 && tid < segs) __hip_atomic_store(&kept_out[g0 + tid], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     __syncthreads();
     if (s_bad) {                                                  // an unusable table anywhere (every block finds it): no selection at all
+        clear_kept();
         if (tid == 0) {
             atomicOr(err, ERR_LAYOUT);
             if (part == 0 && thr_out) thr_out[seq] = 0xFFFFFFFFu;
         }
         return;
     }
-    if (sh.n_seq == 1) bpq = min(bpq, max(1, (tot + SMALL_ONE - 1) / SMALL_ONE));
+    if (!ONE && sh.n_seq == 1) bpq = min(bpq, max(1, (tot + SMALL_ONE - 1) / SMALL_ONE));
     if (part >= bpq) return;
     const uint32_t total = (uint32_t)tot;
     const int64_t want = bud < 0 ? 0 : (bud < (int64_t)total ? bud : (int64_t)total);
+    const int dealt = bpq;
+    uint32_t* word = meet + (size_t)seq * 2 * SMALL_STRIDE;       // arrivals; SMALL_STRIDE behind: blocks that have left
+#pragma unroll 1
+    for (;;) {                                                    // (once more for a block that takes the sequence over)
     // the wavefront's entries: [w0, w1) of the sequence
     const uint32_t share = (total + (uint32_t)(bpq * NW) * 64 - 1) / ((uint32_t)(bpq * NW) * 64) * 64, wno = (uint32_t)(part * NW + wave);
     const uint32_t w0 = min(total, wno * share), w1 = min(total, w0 + share);
@@ -731,6 +746,7 @@ __global__ __launch_bounds__(SMALL_THREADS, 8) void k_sel_small(const float* __r
 #pragma unroll
         for (int u = 0; u < SMALL_ITEMS; ++u) k[u] = key_of_score(v[u]);
     };
+    if (bpq == 1) clear_kept();
     Tile t0;
     uint32_t key[SMALL_ITEMS];
     int sl_rest = sl0;                                            // the segment where the second tile begins
@@ -785,26 +801,33 @@ __global__ __launch_bounds__(SMALL_THREADS, 8) void k_sel_small(const float* __r
         for (int u = 0; u < SMALL_ITEMS; ++u) count(u, t, k[u] >> 21);
     });
 
-    uint32_t* word = meet + (size_t)seq * 2 * SMALL_STRIDE;       // arrivals; SMALL_STRIDE behind: blocks that have left
     uint32_t round = 0;
+    constexpr int MET = 0, TAKE_OVER = 1, LEAVE = 2;
     auto all_here = [&]() {                                       // ... and everything they have stored past the caches is
-        if (bpq == 1) {
-            __syncthreads();
-            return;
-        }
         ++round;
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid == 0) {
-            atomicAdd(word, 1u);
-            uint32_t spins = 0;
-            while (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < round * (uint32_t)bpq) {
-                __builtin_amdgcn_s_sleep(1);
-                if (++spins == SMALL_SPINS) {
-                    atomicOr(err, ERR_LAYOUT);
+            uint32_t v = atomicAdd(word, 1u) + 1u, looked = 0;
+            int met = MET;
+            while (v < round * (uint32_t)bpq || v & SMALL_TAKEN) {
+                if (v & SMALL_TAKEN) {
+                    met = LEAVE;
                     break;
                 }
+                if (round == 1 && looked++ >= wait) {
+                    const uint32_t was = atomicCAS(word, v, v | SMALL_TAKEN);
+                    if (was == v) {
+                        met = TAKE_OVER;
+                        break;
+                    }
+                    v = was;                                      // (another block has come, or taken over)
+                    continue;
+                }
+                __builtin_amdgcn_s_sleep(1);
+                v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
+            s_met = met;
         }
         __syncthreads();
     };
@@ -815,13 +838,14 @@ __global__ __launch_bounds__(SMALL_THREADS, 8) void k_sel_small(const float* __r
         uint32_t* g = hist + ((size_t)seq * 3 + d) * RADIX_BINS;
         __syncthreads();
         // thread 0 owns the highest bins
-        if (bpq > 1) {
+        if (!ONE && bpq > 1) {
 #pragma unroll
             for (int i = 0; i < PER; ++i) {
                 const uint32_t v = h[i * SMALL_THREADS + tid];
                 if (v) atomicAdd(&g[i * SMALL_THREADS + tid], v);
             }
             all_here();
+            if (d == 0 && s_met != MET) return;
             if constexpr (PER == 2) {
                 const uint64_t two = __hip_atomic_load(reinterpret_cast<const uint64_t*>(g + NB - 2 - 2 * tid), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 cnt[0] = (uint32_t)(two >> 32);
@@ -863,9 +887,18 @@ __global__ __launch_bounds__(SMALL_THREADS, 8) void k_sel_small(const float* __r
     bool need_rank = false;
     uint32_t tie0 = 0;                                            // ties of the sequence before this wavefront's
     if (none) {
-        all_here();                                               // (kept_out has been cleared)
+        if (bpq > 1) clear_kept();
     } else {
         find(std::integral_constant<int, 0>{}, want, rank_b);
+        if (!ONE && bpq > 1 && s_met == LEAVE) break;
+        if (!ONE && bpq > 1 && s_met == TAKE_OVER) {
+            bpq = 1;
+            part = 0;
+            for (int i = tid; i < RADIX_BINS; i += SMALL_THREADS) h[i] = 0;
+            __syncthreads();
+            continue;
+        }
+        if (bpq > 1) clear_kept();                                // (the others add theirs two meetings later)
         const uint32_t p0 = s_bin[0][0];
         auto digit1 = [&](const Tile& t, const uint32_t (&k)[SMALL_ITEMS]) {
 #pragma unroll
@@ -898,7 +931,7 @@ __global__ __launch_bounds__(SMALL_THREADS, 8) void k_sel_small(const float* __r
             int32_t mine;
             tie0 = (uint32_t)block_excl_scan<int32_t>(lane == 0 ? (int32_t)n : 0, lds32, &mine);
             tie0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)tie0);
-            if (bpq > 1) {
+            if (!ONE && bpq > 1) {
                 uint32_t* tcount = hist + (size_t)sh.n_seq * 3 * RADIX_BINS + (size_t)seq * SMALL_BLOCKS;
                 if (tid == 0) __hip_atomic_store(&tcount[part], (uint32_t)mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 all_here();
@@ -942,8 +975,11 @@ __global__ __launch_bounds__(SMALL_THREADS, 8) void k_sel_small(const float* __r
             fast_hi[seq] = b > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)b;
         }
     }
-    if (bpq == 1) return;
-    if (tid == 0) s_bad = atomicAdd(word + SMALL_STRIDE, 1u) == (uint32_t)bpq - 1u;
+    if (none) return;                                             // (they did not meet)
+    break;
+    }
+    if (ONE || dealt == 1) return;
+    if (tid == 0) s_bad = atomicAdd(word + SMALL_STRIDE, 1u) == (uint32_t)dealt - 1u;
     __syncthreads();
     if (!s_bad) return;                                           // the last to leave: nobody waits or reads any more
     for (int i = tid; i < 3 * RADIX_BINS; i += SMALL_THREADS) hist[(size_t)seq * 3 * RADIX_BINS + i] = 0;
@@ -992,8 +1028,16 @@ static kvtrim_status launch_select_impl(kvtrim_ctx* ctx, const CacheView& c, con
     if (const int blocks = small_blocks(ctx, c.cap)) {
         ProfScope prof(ctx, K_SEL_SMALL, st);
         const dim3 grid(blocks), block(SMALL_THREADS);
-        if (now) hipLaunchKernelGGL(k_sel_small<true>, grid, block, 0, st, (const float*)nullptr, c, now, score_w, budget, sh, ctx->sel_meet, ctx->sel_small, ws.fast_hi, ws.fl_cap, ws.err, keep, kept, thr);
-        else hipLaunchKernelGGL(k_sel_small<false>, grid, block, 0, st, score, c, now, (float*)nullptr, budget, sh, ctx->sel_meet, ctx->sel_small, ws.fast_hi, ws.fl_cap, ws.err, keep, kept, thr);
+#define KVTRIM_SMALL(scores, one) hipLaunchKernelGGL((k_sel_small<scores, one>), grid, block, 0, st, scores ? (const float*)nullptr : score, c, now, scores ? score_w : (float*)nullptr, \
+                           budget, sh, ctx->sel_meet, ctx->sel_small, ws.fast_hi, ws.fl_cap, (uint32_t)ctx->sel_wait, ws.err, keep, kept, thr)
+        if (blocks == sh.n_seq) {
+            if (now) KVTRIM_SMALL(true, true);
+            else KVTRIM_SMALL(false, true);
+        } else {
+            if (now) KVTRIM_SMALL(true, false);
+            else KVTRIM_SMALL(false, false);
+        }
+#undef KVTRIM_SMALL
         KVTRIM_HIP(ctx, hipGetLastError());
         return KVTRIM_OK;
     }

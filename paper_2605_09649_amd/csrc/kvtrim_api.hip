@@ -253,9 +253,14 @@ kvtrim_status kvtrim_create(kvtrim_ctx** out, const kvtrim_config* cfg) {
     ctx->cfg = *cfg;
     shape_of(cfg, ctx->shape);
     ctx->att_blocks = ATT_BLOCKS;
-    if (const char* e = getenv("KVTRIM_ATT_BLOCKS")) {           // tuning knob
+    if (const char* e = getenv("KVTRIM_ATT_BLOCKS")) {           // tuning knobs
         const int v = atoi(e);
         if (v >= 1 && v <= 65536) ctx->att_blocks = v;
+    }
+    ctx->sel_wait = SEL_WAIT;
+    if (const char* e = getenv("KVTRIM_SEL_WAIT")) {
+        const int v = atoi(e);
+        if (v >= 0 && v <= 1 << 20) ctx->sel_wait = v;
     }
     const Layout l = layout_of(cfg, false);
     ctx->ws_bytes = l.total;

@@ -54,7 +54,8 @@ constexpr int FL_CAP_MIN = 64;
 // step of 256 lists in place 1.0 % faster, on pages 0.8, 16 sequences 1.2, 2 x 112 lists 0.5, 256 lists of 8192 0.5; steps of few
 // blocks the same.
 constexpr int FAST_WORD_STRIDE = 64, FAST_WORD_SEQS = 32;
-constexpr int SMALL_BLOCKS = 16;     // blocks of the selection in one launch, which wait for one another (see k_sel_small)
+constexpr int SMALL_BLOCKS = 16;     // blocks of the selection in one launch, which meet (see k_sel_small)
+constexpr int SEL_WAIT = 256;        // how often one of them looks for the others before it does their work too: some 200 us
 constexpr int SMALL_STRIDE = 64;     // words from one of its counters to the next
 constexpr int FAST_THREADS = 1024;
 constexpr int FAST_ENTRIES_PER_BLOCK = 8192;   // entries of a segment one block covers (blocks per segment from the capacity)
@@ -285,6 +286,7 @@ struct kvtrim_ctx {
     // (not in the workspace's table: only that kernel is given them, and the others' arguments stay as short as they are)
     uint32_t* sel_meet;
     uint32_t* sel_small;
+    int32_t sel_wait;
     void* ws_base;
     size_t ws_bytes;
     int32_t* err_host;           // pinned mirror of the device flag

@@ -374,3 +374,15 @@ def test_one_launch_selection_of_an_unusable_table_selects_nothing():
     kv.kvtrim_score_select(ctx, src, now.to(DEV), bud, score, keep, kept, thr)
     assert kv.kvtrim_poll_error(ctx) == -6                       # KVTRIM_ELAYOUT
     assert torch.all(keep == 7) and torch.all(kept == 0) and torch.all(thr == -1)
+
+
+# A sequence's blocks need not be on the chip together: one that has looked KVTRIM_SEL_WAIT times without seeing all of the others does the
+# whole selection, and those that come later leave.  At 0 the first to arrive takes over in every call, at 1 and 3 now one and now none.
+@pytest.mark.parametrize("wait", [0, 1, 3])
+@pytest.mark.parametrize("S,L,H,lens", [
+    (1, 2, 4, [1024, 1025, 0, 1, 511, 513, 4000, 1117]), (1, 1, 2, [130000, 130001]), (1, 128, 8, [33, 1, 0, 100]),
+    (3, 2, 2, [9000, 0, 100, 64, 0, 0, 0, 0, 1, 8192, 3, 50000]), (15, 1, 1, [1500, 0, 17000, 1, 2])])
+def test_one_launch_selection_by_a_block_that_does_not_wait(S, L, H, lens, wait, monkeypatch):
+    monkeypatch.setenv("KVTRIM_SEL_WAIT", str(wait))
+    for levels in (0, 3):
+        test_one_launch_selection_equals_the_general_kernels(S, L, H, lens, levels)
