@@ -137,7 +137,7 @@ __device__ __forceinline__ void tidy_segment(const PagedView& pc, int g, int32_t
     if (tid == 0) pc.seg_pages[g] = out;
 }
 
-// The same by a wavefront, a few tiles of 64 pages at a time.  all: every page goes, whatever it is marked as.
+// The same by a wavefront, a few tiles of 64 pages at a time.  all: every page goes with all that is in it, whatever it is marked as.
 __device__ __forceinline__ void tidy_segment_by_wave(const PagedView& pc, int g, bool all, int32_t* err) {
     constexpr int TILES = 4;
     const int lane = lane_id(), npg = pc.seg_pages[g];
@@ -162,6 +162,12 @@ __device__ __forceinline__ void tidy_segment_by_wave(const PagedView& pc, int g,
         for (int t = 0; t < TILES; ++t) {
             const bool goes = owner[t] == -2, stays = owner[t] == g;
             const uint64_t mg = __ballot(goes), ms = __ballot(stays);
+            if (all) {
+                for (uint64_t m = mg; m; m &= m - 1) {
+                    const int pg = __builtin_amdgcn_readlane(page[t], __ffsll((long long)m) - 1);
+                    reinterpret_cast<int2*>(pc.pos + (int64_t)pg * P)[lane] = make_int2(-1, -1);
+                }
+            }
             if (mg) {
                 int at = 0;
                 if (lane == 0) at = atomicAdd(pc.n_free, __popcll(mg));
