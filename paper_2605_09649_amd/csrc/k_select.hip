@@ -808,13 +808,11 @@ __global__ __launch_bounds__(SMALL_THREADS, ONE ? 8 : 4) void k_sel_small(const 
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid == 0) {
-            uint32_t v = atomicAdd(word, 1u) + 1u, looked = 0;
+            atomicAdd(word, 1u);
+            const uint32_t all = round * (uint32_t)bpq;
+            uint32_t v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), looked = 0;
             int met = MET;
-            while (v < round * (uint32_t)bpq || v & SMALL_TAKEN) {
-                if (v & SMALL_TAKEN) {
-                    met = LEAVE;
-                    break;
-                }
+            while (v < all) {
                 if (round == 1 && looked++ >= wait) {
                     const uint32_t was = atomicCAS(word, v, v | SMALL_TAKEN);
                     if (was == v) {
@@ -827,6 +825,7 @@ __global__ __launch_bounds__(SMALL_THREADS, ONE ? 8 : 4) void k_sel_small(const 
                 __builtin_amdgcn_s_sleep(1);
                 v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
+            if (met == MET && v & SMALL_TAKEN) met = LEAVE;       // (the mark is above any count)
             s_met = met;
         }
         __syncthreads();
