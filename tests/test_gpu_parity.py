@@ -1037,3 +1037,69 @@ def test_long_mask_over_uneven_segments(shift):
     tied = score[live & (np.arange(cap) >= start[2 * 2100]) & (np.arange(cap) < start[3 * 2100])]
     last = np.sort(tied)[::-1][budget[2] - 1]
     assert (tied == last).sum() > 1 and (tied >= last).sum() > budget[2]   # (fewer survive than tie at the threshold)
+
+
+# The error against 64 bits of a list of several rounds that one block takes is that of a list divided into rounds: kvtrim_compact_attn on
+# the same rows, which has a maximum for every 16 of them and a partial result for every 128.  Both lose what a probability loses
+# as two bf16 terms, 1.5e-6 of the result as a mean over 640 heads; with one maximum for all rounds it was 4 to 18 % more at these
+# lengths, and means over such samples differ by less than 1 %.
+@pytest.mark.parametrize("D,rows", [(128, 128), (128, 240), (128, 300), (128, 384), (128, 385), (64, 240), (64, 384), (64, 500), (64, 512), (64, 513)])
+def test_attention_error_of_undivided_lists_is_that_of_divided_ones(D, rows):
+    H = G = 8
+    n = H * rows
+    err = np.zeros(4)
+    for seed in range(10):
+        g = torch.Generator(device=DEV).manual_seed(1000 * seed + rows)
+        k, v = (torch.randn(n, D, generator=g, device=DEV).bfloat16() for _ in range(2))
+        q = torch.randn(1, 1, H * G, D, generator=g, device=DEV).bfloat16()
+        lens = torch.full((H,), rows, dtype=torch.int32, device=DEV)
+        c = kv.Cache(k, v, torch.zeros(n, device=DEV), torch.arange(rows, dtype=torch.int32, device=DEV).repeat(H), torch.arange(H, device=DEV) * rows, lens)
+        pages = (rows + 127) // 128
+        pc, dst = kv.PagedCache(H, D, H * pages, pages, DEV), kv.Cache.empty(H, D, n, DEV)
+        ctx = kv.Context(1, 1, H, H * G, D, max(n, pc.slots))
+        keep = torch.ones(n, dtype=torch.uint8, device=DEV)
+        now = torch.full((1,), rows, dtype=torch.int32, device=DEV)
+        kv.kvtrim_paged_build(ctx, c, keep, lens, pc)
+        out = [torch.zeros(1, 1, H * G, D, device=DEV) for _ in range(4)]
+        lse = [torch.zeros(1, 1, H * G, device=DEV) for _ in range(4)]
+        s = D ** -0.5
+        kv.kvtrim_decode_attn(ctx, c, q, 0, 1, s, out[0], lse[0])
+        kv.kvtrim_decode_attn_soft(ctx, c, q, now, 0, 1, s, out[1], lse[1])   # (beta = 1: the same sums)
+        kv.kvtrim_paged_attn(ctx, pc, q, 0, 1, s, out[2], lse[2])
+        kv.kvtrim_compact_attn(ctx, c, keep, lens.clone(), dst, 0, q, 0, 1, s, out[3], lse[3])
+        assert kv.kvtrim_poll_error(ctx) == 0
+        kd, vd, qd = (x.cpu().double().view(H, -1, D) for x in (k, v, q))
+        z = torch.matmul(qd, kd.transpose(1, 2).contiguous()) * s
+        ref = torch.matmul(torch.softmax(z, -1), vd)
+        for i in range(4):
+            err[i] += float((out[i].cpu().double().view(H, G, D) - ref).norm() / ref.norm()) / 10
+            assert float((lse[i].cpu().double().view(H, G) - torch.logsumexp(z, -1)).abs().max()) < 5e-6
+    assert np.all(err[:3] <= 1.02 * err[3]) and err[3] < 1.7e-6, err
+
+
+# Tiles whose largest logits lie far apart, in both directions and with a tile that counts for nothing: in a list of several rounds each
+# is relative to its own, or 2^8 below the tile's before.  V up to 1e37: the sums stay below what they are relative to the largest.
+@pytest.mark.parametrize("D,rows", [(128, 384), (128, 300), (64, 512)])
+@pytest.mark.parametrize("step", [-30.0, -5.0, 5.0, 30.0, -300.0, 300.0])
+def test_attention_of_undivided_lists_with_rising_and_falling_logits(D, rows, step):
+    H, G = 4, 3
+    n = H * rows
+    g = torch.Generator().manual_seed(rows)
+    k, v = (torch.randn(n, D, generator=g) for _ in range(2))
+    q = torch.randn(H * G, D, generator=g)
+    q[:, 0] = 8.0
+    k[:, 0] = (torch.arange(rows) // 128).float().repeat(H) * step * D ** 0.5 / 8.0   # (logits a round apart by `step`)
+    v *= 1e37 / 4
+    k, v, q = k.bfloat16(), v.bfloat16(), q.bfloat16()
+    lens = torch.full((H,), rows, dtype=torch.int32, device=DEV)
+    c = kv.Cache(k.to(DEV), v.to(DEV), torch.zeros(n, device=DEV), torch.arange(rows, dtype=torch.int32).repeat(H).to(DEV), torch.arange(H, device=DEV) * rows, lens)
+    ctx = kv.Context(1, 1, H, H * G, D, n)
+    out, lse = torch.zeros(1, 1, H * G, D, device=DEV), torch.zeros(1, 1, H * G, device=DEV)
+    kv.kvtrim_decode_attn(ctx, c, q.view(1, 1, H * G, D).to(DEV), 0, 1, D ** -0.5, out, lse)
+    assert kv.kvtrim_poll_error(ctx) == 0
+    kd, vd, qd = (x.double().view(H, -1, D) for x in (k, v, q))
+    z = torch.matmul(qd, kd.transpose(1, 2).contiguous()) * D ** -0.5
+    ref = torch.matmul(torch.softmax(z, -1), vd)
+    got = out.cpu().double().view(H, G, D)
+    assert torch.isfinite(got).all() and float((got - ref).norm() / ref.norm()) < 2e-4   # (logits of hundreds in fp32)
+    assert float((lse.cpu().double().view(H, G) - torch.logsumexp(z, -1)).abs().max()) < 2e-4
