@@ -216,9 +216,9 @@ kvtrim_status kvtrim_occupancy(kvtrim_ctx *ctx, const kvtrim_cache *c, const int
 /* Stages 3 + 4 fused: exactly kvtrim_compact(src -> dst) followed by
  * kvtrim_decode_attn(dst), with the same arguments, results and device-side errors,
  * but every surviving K/V row is read from HBM once: it is used for the attention of
- * its segment while it is moved (q.k on the vector ALU, p.v on the matrix cores with the
+ * its segment while it is moved (q.k and p.v on the matrix cores, p.v with the
  * probabilities split into two bf16 terms: the product is exact to 2^-16 of every term, sums
- * are fp32; the cost does not depend on the number of query heads per KV head).  With a
+ * are fp32; the cost hardly depends on the number of query heads per KV head).  With a
  * destination of less than a quarter of the source's capacity (few rows can survive) the kernel
  * works a block per chunk of the destination, gathering its rows, instead of a block per chunk
  * of the source.  The library runs the two stages one after the other instead - same results -

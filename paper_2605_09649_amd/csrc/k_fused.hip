@@ -324,9 +324,11 @@ __global__ __launch_bounds__(FUS_THREADS) void k_cmp_attn(CacheView src, const u
     };
     // Attention of this wavefront's 16 rows.
     //   q.k   on the matrix cores, one MFMA 16x16x32 per 32 columns for all heads at once: the wavefront writes its K rows to
-    //         its own LDS and reads them back as the operand (no barrier: LDS serves a wavefront in order).  As packed dot
-    //         products on the vector ALU with a 16-lane all-reduce it took 9 instructions per head, row and lane, and with
-    //         many heads and short rows that was the kernel's time: 48 lists of 16138, 8 heads, D = 64, in place
+    //         its own LDS and reads them back as the operand (no barrier: LDS serves a wavefront in order).  The products of 32
+    //         columns are added by themselves: handed from one MFMA to the next the sum lost more than the packed dot
+    //         products do (logits of +-10, D = 128, 1000 rows a list: error against 64 bits 0.467e-6, dot products 0.388e-6, now 0.388e-6).
+    //         As packed dot products on the vector ALU with a 16-lane all-reduce it took 9 instructions per head, row and
+    //         lane, and with many heads and short rows that was the kernel's time: 48 lists of 16138, 8 heads, D = 64, in place
     //         105.2 -> 94.9 us a step, 18 lists of 668, 8 heads, D = 128 36.4 -> 34.8, 224 of 2048, 7 heads 111.8 -> 110.3.
     //   p.v   on the matrix cores.  A lane holds the same 8 (4) columns of 4 rows, i.e. for one column 4 values along
     //         the reduction (row) dimension - the operand layout of a 16x16x32 MFMA with m = the lane's column block
@@ -351,11 +353,14 @@ __global__ __launch_bounds__(FUS_THREADS) void k_cmp_attn(CacheView src, const u
             *reinterpret_cast<vec*>(sk2 + (m * KP + ((byte >> 4) ^ swz(m))) * 16 + (byte & 15)) = kk[u];
         }
         __builtin_amdgcn_wave_barrier();
-        float4v z = {0.f, 0.f, 0.f, 0.f};
+        float4v part[D / 32];
+        const float4v none = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < D / 32; ++j)
-            z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(sk2 + (col * KP + ((4 * j + sub) ^ swz(col))) * 16)),
-                                                        __builtin_bit_cast(bf16x8, qf[j]), z, 0, 0, 0);
+            part[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(sk2 + (col * KP + ((4 * j + sub) ^ swz(col))) * 16)),
+                                                              __builtin_bit_cast(bf16x8, qf[j]), none, 0, 0, 0);
+        float4v z = part[0] + part[1];
+        if constexpr (D == 128) z += part[2] + part[3];
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int u = 0; u < 4; ++u) zs[u] = r0 + u * 4 + sub < cnt ? z[u] * scale_log2 : -INFINITY;
