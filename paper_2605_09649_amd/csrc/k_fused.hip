@@ -86,9 +86,13 @@ __device__ __forceinline__ float row16_sum(float x) {
 }
 
 // Whether q.k goes to the matrix cores (see attend_rows).  In place, where most blocks only read, a block's chain is shorter with the
-// dot products up to five heads and 256-byte rows: 256 lists of 4096, 4 heads, 147.0 us a step against 150.
+// dot products while the heads are few.  us a step in place, matrix cores / dot products: D = 128, 256 lists of 4096, 1 to 8 heads 152.4 / 153.7,
+// 154.0 / 153.6, 155.3 / 153.2, 156.1 / 154.2, 162.8 / 159.5, 163.0 / 161.3, 165.5 / 177.7, 165.5 / 181.0, 48 lists of 16000, 2, 5, 6, 7
+// 122.5 / 121.5, 128.1 / 125.9, 135.2 / 134.1, 136.9 / 146.0, 18 of 668 and 16 of 65 even up to 6; D = 64, 256 of 4096, 1, 2, 4, 8 heads
+// 100.1 / 98.0, 105.1 / 103.3, 106.0 / 109.2, 112.0 / 127.6.  Out of place the matrix cores are never behind: 200.5 / 207.5 with one head, 203.7 / 209.2
+// with 4 (256 of 4096, D = 128), 115.3 / 115.0 with one at D = 64.
 template <int D, int G, bool INPLACE>
-constexpr bool qk_mfma() { return !(INPLACE && D == 128 && G <= 5); }
+constexpr bool qk_mfma() { return !INPLACE || G > (D == 128 ? 6 : 2); }
 template <int D, int G, bool MFMA>
 struct QueryFrag {                                                // the queries as a lane holds them: the operand / its column slice of every head
     typedef uint4 vec;
