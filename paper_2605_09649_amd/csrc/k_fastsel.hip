@@ -32,21 +32,8 @@ constexpr int SLOW_BATCH = 4;                                     // ... in the 
 constexpr int FAST_BIN_DIRECT = 256;                              // a bin of at most this many entries is ranked directly
 static_assert(FAST_ITEMS * FAST_THREADS == FL_CAP_MAX, "list capacity must be a multiple of the block size");
 
-// Length of segment g, or 0 with *bad set when its table entry is unusable (negative, beyond the buffers, or
-// overlapping its successor).  Every kernel of this file sees a segment through this function.
-__device__ __forceinline__ int seg_checked_len(const CacheView& c, int g, int nseg, int64_t* start, bool* bad) {
-    const int len = c.seg_len[g];
-    const int64_t st = c.seg_start[g];
-    const int64_t nxt = g + 1 < nseg ? c.seg_start[g + 1] : c.cap;
-    *start = st;
-    if (len < 0 || st < 0 || st + len > c.cap || st + len > nxt) {
-        *bad = true;
-        return 0;
-    }
-    return len;
-}
-
-// A segment as the kernels see it.  STEP: its entries [len_old, len) are this step's new tokens - up to the first
+// A segment as the kernels see it (seg_view): empty, with *bad set, when its table entry is unusable - negative, beyond the buffers
+// or overlapping its successor.  STEP: its entries [len_old, len) are this step's new tokens - up to the first
 // padding row (negative position), none if the segment has no room for them (kvtrim_append's rule) - whose
 // metadata is read from the new-token buffers by every block, never from the cache.
 // PAGED: the segment's entries are the slots of its pages in block-table order (entry j = slot j % 128 of the table's
@@ -181,13 +168,12 @@ __device__ __forceinline__ void walk_from_top(ResolveShared* sm, int64_t rank) {
     __syncthreads();
 }
 
-// Where the key of an entry comes from: computed from log beta and the position (SCORE: stage 1 fused, Eq.
-// global_score in log domain - one fp32 multiply, or one fused multiply-add with the cached horizon tail) or
-// read from the caller's score array.  Both are inputs of the call, so any block may read any entry at any time.
-template <bool SCORE, int KIND>
+// Where the key of an entry comes from: log beta and the position (stage 1, Eq. global_score in log domain - one fp32
+// multiply, or one fused multiply-add with the cached horizon tail).  Both are inputs of the call, so any block may
+// read any entry at any time.
+template <int KIND>
 struct KeySource {
     static constexpr bool STEP = KIND == SCAN_STEP, PAGED = KIND == SCAN_PAGED;
-    const float* score_in;
     const float* lb;
     const float* lt;
     const int32_t* pos;
@@ -223,19 +209,10 @@ struct KeySource {
             const int64_t e = place(v, j, &bp);
             p = pos[e];
             if (PAGED && p < 0) return false;
-            if (!SCORE) {
-                *p_out = p;
-                *s_out = score_in[e];
-                return true;
-            }
             b = lb[e];
             if (lt) t = lt[e];
         }
         *p_out = p;
-        if (!SCORE) {
-            *s_out = 0.f;                                         // (a STEP always computes its scores)
-            return true;
-        }
         const float dt = (float)(t1 - p);
         *s_out = lt ? __fmaf_rn(dt, b, t) : __fmul_rn(dt, b);
         return true;
@@ -286,8 +263,8 @@ struct Visit {
 // to a list's first entry is a microsecond, and a batch's loads must not wait for one another: kvtrim_paged_score_select with
 // a list that is no use, 256 lists of 1000 entries 1690 us -> 548, 4 of 500 K 10.2 ms -> 5.1.)
 constexpr int SLOW_SHORT = 8192;
-template <int PASS, bool SCORE, int KIND, typename V = NoVisit>
-__device__ __forceinline__ void slow_pass(const KeySource<SCORE, KIND>& ks, const CacheView& c, const Shape& sh,
+template <int PASS, int KIND, typename V = NoVisit>
+__device__ __forceinline__ void slow_pass(const KeySource<KIND>& ks, const CacheView& c, const Shape& sh,
                                           const StepArgs& sa, int seq, uint32_t prefix, ResolveShared* sm, const V& visit = V()) {
     constexpr int NB = PASS == 2 ? 1024 : 2048, NW = FAST_THREADS / 64;
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -328,8 +305,8 @@ __device__ __forceinline__ void slow_pass(const KeySource<SCORE, KIND>& ks, cons
 // Key of the entry of rank `rank` (1-based, descending key order) of the sequence; *rank_in = its rank among the
 // entries with that key, *ties = how many entries have that key.  The first pass shows every entry to `visit`, which may
 // empty slots of entries that come behind the one looked for.
-template <bool SCORE, int KIND, typename V = NoVisit>
-__device__ __forceinline__ uint32_t slow_radix(const KeySource<SCORE, KIND>& ks, const CacheView& c, const Shape& sh,
+template <int KIND, typename V = NoVisit>
+__device__ __forceinline__ uint32_t slow_radix(const KeySource<KIND>& ks, const CacheView& c, const Shape& sh,
                                                const StepArgs& sa, int seq, int64_t rank, ResolveShared* sm,
                                                int64_t* rank_in, uint32_t* ties, const V& visit = V()) {
     slow_pass<0>(ks, c, sh, sa, seq, 0, sm, visit);
@@ -351,8 +328,8 @@ __device__ __forceinline__ uint32_t slow_radix(const KeySource<SCORE, KIND>& ks,
 
 // One digit of the radix select over the positions of segment g's entries with key == key_thr (taken as
 // 0x7fffffff - position, so that the smallest position is the largest): narrows *prefix and *rank.
-template <int PASS, bool SCORE, int KIND>
-__device__ __forceinline__ void tie_pos_pass(const KeySource<SCORE, KIND>& ks, int g, const SegView& v, uint32_t key_thr,
+template <int PASS, int KIND>
+__device__ __forceinline__ void tie_pos_pass(const KeySource<KIND>& ks, int g, const SegView& v, uint32_t key_thr,
                                              uint32_t* prefix, int64_t* rank, ResolveShared* sm) {
     constexpr int NB = PASS == 2 ? 1024 : 2048;
     const int tid = threadIdx.x;
@@ -374,8 +351,8 @@ __device__ __forceinline__ void tie_pos_pass(const KeySource<SCORE, KIND>& ks, i
 
 // The `quota`-th entry (1-based) with key == key_thr in (segment ascending, position ascending) order:
 // result in sm->found_seg / sm->found_pos.  The caller guarantees that it exists.
-template <bool SCORE, int KIND>
-__device__ __forceinline__ void slow_tie_walk(const KeySource<SCORE, KIND>& ks, const CacheView& c, const Shape& sh,
+template <int KIND>
+__device__ __forceinline__ void slow_tie_walk(const KeySource<KIND>& ks, const CacheView& c, const Shape& sh,
                                               const StepArgs& sa, int seq, uint32_t key_thr, int64_t quota,
                                               ResolveShared* sm) {
     const int tid = threadIdx.x;
@@ -515,8 +492,8 @@ __device__ __forceinline__ void write_step_tables(const CacheView& c, const Shap
 }
 static_assert(STEP_MAX_NEW <= 64, "a lane per new token");
 
-// SCORE: stage 1 is computed here (and written to score_out); otherwise the scores are read from score_in.
-// STEP (implies SCORE): the decode step in one call.  Every block scores its segments' new tokens from the new-token
+// Stage 1 is computed here, and written to score_out.
+// STEP: the decode step in one call.  Every block scores its segments' new tokens from the new-token
 // buffers; more blocks, behind the scanning ones of the grid, write their rows and metadata into the source cache and
 // the row mover's chunk table (write_step_tables).  The last block of a sequence also leaves
 // what the compaction needs: survivors per segment, the destination's segment table and - when the evicted entries
@@ -530,14 +507,13 @@ static_assert(STEP_MAX_NEW <= 64, "a lane per new token");
 // writer waits for before it arrives, and read with device-scope loads - so no block needs a fence, which on this
 // chip means a write-back of a whole L2.  The scores written here are read by the NEXT kernel only; the
 // single-block select, which has to look at every entry, recomputes them from the call's inputs.
-template <bool SCORE, int KIND, int DEAL>
+template <int KIND, int DEAL>
 __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const int32_t* __restrict__ now,
-                                                            const float* score_in, float* score_out,
+                                                            float* score_out,
                                                             const int64_t* __restrict__ budget, Shape sh, Workspace ws,
                                                             int bps, int spb_arg, int limit, int32_t* __restrict__ kept_out,
                                                             uint32_t* __restrict__ thr_out, StepArgs sa) {
     constexpr bool STEP = KIND == SCAN_STEP, PAGED = KIND == SCAN_PAGED, MULTI = DEAL == DEAL_MULTI, WHOLE = DEAL >= DEAL_WHOLE, PARTS = DEAL == DEAL_PARTS;
-    static_assert(!STEP || SCORE, "the one-call step computes the scores itself");
     __shared__ ResolveShared sm;
     __shared__ int s_last, s_ncand;
     __shared__ uint32_t s_base[FAST_SUB];
@@ -610,10 +586,9 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     uint32_t* sub_count = ws.fl_count + (size_t)seq * FAST_SUB * wstride;
     uint32_t* grp_min = ws.fast_min + (size_t)seq * FAST_SUB * wstride;
     uint32_t* done = ws.fast_done + (size_t)seq * (FAST_SUB + 1) * wstride;
-    KeySource<SCORE, KIND> ks;
+    KeySource<KIND> ks;
     ks.bt = sa.pg.block_table;
     ks.n_pages = sa.pg.n_pages;
-    ks.score_in = score_in;
     ks.lb = c.log_beta;
     ks.lt = c.log_tail;
     ks.pos = c.pos;
@@ -621,7 +596,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
     ks.lt_new = sa.lt_new;
     ks.pos_new = sa.pos_new;
     ks.n_new = sa.n_new;
-    ks.t1 = SCORE ? now[seq] + 1 : 0;
+    ks.t1 = now[seq] + 1;
     // (the mask then needs no selection; a vector load, for which nothing waits before the first scores are there: 0.5 us of 47)
     const bool none_stays = PAGED && ld_dev(&budget[seq]) <= 0;
 
@@ -865,32 +840,23 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
                 at[u] = isnew ? (int64_t)seg * sa.n_new + (j - sv0.len_old) : (j < len ? ks.place(sv0, j, &bad_page) : 0);
             }
             if (PAGED && bad_page) atomicOr(ws.err, ERR_LAYOUT);
-            if (SCORE) {
-                float lbv[FAST_BATCH], ltv[FAST_BATCH];
+            float lbv[FAST_BATCH], ltv[FAST_BATCH];
 #pragma unroll
-                for (int u = 0; u < FAST_BATCH; ++u) {
-                    const int j = j0 + u * stride;
-                    const bool in = j < len;
-                    const bool isnew = STEP && j >= sv0.len_old;
-                    pv[u] = in ? (isnew ? sa.pos_new : c.pos)[at[u]] : 0;
-                    lbv[u] = in ? (isnew ? sa.lb_new : c.log_beta)[at[u]] : 0.f;
-                    ltv[u] = (in && c.log_tail) ? (isnew ? sa.lt_new : c.log_tail)[at[u]] : 0.f;
-                }
+            for (int u = 0; u < FAST_BATCH; ++u) {
+                const int j = j0 + u * stride;
+                const bool in = j < len;
+                const bool isnew = STEP && j >= sv0.len_old;
+                pv[u] = in ? (isnew ? sa.pos_new : c.pos)[at[u]] : 0;
+                lbv[u] = in ? (isnew ? sa.lb_new : c.log_beta)[at[u]] : 0.f;
+                ltv[u] = (in && c.log_tail) ? (isnew ? sa.lt_new : c.log_tail)[at[u]] : 0.f;
+            }
 #pragma unroll
-                for (int u = 0; u < FAST_BATCH; ++u) {
-                    const int j = j0 + u * stride;
-                    const float dt = (float)(ks.t1 - pv[u]);
-                    sv[u] = c.log_tail ? __fmaf_rn(dt, lbv[u], ltv[u]) : __fmul_rn(dt, lbv[u]);
-                    if (PAGED && pv[u] < 0) sv[u] = 0.f;          // an empty slot's score reads 0
-                    if (j < len) score_out[STEP ? start + j : at[u]] = sv[u];
-                }
-            } else {
-#pragma unroll
-                for (int u = 0; u < FAST_BATCH; ++u) {
-                    const int j = j0 + u * stride;
-                    sv[u] = j < len ? score_in[at[u]] : 0.f;
-                    pv[u] = (PAGED && j < len) ? c.pos[at[u]] : 0;
-                }
+            for (int u = 0; u < FAST_BATCH; ++u) {
+                const int j = j0 + u * stride;
+                const float dt = (float)(ks.t1 - pv[u]);
+                sv[u] = c.log_tail ? __fmaf_rn(dt, lbv[u], ltv[u]) : __fmul_rn(dt, lbv[u]);
+                if (PAGED && pv[u] < 0) sv[u] = 0.f;              // an empty slot's score reads 0
+                if (j < len) score_out[STEP ? start + j : at[u]] = sv[u];
             }
 #pragma unroll
             for (int u = 0; u < FAST_BATCH; ++u) {
@@ -903,7 +869,7 @@ __global__ __launch_bounds__(FAST_THREADS) void k_fast_scan(CacheView c, const i
                     const int slot = atomicAdd(&s_ncand, 1);
                     if (slot < STAGE) {
                         c_key[slot] = key;
-                        c_pos[slot] = (SCORE || PAGED) ? pv[u] : c.pos[at[u]];
+                        c_pos[slot] = pv[u];
                         c_seg[slot] = seg;
                         if (IDX) c_idx[slot] = STEP ? j : (int)at[u];
                     }
@@ -1572,7 +1538,7 @@ constexpr int SCAN_RESIDENT = 256, MASK_RESIDENT = 512;
 template <int KIND>
 static void launch_scan(const ScanGrid& g, const CacheView& c, const int32_t* now, float* score, const int64_t* budget, const Shape& sh,
                         const Workspace& ws, int32_t* kept, uint32_t* thr, const StepArgs& sa, unsigned more_blocks, hipStream_t st) {
-#define KVTRIM_DEAL(d) hipLaunchKernelGGL((k_fast_scan<true, KIND, d>), dim3(g.blocks + more_blocks, g.parts), dim3(FAST_THREADS), 0, st, c, now, (const float*)nullptr, score, budget, sh, ws, g.bps, g.spb, g.limit, kept, thr, sa)
+#define KVTRIM_DEAL(d) hipLaunchKernelGGL((k_fast_scan<KIND, d>), dim3(g.blocks + more_blocks, g.parts), dim3(FAST_THREADS), 0, st, c, now, score, budget, sh, ws, g.bps, g.spb, g.limit, kept, thr, sa)
     if (g.deal == DEAL_WHOLE) KVTRIM_DEAL(DEAL_WHOLE);
     else if (g.deal == DEAL_PARTS) KVTRIM_DEAL(DEAL_PARTS);
     else if (g.deal == DEAL_MULTI) KVTRIM_DEAL(DEAL_MULTI);
