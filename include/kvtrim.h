@@ -99,7 +99,7 @@ typedef struct {
  * among which the stand-alone attention kernel shares its rows (1 .. 65536, default 768).
  * It changes the order of floating-point sums in attention, nothing else.  KVTRIM_SEL_WAIT = how often a block
  * of the one-launch selection of small caches looks for the sequence's other blocks before it does their work as
- * well (0 .. 1048576, default 256, some 200 us; where the blocks do not get onto the GPU together).  It changes no result.  (KVTRIM_ATT_CHUNK, the rows
+ * well (0 .. 1048576, default 2048, some 220 us; where the blocks do not get onto the GPU together).  It changes no result.  (KVTRIM_ATT_CHUNK, the rows
  * per chunk of an earlier attention kernel, has nothing left to set and is not read.) */
 kvtrim_status kvtrim_create(kvtrim_ctx **out, const kvtrim_config *cfg);
 kvtrim_status kvtrim_destroy(kvtrim_ctx *ctx);

@@ -610,7 +610,7 @@ __global__ __launch_bounds__(SEL_THREADS) void k_sel_mask(const float* __restric
 //
 // Nothing says that the blocks of a launch are on the chip together (they are not on a stream that may use a few compute units
 // only, or beside kernels that fill the chip), so a block waits for none that may not have started.  Where the blocks of a
-// sequence meet first, one that has looked sel_wait times without seeing all of them takes the sequence over: it does the
+// sequence meet first, one that has looked `wait` times without seeing all of them takes the sequence over: it does the
 // whole selection itself, as a sequence of one block is done, and those that come to the meeting behind its mark leave.  Once all
 // have met without such a mark all are running, and the later meetings end by themselves.
 constexpr int SMALL_THREADS = 1024, SMALL_ITEMS = 8, SMALL_SEGS = 1024;

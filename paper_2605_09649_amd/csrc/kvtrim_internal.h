@@ -55,7 +55,7 @@ constexpr int FL_CAP_MIN = 64;
 // blocks the same.
 constexpr int FAST_WORD_STRIDE = 64, FAST_WORD_SEQS = 32;
 constexpr int SMALL_BLOCKS = 16;     // blocks of the selection in one launch, which meet (see k_sel_small)
-constexpr int SEL_WAIT = 256;        // how often one of them looks for the others before it does their work too: some 200 us
+constexpr int SEL_WAIT = 2048;       // how often one of them looks for the others before it does their work too: some 220 us, as long as that takes
 constexpr int SMALL_STRIDE = 64;     // words from one of its counters to the next
 constexpr int FAST_THREADS = 1024;
 constexpr int FAST_ENTRIES_PER_BLOCK = 8192;   // entries of a segment one block covers (blocks per segment from the capacity)
