@@ -97,10 +97,11 @@ typedef struct {
  * workspace on the current device; kvtrim_workspace_bytes says how large it is.
  * Two tuning knobs are read from the environment at creation.  KVTRIM_ATT_BLOCKS = most blocks
  * among which the stand-alone attention kernel shares its rows (1 .. 65536, default 768).
- * It changes the order of floating-point sums in attention, nothing else.  KVTRIM_SEL_WAIT = how often a block
- * of the one-launch selection of small caches looks for the sequence's other blocks before it does their work as
- * well (0 .. 1048576, default 2048, some 220 us; where the blocks do not get onto the GPU together).  It changes no result.  (KVTRIM_ATT_CHUNK, the rows
- * per chunk of an earlier attention kernel, has nothing left to set and is not read.) */
+ * It changes the order of floating-point sums in attention, nothing else.  (KVTRIM_ATT_CHUNK, the rows
+ * per chunk of an earlier attention kernel, has nothing left to set and is not read.)
+ * KVTRIM_SEL_WAIT = how often a block of the one-launch selection of small caches looks for the
+ * sequence's other blocks before it does their work as well, where they do not get onto the GPU
+ * together (0 .. 1048576, default 2048, some 220 us).  It changes no result. */
 kvtrim_status kvtrim_create(kvtrim_ctx **out, const kvtrim_config *cfg);
 kvtrim_status kvtrim_destroy(kvtrim_ctx *ctx);
 size_t kvtrim_workspace_bytes(const kvtrim_config *cfg);
@@ -153,8 +154,8 @@ kvtrim_status kvtrim_select_global(kvtrim_ctx *ctx, const kvtrim_cache *c, const
  *     k + 1 entries of the order are among them and are ranked directly; then the mask pass.  Two kernels.  The
  *     bound follows the threshold from call to call by itself.  A sequence whose list comes up short (no previous
  *     selection on this context, a jump in the budget or the workload) or overflows is selected by a slow single-
- *     block fallback inside the same kernel - correct, but slow, some 2.5 ms per million entries, so pass 0 when the
- *     number of evictions is not small.
+ *     block fallback inside the same kernel - correct, but slow, some 1.2 ms per million entries (on pages 2.5), so pass
+ *     0 when the number of evictions is not small.
  * Device-side error: KVTRIM_ELAYOUT for a segment table that does not fit cap_entries or overlaps. */
 kvtrim_status kvtrim_score_select(kvtrim_ctx *ctx, const kvtrim_cache *c, const int32_t *now, const int64_t *budget,
                                   float *score_out, uint8_t *keep_out, int32_t *kept_out, uint32_t *thr_key_out,
