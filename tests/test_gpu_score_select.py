@@ -386,3 +386,35 @@ def test_one_launch_selection_by_a_block_that_does_not_wait(S, L, H, lens, wait,
     monkeypatch.setenv("KVTRIM_SEL_WAIT", str(wait))
     for levels in (0, 3):
         test_one_launch_selection_equals_the_general_kernels(S, L, H, lens, levels)
+
+
+def test_one_launch_selections_on_many_streams_beside_large_kernels():
+    # a context and a stream each, calls of up to sixteen blocks that meet, beside products that fill the chip: whichever blocks get
+    # onto it together, every call has its own selection
+    w = ki.Workload("t", 0, 1, 4, 4, 4, 64, (0,), (0,), 1, 3.0, 1.5)
+    streams = [torch.cuda.Stream() for _ in range(12)]
+    busy = torch.cuda.Stream()
+    m = torch.randn(4096, 4096, device=DEV).bfloat16()
+    sets = []
+    for i in range(len(streams)):
+        c, now = ki.ragged_cache(w, [3000 + 500 * i + 77 * g for g in range(16)], reserve=1, salt=i)
+        src = kv.Cache.from_dict(c, DEV)
+        bud = torch.tensor([int(sum(c["seg_len"].tolist())) // (2 + i % 3)], dtype=torch.int64, device=DEV)
+        out = [torch.zeros(src.cap, device=DEV), torch.zeros(src.cap, dtype=torch.uint8, device=DEV), torch.zeros(16, dtype=torch.int32, device=DEV),
+               torch.zeros(1, dtype=torch.int32, device=DEV)]
+        want = oracle.select(host_cache(w, c), oracle.score(host_cache(w, c), now.numpy()), bud.cpu().numpy())
+        sets.append((kv.Context(1, 4, 4, 4, 64, src.cap), src, now.to(DEV), bud, out, want, c))
+    torch.cuda.synchronize()
+    with torch.cuda.stream(busy):
+        for _ in range(30):
+            m @ m
+    for call in range(25):
+        for st, (ctx, src, now, bud, out, want, c) in zip(streams, sets):
+            kv.kvtrim_score_select(ctx, src, now, bud, *out, stream=st)
+    torch.cuda.synchronize()
+    for ctx, src, now, bud, (score, keep, kept, thr), (keep_ref, kept_ref, thr_ref), c in sets:
+        assert kv.kvtrim_poll_error(ctx) == 0
+        assert np.array_equal(kept.cpu().numpy(), kept_ref) and np.array_equal(thr.cpu().numpy().view(np.uint32), thr_ref)
+        k = keep.cpu().numpy()
+        for s, n in zip(c["seg_start"].tolist(), c["seg_len"].tolist()):
+            assert np.array_equal(k[s:s + n], keep_ref[s:s + n])
