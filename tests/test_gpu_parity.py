@@ -871,6 +871,13 @@ def test_attention_of_lists_that_one_block_takes(H, G, D, lens):
     test_attention_of_a_list_that_outgrows_the_others(H, G, D, lens)
 
 
+# On pages a round less from 17 lists on (9 at D = 64): the lists of the last round are divided there, ragged ones stay whole.
+@pytest.mark.parametrize("H,D,lens", [(16, 128, [384, 257, 300, 100]), (17, 128, [384, 257, 300, 256, 255]), (40, 128, [384, 0, 129]),
+                                      (8, 64, [512, 385, 400]), (9, 64, [512, 385, 384, 1]), (33, 64, [500, 130, 384])])
+def test_attention_on_pages_of_many_lists_of_few_rounds(H, D, lens):
+    test_attention_of_a_list_that_outgrows_the_others(H, 4, D, [lens[i % len(lens)] for i in range(H)])
+
+
 # out and lse are arrays of floats and need no more than their alignment, also where the last block of a segment merges:
 # attention of a small call (2200 and 40 rows a list), of the row mover (18 chunks and 1), of segments that one block writes
 @pytest.mark.parametrize("G,D", [(4, 128), (3, 64)])
