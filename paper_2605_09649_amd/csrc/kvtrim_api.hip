@@ -253,7 +253,7 @@ kvtrim_status kvtrim_create(kvtrim_ctx** out, const kvtrim_config* cfg) {
     ctx->cfg = *cfg;
     shape_of(cfg, ctx->shape);
     ctx->att_blocks = ATT_BLOCKS;
-    if (const char* e = getenv("KVTRIM_ATT_BLOCKS")) {           // tuning knobs
+    if (const char* e = getenv("KVTRIM_ATT_BLOCKS")) {           // a tuning knob, as the next
         const int v = atoi(e);
         if (v >= 1 && v <= 65536) ctx->att_blocks = v;
     }
